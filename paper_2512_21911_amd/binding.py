@@ -1,8 +1,11 @@
-"""ctypes binding of libsvf: argument marshalling only.
+"""Python binding of libsvf: argument marshalling only.
 
 Every function here has the name of the C entry point it calls (include/svf.h) and does no
 arithmetic of its own.  Tensors are torch CUDA tensors used purely as device memory; work is
 enqueued on torch's current stream.  A missing library is an error: there is no fallback path.
+The calls a program makes in every step go through the native module _svf_calls
+(csrc/py_calls.cpp: a call through ctypes costs about as much host time as the launch takes on the
+GPU); the others go through ctypes.
 """
 from __future__ import annotations
 
@@ -12,7 +15,7 @@ from typing import Optional
 
 import torch
 
-from .build import LIB_PATH
+from .build import CALLS_PATH, LIB_PATH
 
 SVF_F32, SVF_BF16 = 0, 1
 
@@ -159,6 +162,27 @@ def _check(rc: int, where: str):
         raise SvfError(rc, where)
 
 
+def _native_call(name: str):
+    """The function of that name in the native calls module.  Before the module has been built (this
+    package is imported to build it) a stand-in that loads it, or raises, when it is called."""
+    try:
+        from . import _svf_calls
+        return getattr(_svf_calls, name)
+    except ImportError:
+        pass
+
+    def load_and_call(*args, **kwargs):
+        lib()                                             # raises if the library itself is missing
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError(f"{CALLS_PATH} is missing: build it with __graft_entry__.build() "
+                               "or `python -m paper_2512_21911_amd.build`")
+        from . import _svf_calls
+        return getattr(_svf_calls, name)(*args, **kwargs)
+
+    load_and_call.__name__ = name
+    return load_and_call
+
+
 def svf_version() -> int:
     return lib().svf_version()
 
@@ -205,31 +229,22 @@ def new_workspace(shape: SvfShape, device="cuda") -> torch.Tensor:
     return ws
 
 
-def svf_block_reps(shape, K, block_table, seq_lens, reps, first_block=0, n_blocks=-1):
-    _check(lib().svf_block_reps(ctypes.byref(shape), _ptr(K), _ptr(block_table), _ptr(seq_lens),
-                                first_block, n_blocks, _ptr(reps), _stream()), "svf_block_reps")
+# svf_block_reps(shape, K, block_table, seq_lens, reps, first_block=0, n_blocks=-1)
+svf_block_reps = _native_call("svf_block_reps")
 
 
-def svf_score_select(shape, q, reps, seq_lens, sel_idx, sel_cnt, ws, scores=None):
-    _check(lib().svf_score_select(ctypes.byref(shape), _ptr(q), _ptr(reps), _ptr(seq_lens), _ptr(sel_idx),
-                                  _ptr(sel_cnt), _ptr(scores), _ptr(ws), ws.numel(), _stream()),
-           "svf_score_select")
+# svf_score_select(shape, q, reps, seq_lens, sel_idx, sel_cnt, ws, scores=None)
+svf_score_select = _native_call("svf_score_select")
 
 
-def svf_verify_attn(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt,
-                    out, ws, lse=None):
-    _check(lib().svf_verify_attn(ctypes.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(block_table),
-                                 _ptr(seq_lens), _ptr(k_draft), _ptr(v_draft), _ptr(draft_mask),
-                                 _ptr(sel_idx), _ptr(sel_cnt), _ptr(out), _ptr(lse), _ptr(ws), ws.numel(),
-                                 _stream()), "svf_verify_attn")
+# svf_verify_attn(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt, out, ws,
+#     lse=None)
+svf_verify_attn = _native_call("svf_verify_attn")
 
 
-def svf_verify_attn_static_ws(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt,
-                              out, lse=None):
-    _check(lib().svf_verify_attn_static_ws(ctypes.byref(shape), _ptr(q), _ptr(K), _ptr(V), _ptr(block_table),
-                                           _ptr(seq_lens), _ptr(k_draft), _ptr(v_draft), _ptr(draft_mask),
-                                           _ptr(sel_idx), _ptr(sel_cnt), _ptr(out), _ptr(lse), _stream()),
-           "svf_verify_attn_static_ws")
+# svf_verify_attn_static_ws(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt,
+#     out, lse=None)
+svf_verify_attn_static_ws = _native_call("svf_verify_attn_static_ws")
 
 
 SVF_KERNEL_AUTO, SVF_KERNEL_VECTOR_ALU = 0, 1
@@ -270,12 +285,9 @@ def svf_workspace_set_wait_polls(shape, ws, polls):
            "svf_workspace_set_wait_polls")
 
 
-def svf_verify_step(shape, mode, q, reps, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask,
-                    sel_idx, sel_cnt, out, ws, lse=None):
-    _check(lib().svf_verify_step(ctypes.byref(shape), int(mode), _ptr(q), _ptr(reps), _ptr(K), _ptr(V),
-                                 _ptr(block_table), _ptr(seq_lens), _ptr(k_draft), _ptr(v_draft),
-                                 _ptr(draft_mask), _ptr(sel_idx), _ptr(sel_cnt), _ptr(out), _ptr(lse),
-                                 _ptr(ws), ws.numel(), _stream()), "svf_verify_step")
+# svf_verify_step(shape, mode, q, reps, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx,
+#     sel_cnt, out, ws, lse=None)
+svf_verify_step = _native_call("svf_verify_step")
 
 
 # ---- retrieval analytics (argument marshalling only) ------------------------------------------
@@ -324,16 +336,12 @@ def svf_topk_anchors(J, K):
 
 # ---- retrieval variants (argument marshalling only) -------------------------------------------
 
-def svf_block_summaries(shape, retrieval, K, block_table, seq_lens, summaries, first_block=0, n_blocks=-1):
-    _check(lib().svf_block_summaries(ctypes.byref(shape), ctypes.byref(retrieval), _ptr(K), _ptr(block_table),
-                                     _ptr(seq_lens), first_block, n_blocks, _ptr(summaries), _stream()),
-           "svf_block_summaries")
+# svf_block_summaries(shape, retrieval, K, block_table, seq_lens, summaries, first_block=0, n_blocks=-1)
+svf_block_summaries = _native_call("svf_block_summaries")
 
 
-def svf_retrieve(shape, retrieval, q, summaries, seq_lens, sel_idx, sel_cnt, ws, scores=None):
-    _check(lib().svf_retrieve(ctypes.byref(shape), ctypes.byref(retrieval), _ptr(q), _ptr(summaries),
-                              _ptr(seq_lens), _ptr(sel_idx), _ptr(sel_cnt), _ptr(scores), _ptr(ws), ws.numel(),
-                              _stream()), "svf_retrieve")
+# svf_retrieve(shape, retrieval, q, summaries, seq_lens, sel_idx, sel_cnt, ws, scores=None)
+svf_retrieve = _native_call("svf_retrieve")
 
 
 # ---- sparse feed-forward verification (argument marshalling only) ------------------------------
@@ -354,17 +362,14 @@ def new_ffn_workspace(shape: SvfFfnShape, device="cuda") -> torch.Tensor:
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
-def svf_sparse_ffn(shape, x, w_gate, w_up, w_down_t, y, ws, b_gate=None, b_up=None, b_down=None, active=None):
-    _check(lib().svf_sparse_ffn(ctypes.byref(shape), _ptr(x), _ptr(w_gate), _ptr(w_up), _ptr(w_down_t), _ptr(b_gate),
-                                _ptr(b_up), _ptr(b_down), _ptr(y), _ptr(active), _ptr(ws), ws.numel(), _stream()),
-           "svf_sparse_ffn")
+# svf_sparse_ffn(shape, x, w_gate, w_up, w_down_t, y, ws, b_gate=None, b_up=None, b_down=None, active=None)
+svf_sparse_ffn = _native_call("svf_sparse_ffn")
 
 
 # ---- expert skipping, acceptance / resampling (argument marshalling only) -----------------------
 
-def svf_moe_skip(w, m, beta, n_skip, keep_mask):
-    T, k = w.shape
-    _check(lib().svf_moe_skip(_ptr(w), T, k, int(m), _ptr(beta), _ptr(n_skip), _ptr(keep_mask), _stream()), "svf_moe_skip")
+# svf_moe_skip(w, m, beta, n_skip, keep_mask)
+svf_moe_skip = _native_call("svf_moe_skip")
 
 
 def svf_moe_calibrate(w_cal, beta, ws=None):
@@ -374,8 +379,6 @@ def svf_moe_calibrate(w_cal, beta, ws=None):
     _check(lib().svf_moe_calibrate(_ptr(w_cal), T, k, _ptr(beta), _ptr(ws), ws.numel(), _stream()), "svf_moe_calibrate")
 
 
-def svf_accept_resample(p_target, p_draft, draft_tokens, u_accept, u_resample, n_accepted, resampled):
-    B, gamma, V = p_target.shape
-    _check(lib().svf_accept_resample(_ptr(p_target), _ptr(p_draft), _ptr(draft_tokens), _ptr(u_accept), _ptr(u_resample),
-                                     B, gamma, V, _ptr(n_accepted), _ptr(resampled), _stream()), "svf_accept_resample")
+# svf_accept_resample(p_target, p_draft, draft_tokens, u_accept, u_resample, n_accepted, resampled)
+svf_accept_resample = _native_call("svf_accept_resample")
 

@@ -1,4 +1,4 @@
-"""Builds libsvf.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libsvf.so (HIP, gfx950) and the Python calls module _svf_calls.so in-tree."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libsvf.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_svf_calls.so")
 
 SOURCES = ["svf_api.hip", "block_reps.hip", "score_select.hip", "verify_attn_valu.hip", "verify_attn_mfma.hip",
            "analytics.hip", "retrieval_variants.hip", "sparse_ffn.hip", "svf_ffn_api.hip", "spec_rules.hip"]
@@ -61,7 +62,29 @@ def build_lib(verbose: bool = True) -> str:
             size = int(l.split("ScratchSize [bytes/lane]:")[1].split()[0])
             if size != 0:
                 raise RuntimeError(f"{name} uses {size} bytes of scratch memory per lane")
+    build_calls(verbose)
     return LIB_PATH
+
+
+def build_calls(verbose: bool = True) -> str:
+    """Compile csrc/py_calls.cpp (host code only) against libsvf.so and torch; returns its path."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    includes = ["-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+    for d in include_paths("cuda"):
+        includes += ["-isystem", d]
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", *includes,
+           os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS_PATH, "-L", PKG_DIR, "-lsvf", "-Wl,-rpath,$ORIGIN",
+           "-L", torch_lib, "-lc10", "-lc10_hip", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + "\n" + res.stderr)
+    return CALLS_PATH
 
 
 if __name__ == "__main__":
