@@ -157,7 +157,7 @@ int svf_score_select(const svf_shape_t* shape, const void* q, const float* reps,
  * several splits (long budgets), each split's output, normalised by its own denominator, is
  * rounded to bf16 once before the splits are summed in fp32 in split order.  The result is the
  * same bits from call to call and does not depend on how the workgroups happen to be scheduled.
- * The fp32 path and other head dimensions keep everything in fp32.
+ * The fp32 path and head dimension 64 keep everything in fp32 (weights of 24 bits, fp32 sums).
  */
 int svf_verify_attn(const svf_shape_t* shape, const void* q, const void* K, const void* V,
                     const int32_t* block_table, const int32_t* seq_lens,
@@ -196,7 +196,7 @@ int svf_verify_attn_static_ws(const svf_shape_t* shape, const void* q, const voi
  *   SVF_STEP_ANCHOR call on this `ws`, contents unchanged (K, V, q, the drafts and the outputs
  *   may differ: the layers of one verification step share their page table).  A broken promise
  *   gives attention over the anchor call's rows, never an access outside the pools it was built
- *   for.  Shapes that have no gather list (anything but bf16 with d = 128 and block and page
+ *   for.  Shapes that have no gather list (anything but bf16 with block and page
  *   sizes that are multiples of four, or more than 1024 kept blocks) take the SVF_STEP_REUSE path.
  * Any other mode: SVF_ERR_SHAPE.
  */

@@ -108,9 +108,9 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   size_t off = 0;
   pl.off_tickets = off;
   off += align_up(pl.groups * kTicketWords * sizeof(uint64_t));
-  // partial outputs: fp32 (vector-ALU kernel) or bf16 (matrix-core kernels) per split and row
+  // partial outputs: fp32 (vector-ALU kernel, matrix-core kernels at d = 64) or bf16 (d = 128) per split and row
   pl.off_o = off;
-  off += align_up(pairs * pl.n_splits * pl.Mpad * s.d * (pl.mfma ? sizeof(uint16_t) : sizeof(float)));
+  off += align_up(pairs * pl.n_splits * pl.Mpad * s.d * (pl.mfma && s.d == 128 ? sizeof(uint16_t) : sizeof(float)));
   // maxima and denominators: two fp32 arrays for the vector-ALU kernel; 16 bytes per split and row
   // for the matrix-core kernels (a tagged record)
   pl.off_m = off;

@@ -98,8 +98,8 @@ struct AttnParams {
   float* lse;                  // may be null
   // split partials.  Vector-ALU kernel: fp32 unnormalised outputs [B][Hkv][S][Mpad][d] with their
   // running maxima (log2 domain) and denominators in part_m / part_l.  Matrix-core kernels: outputs
-  // normalised by their own denominator and rounded to bf16, [B][Hkv][S][Mpad][d] 2-byte elements
-  // in part_o, and 16-byte records (maximum, tag, denominator, tag) in part_rec, valid for the call
+  // normalised by their own denominator, [B][Hkv][S][Mpad] rows of 256 bytes (d = 128: rounded to
+  // bf16, d = 64: fp32) in part_o, and 16-byte records (maximum, tag, denominator, tag) in part_rec, valid for the call
   // whose tag both halves carry.  part_m and part_rec name the same region.
   float* part_o;
   float* part_m;               // [B][Hkv][S][Mpad]
@@ -254,7 +254,7 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 struct AttnPlan {
   int32_t M, Mpad, n_splits;
   int32_t slice_rows;        // rows of a row group one workgroup merges: ceil(32 / min(n_splits, 16))
-  bool mfma;                 // bf16, d = 128: matrix-core kernel; otherwise the vector-ALU kernel
+  bool mfma;                 // bf16: matrix-core kernel; otherwise the vector-ALU kernel
   bool fused_select;         // anchor layers retrieve inside the attention kernel
   bool gather;               // the shape can use a gather list
   int32_t gather_groups;     // entries per (sequence, KV head): a whole number of 32-token tiles

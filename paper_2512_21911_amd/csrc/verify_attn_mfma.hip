@@ -1,4 +1,4 @@
-// Verification attention, matrix-core kernel: bf16 inputs, head dimension 128 (Sec. 3.1 / 3.3:
+// Verification attention, matrix-core kernel: bf16 inputs, head dimension 128 or 64 (Sec. 3.1 / 3.3:
 // the draft queries attend to the retrieved blocks of their KV head and, through the draft
 // mask, to each other).
 //
@@ -53,6 +53,10 @@
 // group's call counter plus one, kept in the workspace and advanced by the workgroup that
 // arrives last, so the kernel needs no clearing between calls.
 //
+// Measured at D = 64 (three sequences of 5k - 16k tokens, 8 KV heads of 4 query heads, 7 drafts, 24
+// blocks of 64, two anchor and two reuse layers): 262 us with the vector-ALU kernel, its merge kernel
+// and the two retrieval kernels, 41 us with this one, 10 us per launch: latency (9 MB are streamed).
+//
 // Scope of the exchange.  Workgroup ids are mapped so that all splits of a group share id mod 8,
 // which the dispatcher places on one XCD; each workgroup also adds its XCD number to a
 // per-group counter, and only if every arrival so far came from the XCD it runs on does it
@@ -69,10 +73,16 @@ namespace {
 constexpr int kThreads = 512;
 constexpr int kWaves = 8;
 constexpr int kTile = 32;            // tokens per tile
-constexpr int kD = 128;              // head dimension
-constexpr int kRowBytes = kD * 2;    // one bf16 K/V row
-constexpr int kTileBytes = kTile * kRowBytes;          // 8 KB: K (or V) part of a stage
-constexpr int kStageBytes = 2 * kTileBytes;            // K then V
+// Head dimension D = 128 or 64.  A row of a stage is 256 bytes: at D = 128 one K or V row (a stage
+// holds 32 K rows, then 32 V rows), at D = 64 a token's K row and its V row side by side (chunks
+// 0 .. 7 and 8 .. 15 of the sixteen 16-byte chunks), so that one load instruction brings four
+// tokens' keys and values and every swizzle and fragment address is the one of D = 128.
+constexpr int kRowBytes = 256;
+constexpr int kTileBytes = kTile * kRowBytes;          // 8 KB
+template <int D> constexpr int kStageBytes = D == 128 ? 2 * kTileBytes : kTileBytes;
+template <int D> constexpr int kTileLoads = D == 128 ? 16 : 8;   // load instructions of a tile
+constexpr int kScratchBytes = 16 * 1024;               // retrieval: one region for the scratch arrays, one for the page-table row
+// A split's partial row is 256 bytes for both: D = 128 in bf16, D = 64 in fp32.
 constexpr int kMaxTiles = 4;         // tiles a wavefront may own (processed one after the other)
 constexpr int kXcds = 8;
 constexpr float kRescaleGap = 8.0f;  // log2 units the running maximum may lag behind
@@ -130,6 +140,17 @@ template <int E, int KS2>
 __device__ __forceinline__ u32x2 lds_read_vt_piece(uint32_t even, uint32_t odd) {
   constexpr int nt = E >> 1, h = E & 1;
   return lds_read8_tr<64 * (nt & 1) + 128 * ((nt >> 1) ^ h) + h * 8 * kRowBytes + KS2 * 16 * kRowBytes>((nt & 1) ? odd : even);
+}
+// Both k-steps at D = 64: the V row is chunks 8 .. 15, i.e. products nt = 2, 3; x[4 * KS2 + 2 * (nt - 2) + h].
+__device__ __forceinline__ void lds_read_vt64(u32x2 (&x)[8], uint32_t even, uint32_t odd) {
+  x[0] = lds_read_vt_piece<4, 0>(even, odd);
+  x[1] = lds_read_vt_piece<5, 0>(even, odd);
+  x[2] = lds_read_vt_piece<6, 0>(even, odd);
+  x[3] = lds_read_vt_piece<7, 0>(even, odd);
+  x[4] = lds_read_vt_piece<4, 1>(even, odd);
+  x[5] = lds_read_vt_piece<5, 1>(even, odd);
+  x[6] = lds_read_vt_piece<6, 1>(even, odd);
+  x[7] = lds_read_vt_piece<7, 1>(even, odd);
 }
 template <int KS2>
 __device__ __forceinline__ void lds_read_vt(u32x2 (&x)[8], uint32_t even, uint32_t odd) {
@@ -237,21 +258,6 @@ __device__ __forceinline__ void wait_vmcnt_upto24(int n) {
     default: wait_vmcnt<16>(); break;
   }
 }
-// The same for n in 0 .. 16.
-__device__ __forceinline__ void wait_vmcnt_upto16(int n) {
-  switch (n) {
-    case 0: wait_vmcnt<0>(); break;
-    case 2: wait_vmcnt<2>(); break;
-    case 4: wait_vmcnt<4>(); break;
-    case 6: wait_vmcnt<6>(); break;
-    case 8: wait_vmcnt<8>(); break;
-    case 10: wait_vmcnt<10>(); break;
-    case 12: wait_vmcnt<12>(); break;
-    case 14: wait_vmcnt<14>(); break;
-    default: wait_vmcnt<16>(); break;
-  }
-}
-
 // Lane i ^ 4 of every lane i (two row rotations, each written to the banks of four lanes it is
 // right for: banks 0 and 2 take lane i + 4, banks 1 and 3 lane i - 4).
 __device__ __forceinline__ uint32_t swap_lanes_xor4(uint32_t x) {
@@ -263,6 +269,12 @@ __device__ __forceinline__ uint32_t swap_lanes_xor4(uint32_t x) {
 // bits of j go to the top, so that the eight threads that read j = 4c + n (c = 0 .. 7, same n) of a
 // row at once hit eight different 16-byte bank groups.
 __device__ __forceinline__ int parked_position(int j) { return (j >> 2) | ((j & 3) << 3); }
+// Index (in float4) of float4 j of parked row r.  D = 64: sixteen float4 per row, read as j = 2c + n.
+template <int D>
+__device__ __forceinline__ int parked_index(int r, int j) {
+  if constexpr (D == 128) return r * 32 + (parked_position(j) ^ r);
+  else return r * 16 + (((j >> 1) | ((j & 1) << 3)) ^ (r & 15));
+}
 // Lane N of every row of sixteen lanes, to all lanes of that row.
 template <int N>
 __device__ __forceinline__ uint32_t row_lane(uint32_t x) {
@@ -281,13 +293,32 @@ __device__ __forceinline__ void row_lanes_from(uint32_t x, uint32_t (&out)[8]) {
   if constexpr (N > 0) row_lanes_from<B0, N - 1>(x, out);
 }
 
-// The eight 16-byte fragments of a lane's query row, loaded by hand: not valid before a wait of
+// Requests the K and V rows of four tokens (sixteen lanes per token) into one kilobyte of a stage
+// (D = 128: one of its K part and one of its V part).  kb: K row of the group's first token (scalar),
+// dv: from there to the V row (scalar), off: this lane's token within the group in bytes, chunk: which
+// of the sixteen 16-byte chunks of the stage's row this lane fetches.  D = 64: chunks 8 .. 15 are the V row's.
+template <int D>
+__device__ __forceinline__ void request_rows(const char* kb, int64_t dv, uint32_t off, uint32_t chunk, unsigned char* dst) {
+  if constexpr (D == 128) {
+    const uint32_t o = off + (chunk << 4);
+    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + o), SVF_LDS_PTR(dst), 16, 0, 2);
+    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + dv + o), SVF_LDS_PTR(dst + kTileBytes), 16, 0, 2);
+  } else {
+    const char* src = (chunk & 8u) ? kb + dv : kb;
+    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(src + (off + ((chunk & 7u) << 4))), SVF_LDS_PTR(dst), 16, 0, 2);
+  }
+}
+
+// The 16-byte fragments of a lane's query row, loaded by hand: not valid before a wait of
 // the caller's own has covered them and query_fragments_arrived() has been given the registers.
 __device__ __forceinline__ void load_query_fragments(bf16x8 (&qf)[8], const void* row) {
 #define SVF_QFRAG(i)                                                                                   \
   asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qf[i]) : "v"(row), "n"((i) * 32) : "memory")
   SVF_QFRAG(0); SVF_QFRAG(1); SVF_QFRAG(2); SVF_QFRAG(3);
   SVF_QFRAG(4); SVF_QFRAG(5); SVF_QFRAG(6); SVF_QFRAG(7);
+}
+__device__ __forceinline__ void load_query_fragments(bf16x8 (&qf)[4], const void* row) {
+  SVF_QFRAG(0); SVF_QFRAG(1); SVF_QFRAG(2); SVF_QFRAG(3);
 #undef SVF_QFRAG
 }
 __device__ __forceinline__ u32x2 load8_plain(const void* p) {
@@ -309,13 +340,21 @@ __device__ __forceinline__ void query_fragments_arrived(bf16x8 (&qf)[8]) {
                : "memory");
 }
 
+__device__ __forceinline__ void query_fragments_arrived(bf16x8 (&qf)[4]) {
+  asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]) : : "memory");
+}
+
 // One 32-token tile against the workgroup's 32 query rows.  stage: LDS address of the stage;
 // allowed: bit t set = token t of the tile is visible to this lane's row.  Register use is kept
 // low (two wavefronts share a SIMD): fragment addresses are recomputed, K fragments come in two
 // batches of four, the V rows of the second half reuse the registers of the first.
-__device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[8], uint32_t allowed,
+// D = 64: the softmax weights keep their 24 bits (the contract of that head dimension): they enter the
+// second product as the sum of three bf16 values, each the rounding of what the ones before it leave
+// (8 + 8 + 8 bits), and the partials stay in fp32; 16 MFMA per tile, as many as D = 128 has.
+template <int D>
+__device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[D / 16], uint32_t allowed,
                                              bool all_visible, float scale_log2, int l32, int g, float& m_run,
-                                             float& l_run, floatx16 (&oacc)[4]) {
+                                             float& l_run, floatx16 (&oacc)[D / 32]) {
   // K fragment of k-step ks: row l32, 16-byte chunk 2*ks + g at swizzled position
   const uint32_t kbase = stage + l32 * kRowBytes;
   const uint32_t kx = (uint32_t)((g ^ (l32 & 15)) << 4);
@@ -325,7 +364,7 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
   // channels 32*nt + 16*((lane/16)%2) + 4*(lane%4): 16-byte chunk 4*nt + vc, half vh.
   const uint32_t vtok = (uint32_t)(4 * g + ((l32 & 15) >> 2));
   const uint32_t vc = (uint32_t)(2 * ((l32 >> 4) & 1) + ((l32 & 3) >> 1));
-  const uint32_t vbase = stage + kTileBytes + vtok * kRowBytes + ((uint32_t)(l32 & 1) << 3);
+  const uint32_t vbase = stage + (D == 128 ? kTileBytes : 0) + vtok * kRowBytes + ((uint32_t)(l32 & 1) << 3);
   const uint32_t vswz = (vc ^ (vtok & 3u)) << 4;
   const uint32_t v_even = vbase + vswz + ((uint32_t)g << 6), v_odd = vbase + vswz - ((uint32_t)g << 6);
 
@@ -334,7 +373,7 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int half = 0; half < D / 64; ++half) {
     u32x4 kf[4];
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) kf[k4] = lds_read16<0>(kbase + (kx ^ (uint32_t)((4 * half + k4) << 5)));
@@ -346,7 +385,8 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
   }
   // the V^T fragments of the first k-step: in flight while the softmax runs.  x[2 * nt + h]
   u32x2 x[8];
-  lds_read_vt<0>(x, v_even, v_odd);
+  if constexpr (D == 128) lds_read_vt<0>(x, v_even, v_odd);
+  else lds_read_vt64(x, v_even, v_odd);
 
   // online softmax; value v of a lane is token 8*(v/4) + 4*g + v%4 of the tile.
   // Invisible tokens drop out by setting their raw score to -inf (the scale is positive).
@@ -370,7 +410,7 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
       const float alpha = m_new == m_ref ? 1.0f : fast_exp2(m_ref - m_new);   // -inf - finite -> 0
       l_run *= alpha;
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
+      for (int nt = 0; nt < D / 32; ++nt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[nt][v] *= alpha;
     }
@@ -386,39 +426,66 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
     ls += pe[v];
   }
   l_run += ls;
-  bf16x8 pf[2];
+  bf16x8 pf[2], pf_mid[2], pf_low[2];
 #pragma unroll
   for (int ks2 = 0; ks2 < 2; ++ks2) {
-    u32x4 w;
+    u32x4 w, mid, low;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = pack_bf16(pe[8 * ks2 + 2 * j], pe[8 * ks2 + 2 * j + 1]);
+    for (int j = 0; j < 4; ++j) {
+      const float a = pe[8 * ks2 + 2 * j], c = pe[8 * ks2 + 2 * j + 1];
+      w[j] = pack_bf16(a, c);
+      if constexpr (D == 64) {
+        const float ra = a - bf16_lo(w[j]), rc = c - bf16_hi(w[j]);            // (exact)
+        mid[j] = pack_bf16(ra, rc);
+        low[j] = pack_bf16(ra - bf16_lo(mid[j]), rc - bf16_hi(mid[j]));
+      }
+    }
     pf[ks2] = __builtin_bit_cast(bf16x8, w);
+    if constexpr (D == 64) {
+      pf_mid[ks2] = __builtin_bit_cast(bf16x8, mid);
+      pf_low[ks2] = __builtin_bit_cast(bf16x8, low);
+    }
   }
 
   // O^T += V^T P^T : A row m = lane mod 32 of product nt is channel 32*nt + m; k-slot e of lane
   // group g is token 16*ks2 + 8*(e/4) + 4*g + e%4.  x[2*nt + h] holds k-slots 4*h .. 4*h+3.
 #pragma unroll
   for (int ks2 = 0; ks2 < 2; ++ks2) {
-    if (ks2 == 1) lds_read_vt<1>(x, v_even, v_odd);
-    lds_wait8(x);
+    if constexpr (D == 128)
+      if (ks2 == 1) lds_read_vt<1>(x, v_even, v_odd);
+    if (D == 128 || ks2 == 0) lds_wait8(x);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const u32x4 w = {x[2 * nt][0], x[2 * nt][1], x[2 * nt + 1][0], x[2 * nt + 1][1]};
+    for (int nt = 0; nt < D / 32; ++nt) {
+      const int e = (D == 64 ? 4 * ks2 : 0) + 2 * nt;
+      const u32x4 w = {x[e][0], x[e][1], x[e + 1][0], x[e + 1][1]};
       oacc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), pf[ks2], oacc[nt], 0, 0, 0);
+      if constexpr (D == 64) {
+        oacc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), pf_mid[ks2], oacc[nt], 0, 0, 0);
+        oacc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), pf_low[ks2], oacc[nt], 0, 0, 0);
+      }
     }
   }
 }
 
+// Value c of a 16-byte (or 8-byte) chunk of a partial row: bf16 at D = 128, fp32 at D = 64.
+template <int D, typename Chunk>
+__device__ __forceinline__ float chunk_value(const Chunk& t, int c) {
+  if constexpr (D == 64) return __uint_as_float(t[c]);
+  else return (c & 1) ? bf16_hi(t[c >> 1]) : bf16_lo(t[c >> 1]);
+}
+
 // Merge of a group's split partials by one workgroup (512 threads), used behind the rows
-// kernel: sixteen threads per row, 8 channels each.  All splits are read in split order; the
+// kernel: sixteen threads per row, D / 16 channels each.  All splits are read in split order; the
 // loads of kMergeBatch splits are in flight before the first is used.  A split's (m, l) is
 // loaded by one of the row's sixteen threads and handed round inside the row.
+template <int D>
 __device__ __forceinline__ void merge_splits(const AttnParams& p, int64_t g_row, int64_t orow, bool row_ok, int cg) {
   constexpr int kMergeBatch = 8;
-  const uint16_t* part_o = reinterpret_cast<const uint16_t*>(p.part_o);
-  float acc[8];
+  constexpr int CH = D / 16;
+  const char* part_o = reinterpret_cast<const char*>(p.part_o);
+  float acc[CH];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+  for (int c = 0; c < CH; ++c) acc[c] = 0.f;
   float m_acc = -INFINITY, l_acc = 0.f;
   for (int s0 = 0; s0 < p.n_splits; s0 += kMergeBatch) {
     u32x4 t[kMergeBatch];
@@ -432,7 +499,7 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, int64_t g_row,
     for (int u = 0; u < kMergeBatch; ++u) {
       // entries past the last split (index clamped) get weight 0 below
       const int64_t pr = g_row + (int64_t)min(s0 + u, p.n_splits - 1) * p.Mpad;
-      t[u] = *reinterpret_cast<const u32x4*>(part_o + pr * kD + cg * 8);
+      t[u] = *reinterpret_cast<const u32x4*>(part_o + pr * kRowBytes + cg * 16);
     }
     uint32_t mbits[kMergeBatch], lbits[kMergeBatch];
     row_lanes_upto<kMergeBatch - 1>(ml[0], mbits);
@@ -448,38 +515,40 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, int64_t g_row,
     const float fa = m_acc == -INFINITY ? 0.f : fast_exp2(m_acc - mb);
     l_acc *= fa;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] *= fa;
+    for (int c = 0; c < CH; ++c) acc[c] *= fa;
 #pragma unroll
     for (int u = 0; u < kMergeBatch; ++u) {
       // weight of split s: exp2(m_s - m) * l_s, applied to its normalised output
       const float w = pm[u] != -INFINITY ? fast_exp2(pm[u] - mb) * pl[u] : 0.f;
       l_acc += w;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        acc[2 * c] += w * bf16_lo(t[u][c]);
-        acc[2 * c + 1] += w * bf16_hi(t[u][c]);
-      }
+      for (int c = 0; c < CH; ++c) acc[c] += w * chunk_value<D>(t[u], c);
     }
     m_acc = mb;
   }
   if (row_ok) {
     const float inv = l_acc > 0.f ? 1.0f / l_acc : 0.f;      // a row that saw no key at all: zero, lse = -inf
-    u32x4 o;
+    __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(p.out) + orow * D + cg * CH;
+    if constexpr (D == 128) {
+      u32x4 o;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) o[c] = pack_bf16(acc[2 * c] * inv, acc[2 * c + 1] * inv);
-    store_coherent16(static_cast<__hip_bfloat16*>(p.out) + orow * kD + cg * 8, o);
+      for (int c = 0; c < 4; ++c) o[c] = pack_bf16(acc[2 * c] * inv, acc[2 * c + 1] * inv);
+      store_coherent16(dst, o);
+    } else {
+      store_coherent8(dst, u32x2{pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)});
+    }
     if (p.lse && cg == 0) p.lse[orow] = (m_acc + log2f(l_acc)) * 0.6931471805599453f;
   }
 }
 
 // ---- merging the splits of a group ----------------------------------------------------------------
-// A split's partial of a row is its output normalised by its own denominator (bf16) and a 16-byte
+// A split's partial of a row is its output normalised by its own denominator (256 bytes) and a 16-byte
 // record (maximum, tag, denominator, tag); the record is written after the output has been
 // acknowledged, so a record whose two tags are this call's vouches for the output beside it.
 // Merge rule (log-sum-exp), the same sums in the same order whoever computes them: splits in
 // order, in batches of eight, each batch brought to the running maximum.
-// The merging threads are two wavefronts (128 threads): CH channels per thread (4 or 8), 128 / CH
-// threads per row, 4 or 8 rows per pass.
+// The merging threads are two wavefronts (128 threads): CH channels per thread (4 or 8; at D = 64 always
+// 4), D / CH threads per row (at least sixteen), 4 or 8 rows per pass.
 
 // Device-scope loads of what other workgroups have written through (they bypass the per-CU cache;
 // an L2 serves them, also for lines that a workgroup on another XCD has written through).  Issued
@@ -512,19 +581,21 @@ __device__ __forceinline__ void chunks_wait(T (&o)[8]) {
                :
                : "memory");
 }
-template <int CH> struct ChunkOf;
-template <> struct ChunkOf<4> { typedef u32x2 type; };
-template <> struct ChunkOf<8> { typedef u32x4 type; };
+template <int CH, int D> struct ChunkOf;           // CH channels of a partial row
+template <> struct ChunkOf<4, 128> { typedef u32x2 type; };
+template <> struct ChunkOf<8, 128> { typedef u32x4 type; };
+template <> struct ChunkOf<4, 64> { typedef u32x4 type; };
+template <int D> constexpr int kWideMerge = D == 128 ? 8 : 4;   // channels per thread with eight rows per pass
 
 constexpr int kMergeThreads = 128;          // wavefronts kMergeWave0 and kMergeWave0 + 1
 constexpr int kMergeWave0 = 4;
 constexpr int kLastResortPolls = 1 << 16;   // for waits that are known to end: every writer has arrived
 
 // One merging thread's view of one pass over rows r0 .. r0 + rows per pass.
-template <int CH>
+template <int CH, int D>
 struct MergeLane {
-  typedef typename ChunkOf<CH>::type Chunk;
-  static constexpr int kLanesPerRow = kD / CH;                  // 32 or 16
+  typedef typename ChunkOf<CH, D>::type Chunk;
+  static constexpr int kLanesPerRow = D / CH;                   // 32 or 16
   static constexpr int kRowsPerPass = kMergeThreads / kLanesPerRow;
   int row;            // row of the row group (clamped to a valid one), cl: which CH channels
   int cl;
@@ -543,7 +614,7 @@ struct MergeLane {
 };
 
 // This workgroup's own partial of the rows it merges, left in LDS by the threads that formed it:
-// [rows][kD] bf16, then (maximum, denominator) per row.  own_split < 0: nothing is taken from LDS.
+// [rows][256 bytes], then (maximum, denominator) per row.  own_split < 0: nothing is taken from LDS.
 struct OwnRows {
   const unsigned char* o;
   const float* ml;
@@ -557,8 +628,8 @@ struct OwnRows {
 // watch / watched_for (optional): the LDS word at address `watch` is read along with every poll;
 // *watch_hit tells whether it was seen to hold `watched_for` (what the caller waits for next: by
 // the time the records are in, it has usually happened, and no further look is needed).
-template <int CH>
-__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH>& L, int64_t g_row, int c0, uint32_t tag,
+template <int CH, int D>
+__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, D>& L, int64_t g_row, int c0, uint32_t tag,
                                              int budget, int own_split, uint32_t watch = 0, uint32_t watched_for = 0,
                                              bool* watch_hit = nullptr) {
   const int S = p.n_splits;
@@ -582,8 +653,8 @@ __device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH>&
 // Requests the outputs of splits c0 + B0 .. c0 + B0 + 7 of the lane's row (past the last split: the
 // batch's first split again, weight 0 later; the own split's is fetched like the others even when
 // LDS holds it: one address chain, a step of one split's partial at a time).
-template <int CH, int B0>
-__device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkOf<CH>::type (&t)[8], int pair, uint32_t voff,
+template <int CH, int D, int B0>
+__device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkOf<CH, D>::type (&t)[8], int pair, uint32_t voff,
                                             int c0) {
   const int S = p.n_splits;
   const uint64_t step = (uint64_t)p.Mpad * kRowBytes;
@@ -597,18 +668,13 @@ __device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkO
   }
 }
 
-template <int CH>
-__device__ __forceinline__ float chunk_value(const typename ChunkOf<CH>::type& t, int c) {
-  return (c & 1) ? bf16_hi(t[c >> 1]) : bf16_lo(t[c >> 1]);
-}
-
 // Splits c0 + B0 .. c0 + B0 + 7 into the running merge, in two steps.  batch_weights() needs the
 // records only (and the own split's maximum and denominator from LDS): it runs while the outputs
 // are being fetched, and is free of branches, because the compiler does not know that the
 // registers of a hand-issued load are in flight (see merge_fetch_weigh).  m_before: the running
 // maximum in front of the batch.
-template <int CH, int B0>
-__device__ __forceinline__ void batch_weights(MergeLane<CH>& L, int c0, const OwnRows& own, float m_before, float (&w)[8],
+template <int CH, int D, int B0>
+__device__ __forceinline__ void batch_weights(MergeLane<CH, D>& L, int c0, const OwnRows& own, float m_before, float (&w)[8],
                                               float& fa, float& mb_out) {
   const int ou = own.split - c0 - B0;                  // (uniform) the own split's place in this batch
   const bool from_lds = ou >= 0 && ou < 8;
@@ -616,8 +682,8 @@ __device__ __forceinline__ void batch_weights(MergeLane<CH>& L, int c0, const Ow
   // that split's record, its output in place of what is fetched (the reads are unconditional: own.o
   // and own.ml always point into LDS)
   const int orow = min(max(L.row - own.lo, 0), 31);
-  const typename ChunkOf<CH>::type oc =
-      *reinterpret_cast<const typename ChunkOf<CH>::type*>(own.o + orow * kRowBytes + L.cl * (CH * 2));
+  const typename ChunkOf<CH, D>::type oc =
+      *reinterpret_cast<const typename ChunkOf<CH, D>::type*>(own.o + orow * kRowBytes + L.cl * (int)sizeof(typename ChunkOf<CH, D>::type));
   const uint32_t om = __float_as_uint(own.ml[2 * orow]), ol = __float_as_uint(own.ml[2 * orow + 1]);
   L.own_chunk = (B0 == 0 || from_lds) ? oc : L.own_chunk;        // (the own split lies in one batch at most)
   const bool here = from_lds && (L.cl & 15) == B0 + ou;
@@ -640,8 +706,8 @@ __device__ __forceinline__ void batch_weights(MergeLane<CH>& L, int c0, const Ow
   mb_out = mb;
 }
 
-template <int CH, int B0>
-__device__ __forceinline__ void batch_accumulate(MergeLane<CH>& L, typename ChunkOf<CH>::type (&t)[8], int c0, const OwnRows& own,
+template <int CH, int D, int B0>
+__device__ __forceinline__ void batch_accumulate(MergeLane<CH, D>& L, typename ChunkOf<CH, D>::type (&t)[8], int c0, const OwnRows& own,
                                                  const float (&w)[8], float fa, float mb) {
   const int ou = own.split - c0 - B0;
   if (ou >= 0 && ou < 8) {
@@ -666,15 +732,15 @@ __device__ __forceinline__ void batch_accumulate(MergeLane<CH>& L, typename Chun
   for (int u = 0; u < 8; ++u) {
     L.l_acc += w[u];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) L.acc[c] += w[u] * chunk_value<CH>(t[u], c);
+    for (int c = 0; c < CH; ++c) L.acc[c] += w[u] * chunk_value<D>(t[u], c);
   }
   L.m_acc = mb;
 }
 
-template <int CH>
-__device__ __forceinline__ void init_lane(MergeLane<CH>& L, int mt, int r0, int hi) {
-  const int rr = r0 + mt / MergeLane<CH>::kLanesPerRow;
-  L.cl = mt % MergeLane<CH>::kLanesPerRow;
+template <int CH, int D>
+__device__ __forceinline__ void init_lane(MergeLane<CH, D>& L, int mt, int r0, int hi) {
+  const int rr = r0 + mt / MergeLane<CH, D>::kLanesPerRow;
+  L.cl = mt % MergeLane<CH, D>::kLanesPerRow;
   L.active = rr < hi && rr < 32;
   L.row = L.active ? rr : r0;
 #pragma unroll
@@ -684,22 +750,22 @@ __device__ __forceinline__ void init_lane(MergeLane<CH>& L, int mt, int r0, int 
 }
 
 // The merged row goes out (CH channels per thread) with its log-sum-exp.
-template <int CH>
-__device__ __forceinline__ void merged_row_address(const AttnParams& p, MergeLane<CH>& L, int row0, int64_t orow_pair) {
+template <int CH, int D>
+__device__ __forceinline__ void merged_row_address(const AttnParams& p, MergeLane<CH, D>& L, int row0, int64_t orow_pair) {
   const int grow = row0 + L.row;
   const int oi = (int)(((uint64_t)(uint32_t)grow * p.g_magic) >> 32), oj = grow - oi * p.G;
   L.orow = (L.active && grow < p.M) ? orow_pair + (int64_t)oi * p.Hq + oj : -1;
   asm volatile("" : "+v"(L.orow));                       // worked out here, not behind the wait for the outputs
 }
-template <int CH>
-__device__ __forceinline__ void store_merged(const AttnParams& p, const MergeLane<CH>& L) {
+template <int CH, int D>
+__device__ __forceinline__ void store_merged(const AttnParams& p, const MergeLane<CH, D>& L) {
   const int64_t orow = L.orow;
   if (orow < 0) return;
   const float inv = L.l_acc > 0.f ? __builtin_amdgcn_rcpf(L.l_acc) : 0.f;   // a row that saw no key at all: zero, lse = -inf
-  typename ChunkOf<CH>::type o;
+  typename ChunkOf<CH, 128>::type o;                     // CH bf16 values
 #pragma unroll
   for (int c = 0; c < CH / 2; ++c) o[c] = pack_bf16(L.acc[2 * c] * inv, L.acc[2 * c + 1] * inv);
-  *reinterpret_cast<typename ChunkOf<CH>::type*>(static_cast<__hip_bfloat16*>(p.out) + orow * kD + L.cl * CH) = o;
+  *reinterpret_cast<typename ChunkOf<CH, 128>::type*>(static_cast<__hip_bfloat16*>(p.out) + orow * D + L.cl * CH) = o;
   if (p.lse && L.cl == 0) p.lse[orow] = (L.m_acc + log2f(L.l_acc)) * 0.6931471805599453f;
 }
 
@@ -715,42 +781,42 @@ __device__ __forceinline__ void chunks_wait16(T (&a)[8], T (&b)[8]) {
 // Splits c0 .. c0 + 15 of the lane's row, once their records are in (poll_records): fetches their
 // outputs and, while those are on their way, forms the weights.  The own split's rows, if LDS holds
 // them, must be complete.
-template <int CH>
-__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH>& L, int pair, int row0, int c0,
+template <int CH, int D>
+__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH, D>& L, int pair, int row0, int c0,
                                                   const OwnRows& own, int64_t orow_pair) {
   const int S = p.n_splits;
-  const uint32_t voff = (uint32_t)(((row0 + L.row) * kD + L.cl * CH) * 2);
+  const uint32_t voff = (uint32_t)((row0 + L.row) * kRowBytes + L.cl * (int)sizeof(typename MergeLane<CH, D>::Chunk));
   // (straight-line code between every hand-issued load and its wait: the compiler does not know
   // that the registers are still in flight, and a copy it places at a branch or a join in between
   // would copy what was there before)
   if (c0 + 8 < S) {
-    fetch_batch<CH, 0>(p, L.t0, pair, voff, c0);
-    fetch_batch<CH, 8>(p, L.t1, pair, voff, c0);
-    batch_weights<CH, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
-    batch_weights<CH, 8>(L, c0, own, L.mb0, L.w1, L.fa1, L.mb1);
+    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, c0);
+    fetch_batch<CH, D, 8>(p, L.t1, pair, voff, c0);
+    batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
+    batch_weights<CH, D, 8>(L, c0, own, L.mb0, L.w1, L.fa1, L.mb1);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait16(L.t0, L.t1);
   } else {
-    fetch_batch<CH, 0>(p, L.t0, pair, voff, c0);
-    batch_weights<CH, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
+    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, c0);
+    batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait(L.t0);
   }
 }
-template <int CH>
-__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH>& L, int c0, const OwnRows& own) {
-  batch_accumulate<CH, 0>(L, L.t0, c0, own, L.w0, L.fa0, L.mb0);
-  if (c0 + 8 < p.n_splits) batch_accumulate<CH, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
+template <int CH, int D>
+__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH, D>& L, int c0, const OwnRows& own) {
+  batch_accumulate<CH, D, 0>(L, L.t0, c0, own, L.w0, L.fa0, L.mb0);
+  if (c0 + 8 < p.n_splits) batch_accumulate<CH, D, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
 }
 
 // Merges rows lo <= r < hi of the row group (all passes, all splits) and writes them out.  Returns
 // false for the whole wavefront, with nothing of the current pass written, when a record was still
 // missing after `budget` polls.  Called by the two merging wavefronts, each for itself.
-template <int CH>
+template <int CH, int D>
 __device__ __forceinline__ bool merge_rows(const AttnParams& p, int lo, int hi, int budget, uint32_t tag, int pair, int row0,
                                            int64_t orow_pair, int mt, const OwnRows& own) {
-  for (int r0 = lo; r0 < hi; r0 += MergeLane<CH>::kRowsPerPass) {
-    MergeLane<CH> L;
+  for (int r0 = lo; r0 < hi; r0 += MergeLane<CH, D>::kRowsPerPass) {
+    MergeLane<CH, D> L;
     init_lane(L, mt, r0, hi);
     if (!__any(L.active)) continue;
     for (int c0 = 0; c0 < p.n_splits; c0 += 16) {
@@ -873,7 +939,7 @@ __device__ __forceinline__ void workgroup_select(const uint32_t* keys, SelectScr
 // the workgroups of an exchange group share the scoring: each scores every n_splits-th pass of 64
 // blocks and publishes its keys as 64-bit words (key, tag of this call); the others poll those
 // words.  The tag is a per-group counter in the workspace that moves on by one per call.
-constexpr int kScoreChunks = kD / (4 * kScoreLanes);   // 16-byte chunks of a representative per lane
+template <int D> constexpr int kScoreChunks = D / (4 * kScoreLanes);   // 16-byte chunks of a representative per lane
 constexpr int kScoreBatch = 8;                         // passes (of 64 blocks) in flight
 
 // Polls a workgroup spends waiting for the other workgroups of its group, from the high half of
@@ -894,6 +960,7 @@ __device__ __forceinline__ void finish_call(const AttnParams& p, int64_t group, 
 }
 
 // What a retrieving workgroup loads up front, together with its query loads.
+template <int D>
 struct RetrievalLoads {
   QueryHeads<__hip_bfloat16> q0h;       // channel tid mod 128 of the group's first-draft query heads
   const __hip_bfloat16* q0ch;
@@ -904,36 +971,39 @@ struct RetrievalLoads {
   bool share_scores;
   uint64_t epoch_word;                  // the group's call counter (low half) and wait budget (high half) as loaded
   int rot;                              // first pass of a workgroup that scores alone
-  float4 r[kScoreBatch][kScoreChunks];  // first batch of representative rows
+  float4 r[kScoreBatch][kScoreChunks<D>];  // first batch of representative rows
 };
 
+template <int D>
 __device__ __forceinline__ const float* reps_lane_ptr(const AttnParams& p, int pair, int tid) {
-  return p.reps + (int64_t)pair * p.nb_max * kD + (tid % kScoreLanes) * 4;
+  return p.reps + (int64_t)pair * p.nb_max * D + (tid % kScoreLanes) * 4;
 }
 
 // Loads the representative rows of passes first, first + stride, ... into r (pass = 64 blocks).
+template <int D>
 __device__ __forceinline__ void load_score_batch(const AttnParams& p, const float* rp, int jrow, int first, int stride,
-                                                 bool rotate, int rot, float4 (&r)[kScoreBatch][kScoreChunks]) {
+                                                 bool rotate, int rot, float4 (&r)[kScoreBatch][kScoreChunks<D>]) {
 #pragma unroll
   for (int u = 0; u < kScoreBatch; ++u) {
     const int ps = first + stride * (rotate ? (u + rot) % kScoreBatch : u);
     if (ps * 64 < p.nb_max) {
-      const float* row = rp + (int64_t)min(ps * 64 + jrow, p.nb_max - 1) * kD;
+      const float* row = rp + (int64_t)min(ps * 64 + jrow, p.nb_max - 1) * D;
 #pragma unroll
-      for (int i = 0; i < kScoreChunks; ++i) r[u][i] = *reinterpret_cast<const float4*>(row + i * 4 * kScoreLanes);
+      for (int i = 0; i < kScoreChunks<D>; ++i) r[u][i] = *reinterpret_cast<const float4*>(row + i * 4 * kScoreLanes);
     }
   }
 }
 
-__device__ __forceinline__ RetrievalLoads issue_retrieval_loads(const AttnParams& p, int b, int h, int pair, int split,
+template <int D>
+__device__ __forceinline__ RetrievalLoads<D> issue_retrieval_loads(const AttnParams& p, int b, int h, int pair, int split,
                                                                 int xgroup, int rot, int tid, int vzero) {
-  RetrievalLoads R;
+  RetrievalLoads<D> R;
   // first in the queue, so that nothing slower has to come back before it
-  R.q0ch = static_cast<const __hip_bfloat16*>(p.q) + ((int64_t)b * p.gamma * p.Hq + (int64_t)h * p.G) * kD + (tid & (kD - 1));
-  // (only the first kD threads use theirs.  A workgroup can hand the memory pipeline one load
+  R.q0ch = static_cast<const __hip_bfloat16*>(p.q) + ((int64_t)b * p.gamma * p.Hq + (int64_t)h * p.G) * D + (tid & (D - 1));
+  // (only the first D threads use theirs.  A workgroup can hand the memory pipeline one load
   // instruction per ~20 cycles, whatever its size, so the instructions issued up front, not their
   // bytes, set how soon the retrieval starts.)
-  if (tid < kD) R.q0h = load_query_heads<__hip_bfloat16>(R.q0ch, p.G, kD);
+  if (tid < D) R.q0h = load_query_heads<__hip_bfloat16>(R.q0ch, p.G, D);
   // the page-table row goes to LDS while the scores are computed, so that turning kept blocks
   // into addresses afterwards costs no further trip to memory
   R.table_row = p.table + (int64_t)b * p.kv.max_pages;
@@ -963,11 +1033,12 @@ __device__ __forceinline__ RetrievalLoads issue_retrieval_loads(const AttnParams
 }
 
 // The first batch of representative rows: this workgroup's share, or the first passes of all.
-__device__ __forceinline__ void issue_first_score_batch(const AttnParams& p, RetrievalLoads& R, int pair, int split,
+template <int D>
+__device__ __forceinline__ void issue_first_score_batch(const AttnParams& p, RetrievalLoads<D>& R, int pair, int split,
                                                         int tid) {
-  const float* rp = reps_lane_ptr(p, pair, tid);
-  if (R.share_scores) load_score_batch(p, rp, tid / kScoreLanes, split, p.n_splits, false, R.rot, R.r);
-  else load_score_batch(p, rp, tid / kScoreLanes, 0, 1, true, R.rot, R.r);
+  const float* rp = reps_lane_ptr<D>(p, pair, tid);
+  if (R.share_scores) load_score_batch<D>(p, rp, tid / kScoreLanes, split, p.n_splits, false, R.rot, R.r);
+  else load_score_batch<D>(p, rp, tid / kScoreLanes, 0, 1, true, R.rot, R.r);
 }
 
 struct Retrieved {
@@ -982,20 +1053,20 @@ struct Retrieved {
 // into them before its own next barrier.  L_raw: the sequence length as loaded (per lane, not yet uniform).
 // meanwhile(): work of the caller's that may run behind the first barrier (what the caller wrote
 // to its stages before the call is visible there) while the other workgroups' keys are on their way.
-template <typename Meanwhile>
-__device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, RetrievalLoads& R, unsigned char* smem,
+template <int D, typename Meanwhile>
+__device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, RetrievalLoads<D>& R, unsigned char* smem,
                                                      int32_t* s_sel, int* s_exchange_failed, int L_raw, int pair,
                                                      int split, int xgroup, int tid, int lane, int wave,
                                                      Meanwhile&& meanwhile) {
-  int32_t* s_table = reinterpret_cast<int32_t*>(smem + kStageBytes);
+  int32_t* s_table = reinterpret_cast<int32_t*>(smem + kScratchBytes);
   float* s_q0 = reinterpret_cast<float*>(smem);
-  uint32_t* s_keys = reinterpret_cast<uint32_t*>(smem + kD * 4);
-  SelectScratch* s_sc = reinterpret_cast<SelectScratch*>(smem + kD * 4 + kMaxSelectBlocks * 4);
+  uint32_t* s_keys = reinterpret_cast<uint32_t*>(smem + D * 4);
+  SelectScratch* s_sc = reinterpret_cast<SelectScratch*>(smem + D * 4 + kMaxSelectBlocks * 4);
   const int sub = tid % kScoreLanes, jrow = tid / kScoreLanes;
-  const float* rp = reps_lane_ptr(p, pair, tid);
+  const float* rp = reps_lane_ptr<D>(p, pair, tid);
   uint64_t* const xk = p.xkeys + (int64_t)xgroup * p.nb_max;
 
-  if (tid < kD) s_q0[tid] = mean_query_channel<__hip_bfloat16>(R.q0h, R.q0ch, p.G, kD);
+  if (tid < D) s_q0[tid] = mean_query_channel<__hip_bfloat16>(R.q0h, R.q0ch, p.G, D);
   for (int i = tid; i < 4 * 256; i += kThreads) (&s_sc->hist[0][0])[i] = 0;
   if (tid == 0) *s_exchange_failed = 0;
   if (R.table_in_lds) {
@@ -1020,9 +1091,9 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
   out.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)R.epoch_word) + 1u;
   const uint32_t tag = out.tag;
   const int poll_budget = wait_polls_of(__builtin_amdgcn_readfirstlane((int)(uint32_t)(R.epoch_word >> 32)));
-  float4 qv[kScoreChunks];
+  float4 qv[kScoreChunks<D>];
 #pragma unroll
-  for (int i = 0; i < kScoreChunks; ++i) qv[i] = *reinterpret_cast<const float4*>(s_q0 + sub * 4 + i * 4 * kScoreLanes);
+  for (int i = 0; i < kScoreChunks<D>; ++i) qv[i] = *reinterpret_cast<const float4*>(s_q0 + sub * 4 + i * 4 * kScoreLanes);
   // scores the rows in R.r (passes first, first + stride, ...): keys go to LDS and, if published,
   // tagged to the group's exchange array through a write-through store
   // (publish: also counted into the first histogram of the selection, like the keys that come in
@@ -1032,7 +1103,7 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
     for (int u = 0; u < kScoreBatch; ++u) {
       const int ps = first + stride * (rotate ? (u + R.rot) % kScoreBatch : u);
       if (ps * 64 < nb) {                              // uniform
-        const float v = block_score<kScoreChunks>(R.r[u], qv);
+        const float v = block_score<kScoreChunks<D>>(R.r[u], qv);
         const int j = ps * 64 + jrow;
         if (sub == 0 && j < nb) {
           const uint32_t key = (j < p.n_sink || j >= nb - p.n_local) ? 0xffffffffu : score_key(v + 0.0f);
@@ -1094,7 +1165,7 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
       for (int i = tid; i < 256; i += kThreads) s_sc->hist[0][i] = 0;
     const bool loaded = !R.share_scores;               // the up-front batch was this one
     for (int f = 0; f * 64 < nb; f += kScoreBatch) {
-      if (!(loaded && f == 0)) load_score_batch(p, rp, jrow, f, 1, true, R.rot, R.r);
+      if (!(loaded && f == 0)) load_score_batch<D>(p, rp, jrow, f, 1, true, R.rot, R.r);
       score_batch(f, 1, true, false);
     }
     __syncthreads();                                   // (after an exchange the barrier above has done this)
@@ -1105,8 +1176,9 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
 }
 
 // Gather entry of the four selected-token slots 4e .. 4e+3 from the selection in LDS.
+template <int D>
 __device__ __forceinline__ uint64_t gather_entry_of(const AttnParams& p, const int32_t* s_sel, const Retrieved& rt,
-                                                    const RetrievalLoads& R, int e, int b, int h) {
+                                                    const RetrievalLoads<D>& R, int e, int b, int h) {
   const int slot0 = 4 * e;
   if (slot0 >= rt.cnt * p.block_size) return 0ull;
   const int bi = p.block_shift >= 0 ? slot0 >> p.block_shift : slot0 / p.block_size;
@@ -1157,11 +1229,11 @@ struct TileInfo {
 // cost is its instruction count: 0.5 instead of 1.0 us), four wavefronts instead of eight load
 // query fragments, and the tiles that arrive last are computed by wavefronts that have the SIMD
 // to themselves.  Also (MODE kGather): which of the up-front loads go out first, see below.
-template <int MODE, bool kOneTile>
+template <int D, int MODE, bool kOneTile>
 __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p, int pairs) {
   // one stage per wavefront, plus one for draft tile 0 (its owner then streams its cache tile
   // at the same time); after the main loop stage w becomes wavefront w's fp32 output buffer
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[(kWaves + 1) * kStageBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[(kWaves + 1) * kStageBytes<D>];
   __shared__ float sm_m[kWaves][32];
   __shared__ float sm_l[kWaves][32];
   __shared__ uint32_t sm_pair_valid[kWaves / 2];   // (kOneTile) what wavefront w + 4 fetched: valid slots,
@@ -1212,7 +1284,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int k = 0; k < kTileBytes / 1024; ++k)
-      *reinterpret_cast<u32x4*>(smem + kWaves * kStageBytes + kTileBytes + k * 1024 + lane * 16) = zero;
+      *reinterpret_cast<u32x4*>(smem + kWaves * kStageBytes<D> + (D == 128 ? kTileBytes : 0) + k * 1024 + lane * 16) = zero;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
   const int tiles_d = (p.gamma + kTile - 1) / kTile;           // draft tiles come first
@@ -1233,9 +1305,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     qj = row - qi * p.G;
   }
   // (retrieval only) what the retrieval needs goes out first, ahead of the query fragments
-  RetrievalLoads rl;
+  RetrievalLoads<D> rl;
   if (MODE == kSelect)
-    rl = issue_retrieval_loads(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
+    rl = issue_retrieval_loads<D>(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
   const int32_t* const table_row = p.table + (int64_t)b * p.kv.max_pages;
   // With a gather list the tile loads wait for nothing but their gather entries.  Where a
   // wavefront has one tile (kOneTile) the entries (with the draft mask and the pair's block
@@ -1265,31 +1337,33 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     epoch_raw = load8_plain(p.epochs + group + vzero);
   };
   if (MODE == kGather && kOneTile) request_entries();
-  bf16x8 qf[8];
+  bf16x8 qf[D / 16];
   // A retrieving workgroup has barriers ahead anyway: its 32 query rows come in once (16 bytes
   // per thread) and reach the wavefronts' registers through LDS (chunk c of row r at position
   // c ^ (r & 15)), instead of eight loads per lane in each of the eight wavefronts.
-  unsigned char* const q_stage = smem + 2 * kStageBytes;
+  unsigned char* const q_stage = smem + 2 * kScratchBytes;
+  constexpr int kQChunks = D / 8;        // 16-byte chunks of a query row
   u32x4 qpiece = {0u, 0u, 0u, 0u};
-  if (MODE == kSelect) {
-    const int r = tid >> 4, rrow = row0 + r;
+  if (MODE == kSelect && tid < 32 * kQChunks) {
+    const int r = tid / kQChunks, rrow = row0 + r;
     int ri = 0, rj = 0;
     if (rrow < p.M) {
       ri = (int)(((uint64_t)(uint32_t)rrow * p.g_magic) >> 32);
       rj = rrow - ri * p.G;
     }
     qpiece = *reinterpret_cast<const u32x4*>(static_cast<const __hip_bfloat16*>(p.q) +
-                                             (((int64_t)b * p.gamma + ri) * p.Hq + h * p.G + rj) * kD + (tid & 15) * 8);
-  } else {
+                                             (((int64_t)b * p.gamma + ri) * p.Hq + h * p.G + rj) * D + tid % kQChunks * 8);
+  }
+  if (MODE != kSelect) {
     const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
-                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * kD + g * 8;
+                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
     if (MODE == kGather) {
       // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
       // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
       if (computes) load_query_fragments(qf, qrow);
     } else if (computes) {
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
     }
   }
   if (MODE == kGather && !kOneTile) request_entries();
@@ -1301,18 +1375,17 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   auto request_draft_tile = [&]() {
     const int er = lane >> 4;
     const uint32_t ecx = (uint32_t)((lane & 15) ^ er);
-    const uint32_t drow = (uint32_t)p.Hkv * kRowBytes;
-    const char* kd = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * kRowBytes;
+    const uint32_t drow = (uint32_t)p.Hkv * (D * 2);
+    const char* kd = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * (D * 2);
     const int64_t dvd = Vd - Kd;
-    unsigned char* xs = smem + kWaves * kStageBytes;
+    unsigned char* xs = smem + kWaves * kStageBytes<D>;
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       const int nvn = min(max(p.gamma - 4 * n, 0), 4);     // drafts in slots 4n .. 4n + 3 (uniform)
       if (nvn == 0) continue;
-      const uint32_t off = (uint32_t)(4 * n + min(er, nvn - 1)) * drow + ((ecx ^ (uint32_t)((4 * n) & 15)) << 4);
-      __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kd + off), SVF_LDS_PTR(xs + n * 1024), 16, 0, 2);
-      __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kd + dvd + off), SVF_LDS_PTR(xs + kTileBytes + n * 1024), 16, 0, 2);
-      early_draft_loads += 2;
+      const uint32_t off = (uint32_t)(4 * n + min(er, nvn - 1)) * drow;
+      request_rows<D>(kd, dvd, off, ecx ^ (uint32_t)((4 * n) & 15), xs + n * 1024);
+      early_draft_loads += D == 128 ? 2 : 1;
     }
   };
   // (with a gather list: now, without waiting for the entries)
@@ -1322,9 +1395,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int L = 0;
   if (MODE != kGather) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
   if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
-  if (MODE == kSelect) {
-    const int r = tid >> 4;
-    *reinterpret_cast<u32x4*>(q_stage + r * kRowBytes + (((tid & 15) ^ (r & 15)) << 4)) = qpiece;
+  if (MODE == kSelect && tid < 32 * kQChunks) {
+    const int r = tid / kQChunks;
+    *reinterpret_cast<u32x4*>(q_stage + r * (D * 2) + ((tid % kQChunks ^ (r & (kQChunks - 1))) << 4)) = qpiece;
   }
   int cnt;
   // the group's epoch word: this call's tag (for the key exchange of a retrieval and for the
@@ -1333,11 +1406,11 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   if (MODE == kResolve) epoch_word = p.epochs[group + vzero];
   if (MODE == kSelect) {
     epoch_word = rl.epoch_word;
-    const Retrieved rt = retrieve_blocks(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, group, tid, lane, wave, [&]() {
+    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, group, tid, lane, wave, [&]() {
       if (computes) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-          qf[ks] = *reinterpret_cast<const bf16x8*>(q_stage + l32 * kRowBytes + (((2 * ks + g) ^ (l32 & 15)) << 4));
+        for (int ks = 0; ks < D / 16; ++ks)
+          qf[ks] = *reinterpret_cast<const bf16x8*>(q_stage + l32 * (D * 2) + (((2 * ks + g) ^ (l32 & (kQChunks - 1))) << 4));
       }
     });
     L = rt.L;
@@ -1352,8 +1425,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     }
     __syncthreads();                 // the last reads of the staged page table and the query rows are done
   } else if (MODE == kGather) {
-    // everything requested ahead of the eight query fragments (and of an early draft tile), or everything
-    if (kOneTile && computes) wait_vmcnt_upto24(8 + early_draft_loads); else wait_vmcnt_upto24(early_draft_loads);
+    // everything requested ahead of the query fragments (and of an early draft tile), or everything
+    // (an even count: with one load more in than needed where the number is odd)
+    if (kOneTile && computes) wait_vmcnt_upto24((D / 16 + early_draft_loads) & ~1); else wait_vmcnt_upto24(early_draft_loads & ~1);
     front_loads_arrived(gent_raw, rmask_raw, cnt_raw, epoch_raw);
     epoch_word = (uint64_t)epoch_raw[0] | ((uint64_t)epoch_raw[1] << 32);
     if (gent_wanted) gent = (uint64_t)gent_raw[0] | ((uint64_t)gent_raw[1] << 32);
@@ -1383,15 +1457,15 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const int lrow = lane >> 4;                              // row of this lane inside a load
   const uint32_t cx = (uint32_t)((lane & 15) ^ lrow);     // chunk of load n: cx ^ (4n & 15)
   const uint32_t tok_bytes = (uint32_t)p.kv.stride_tok * 2u;
-  const uint32_t drow_bytes = (uint32_t)p.Hkv * kRowBytes;
+  const uint32_t drow_bytes = (uint32_t)p.Hkv * (D * 2);
   const int64_t dv_c = Vc - Kc, dv_d = Vd - Kd;
-  const char* const kd_pair = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * kRowBytes;
+  const char* const kd_pair = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * (D * 2);
   // cache rows of this pair: page 0 (or, without paging, the sequence's own slab), token 0
   const char* const kc_pair = Kc + ((int64_t)(p.kv.page_size == 0 ? b : 0) * p.kv.stride_page +
                                     (int64_t)h * p.kv.stride_head) * 2;
   const int64_t orow_pair = (int64_t)b * p.gamma * p.Hq + h * p.G;      // output row of (draft 0, head 0)
 
-  // Resolves the addresses of tile t (the wavefront's u-th) and issues its 16 loads into the
+  // Resolves the addresses of tile t (the wavefront's u-th) and issues its loads into the
   // stage at `dst`.  Lane 8u + n resolves the group of slots 4n .. 4n+3 (without a gather list
   // every lane with lane & 7 == n does); the groups' bases then move to scalar registers.  Rows that do not exist (past the drafts, past the kept blocks, past the
   // sequence's end) are redirected to the nearest valid row of their group, or, if the whole
@@ -1446,7 +1520,6 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     // slot validity: slot s is valid iff (s mod 4) < nv of group s / 4 (collected below from the
     // groups' counts as they pass through scalar registers)
     uint32_t valid = 0;
-    unsigned char* vdst = dst + kTileBytes;
     // (one multiplication per tile, not one per group: min(row, k) x bytes = min(row x bytes, k x bytes))
     const uint32_t lrow_off = (uint32_t)lrow * row_bytes;
 #pragma unroll
@@ -1457,28 +1530,25 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       valid |= ((1u << nvn) - 1u) << (4 * n);
       const bool fd = __builtin_amdgcn_readlane((int)from_draft, src0 + n) != 0;
       const char* kb = reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
-      const char* vb = kb + (fd ? dv_d : dv_c);
       // rows past the group's last valid row re-read that row
       const uint32_t last_off = (uint32_t)max(nvn - 1, 0) * (uint32_t)__builtin_amdgcn_readfirstlane((int)row_bytes);
-      const uint32_t off = min(lrow_off, last_off) + ((cx ^ (uint32_t)((4 * n) & 15)) << 4);
       if (skip_void_groups && nvn == 0) continue;        // (wave-uniform)
-      __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + off), SVF_LDS_PTR(dst + n * 1024), 16, 0, 2);
-      __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(vb + off), SVF_LDS_PTR(vdst + n * 1024), 16, 0, 2);
+      request_rows<D>(kb, fd ? dv_d : dv_c, min(lrow_off, last_off), cx ^ (uint32_t)((4 * n) & 15), dst + n * 1024);
     }
     ti.valid = valid;
     return ti;
   };
 
   float m_run = -INFINITY, l_run = 0.f;
-  floatx16 oacc[4];
+  floatx16 oacc[D / 32];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int nt = 0; nt < D / 32; ++nt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[nt][v] = 0.f;
 
   // ---- main loop -----------------------------------------------------------------------------
-  unsigned char* const my_stage = smem + wave * kStageBytes;
-  unsigned char* const x_stage = smem + kWaves * kStageBytes;
+  unsigned char* const my_stage = smem + wave * kStageBytes<D>;
+  unsigned char* const x_stage = smem + kWaves * kStageBytes<D>;
   const bool own_x = gw == 0;            // owner of draft tile 0
   // Without a gather list everything loaded so far is needed before the stream starts anyway
   // (draining the counter here keeps later register reuse from being mistaken for a hazard
@@ -1515,7 +1585,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     }
     // The query fragments were requested before the tiles and loads complete in order: with at
     // most one tile's loads outstanding they are in (a second tile may still be in flight).
-    if (MODE == kGather && computes) wait_vmcnt<16>();
+    if (MODE == kGather && computes) wait_vmcnt<kTileLoads<D>>();
   } else if (MODE == kGather) {
     wait_vmcnt<0>();
   }
@@ -1529,13 +1599,13 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       cur = issue_tile(gw + u * NW, u, my_stage, false);
       issued = u + 1;
     }
-    // tiles are issued in order, 16 loads each
-    if (issued - (u + 1) >= 1) wait_vmcnt<16>(); else wait_vmcnt<0>();
+    // tiles are issued in order, kTileLoads each
+    if (issued - (u + 1) >= 1) wait_vmcnt<kTileLoads<D>>(); else wait_vmcnt<0>();
     uint32_t allowed = cur.valid;
     if (cur.draft_base >= 0) allowed &= (uint32_t)(rmask >> (cur.draft_base & 63));
     const bool all_visible = cur.draft_base < 0 && cur.valid == 0xffffffffu;
     const uint32_t stage = (uint32_t)(uintptr_t)SVF_LDS_PTR((own_x && u == 0) ? x_stage : my_stage);
-    process_tile(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
+    process_tile<D>(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
     cur = nxt;
   }
   if (kOneTile) {
@@ -1556,8 +1626,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         uint32_t allowed = pvalid;
         if (pdraft >= 0) allowed &= (uint32_t)(rmask >> (pdraft & 63));
         const bool all_visible = pdraft < 0 && pvalid == 0xffffffffu;
-        const uint32_t stage = (uint32_t)(uintptr_t)SVF_LDS_PTR(smem + (wave + kSlices) * kStageBytes);
-        process_tile(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
+        const uint32_t stage = (uint32_t)(uintptr_t)SVF_LDS_PTR(smem + (wave + kSlices) * kStageBytes<D>);
+        process_tile<D>(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
       }
     }
   }
@@ -1581,8 +1651,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        mine[l32 * 32 + (parked_position(nt * 8 + k * 2 + g) ^ l32)] =
+      for (int nt = 0; nt < D / 32; ++nt)
+        mine[parked_index<D>(l32, nt * 8 + k * 2 + g)] =
             make_float4(oacc[nt][4 * k], oacc[nt][4 * k + 1], oacc[nt][4 * k + 2], oacc[nt][4 * k + 3]);
   }
   if (tid == kMergeWave0 * 64) sm_own_ready = 0;
@@ -1617,12 +1687,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   uint64_t* const arrivals = p.tickets + (int64_t)group * kTicketWords + (tag & 1u);
   const int R = p.slice_rows;
   const int lo = split * R, hi = min(lo + R, 32);            // the workgroup's own slice (empty if lo >= 32)
-  unsigned char* const own_o = x_stage;                     // [R][kD] bf16, R <= 16
+  unsigned char* const own_o = x_stage;                     // [R][256 bytes], R <= 16
   float* const own_ml = reinterpret_cast<float*>(x_stage + 16 * kRowBytes);
   uint64_t prev = 0;
   int64_t pr_rec = 0;
   float mw = -INFINITY, lw = 0.f;
-  const int r = tid >> 3, c16 = tid & 7;                     // (wavefronts 0 .. 3) row, block of 16 channels
+  const int r = tid >> 3, c16 = tid & 7;                     // (wavefronts 0 .. 3) row, block of D / 8 channels
   if (wave < 4) {
     float fw[kSlices];
 #pragma unroll
@@ -1635,34 +1705,47 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       fw[w] = fw[w] == -INFINITY ? 0.f : fast_exp2(fw[w] - mw);      // a slice that saw no token counts nothing
       lw = __builtin_fmaf(sm_l[w][r], fw[w], lw);
     }
-    float racc[16];
+    float racc[D / 8];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) racc[c] = 0.f;
+    for (int c = 0; c < D / 8; ++c) racc[c] = 0.f;
 #pragma unroll
     for (int w = 0; w < kSlices; ++w)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const float4 t = reinterpret_cast<const float4*>(smem + w * kStageBytes)[r * 32 + (parked_position(c16 * 4 + nt) ^ r)];
+      for (int nt = 0; nt < D / 32; ++nt) {
+        const float4 t = reinterpret_cast<const float4*>(smem + w * kStageBytes<D>)[parked_index<D>(r, c16 * (D / 32) + nt)];
         racc[4 * nt] = __builtin_fmaf(t.x, fw[w], racc[4 * nt]);
         racc[4 * nt + 1] = __builtin_fmaf(t.y, fw[w], racc[4 * nt + 1]);
         racc[4 * nt + 2] = __builtin_fmaf(t.z, fw[w], racc[4 * nt + 2]);
         racc[4 * nt + 3] = __builtin_fmaf(t.w, fw[w], racc[4 * nt + 3]);
       }
     const float inv = lw > 0.f ? __builtin_amdgcn_rcpf(lw) : 0.f;
+    // 32 bytes of the partial row: sixteen channels in bf16, or eight in fp32
     u32x4 o0, o1;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      o0[c] = pack_bf16(racc[2 * c] * inv, racc[2 * c + 1] * inv);
-      o1[c] = pack_bf16(racc[8 + 2 * c] * inv, racc[8 + 2 * c + 1] * inv);
+      if constexpr (D == 128) {
+        o0[c] = pack_bf16(racc[2 * c] * inv, racc[2 * c + 1] * inv);
+        o1[c] = pack_bf16(racc[8 + 2 * c] * inv, racc[8 + 2 * c + 1] * inv);
+      } else {
+        o0[c] = __float_as_uint(racc[c] * inv);
+        o1[c] = __float_as_uint(racc[4 + c] * inv);
+      }
     }
     const int orow_row = row0 + r;
     if (single) {
       if (orow_row < p.M) {
         const int oi = (int)(((uint64_t)(uint32_t)orow_row * p.g_magic) >> 32), oj = orow_row - oi * p.G;
         const int64_t orow = orow_pair + (int64_t)oi * p.Hq + oj;
-        __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(p.out) + orow * kD + c16 * 16;
-        *reinterpret_cast<u32x4*>(dst) = o0;
-        *reinterpret_cast<u32x4*>(dst + 8) = o1;
+        __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(p.out) + orow * D + c16 * (D / 8);
+        if constexpr (D == 128) {
+          *reinterpret_cast<u32x4*>(dst) = o0;
+          *reinterpret_cast<u32x4*>(dst + 8) = o1;
+        } else {
+          u32x4 o;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) o[c] = pack_bf16(racc[2 * c] * inv, racc[2 * c + 1] * inv);
+          *reinterpret_cast<u32x4*>(dst) = o;
+        }
         if (p.lse && c16 == 0) p.lse[orow] = (mw + log2f(lw)) * 0.6931471805599453f;
       }
     } else {
@@ -1675,9 +1758,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
 #pragma unroll
       for (int c = 0; c < 4; ++c) got[c] = swap_lanes_xor4(o1[c]);
       const u32x4 first = low ? o0 : got, second = low ? got : o0;
-      uint16_t* dst = reinterpret_cast<uint16_t*>(p.part_o) + pr_rec * kD;
-      uint16_t* dst0 = dst + (low ? 2 * c16 : 2 * c16 - 7) * 8;
-      uint16_t* dst1 = dst + (low ? 2 * c16 + 9 : 2 * c16) * 8;
+      char* dst = reinterpret_cast<char*>(p.part_o) + pr_rec * kRowBytes;
+      char* dst0 = dst + (low ? 2 * c16 : 2 * c16 - 7) * 16;
+      char* dst1 = dst + (low ? 2 * c16 + 9 : 2 * c16) * 16;
       const bool one_xcd = sm_one_xcd != 0;               // (the same for the whole workgroup)
       if (one_xcd) {
         store_l2_16(dst0, first);
@@ -1717,11 +1800,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
 
   const bool merger = wave == kMergeWave0 || wave == kMergeWave0 + 1;
   const int mt = tid - kMergeWave0 * 64;
-  const bool ch4 = R <= 4;                                   // 4 channels per merging thread, else 8
+  constexpr int WM = kWideMerge<D>;
+  const bool ch4 = D == 64 || R <= 4;                        // 4 channels per merging thread, else 8
   // one pass over the rows and one batch of records: the other splits' records are waited for now
-  const bool prefetch = S <= 16 && R <= (ch4 ? 4 : 8) && lo < 32;
-  MergeLane<4> L4;
-  MergeLane<8> L8;
+  const bool prefetch = S <= 16 && R <= 8 && lo < 32;
+  MergeLane<4, D> L4;
+  MergeLane<WM, D> L8;
   bool records_in = false;
   // the own rows are in LDS once wavefronts 0 .. 3 have all said so (they wait for nobody); the
   // polls for the records look at that counter as well
@@ -1779,8 +1863,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         todo &= todo - 1u;
         const bool from_lds = x == split;                  // the own slice's own rows are in LDS
         const OwnRows own = {own_o, own_ml, lo, from_lds ? split : -1};
-        const bool ok = ch4 ? merge_rows<4>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
-                            : merge_rows<8>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
+        const bool ok = ch4 ? merge_rows<4, D>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
+                            : merge_rows<WM, D>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
         gave_up = !ok;                                     // (only with a bounded budget: the own slice in round 0)
       }
       if (gave_up) {
@@ -1818,7 +1902,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
 // One workgroup per (pair, set of up to eight row groups, split); wavefront w owns row group w and
 // all wavefronts walk the same tiles, so a key/value row is fetched once for up to 256 query rows
 // instead of once per row group.  A tile is fetched by the eight wavefronts together (wavefront w
-// fetches the four-token group w: one K and one V load) into a ring of nine 16 KB stages; one
+// fetches the four-token group w: one K and one V load) into a ring of nine 16 KB (D = 64: 8 KB) stages; one
 // barrier per tile (after each wavefront has seen its own two loads land).  No combination through
 // LDS at the end: every wavefront writes its rows itself: the output if there is one split, else
 // a partial; the partials are merged by the group's workgroups themselves (up to 16 splits) or by
@@ -1827,6 +1911,22 @@ constexpr int kRowStages = kWaves + 1;
 constexpr int kRowWindow = 3;                // most tiles between two barriers
 constexpr int kRowAhead = 3;                 // tiles requested beyond the window at hand
 constexpr int kRowFirst = 3;                 // tiles requested before the first window
+template <int D> constexpr int kRowLoads = D == 128 ? 2 : 1;   // load instructions of a wavefront per tile
+// Waits until at most the loads of `tiles` (0 .. 8) tiles are outstanding.
+template <int D>
+__device__ __forceinline__ void wait_row_tiles(int tiles) {
+  switch (tiles) {
+    case 0: wait_vmcnt<0>(); break;
+    case 1: wait_vmcnt<kRowLoads<D>>(); break;
+    case 2: wait_vmcnt<2 * kRowLoads<D>>(); break;
+    case 3: wait_vmcnt<3 * kRowLoads<D>>(); break;
+    case 4: wait_vmcnt<4 * kRowLoads<D>>(); break;
+    case 5: wait_vmcnt<5 * kRowLoads<D>>(); break;
+    case 6: wait_vmcnt<6 * kRowLoads<D>>(); break;
+    case 7: wait_vmcnt<7 * kRowLoads<D>>(); break;
+    default: wait_vmcnt<8 * kRowLoads<D>>(); break;
+  }
+}
 static_assert(kRowFirst >= 1 && kRowFirst <= kRowStages, "the first window is one tile");
 // (the tiles of a window are requested at the barrier of the window before, at the latest)
 static_assert(kRowAhead >= kRowWindow && kRowWindow + kRowAhead <= kRowStages, "tiles in flight must cover the next window and fit the ring");
@@ -1845,11 +1945,12 @@ struct RowTileIssue {
   uint32_t lrow_tok_off, lrow_draft_off;     // lrow x tok_bytes, lrow x drow_bytes
 };
 
-// This wavefront's two loads of the workgroup's i-th tile (slots 4 * wave .. 4 * wave + 3).
+// This wavefront's kRowLoads loads of the workgroup's i-th tile (slots 4 * wave .. 4 * wave + 3).
+template <int D>
 __device__ __forceinline__ void issue_row_tile(const RowTileIssue& c, int i) {
   const int t = c.split + i * c.S;
   const int st = i % kRowStages;
-  unsigned char* dst = c.smem + st * kStageBytes;
+  unsigned char* dst = c.smem + st * kStageBytes<D>;
   int nv;
   const char* kb;
   bool from_draft;
@@ -1874,18 +1975,17 @@ __device__ __forceinline__ void issue_row_tile(const RowTileIssue& c, int i) {
     row_bytes = c.tok_bytes;
   }
   const uint64_t fd = (uint64_t)0 - (uint64_t)from_draft;
-  const char* vb = kb + (int64_t)(((uint64_t)c.dv_d & fd) | ((uint64_t)c.dv_c & ~fd));
+  const int64_t dv = (int64_t)(((uint64_t)c.dv_d & fd) | ((uint64_t)c.dv_c & ~fd));
   // (min(row, k) x bytes = min(row x bytes, k x bytes): the lane's product is formed once)
   const uint32_t dt = 0u - (uint32_t)(t < c.tiles_d);          // (a draft tile: its rows lie drow_bytes apart)
   const uint32_t lrow_off = (c.lrow_draft_off & dt) | (c.lrow_tok_off & ~dt);
-  const uint32_t off = min(lrow_off, (uint32_t)max(nv - 1, 0) * row_bytes) + ((c.cx ^ (uint32_t)((4 * c.wave) & 15)) << 4);
-  __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + off), SVF_LDS_PTR(dst + c.wave * 1024), 16, 0, 2);
-  __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(vb + off), SVF_LDS_PTR(dst + kTileBytes + c.wave * 1024), 16, 0, 2);
+  const uint32_t off = min(lrow_off, (uint32_t)max(nv - 1, 0) * row_bytes);
+  request_rows<D>(kb, dv, off, c.cx ^ (uint32_t)((4 * c.wave) & 15), dst + c.wave * 1024);
 }
 
-template <int MODE>
+template <int D, int MODE>
 __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnParams p, int pairs) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kRowStages * kStageBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kRowStages * kStageBytes<D>];
   // per (tile of the workgroup, four-token group): bit s set = slot s of the group holds a real token
   __shared__ __attribute__((aligned(8))) unsigned char s_group_valid[kMaxRowTiles][kWaves];
   __shared__ int sm_last;
@@ -1930,9 +2030,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     qi = (int)(((uint64_t)(uint32_t)row * p.g_magic) >> 32);
     qj = row - qi * p.G;
   }
-  RetrievalLoads rl;
+  RetrievalLoads<D> rl;
   if (MODE == kSelect)
-    rl = issue_retrieval_loads(p, b, h, pair, split, xgroup, (split + zs * S) % kScoreBatch, tid, vzero);
+    rl = issue_retrieval_loads<D>(p, b, h, pair, split, xgroup, (split + zs * S) % kScoreBatch, tid, vzero);
   // gather entries: lane u holds (the workgroup's u-th tile, group = this wavefront).  With a gather
   // list they and the pair's block count are all the first tile requests wait for: they are loaded
   // ahead of the query fragments (loads come back in the order issued), and the first tiles are
@@ -1946,12 +2046,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     if (e_ok) gent = p.gather[(int64_t)pair * p.gather_groups + e_u];
     cnt_raw = p.sel_cnt[pair + vzero];
   }
-  bf16x8 qf[8];
+  bf16x8 qf[D / 16];
   {
     const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
-                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * kD + g * 8;
+                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+    for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
   }
   uint64_t rmask = 0;
   if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
@@ -1964,7 +2064,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   if (MODE != kSelect) epoch_word = p.epochs[xgroup + vzero];
   if (MODE == kSelect) {
     epoch_word = rl.epoch_word;
-    const Retrieved rt = retrieve_blocks(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, []() {});
+    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, []() {});
     L = rt.L;
     cnt = rt.cnt;
     if (e_ok) gent = gather_entry_of(p, s_sel, rt, rl, e_u, b, h);
@@ -2004,9 +2104,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   const int lrow = lane >> 4;
   const uint32_t cx = (uint32_t)((lane & 15) ^ lrow);
   const uint32_t tok_bytes = (uint32_t)p.kv.stride_tok * 2u;
-  const uint32_t drow_bytes = (uint32_t)p.Hkv * kRowBytes;
+  const uint32_t drow_bytes = (uint32_t)p.Hkv * (D * 2);
   const int64_t dv_c = Vc - Kc, dv_d = Vd - Kd;
-  const char* const kd_pair = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * kRowBytes;
+  const char* const kd_pair = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * (D * 2);
   const int64_t orow_pair = (int64_t)b * p.gamma * p.Hq + h * p.G;
 
   RowTileIssue ic;
@@ -2030,9 +2130,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   ic.lrow_draft_off = (uint32_t)lrow * drow_bytes;
 
   float m_run = -INFINITY, l_run = 0.f;
-  floatx16 oacc[4];
+  floatx16 oacc[D / 32];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int nt = 0; nt < D / 32; ++nt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[nt][v] = 0.f;
 
@@ -2041,7 +2141,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   if (MODE != kGather) wait_vmcnt<0>();
   int issued = 0;
   if (MODE == kGather)
-    for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile(ic, issued);
+    for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile<D>(ic, issued);
   if (!p.draft_mask) rmask = qi >= 63 ? ~0ull : ((2ull << qi) - 1ull);
   if (!row_valid) rmask = 0;
 
@@ -2073,12 +2173,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   // Only the first tiles are requested up front and the others as the windows advance (the window
   // at hand plus kRowAhead tiles are in flight): with every tile of every workgroup requested at
   // once, a workgroup's first tile is served no sooner than most of the launch's bytes.
-  for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile(ic, issued);
+  for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile<D>(ic, issued);
   for (int i0 = 0, nw = 0; i0 < n_my; i0 += nw) {
     nw = min(min(i0 == 0 ? 1 : (i0 == 1 ? 2 : kRowWindow), kRowWindow), n_my - i0);
-    // this wavefront's loads of the window's tiles have landed (two loads per tile, issued in
+    // this wavefront's loads of the window's tiles have landed (kRowLoads per tile, issued in
     // order; the window's tiles were all requested at the barrier before, or up front)
-    wait_vmcnt_upto16(2 * (issued - (i0 + nw)));
+    wait_row_tiles<D>(issued - (i0 + nw));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -2086,7 +2186,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     // the barrier before)
 #pragma unroll 1
     while (issued < n_my && issued < i0 + nw + kRowAhead && issued < i0 + kRowStages) {
-      issue_row_tile(ic, issued);
+      issue_row_tile<D>(ic, issued);
       ++issued;
     }
     for (int k = 0; k < nw; ++k) {
@@ -2100,9 +2200,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
         if (draft_base >= 0) allowed &= (uint32_t)(rmask >> (draft_base & 63));
         const bool all_visible = draft_base < 0 && valid == 0xffffffffu;
         // (one scalar, so that every fragment address is one addition away from it)
-        uint32_t stage = (uint32_t)(uintptr_t)SVF_LDS_PTR(smem + st * kStageBytes);
+        uint32_t stage = (uint32_t)(uintptr_t)SVF_LDS_PTR(smem + st * kStageBytes<D>);
         asm volatile("" : "+s"(stage));
-        process_tile(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
+        process_tile<D>(stage, qf, allowed, all_visible, p.scale_log2, l32, g, m_run, l_run, oacc);
       }
     }
   }
@@ -2113,20 +2213,26 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   if (S == 1 && !has_rows) return;   // (with one split: no barrier from here on)
 
   // ---- this wavefront's 32 rows: output or partial ------------------------------------------------
-  // The normalised rows go through LDS once (bf16, [row][128 channels], 16-byte chunk c of row r
-  // at position c ^ (r & 15)) so that they leave in whole 256-byte rows: a lane's registers hold
+  // The normalised rows go through LDS once ([row][256 bytes]: 128 channels in bf16 or 64 in fp32;
+  // 16-byte chunk c of row r at position c ^ (r & 15)) so that they leave in whole rows: a lane's registers hold
   // 8-byte pieces of 32 different rows.  Behind the barrier above nobody reads a stage any more
   // and no load is in flight.
   l_run = halves_sum(l_run);
   const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
   if (has_rows) {
     const int last_st = n_my > 0 ? (n_my - 1) % kRowStages : 0;
-    unsigned char* mine = smem + ((last_st + 1 + wave) % kRowStages) * kStageBytes;
+    unsigned char* mine = smem + ((last_st + 1 + wave) % kRowStages) * kStageBytes<D>;
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < D / 32; ++nt)
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        // accumulator nt, values 4k .. 4k + 3: channels 32 nt + 8k + 4g + 0 .. 3 (half g of chunk 4 nt + k)
+        // accumulator nt, values 4k .. 4k + 3: channels 32 nt + 8k + 4g + 0 .. 3 (bf16: half g of
+        // chunk 4 nt + k; fp32: chunk 8 nt + 2k + g)
+        if constexpr (D == 64) {
+          *reinterpret_cast<float4*>(mine + l32 * kRowBytes + (((8 * nt + 2 * k + g) ^ (l32 & 15)) << 4)) =
+              make_float4(oacc[nt][4 * k] * inv, oacc[nt][4 * k + 1] * inv, oacc[nt][4 * k + 2] * inv, oacc[nt][4 * k + 3] * inv);
+          continue;
+        }
         const u32x2 w = {pack_bf16(oacc[nt][4 * k] * inv, oacc[nt][4 * k + 1] * inv),
                          pack_bf16(oacc[nt][4 * k + 2] * inv, oacc[nt][4 * k + 3] * inv)};
         *reinterpret_cast<u32x2*>(mine + l32 * kRowBytes + ((((4 * nt + k) ^ (l32 & 15)) << 4) | (g << 3))) = w;
@@ -2143,11 +2249,15 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
         if (grow < p.M) {
           const int oi = (int)(((uint64_t)(uint32_t)grow * p.g_magic) >> 32);
           const int oj = grow - oi * p.G;
-          store_coherent16(static_cast<__hip_bfloat16*>(p.out) + (orow_pair + (int64_t)oi * p.Hq + oj) * kD + c * 8, w);
+          __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(p.out) + (orow_pair + (int64_t)oi * p.Hq + oj) * D + c * (D / 16);
+          if constexpr (D == 128) store_coherent16(dst, w);
+          else
+            store_coherent8(dst, u32x2{pack_bf16(__uint_as_float(w[0]), __uint_as_float(w[1])),
+                                       pack_bf16(__uint_as_float(w[2]), __uint_as_float(w[3]))});
         }
       } else {
         const int64_t pr = ((int64_t)pair * S + split) * p.Mpad + grow;
-        store_coherent16(reinterpret_cast<uint16_t*>(p.part_o) + pr * kD + c * 8, w);
+        store_coherent16(reinterpret_cast<char*>(p.part_o) + pr * kRowBytes + c * 16, w);
       }
     }
   }
@@ -2194,7 +2304,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
         todo &= todo - 1u;
         bool ok = true;
         for (int mrg = x; ok && mrg < nrg; mrg += S)
-          ok = merge_rows<8>(p, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
+          ok = merge_rows<kWideMerge<D>, D>(p, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
         gave_up = !ok;
       }
       if (gave_up) {
@@ -2231,6 +2341,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
 // per row, splits in order (bit-stable).  Runs behind the rows kernel on the same stream; it also
 // moves the key-exchange tag of a retrieving call on (every workgroup of that call has finished).
 // grid: (pairs, row groups)
+template <int D>
 __global__ __launch_bounds__(kThreads) void merge_rows_kernel(AttnParams p, int pairs, int advance_tags) {
   const int pair = blockIdx.x, rg = blockIdx.y;
   const int tid = threadIdx.x;
@@ -2249,15 +2360,15 @@ __global__ __launch_bounds__(kThreads) void merge_rows_kernel(AttnParams p, int 
     const int64_t xg = (int64_t)(rg / kWaves) * pairs + pair;
     finish_call(p, xg, *reinterpret_cast<const uint32_t*>(p.epochs + xg) + 1u);
   }
-  merge_splits(p, g_row, orow, rok, cg);
+  merge_splits<D>(p, g_row, orow, rok, cg);
 }
 
 }  // namespace
 
-// bf16, d = 128, and groups of four consecutive tokens never straddle a block or a page
+// bf16, and groups of four consecutive tokens never straddle a block or a page
 bool mfma_supported(const svf_shape_t& s) {
   // (the last two keep the reciprocal-multiply divisions by Hkv and G exact)
-  return s.dtype == SVF_BF16 && s.d == 128 && s.block_size % 4 == 0 && s.page_size % 4 == 0 &&
+  return s.dtype == SVF_BF16 && s.block_size % 4 == 0 && s.page_size % 4 == 0 &&
          (int64_t)s.kv_stride_tok * 2 * 3 + 256 < ((int64_t)1 << 31) && (int64_t)s.B * s.Hkv < 65536 &&
          s.Hq < 65536;
 }
@@ -2303,8 +2414,9 @@ int mfma_rows_splits(const svf_shape_t& s) {
 // workgroup that finishes last moves the group's tag on.  No page table is touched (p.kv.page_size
 // must be 0 here) and no gather list is written.
 // grid: x = kXcds * n_splits, y = ceil(pairs / kXcds)
+template <int D>
 __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, int pairs) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kStageBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kScratchBytes];
   __shared__ int32_t s_sel[kMaxSelectBlocks];
   __shared__ int s_exchange_failed;
   {
@@ -2322,10 +2434,10 @@ __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, i
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  RetrievalLoads rl = issue_retrieval_loads(p, b, h, pair, split, pair, split % kScoreBatch, tid, vzero);
+  RetrievalLoads<D> rl = issue_retrieval_loads<D>(p, b, h, pair, split, pair, split % kScoreBatch, tid, vzero);
   const int L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
   issue_first_score_batch(p, rl, pair, split, tid);
-  const Retrieved rt = retrieve_blocks(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, pair, tid, lane, wave, []() {});
+  const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, pair, tid, lane, wave, []() {});
   if (split == p.n_splits - 1) publish_selection(p, s_sel, rt.cnt, pair, tid);
   if (rl.share_scores && tid == 0) {
     // every workgroup that takes a ticket has read all the keys it needed
@@ -2341,23 +2453,25 @@ __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, i
 hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st) {
   const int pairs = p.B * p.Hkv;
   const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds));
-  hipLaunchKernelGGL(retrieve_only_kernel, grid, dim3(kThreads), 0, st, p, pairs);
+  if (p.d == 64) hipLaunchKernelGGL(retrieve_only_kernel<64>, grid, dim3(kThreads), 0, st, p, pairs);
+  else hipLaunchKernelGGL(retrieve_only_kernel<128>, grid, dim3(kThreads), 0, st, p, pairs);
   return hipGetLastError();
 }
 
-hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st) {
+template <int D>
+static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   const int row_groups = (p.M + 31) / 32;
   const int pairs = p.B * p.Hkv;
   if (row_groups >= kRowsModeFrom) {
     const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds),
                     (unsigned)((row_groups + kWaves - 1) / kWaves));
-    if (p.reps) hipLaunchKernelGGL(verify_attn_mfma_rows_kernel<kSelect>, grid, dim3(kThreads), 0, st, p, pairs);
-    else if (p.gather) hipLaunchKernelGGL(verify_attn_mfma_rows_kernel<kGather>, grid, dim3(kThreads), 0, st, p, pairs);
-    else hipLaunchKernelGGL(verify_attn_mfma_rows_kernel<kResolve>, grid, dim3(kThreads), 0, st, p, pairs);
+    if (p.reps) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kSelect>), grid, dim3(kThreads), 0, st, p, pairs);
+    else if (p.gather) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kGather>), grid, dim3(kThreads), 0, st, p, pairs);
+    else hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kResolve>), grid, dim3(kThreads), 0, st, p, pairs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_splits <= kMaxSplitsMergedInKernel) return e;
     const int advance_tags = p.reps != nullptr;
-    hipLaunchKernelGGL(merge_rows_kernel, dim3((unsigned)pairs, (unsigned)row_groups), dim3(kThreads), 0, st, p, pairs,
+    hipLaunchKernelGGL(merge_rows_kernel<D>, dim3((unsigned)pairs, (unsigned)row_groups), dim3(kThreads), 0, st, p, pairs,
                        advance_tags);
     return hipGetLastError();
   }
@@ -2368,14 +2482,18 @@ hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st) {
   const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits;
 #define SVF_LAUNCH_ATTN(MODE)                                                                              \
   do {                                                                                                     \
-    if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
-    else hipLaunchKernelGGL((verify_attn_mfma_kernel<MODE, false>), grid, dim3(kThreads), 0, st, p, pairs);          \
+    if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<D, MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
+    else hipLaunchKernelGGL((verify_attn_mfma_kernel<D, MODE, false>), grid, dim3(kThreads), 0, st, p, pairs);          \
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(kSelect);
   else if (p.gather) SVF_LAUNCH_ATTN(kGather);
   else SVF_LAUNCH_ATTN(kResolve);
 #undef SVF_LAUNCH_ATTN
   return hipGetLastError();
+}
+
+hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st) {
+  return p.d == 64 ? launch_attn<64>(p, st) : launch_attn<128>(p, st);
 }
 
 }  // namespace svf

@@ -1,7 +1,7 @@
 // Verification attention, vector-ALU kernel (Sec. 3.1 / 3.3: the draft queries attend to the
 // retrieved blocks of their KV head and, through the draft mask, to each other).
 //
-// Used for fp32 inputs and for head dimensions the matrix-core kernel does not cover.
+// Used for fp32 inputs and for block or page sizes the matrix-core kernel does not cover.
 // Split-K over the selected tokens: workgroup (split, kv head, sequence x row group) walks
 // its share of 32-token tiles (prefix tiles first, then the draft tile(s)), staging K and V
 // through LDS as fp32; thread (r, sub) owns query row r of the row group and the channels
