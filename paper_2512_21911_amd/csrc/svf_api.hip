@@ -15,6 +15,7 @@ hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st);
 hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st);
 bool mfma_supported(const svf_shape_t& s);
 int mfma_splits(const svf_shape_t& s);
+int mfma_shared_splits(const svf_shape_t& s);
 bool mfma_rows_mode(const svf_shape_t& s);
 int mfma_rows_splits(const svf_shape_t& s);
 
@@ -102,6 +103,9 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
     if (want < 1) want = 1;
     pl.n_splits = (int)want;
   }
+  const int shared = pl.mfma && !mfma_rows_mode(s) ? mfma_shared_splits(s) : 0;
+  pl.share_splits = shared > 0;
+  pl.split_stride = shared > 0 ? shared : pl.n_splits;
   const size_t pairs = (size_t)s.B * s.Hkv;
   pl.groups = pairs * (pl.Mpad / 32);
   pl.slice_rows = (32 + (pl.n_splits < 16 ? pl.n_splits : 16) - 1) / (pl.n_splits < 16 ? pl.n_splits : 16);
@@ -110,12 +114,12 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   off += align_up(pl.groups * kTicketWords * sizeof(uint64_t));
   // partial outputs: fp32 (vector-ALU kernel, matrix-core kernels at d = 64) or bf16 (d = 128) per split and row
   pl.off_o = off;
-  off += align_up(pairs * pl.n_splits * pl.Mpad * s.d * (pl.mfma && s.d == 128 ? sizeof(uint16_t) : sizeof(float)));
+  off += align_up(pairs * pl.split_stride * pl.Mpad * s.d * (pl.mfma && s.d == 128 ? sizeof(uint16_t) : sizeof(float)));
   // maxima and denominators: two fp32 arrays for the vector-ALU kernel; 16 bytes per split and row
   // for the matrix-core kernels (a tagged record)
   pl.off_m = off;
-  pl.off_l = off + pairs * pl.n_splits * pl.Mpad * sizeof(float);
-  off += align_up((pl.mfma ? 4 : 2) * pairs * pl.n_splits * pl.Mpad * sizeof(float));
+  pl.off_l = off + pairs * pl.split_stride * pl.Mpad * sizeof(float);
+  off += align_up((pl.mfma ? 4 : 2) * pairs * pl.split_stride * pl.Mpad * sizeof(float));
   pl.gather = pl.mfma && s.k_blocks <= kMaxGatherBlocks;
   pl.fused_select = pl.gather && nb_max_of(s) <= kMaxGatherBlocks;
   pl.gather_groups = pl.gather ? (int32_t)(((int64_t)s.k_blocks * s.block_size + 31) / 32 * 8) : 0;
@@ -421,6 +425,8 @@ static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void*
   p.k_blocks = shape->k_blocks;
   p.n_splits = pl.n_splits;
   p.mask_per_batch = shape->mask_per_batch;
+  p.split_stride = pl.split_stride;
+  p.share_splits = pl.share_splits;
   p.block_shift = -1;
   if ((shape->block_size & (shape->block_size - 1)) == 0)
     for (int sh = 0; sh < 31; ++sh)

@@ -128,6 +128,8 @@ struct AttnParams {
   uint64_t* epochs;            // [groups]
   int32_t slice_rows;          // rows of a row group that one workgroup merges: ceil(32 / min(n_splits, 16))
   int32_t B, gamma, Hq, Hkv, G, d, M, Mpad, block_size, k_blocks, n_splits, mask_per_batch, max_seq_len;
+  int32_t split_stride;        // splits per pair that the partials have room for (>= n_splits)
+  int32_t share_splits;        // the launch may share the splits out by the pairs' counts
   int32_t block_shift;         // log2(block_size) if a power of two, else -1
   uint64_t g_magic;            // floor(2^32 / G) + 1: n / G == (n * g_magic) >> 32 for n, G < 65536
   uint64_t hkv_magic;          // the same for Hkv
@@ -253,6 +255,8 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 // Host-side planning shared by svf_workspace_bytes and the attention launcher.
 struct AttnPlan {
   int32_t M, Mpad, n_splits;
+  int32_t split_stride;      // splits per pair that the partials have room for
+  bool share_splits;         // see mfma_shared_splits
   int32_t slice_rows;        // rows of a row group one workgroup merges: ceil(32 / min(n_splits, 16))
   bool mfma;                 // bf16: matrix-core kernel; otherwise the vector-ALU kernel
   bool fused_select;         // anchor layers retrieve inside the attention kernel

@@ -629,10 +629,9 @@ struct OwnRows {
 // *watch_hit tells whether it was seen to hold `watched_for` (what the caller waits for next: by
 // the time the records are in, it has usually happened, and no further look is needed).
 template <int CH, int D>
-__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, D>& L, int64_t g_row, int c0, uint32_t tag,
+__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, D>& L, int64_t g_row, int S, int c0, uint32_t tag,
                                              int budget, int own_split, uint32_t watch = 0, uint32_t watched_for = 0,
                                              bool* watch_hit = nullptr) {
-  const int S = p.n_splits;
   const int sp = c0 + (L.cl & 15);
   const uint32_t* recp = p.part_rec + (g_row + (int64_t)min(sp, S - 1) * p.Mpad) * 4;
   // (past the last split: a record that weighs nothing)
@@ -655,10 +654,9 @@ __device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, 
 // LDS holds it: one address chain, a step of one split's partial at a time).
 template <int CH, int D, int B0>
 __device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkOf<CH, D>::type (&t)[8], int pair, uint32_t voff,
-                                            int c0) {
-  const int S = p.n_splits;
+                                            int S, int c0) {
   const uint64_t step = (uint64_t)p.Mpad * kRowBytes;
-  const uint64_t first = (uint64_t)(uintptr_t)p.part_o + ((uint64_t)pair * S + (uint64_t)(c0 + B0)) * step;
+  const uint64_t first = (uint64_t)(uintptr_t)p.part_o + ((uint64_t)pair * p.split_stride + (uint64_t)(c0 + B0)) * step;
   const int n = S - c0 - B0;                             // splits of this batch that exist (>= 1)
   uint64_t at = first;
 #pragma unroll
@@ -782,48 +780,47 @@ __device__ __forceinline__ void chunks_wait16(T (&a)[8], T (&b)[8]) {
 // outputs and, while those are on their way, forms the weights.  The own split's rows, if LDS holds
 // them, must be complete.
 template <int CH, int D>
-__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH, D>& L, int pair, int row0, int c0,
-                                                  const OwnRows& own, int64_t orow_pair) {
-  const int S = p.n_splits;
+__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH, D>& L, int pair, int row0, int S,
+                                                  int c0, const OwnRows& own, int64_t orow_pair) {
   const uint32_t voff = (uint32_t)((row0 + L.row) * kRowBytes + L.cl * (int)sizeof(typename MergeLane<CH, D>::Chunk));
   // (straight-line code between every hand-issued load and its wait: the compiler does not know
   // that the registers are still in flight, and a copy it places at a branch or a join in between
   // would copy what was there before)
   if (c0 + 8 < S) {
-    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, c0);
-    fetch_batch<CH, D, 8>(p, L.t1, pair, voff, c0);
+    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, S, c0);
+    fetch_batch<CH, D, 8>(p, L.t1, pair, voff, S, c0);
     batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
     batch_weights<CH, D, 8>(L, c0, own, L.mb0, L.w1, L.fa1, L.mb1);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait16(L.t0, L.t1);
   } else {
-    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, c0);
+    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, S, c0);
     batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait(L.t0);
   }
 }
 template <int CH, int D>
-__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH, D>& L, int c0, const OwnRows& own) {
+__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH, D>& L, int S, int c0, const OwnRows& own) {
   batch_accumulate<CH, D, 0>(L, L.t0, c0, own, L.w0, L.fa0, L.mb0);
-  if (c0 + 8 < p.n_splits) batch_accumulate<CH, D, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
+  if (c0 + 8 < S) batch_accumulate<CH, D, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
 }
 
 // Merges rows lo <= r < hi of the row group (all passes, all splits) and writes them out.  Returns
 // false for the whole wavefront, with nothing of the current pass written, when a record was still
 // missing after `budget` polls.  Called by the two merging wavefronts, each for itself.
 template <int CH, int D>
-__device__ __forceinline__ bool merge_rows(const AttnParams& p, int lo, int hi, int budget, uint32_t tag, int pair, int row0,
-                                           int64_t orow_pair, int mt, const OwnRows& own) {
+__device__ __forceinline__ bool merge_rows(const AttnParams& p, int S, int lo, int hi, int budget, uint32_t tag, int pair,
+                                           int row0, int64_t orow_pair, int mt, const OwnRows& own) {
   for (int r0 = lo; r0 < hi; r0 += MergeLane<CH, D>::kRowsPerPass) {
     MergeLane<CH, D> L;
     init_lane(L, mt, r0, hi);
     if (!__any(L.active)) continue;
-    for (int c0 = 0; c0 < p.n_splits; c0 += 16) {
-      const int64_t g_row = (int64_t)pair * p.n_splits * p.Mpad + row0 + L.row;
-      if (!poll_records(p, L, g_row, c0, tag, budget, own.split)) return false;
-      merge_fetch_weigh(p, L, pair, row0, c0, own, orow_pair);
-      merge_finish(p, L, c0, own);
+    for (int c0 = 0; c0 < S; c0 += 16) {
+      const int64_t g_row = (int64_t)pair * p.split_stride * p.Mpad + row0 + L.row;
+      if (!poll_records(p, L, g_row, S, c0, tag, budget, own.split)) return false;
+      merge_fetch_weigh(p, L, pair, row0, S, c0, own, orow_pair);
+      merge_finish(p, L, S, c0, own);
     }
     store_merged(p, L);
   }
@@ -1210,7 +1207,83 @@ struct TileInfo {
   int draft_base;      // >= 0: draft tile, index of its first draft; -1: cache tile
 };
 
-// grid: x = kXcds * n_splits, y = ceil(pairs / kXcds), z = row groups; pairs = B * Hkv.
+// Splits of the pairs where their counts differ (a budget over all KV heads of a sequence: k_blocks is
+// then the most one head can be given, and the heads' counts are known here only).  n_splits is planned
+// for k_blocks; used as planned, most workgroups would hold a tile or none, in several rounds, and
+// the few long lists would set the pace with four tiles per wavefront.  Instead the 256 compute units are
+// shared out in proportion to the pairs' tiles, at most split_stride splits for one, at least so many
+// that no wavefront gets more than kMaxTiles tiles; the rest of the grid leaves.  Every workgroup works
+// the shares out for itself, from the same counts.  Neighbouring shares go to one XCD.
+// Where every count is the per-head rule's own, min(k_blocks, blocks of the sequence), nothing is
+// changed: the step modes must then add up in the same order.
+// Returns false if this workgroup has no part.
+// (4 sequences, 8 heads, 256 kept blocks of 64 among them, most of them in one or two heads: 63 us as
+// planned, 19 us so.)
+constexpr int kShareChunks = 4;              // pairs this handles: 64 per chunk
+constexpr int kMaxSharedSplits = 32;         // splits of one pair: two batches of sixteen in the merge
+__device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs, int lane, int row_groups, int& pair,
+                                                 int& split, int& S) {
+  int cnt[kShareChunks], L[kShareChunks], tiles[kShareChunks];
+#pragma unroll
+  for (int c = 0; c < kShareChunks; ++c) {
+    cnt[c] = L[c] = 0;
+    if (c * 64 < pairs) {
+      const int i = min(c * 64 + lane, pairs - 1);
+      cnt[c] = p.sel_cnt[i];
+      L[c] = p.seq_lens[(uint32_t)(((uint64_t)(uint32_t)i * p.hkv_magic) >> 32)];
+    }
+  }
+  const int tiles_d = (p.gamma + kTile - 1) / kTile;
+  bool uneven = false;
+  int total = 0;
+#pragma unroll
+  for (int c = 0; c < kShareChunks; ++c) {
+    tiles[c] = 0;
+    if (c * 64 < pairs) {
+      const int n = min(max(cnt[c], 0), p.k_blocks);
+      uneven = uneven || (n < p.k_blocks && n * p.block_size < min(L[c], p.max_seq_len));
+      if (c * 64 + lane < pairs) tiles[c] = tiles_d + (n * p.block_size + kTile - 1) / kTile;
+      total += __builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)tiles[c]), 63);
+    }
+  }
+  const int id = blockIdx.y * gridDim.x + blockIdx.x;
+  if (!__any(uneven)) {
+    // (gridDim.x is a multiple of kXcds)
+    split = blockIdx.y;
+    pair = blockIdx.x;
+    return split < S && pair < pairs;
+  }
+  const float per_tile = (float)(256 / row_groups) / (float)total;
+  int s[kShareChunks], incl[kShareChunks], shares = 0;
+#pragma unroll
+  for (int c = 0; c < kShareChunks; ++c) {
+    s[c] = incl[c] = 0;
+    if (c * 64 < pairs) {
+      const int most = min((tiles[c] + kWaves - 1) / kWaves, p.split_stride);
+      const int least = (tiles[c] + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
+      if (c * 64 + lane < pairs) s[c] = max(max(min((int)((float)tiles[c] * per_tile), most), least), 1);
+      incl[c] = shares + (int)wave_inclusive_sum((uint32_t)s[c]);
+      shares = __builtin_amdgcn_readlane(incl[c], 63);
+    }
+  }
+  const int per_xcd = (shares + kXcds - 1) / kXcds;
+  const int mine = (id % kXcds) * per_xcd + id / kXcds;
+  if (id / kXcds >= per_xcd || mine >= shares) return false;
+#pragma unroll
+  for (int c = 0; c < kShareChunks; ++c) {
+    const uint64_t hit = __ballot(mine < incl[c] && mine >= incl[c] - s[c]);
+    if (hit) {                                             // (one lane of one chunk)
+      const int l = __builtin_ctzll(hit);
+      pair = c * 64 + l;
+      S = __builtin_amdgcn_readlane(s[c], l);
+      split = mine - (__builtin_amdgcn_readlane(incl[c], l) - S);
+    }
+  }
+  return true;
+}
+
+// grid: x = kXcds * n_splits, y = ceil(pairs / kXcds), z = row groups; pairs = B * Hkv.  (kResolve with
+// share_splits: x = pairs rounded up to a multiple of kXcds, y = as many as the shares can need.)
 // Workgroups are handed to the XCDs round-robin in x-fastest order and gridDim.x is a multiple
 // of kXcds, so blockIdx.x mod kXcds names the XCD: all splits and all row groups of a pair
 // share it (the second reader of a pair's K/V finds them in that XCD's L2).
@@ -1259,10 +1332,14 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // load would stall the next read of a kernel argument until it is back.
   int vzero;
   asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-  const int split = blockIdx.x / kXcds;
-  const int pair = blockIdx.y * kXcds + blockIdx.x % kXcds;
+  int split = blockIdx.x / kXcds;
+  int pair = blockIdx.y * kXcds + blockIdx.x % kXcds;
+  int S = p.n_splits;                                           // splits of this pair
   const int rg = blockIdx.z;
-  if (pair >= pairs) return;
+  if (MODE == kResolve && !kOneTile && p.share_splits) {   // (with one tile per wavefront as planned they are not shared out)
+    if (!share_out_splits(p, pairs, threadIdx.x & 63, gridDim.z, pair, split, S)) return;
+  }
+  if (pair >= pairs || split >= S) return;
   const int group = rg * pairs + pair;                          // index of the group's ticket
   const int b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32), h = pair - b * p.Hkv;   // pair / Hkv
 
@@ -1271,7 +1348,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const int lane = tid & 63;
   const int l32 = lane & 31, g = lane >> 5;
   const int row0 = rg * 32;
-  const int NW = kWaves * p.n_splits;
+  const int NW = kWaves * S;
   const int gw = split * kWaves + wave;
   constexpr int kSlices = kOneTile ? kWaves / 2 : kWaves;      // wavefronts that compute
   const bool computes = wave < kSlices;                         // (wave-uniform)
@@ -1448,7 +1525,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // finds all n_splits of them counted on its own XCD knows that every reader of its partial sits
   // behind the same L2, and may leave the partial there instead of writing it through to memory.
   uint64_t* const where_word = p.tickets + (int64_t)group * kTicketWords + 4 + (((uint32_t)epoch_word + 1u) & 1u);
-  const bool counts_xcds = p.n_splits >= 2 && p.n_splits <= 255;
+  const bool counts_xcds = S >= 2 && S <= 255;
   if (counts_xcds && wave == kWaves - 1 && lane == 0)
     __hip_atomic_fetch_add(where_word, 1ull << (8 * xcc_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
@@ -1657,7 +1734,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   }
   if (tid == kMergeWave0 * 64) sm_own_ready = 0;
   if (wave == kWaves - 1 && lane == 0)
-    sm_one_xcd = counts_xcds && where == (uint64_t)p.n_splits << (8 * xcc_id()) ? 1 : 0;
+    sm_one_xcd = counts_xcds && where == (uint64_t)S << (8 * xcc_id()) ? 1 : 0;
   __syncthreads();
 
   // ---- what happens to the workgroup's result --------------------------------------------------------
@@ -1680,12 +1757,11 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // before it and merges them too.  So every row is merged whatever is resident when, and every
   // wait ends.  The words of calls with an even / odd tag alternate; the last arriver clears the
   // other one and moves the call counter on (which also works under graph replay).
-  const int S = p.n_splits;
   const bool single = S == 1;
   const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)epoch_word) + 1u;
   const int wait_polls = wait_polls_of(__builtin_amdgcn_readfirstlane((int)(uint32_t)(epoch_word >> 32)));
   uint64_t* const arrivals = p.tickets + (int64_t)group * kTicketWords + (tag & 1u);
-  const int R = p.slice_rows;
+  const int R = S == p.n_splits ? p.slice_rows : (32 + min(S, 16) - 1) / min(S, 16);
   const int lo = split * R, hi = min(lo + R, 32);            // the workgroup's own slice (empty if lo >= 32)
   unsigned char* const own_o = x_stage;                     // [R][256 bytes], R <= 16
   float* const own_ml = reinterpret_cast<float*>(x_stage + 16 * kRowBytes);
@@ -1749,7 +1825,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         if (p.lse && c16 == 0) p.lse[orow] = (mw + log2f(lw)) * 0.6931471805599453f;
       }
     } else {
-      pr_rec = ((int64_t)pair * S + split) * p.Mpad + orow_row;
+      pr_rec = ((int64_t)pair * p.split_stride + split) * p.Mpad + orow_row;
       // Each of the two store instructions covers whole 128-byte lines (the eight threads of a row
       // write eight consecutive 16-byte chunks; threads c and c ^ 4 trade their second chunk): the
       // L2 then passes complete lines on instead of twice as many half-written ones.
@@ -1812,13 +1888,13 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const uint32_t ready = (uint32_t)(uintptr_t)SVF_LDS_PTR(&sm_own_ready);
   bool own_rows_in = false;
   if (merger && prefetch) {
-    const int64_t g_row0 = (int64_t)pair * S * p.Mpad + row0;
+    const int64_t g_row0 = (int64_t)pair * p.split_stride * p.Mpad + row0;
     if (ch4) {
       init_lane(L4, mt, lo, hi);
-      records_in = !__any(L4.active) || poll_records(p, L4, g_row0 + L4.row, 0, tag, wait_polls, split, ready, 4u, &own_rows_in);
+      records_in = !__any(L4.active) || poll_records(p, L4, g_row0 + L4.row, S, 0, tag, wait_polls, split, ready, 4u, &own_rows_in);
     } else {
       init_lane(L8, mt, lo, hi);
-      records_in = !__any(L8.active) || poll_records(p, L8, g_row0 + L8.row, 0, tag, wait_polls, split, ready, 4u, &own_rows_in);
+      records_in = !__any(L8.active) || poll_records(p, L8, g_row0 + L8.row, S, 0, tag, wait_polls, split, ready, 4u, &own_rows_in);
     }
   }
   if (merger && !own_rows_in) {
@@ -1844,13 +1920,13 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       const OwnRows own = {own_o, own_ml, lo, split};
       if (ch4) {
         if (__any(L4.active)) {
-          merge_fetch_weigh(p, L4, pair, row0, 0, own, orow_pair);
-          merge_finish(p, L4, 0, own);
+          merge_fetch_weigh(p, L4, pair, row0, S, 0, own, orow_pair);
+          merge_finish(p, L4, S, 0, own);
           store_merged(p, L4);
         }
       } else if (__any(L8.active)) {
-        merge_fetch_weigh(p, L8, pair, row0, 0, own, orow_pair);
-        merge_finish(p, L8, 0, own);
+        merge_fetch_weigh(p, L8, pair, row0, S, 0, own, orow_pair);
+        merge_finish(p, L8, S, 0, own);
         store_merged(p, L8);
       }
     }
@@ -1863,8 +1939,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         todo &= todo - 1u;
         const bool from_lds = x == split;                  // the own slice's own rows are in LDS
         const OwnRows own = {own_o, own_ml, lo, from_lds ? split : -1};
-        const bool ok = ch4 ? merge_rows<4, D>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
-                            : merge_rows<WM, D>(p, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
+        const bool ok = ch4 ? merge_rows<4, D>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
+                            : merge_rows<WM, D>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
         gave_up = !ok;                                     // (only with a bounded budget: the own slice in round 0)
       }
       if (gave_up) {
@@ -2304,7 +2380,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
         todo &= todo - 1u;
         bool ok = true;
         for (int mrg = x; ok && mrg < nrg; mrg += S)
-          ok = merge_rows<kWideMerge<D>, D>(p, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
+          ok = merge_rows<kWideMerge<D>, D>(p, S, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
         gave_up = !ok;
       }
       if (gave_up) {
@@ -2385,6 +2461,23 @@ int mfma_splits(const svf_shape_t& s) {
   if (want > hi) want = hi;
   if (want < lo) want = lo;
   return (int)want;
+}
+
+// Splits a pair may be given where the launch shares them out by the pairs' counts (share_out_splits), or
+// 0 where it uses mfma_splits for every pair: with one tile per wavefront as planned there is nothing to
+// gain, and the shares are worked out for up to 64 kShareChunks pairs.  The partials it takes are held to
+// 8 MB, which keeps small workspaces small.
+int mfma_shared_splits(const svf_shape_t& s) {
+  const int M = s.gamma * (s.Hq / s.Hkv);
+  const int row_groups = (M + 31) / 32;
+  const int64_t pairs = (int64_t)s.B * s.Hkv;
+  const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
+  const int64_t cover = (256 + pairs * row_groups - 1) / (pairs * row_groups);
+  if (pairs > 64 * kShareChunks || tiles - 1 <= kWaves * cover) return 0;
+  const int64_t most = (tiles + kWaves - 1) / kWaves < kMaxSharedSplits ? (tiles + kWaves - 1) / kWaves : kMaxSharedSplits;
+  const int64_t n = mfma_splits(s);
+  const int64_t room = ((int64_t)8 << 20) / (pairs * row_groups * 32 * kRowBytes);
+  return (int)(n > (most < room ? most : room) ? n : (most < room ? most : room));
 }
 
 // More than two row groups: one workgroup takes up to eight of them (see the rows kernel).
@@ -2475,7 +2568,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
                        advance_tags);
     return hipGetLastError();
   }
-  const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds), (unsigned)row_groups);
+  dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds), (unsigned)row_groups);
   // one tile per wavefront (the owner of draft tile 0 streams a second one beside it)?  The same
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
@@ -2487,7 +2580,17 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(kSelect);
   else if (p.gather) SVF_LAUNCH_ATTN(kGather);
-  else SVF_LAUNCH_ATTN(kResolve);
+  else {
+    if (p.share_splits) {
+      // as planned: n_splits rows of the grid.  Shared out: one share per compute unit and one more per
+      // pair for the least share, or the least shares alone (n_splits per pair where all are full)
+      const int64_t x = (pairs + kXcds - 1) / kXcds * kXcds;
+      int64_t y = (256 / row_groups + 2 * (int64_t)pairs + kXcds + x - 1) / x;
+      if (y < p.n_splits + 1) y = p.n_splits + 1;
+      grid = dim3((unsigned)x, (unsigned)y, (unsigned)row_groups);
+    }
+    SVF_LAUNCH_ATTN(kResolve);
+  }
 #undef SVF_LAUNCH_ATTN
   return hipGetLastError();
 }
