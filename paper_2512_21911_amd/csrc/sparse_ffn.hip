@@ -284,98 +284,178 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_kernel(FfnParams p) {
   }
 }
 
-// The same result with the gate and the up matrix walked together: x is fetched once per chunk for
-// both, and the workgroup's memory pipeline does not run dry between a gate and an up walk; the
-// price is that every row of W_up is read, needed or not.
-//   TILES channel tiles per workgroup share the x pieces as well (TILES = 2 for more than 32
-//   tokens, where fetching x costs as much as fetching the weights), WAVES wavefronts split the
-//   model dimension; TILES * WAVES = 4, 128 KB of stages, one workgroup per compute unit.  So
-//   the tile height p.tile_rows <= 32 is chosen such that the workgroups fill whole rounds; the
-//   rows of the 32-row matrix-core tile past it repeat its last row, and a tile that would
-//   reach past d_ff is moved back to end there (the channels it shares with its neighbour are
-//   computed twice, to the same bits).
-// grid: (ceil(ceil(d_ff / tile_rows) / TILES)); block: 64 WAVES
-template <int NT, int TILES, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void ffn_gate_up_fused_kernel(FfnParams p) {
-  constexpr int RS = 32 * NT + 1;
-  constexpr int NMAT = 2 * TILES;                        // gate tiles, then up tiles
-  constexpr int kWaveBytes = kStages * NMAT * kChunkBytes;
-  constexpr int kThreads = WAVES * 64;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[WAVES * kWaveBytes];
-  static_assert(NMAT * kTileRows * RS * 4 <= kWaveBytes, "a wavefront's partial tiles fit its own stages");
+// The same result with the gate and the up matrix walked together: the workgroup's memory pipeline does
+// not run dry between a gate and an up walk; the price is that every row of W_up is read, needed or not.
+//
+// Bound by HBM, and that by the bytes a compute unit keeps in flight: a workgroup is four wavefronts, one
+// per (matrix, channel tile) of two tiles, that walk the model dimension together in chunks of 64.
+// A chunk of all four (32 rows x 128 bytes each) and of x goes straight to LDS; 6 (more than 32 tokens)
+// or 7 chunks' stages form a ring of which all but one are on their way, 80 - 96 KB of weights per compute
+// unit.  One barrier per chunk: behind it the chunk has landed for everybody, and everybody has left
+// the one before, whose stage takes the next request.  x is shared by the four wavefronts, and a
+// wavefront has its tile's whole sum: nothing is added up afterwards.
+// (Wavefronts that split the model dimension with two private stages of 128 each kept 64 KB in flight at
+// most, fetched x from L2 into registers and added four partial tiles at the end.)
+//   One workgroup per compute unit, so the tile height p.tile_rows <= 32 is chosen such that the
+//   workgroups fill whole rounds; the rows of the 32-row matrix-core tile past it repeat its last
+//   row, and a tile that would reach past d_ff is moved back to end there (the channels it shares with
+//   its neighbour are computed twice, to the same bits).
+constexpr int kWalkK = 64;                               // model dimensions per chunk
+constexpr int kWalkRow = kWalkK * 2;                     // 128 bytes
+constexpr int kWalkTile = kTileRows * kWalkRow;          // 4 KB: one wavefront's rows, or 32 tokens of x
+template <int NT> constexpr int kWalkStage = (kGuWaves + NT) * kWalkTile;
+template <int NT> constexpr int kWalkStages = NT == 1 ? 7 : 6;
+template <int NT> constexpr int kWalkLoads = 4 + NT;     // load instructions of a wavefront per chunk
+
+// Waits until this wavefront's loads of all but `chunks` (0 .. 5) chunks have landed.
+template <int NT>
+__device__ __forceinline__ void wait_walk(int chunks) {
+  switch (chunks) {
+    case 0: wait_vmcnt<0>(); break;
+    case 1: wait_vmcnt<kWalkLoads<NT>>(); break;
+    case 2: wait_vmcnt<2 * kWalkLoads<NT>>(); break;
+    case 3: wait_vmcnt<3 * kWalkLoads<NT>>(); break;
+    case 4: wait_vmcnt<4 * kWalkLoads<NT>>(); break;
+    default: wait_vmcnt<5 * kWalkLoads<NT>>(); break;
+  }
+}
+
+// Four reads of a 32-row piece of a stage (row l32, k-steps 0 .. 3): piece c of row r sits at position
+// c ^ ((r / 2) mod 8), so that sixteen neighbouring rows hit different banks.
+__device__ __forceinline__ void read_fragments(u32x4 (&f)[4], uint32_t row, uint32_t kx) {
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) f[ks] = lds_read16(row + (kx ^ (uint32_t)(ks << 5)));
+}
+__device__ __forceinline__ void fragments_wait(u32x4 (&f)[4]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : : "memory");
+}
+
+// grid: (ceil(ceil(d_ff / tile_rows) / 2)); block: 256
+template <int NT>
+__global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams p) {
+  constexpr int RS = 32 * NT + 1;                        // row stride of the [matrix tile][channel][token] sums
+  constexpr int S = kWalkStages<NT>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[S * kWalkStage<NT>];
+  static_assert(kGuWaves * kTileRows * RS * 4 <= S * kWalkStage<NT>, "the sums fit the stages");
+  static_assert(S - 2 <= 5, "wait_walk");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int l32 = lane & 31, g = lane >> 5;
   const int R = p.tile_rows;
-  int c0[TILES];
+  const int n_chunks = p.d_model / kWalkK;
+  // wavefront w: tile w / 2 of the workgroup's two, gate (even) or up (odd) matrix
+  const int c0 = min((blockIdx.x * 2 + (wave >> 1)) * R, p.d_ff - R);
+  // (a tile's and x's offsets fit 32 bits: at most 64 rows of 2 MB)
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+  const char* const w_tile = static_cast<const char*>((wave & 1) ? p.w_up : p.w_gate) + (int64_t)c0 * row_bytes;
+  // load n of a tile brings rows 8n .. 8n + 7, eight lanes per row
+  uint32_t w_off[4], x_off[NT];
+  const int lrow = lane >> 3, lcol = lane & 7;
 #pragma unroll
-  for (int s = 0; s < TILES; ++s) c0[s] = min((blockIdx.x * TILES + s) * R, p.d_ff - R);
-  unsigned char* stage = smem + wave * kWaveBytes;
-  const int64_t row_bytes = (int64_t)p.d_model * 2;
-
-  floatx16 acc[NMAT][NT];
-#pragma unroll
-  for (int mat = 0; mat < NMAT; ++mat)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[mat][t][v] = 0.f;
-  {
-    const char* rows[NMAT];
-#pragma unroll
-    for (int s = 0; s < TILES; ++s) {
-      rows[s] = static_cast<const char*>(p.w_gate) + (int64_t)c0[s] * row_bytes;
-      rows[TILES + s] = static_cast<const char*>(p.w_up) + (int64_t)c0[s] * row_bytes;
-    }
-    const char* const(&crows)[NMAT] = rows;
-    walk_tile<NT, NMAT>(p, crows, [=](int r) { return min(r, R - 1); }, static_cast<const char*>(p.x), stage, wave,
-                        WAVES, lane, acc);
+  for (int n = 0; n < 4; ++n) {
+    const int r = 8 * n + lrow;
+    w_off[n] = (uint32_t)min(r, R - 1) * row_bytes + (uint32_t)((lcol ^ ((r >> 1) & 7)) << 4);
   }
-  // partial tiles [matrix][channel][token] into this wavefront's own stages
-  float* red = reinterpret_cast<float*>(stage);
+  // x: wavefront w brings loads w NT .. w NT + NT - 1 of its 4 NT (tokens past the last repeat it)
 #pragma unroll
-  for (int mat = 0; mat < NMAT; ++mat)
+  for (int t = 0; t < NT; ++t) {
+    const int r = 8 * (wave * NT + t) + lrow;
+    x_off[t] = (uint32_t)min(r, p.M - 1) * row_bytes + (uint32_t)((lcol ^ ((r >> 1) & 7)) << 4);
+  }
+  // Workgroups start at different chunks: a chunk of x lies in rows d_model apart, a power of two as a
+  // rule, which is few memory channels, and the 32 compute units of an XCD would all ask them at once.
+  const int first = (int)((blockIdx.x / 8) % 32 * (uint32_t)n_chunks / 32);
+  auto request = [&](int i, unsigned char* st) {
+    const int k = i + first;
+    uint32_t koff = (uint32_t)(k >= n_chunks ? k - n_chunks : k) * kWalkRow;
+    asm volatile("" : "+s"(koff));                       // (a scalar of its own: no per-lane pointers advanced in every round)
+    const char* wb = w_tile + koff;
+    const char* xb = static_cast<const char*>(p.x) + koff;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+      __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(wb + w_off[n]), FFN_LDS_PTR(st + wave * kWalkTile + n * 1024), 16, 0, 2);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
+      __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(xb + x_off[t]),
+                                       FFN_LDS_PTR(st + kGuWaves * kWalkTile + (wave * NT + t) * 1024), 16, 0, 0);
+  };
+
+  floatx16 acc[NT];
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        red[(mat * kTileRows + 8 * (v >> 2) + 4 * g + (v & 3)) * RS + l32 + 32 * t] = acc[mat][t][v];
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+
+  const uint32_t lds = (uint32_t)(uintptr_t)FFN_LDS_PTR(smem);
+  const uint32_t kx = (uint32_t)((g ^ ((l32 >> 1) & 7)) << 4);
+  const uint32_t frag = lds + (uint32_t)l32 * kWalkRow;
+  for (int i = 0; i < min(S - 1, n_chunks); ++i) request(i, smem + i * kWalkStage<NT>);
+  int st = 0;                                            // stage of chunk i
+  for (int i = 0; i < n_chunks; ++i) {
+    wait_walk<NT>(min(S - 2, n_chunks - 1 - i));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int prev = st == 0 ? S - 1 : st - 1;
+    if (i + S - 1 < n_chunks) request(i + S - 1, smem + prev * kWalkStage<NT>);
+    uint32_t base = frag + (uint32_t)st * kWalkStage<NT>;
+    u32x4 wf[4], xf[NT][4];
+    read_fragments(wf, base + (uint32_t)wave * kWalkTile, kx);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) read_fragments(xf[t], base + (uint32_t)(kGuWaves + t) * kWalkTile, kx);
+    fragments_wait(wf);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fragments_wait(xf[t]);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ks]),
+                                                         __builtin_bit_cast(bf16x8, xf[t][ks]), acc[t], 0, 0, 0);
+    st = st == S - 1 ? 0 : st + 1;
+  }
+  __syncthreads();                                       // everybody has left the last stages
+  // value v of a lane is channel 8 (v / 4) + 4 g + v % 4, token l32 (+ 32 t)
+  float* sums = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      sums[(wave * kTileRows + 8 * (v >> 2) + 4 * g + (v & 3)) * RS + l32 + 32 * t] = acc[t][v];
   __syncthreads();
-  // thread: tile row tid / 8 (+ 8 WAVES per round), tokens (tid % 8) * 4 NT ... + 4 NT
-  const int m0 = (tid & 7) * 4 * NT;
-  for (int cc = tid >> 3; cc < TILES * kTileRows; cc += kThreads / 8) {
-    const int s = cc / kTileRows, c = cc - s * kTileRows;
-    if (c >= R) continue;                                 // (the eight threads of a row go together)
-    const int ch = c0[s] + c;
-    const float bg = p.b_gate ? p.b_gate[ch] : 0.f;
-    const float bu = p.b_up ? p.b_up[ch] : 0.f;
-    uint64_t bits = 0;
+  // A lane is a token (two groups of channels side by side where 32 lanes hold all tokens): the active
+  // bits of a channel are one ballot, and four channels of h * up leave in one store.
+  constexpr int kSide = NT == 1 ? 2 : 1;
+  const int m = NT == 1 ? l32 : lane, side = NT == 1 ? g : 0;
+  const int quads = R / 4;                               // groups of four channels per tile
+  for (int q0 = wave * kSide; q0 < 2 * quads; q0 += kGuWaves * kSide) {
+    const int q = q0 + side;
+    const bool here = q < 2 * quads;
+    const int tile = q >= quads ? 1 : 0, c = here ? 4 * (q - tile * quads) : 0;
+    const int ch = min((blockIdx.x * 2 + tile) * R, p.d_ff - R) + c;
+    const float* zg = sums + (2 * tile * kTileRows + c) * RS + m;
+    const float* zu = zg + kTileRows * RS;
+    float hu[4];
+    uint64_t bits[4];
 #pragma unroll
-    for (int i = 0; i < 4 * NT; ++i) {
-      const int m = m0 + i;
-      float zg = 0.f, zu = 0.f;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) {
-        const float* r = reinterpret_cast<const float*>(smem + w * kWaveBytes);
-        zg += r[(s * kTileRows + c) * RS + m];
-        zu += r[((TILES + s) * kTileRows + c) * RS + m];
+    for (int j = 0; j < 4; ++j) {
+      const float bg = p.b_gate ? p.b_gate[ch + j] : 0.f;
+      const float bu = p.b_up ? p.b_up[ch + j] : 0.f;
+      const float h = activate(zg[j * RS] + bg, p.act);
+      const bool on = here && m < p.M && !(fabsf(h) < p.tau);
+      bits[j] = __ballot(on);
+      if (NT == 1) bits[j] = side ? bits[j] >> 32 : bits[j] & 0xffffffffull;
+      hu[j] = on ? h * (zu[j * RS] + bu) : 0.f;
+    }
+    if (here) {
+      *reinterpret_cast<u32x2*>(static_cast<char*>(p.h_up) + ((int64_t)m * p.d_ff + ch) * 2) =
+          u32x2{pack_bf16(hu[0], hu[1]), pack_bf16(hu[2], hu[3])};
+      if (m < 4) {
+        const uint64_t mine = m == 0 ? bits[0] : m == 1 ? bits[1] : m == 2 ? bits[2] : bits[3];
+        p.rowany[ch + m] = mine != 0 ? 1 : 0;
+        if (p.active) p.active[ch + m] = mine;
       }
-      const float h = activate(zg + bg, p.act);
-      const bool on = m < p.M && !(fabsf(h) < p.tau);
-      if (on) bits |= 1ull << m;
-      const float hu = on ? h * (zu + bu) : 0.f;
-      reinterpret_cast<__hip_bfloat16*>(p.h_up)[(int64_t)m * p.d_ff + ch] = __float2bfloat16(hu);
-    }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-      const uint32_t lo = __shfl_xor((uint32_t)bits, o, 64), hi = __shfl_xor((uint32_t)(bits >> 32), o, 64);
-      bits |= (uint64_t)lo | ((uint64_t)hi << 32);
-    }
-    if ((tid & 7) == 0) {
-      p.rowany[ch] = bits != 0 ? 1 : 0;
-      if (p.active) p.active[ch] = bits;
     }
   }
 }
@@ -532,8 +612,8 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(FfnParams p) {
 // Channels per tile of the fused walk: one workgroup per compute unit runs at a time, so the
 // cost is (rounds of 256 workgroups) x (rows per tile); the largest multiple of four that
 // minimises it.
-int ffn_fused_tile_rows(int d_ff, int M) {
-  const int per_wg = M <= 32 ? 1 : 2;                     // channel tiles per workgroup
+int ffn_fused_tile_rows(int d_ff) {
+  const int per_wg = 2;                                   // channel tiles per workgroup
   int best = kTileRows;
   int64_t best_cost = -1;
   for (int r = kTileRows; r >= 16; r -= 4) {
@@ -556,8 +636,8 @@ hipError_t launch_sparse_ffn(const FfnParams& p, hipStream_t st) {
   const dim3 gu(p.d_ff / kTileRows);
   if (p.fused_walk) {
     const int tiles = (p.d_ff + p.tile_rows - 1) / p.tile_rows;
-    if (p.M <= 32) hipLaunchKernelGGL((ffn_gate_up_fused_kernel<1, 1, 4>), dim3(tiles), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((ffn_gate_up_fused_kernel<2, 2, 2>), dim3((tiles + 1) / 2), dim3(128), 0, st, p);
+    if (p.M <= 32) hipLaunchKernelGGL(ffn_gate_up_fused_kernel<1>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
+    else hipLaunchKernelGGL(ffn_gate_up_fused_kernel<2>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
   } else {
     if (p.M <= 32) hipLaunchKernelGGL(ffn_gate_up_kernel<1>, gu, dim3(kGuThreads), 0, st, p);
     else hipLaunchKernelGGL(ffn_gate_up_kernel<2>, gu, dim3(kGuThreads), 0, st, p);
