@@ -6,17 +6,16 @@
 // in long contiguous runs, and the rows of W_up / W_down of hidden channels that are inactive
 // for all M tokens are not read at all.
 //
-//   gate/up kernels one workgroup of four wavefronts per tile of hidden channels; the wavefronts
-//                   split the model dimension in chunks of 128.  A chunk of the tile (32 rows x
-//                   256 bytes per matrix) goes straight from global memory to the wavefront's
-//                   own LDS stage (two stages, the next chunk is in flight while this one is
-//                   multiplied), the matching piece of x comes through registers.
+//   gate/up kernels one workgroup of four wavefronts per tile (pair of tiles) of hidden channels.
 //                   Joint walk (default): the gate and the up matrix together, then
 //                   h = act(W_gate x + b_gate), the active bits |h| >= tau per (channel, token),
-//                   and h * up, masked per token, out as bf16 [tokens][d_ff]; x is fetched once
+//                   and h * up, masked per token, out as bf16 to the workspace; x is fetched once
 //                   for both matrices and nothing waits between them, but every row of W_up is
 //                   read.  Gate first: the gate walk, the active bits, then the same walk over
-//                   W_up where a row that no token needs is replaced by a row that is read anyway.
+//                   W_up where a row that no token needs is replaced by a row that is read anyway;
+//                   the wavefronts split the model dimension in chunks of 128, a chunk of the tile
+//                   (32 rows x 256 bytes) goes to the wavefront's own LDS stage (two stages), the
+//                   matching piece of x comes through registers.
 //   down kernel     y^T = W_down^T-rows times h_up: one workgroup of eight wavefronts per
 //                   (128 output columns, slice of the hidden channels).  The weight rows are
 //                   contiguous along the output dimension while the matrix core wants its
@@ -80,6 +79,13 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 __device__ __forceinline__ float activate(float z, int act) {
   if (act == SVF_ACT_SILU) return z / (1.0f + __expf(-z));
   return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
+}
+
+// h * up of token m and hidden channel c in the workspace: [d_ff / 16][32 NT tokens][16 channels], so that
+// what a step of the down projection reads (16 channels of all tokens) is contiguous.
+template <int NT>
+__device__ __forceinline__ char* h_up_at(const FfnParams& p, int m, int c) {
+  return static_cast<char*>(p.h_up) + (((int64_t)(c >> 4) * (32 * NT) + m) * 16 + (c & 15)) * 2;
 }
 
 // One walk of a wavefront over its chunks of a 32-row tile of NMAT matrices at once (the same
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_kernel(FfnParams p) {
   for (int i = 0; i < 8; ++i) zero8[i] = 0;
   // thread: token tid / 4, channels (tid % 4) * 8 ... + 8 (16 bytes of h_up)
   const int om = tid >> 2, oc = (tid & 3) * 8;
-  char* out = static_cast<char*>(p.h_up) + ((int64_t)om * p.d_ff + c0 + oc) * 2;
+  char* out = h_up_at<NT>(p, om, c0 + oc);
   if (rowmask == 0) {                                     // uniform: nothing of this tile is used
     if (om < 32 * NT) *reinterpret_cast<bf16x8*>(out) = zero8;
     return;
@@ -284,6 +290,36 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_kernel(FfnParams p) {
   }
 }
 
+// Four channels ch .. ch + 3 of all tokens: activation, active bits, h * up (Eq. 10, 12, 13).  A lane is a
+// token (two groups of channels side by side where 32 lanes hold all tokens): the active bits of a channel
+// are one ballot, and the four channels of h * up leave in one store.  gate(j, m), up(j, m): the sums of
+// channel j of the four; here: whether this lane's four channels are to be written.  All lanes must call.
+template <int NT> constexpr int kSide = NT == 1 ? 2 : 1;
+template <int NT, typename Gate, typename Up>
+__device__ __forceinline__ void finish_channels(const FfnParams& p, int lane, int ch, bool here, Gate&& gate, Up&& up) {
+  const int m = NT == 1 ? lane & 31 : lane;
+  float hu[4];
+  uint64_t bits[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float bg = p.b_gate ? p.b_gate[ch + j] : 0.f;
+    const float bu = p.b_up ? p.b_up[ch + j] : 0.f;
+    const float h = activate(gate(j, m) + bg, p.act);
+    const bool on = here && m < p.M && !(fabsf(h) < p.tau);
+    bits[j] = __ballot(on);
+    if (NT == 1) bits[j] = lane >= 32 ? bits[j] >> 32 : bits[j] & 0xffffffffull;
+    hu[j] = on ? h * (up(j, m) + bu) : 0.f;
+  }
+  if (here) {
+    *reinterpret_cast<u32x2*>(h_up_at<NT>(p, m, ch)) = u32x2{pack_bf16(hu[0], hu[1]), pack_bf16(hu[2], hu[3])};
+    if (m < 4) {
+      const uint64_t mine = m == 0 ? bits[0] : m == 1 ? bits[1] : m == 2 ? bits[2] : bits[3];
+      p.rowany[ch + m] = mine != 0 ? 1 : 0;
+      if (p.active) p.active[ch + m] = mine;
+    }
+  }
+}
+
 // The same result with the gate and the up matrix walked together: the workgroup's memory pipeline does
 // not run dry between a gate and an up walk; the price is that every row of W_up is read, needed or not.
 //
@@ -295,11 +331,12 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_kernel(FfnParams p) {
 // the one before, whose stage takes the next request.  x is shared by the four wavefronts, and a
 // wavefront has its tile's whole sum: nothing is added up afterwards.
 // (Wavefronts that split the model dimension with two private stages of 128 each kept 64 KB in flight at
-// most, fetched x from L2 into registers and added four partial tiles at the end.)
+// most, fetched x from L2 into registers and added four partial tiles at the end.  14336 x 4096: 40.6 -> 38.2 us,
+// 6.1 TB/s, for 8 tokens; 51.4 -> 40.8 us for 60, of which 10 for the order of the chunks, see `first`.)
 //   One workgroup per compute unit, so the tile height p.tile_rows <= 32 is chosen such that the
 //   workgroups fill whole rounds; the rows of the 32-row matrix-core tile past it repeat its last
 //   row, and a tile that would reach past d_ff is moved back to end there (the channels it shares with
-//   its neighbour are computed twice, to the same bits).
+//   the tile before it are that tile's to write: workgroups add in different orders).
 constexpr int kWalkK = 64;                               // model dimensions per chunk
 constexpr int kWalkRow = kWalkK * 2;                     // 128 bytes
 constexpr int kWalkTile = kTileRows * kWalkRow;          // 4 KB: one wavefront's rows, or 32 tokens of x
@@ -424,39 +461,147 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams
     for (int v = 0; v < 16; ++v)
       sums[(wave * kTileRows + 8 * (v >> 2) + 4 * g + (v & 3)) * RS + l32 + 32 * t] = acc[t][v];
   __syncthreads();
-  // A lane is a token (two groups of channels side by side where 32 lanes hold all tokens): the active
-  // bits of a channel are one ballot, and four channels of h * up leave in one store.
-  constexpr int kSide = NT == 1 ? 2 : 1;
-  const int m = NT == 1 ? l32 : lane, side = NT == 1 ? g : 0;
   const int quads = R / 4;                               // groups of four channels per tile
-  for (int q0 = wave * kSide; q0 < 2 * quads; q0 += kGuWaves * kSide) {
-    const int q = q0 + side;
-    const bool here = q < 2 * quads;
-    const int tile = q >= quads ? 1 : 0, c = here ? 4 * (q - tile * quads) : 0;
-    const int ch = min((blockIdx.x * 2 + tile) * R, p.d_ff - R) + c;
-    const float* zg = sums + (2 * tile * kTileRows + c) * RS + m;
-    const float* zu = zg + kTileRows * RS;
-    float hu[4];
-    uint64_t bits[4];
+  for (int q0 = wave * kSide<NT>; q0 < 2 * quads; q0 += kGuWaves * kSide<NT>) {
+    const int q = q0 + (NT == 1 ? g : 0);
+    const int tile = q >= quads ? 1 : 0, c = q < 2 * quads ? 4 * (q - tile * quads) : 0;
+    const int nominal = (blockIdx.x * 2 + tile) * R;
+    const int ch = min(nominal, p.d_ff - R) + c;
+    const float* zg = sums + (2 * tile * kTileRows + c) * RS;
+    finish_channels<NT>(p, lane, ch, q < 2 * quads && ch >= nominal, [&](int j, int m) { return zg[j * RS + m]; },
+                        [&](int j, int m) { return zg[(kTileRows + j) * RS + m]; });
+  }
+}
+
+// The same for few hidden channels, where the walk above would leave compute units idle: a workgroup takes
+// RC channels only (16, or 8), gate and up rows in one 32-row matrix-core tile, and its four
+// wavefronts split the model dimension (wavefront w: chunks w, w + 4, ...), each with a ring of
+// stages of its own, so that nothing but the final addition needs a barrier.  Bound by the chain of trips to
+// memory: a quarter as long as the walk above's, with everything that fits LDS on its way.  x takes
+// XR kilobytes of a stage (eight tokens each: few tokens leave room for more stages).
+// (Whole layer, all three launches: 4096 x 2048, 4 tokens 22.5 -> 18.0 us; 4096 x 1024, 60 tokens 52 ->
+// 25.7 us; 5120 x 3072, 64 tokens 66 -> 39 us.)
+// grid: (d_ff / RC); block: 256
+template <int RC, int XR> constexpr int kSplitStage = RC * 2 * kWalkRow + XR * 8 * kWalkRow;
+template <int RC, int XR> constexpr int kSplitStages = 36 * 1024 / kSplitStage<RC, XR> < 8 ? 36 * 1024 / kSplitStage<RC, XR> : 8;
+template <int RC, int XR>
+__device__ __forceinline__ void wait_split(int chunks) {   // all but `chunks` (0 .. 7) chunks have landed
+  constexpr int LPC = RC / 4 + XR;                       // load instructions of a chunk
+  switch (chunks) {
+    case 0: wait_vmcnt<0>(); break;
+    case 1: wait_vmcnt<LPC>(); break;
+    case 2: wait_vmcnt<2 * LPC>(); break;
+    case 3: wait_vmcnt<3 * LPC>(); break;
+    case 4: wait_vmcnt<4 * LPC < 64 ? 4 * LPC : 63>(); break;
+    case 5: wait_vmcnt<5 * LPC < 64 ? 5 * LPC : 63>(); break;
+    case 6: wait_vmcnt<6 * LPC < 64 ? 6 * LPC : 63>(); break;
+    default: wait_vmcnt<7 * LPC < 64 ? 7 * LPC : 63>(); break;
+  }
+}
+template <int RC, int XR>
+__global__ __launch_bounds__(kGuThreads) void ffn_gate_up_split_kernel(FfnParams p) {
+  constexpr int NT = XR == 8 ? 2 : 1;
+  constexpr int RS = 32 * NT + 1;
+  constexpr int S = kSplitStages<RC, XR>, SB = kSplitStage<RC, XR>;
+  static_assert((S - 1) * (RC / 4 + XR) < 64, "the wait counts of a full ring are exact");
+  constexpr int kSums = kGuWaves * kTileRows * RS * 4;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kGuWaves * S * SB > kSums ? kGuWaves * S * SB : kSums];
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int l32 = lane & 31, g = lane >> 5;
+  const int c0 = blockIdx.x * RC;
+  const int n_chunks = p.d_model / kWalkK;
+  const int n = (n_chunks - wave + kGuWaves - 1) / kGuWaves;              // of this wavefront (may be 0)
+  const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
+  const char* const wg = static_cast<const char*>(p.w_gate) + (int64_t)c0 * row_bytes;
+  const char* const wu = static_cast<const char*>(p.w_up) + (int64_t)c0 * row_bytes;
+  unsigned char* const ring = smem + wave * (S * SB);
+  // load j brings rows 8j .. 8j + 7 (eight lanes per row) of: RC gate rows, RC up rows, 8 XR tokens
+  const int lrow = lane >> 3, lcol = lane & 7;
+  auto swizzled = [&](int r) { return (uint32_t)((lcol ^ ((r >> 1) & 7)) << 4); };
+  uint32_t w_off[RC / 8], x_off[XR];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float bg = p.b_gate ? p.b_gate[ch + j] : 0.f;
-      const float bu = p.b_up ? p.b_up[ch + j] : 0.f;
-      const float h = activate(zg[j * RS] + bg, p.act);
-      const bool on = here && m < p.M && !(fabsf(h) < p.tau);
-      bits[j] = __ballot(on);
-      if (NT == 1) bits[j] = side ? bits[j] >> 32 : bits[j] & 0xffffffffull;
-      hu[j] = on ? h * (zu[j * RS] + bu) : 0.f;
+  for (int j = 0; j < RC / 8; ++j) w_off[j] = (uint32_t)(8 * j + lrow) * row_bytes + swizzled(8 * j + lrow);
+#pragma unroll
+  for (int j = 0; j < XR; ++j) x_off[j] = (uint32_t)min(8 * j + lrow, p.M - 1) * row_bytes + swizzled(8 * j + lrow);
+  // (workgroups start at different chunks, see above)
+  const int first = (int)((blockIdx.x / 8) % 32 * (uint32_t)n / 32);
+  auto request = [&](int i, unsigned char* st) {
+    const int k = i + first;
+    uint32_t koff = (uint32_t)(wave + kGuWaves * (k >= n ? k - n : k)) * kWalkRow;
+    asm volatile("" : "+s"(koff));
+#pragma unroll
+    for (int j = 0; j < RC / 8; ++j) {
+      __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(wg + koff + w_off[j]), FFN_LDS_PTR(st + j * 1024), 16, 0, 2);
+      __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(wu + koff + w_off[j]), FFN_LDS_PTR(st + (RC / 8 + j) * 1024), 16, 0, 2);
     }
-    if (here) {
-      *reinterpret_cast<u32x2*>(static_cast<char*>(p.h_up) + ((int64_t)m * p.d_ff + ch) * 2) =
-          u32x2{pack_bf16(hu[0], hu[1]), pack_bf16(hu[2], hu[3])};
-      if (m < 4) {
-        const uint64_t mine = m == 0 ? bits[0] : m == 1 ? bits[1] : m == 2 ? bits[2] : bits[3];
-        p.rowany[ch + m] = mine != 0 ? 1 : 0;
-        if (p.active) p.active[ch + m] = mine;
-      }
-    }
+#pragma unroll
+    for (int j = 0; j < XR; ++j)
+      __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(static_cast<const char*>(p.x) + koff + x_off[j]),
+                                       FFN_LDS_PTR(st + (RC / 4 + j) * 1024), 16, 0, 0);
+  };
+
+  floatx16 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+
+  // Matrix-core row l32: gate channel l32 (< 16) or up channel l32 - 16; at RC = 8 the upper eight of either repeat
+  // the lower, and tokens past the staged ones repeat them (their results are not looked at).
+  const int wr = (l32 & (RC - 1)) + (l32 >> 4) * RC;      // (swizzled by the row within its matrix)
+  const uint32_t lds = (uint32_t)(uintptr_t)FFN_LDS_PTR(ring);
+  const uint32_t w_row = lds + (uint32_t)wr * kWalkRow, w_kx = (uint32_t)((g ^ (((wr & (RC - 1)) >> 1) & 7)) << 4);
+  uint32_t x_row[NT], x_kx[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int r = (l32 + 32 * t) & (8 * XR - 1);
+    x_row[t] = lds + (uint32_t)(RC * 2 + r) * kWalkRow;
+    x_kx[t] = (uint32_t)((g ^ ((r >> 1) & 7)) << 4);
+  }
+  for (int i = 0; i < min(S, n); ++i) request(i, ring + i * SB);
+  int st = 0;
+  for (int i = 0; i < n; ++i) {
+    wait_split<RC, XR>(min(S, n - i) - 1);
+    const uint32_t at = (uint32_t)st * SB;
+    u32x4 wf[4], xf[NT][4];
+    read_fragments(wf, w_row + at, w_kx);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) read_fragments(xf[t], x_row[t] + at, x_kx[t]);
+    fragments_wait(wf);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) fragments_wait(xf[t]);
+    if (i + S < n) request(i + S, ring + st * SB);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ks]),
+                                                         __builtin_bit_cast(bf16x8, xf[t][ks]), acc[t], 0, 0, 0);
+    st = st == S - 1 ? 0 : st + 1;
+  }
+  __syncthreads();                                       // everybody has left the rings
+  float* sums = reinterpret_cast<float*>(smem);          // [wavefront][row][token]
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      sums[(wave * kTileRows + 8 * (v >> 2) + 4 * g + (v & 3)) * RS + l32 + 32 * t] = acc[t][v];
+  __syncthreads();
+  auto total = [&](int row, int m) {
+    float z = 0.f;
+#pragma unroll
+    for (int w = 0; w < kGuWaves; ++w) z += sums[(w * kTileRows + row) * RS + m];
+    return z;
+  };
+  constexpr int kQuads = RC / 4;
+  for (int q0 = wave * kSide<NT>; q0 < kQuads; q0 += kGuWaves * kSide<NT>) {
+    const int q = q0 + (NT == 1 ? g : 0);
+    const int c = q < kQuads ? 4 * q : 0;
+    finish_channels<NT>(p, lane, c0 + c, q < kQuads, [&](int j, int m) { return total(c + j, m); },
+                        [&](int j, int m) { return total(16 + c + j, m); });
   }
 }
 
@@ -473,7 +618,12 @@ struct DownLoads {
   uint32_t bits;                                         // which of the step's 16 channels are needed
 };
 
-// grid: (d_model / 128, k_splits); block: 512
+// grid: (k_splits * d_model / 128), slices fastest: workgroups are dealt to the eight XCDs in turn, so with
+// eight slices an XCD reads whole rows of the weights and one slice of h * up.  (Column tiles fastest, an
+// XCD read every eighth 256-byte piece of all rows, d_model apart: a few of its L2's channels.  14336 x
+// 4096, 80 % of the rows: 20.2 -> 19.0 us for 8 tokens; 31.5 -> 26.0 us for 60, whose h * up was 32 rows
+// d_ff apart per load.)
+// block: 512
 template <int NT>
 __global__ __launch_bounds__(kDnThreads) void ffn_down_kernel(FfnParams p) {
   constexpr int kRedStride = kDnCols + 4;                // floats per token row: keeps rows off each other's banks
@@ -483,13 +633,13 @@ __global__ __launch_bounds__(kDnThreads) void ffn_down_kernel(FfnParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int l32 = lane & 31, g = lane >> 5;
-  const int n0 = blockIdx.x * kDnCols;
+  const int slice = blockIdx.x % p.k_splits;
+  const int n0 = blockIdx.x / p.k_splits * kDnCols;
   const int n_steps = p.d_ff / 16;
   const int stride = kDnWaves * p.k_splits;
-  const int first = blockIdx.y * kDnWaves + wave;
+  const int first = slice * kDnWaves + wave;
   const int64_t row_bytes = (int64_t)p.d_model * 2;
   const char* wd = static_cast<const char*>(p.w_down_t) + (int64_t)(n0 + 4 * l32) * 2;
-  const char* hu = static_cast<const char*>(p.h_up);
 
   floatx16 acc[NT][4];
 #pragma unroll
@@ -518,7 +668,7 @@ __global__ __launch_bounds__(kDnThreads) void ffn_down_kernel(FfnParams p) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (d.bits != 0) v = *reinterpret_cast<const u32x4*>(hu + ((int64_t)(l32 + 32 * t) * p.d_ff + 16 * s + 8 * g) * 2);
+      if (d.bits != 0) v = *reinterpret_cast<const u32x4*>(h_up_at<NT>(p, l32 + 32 * t, 16 * s + 8 * g));
       d.h[t] = v;
     }
   };
@@ -576,7 +726,7 @@ __global__ __launch_bounds__(kDnThreads) void ffn_down_kernel(FfnParams p) {
         const float4 o = *reinterpret_cast<const float4*>(&s_red[w][m * kRedStride + 4 * c4]);
         sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
       }
-      *reinterpret_cast<float4*>(p.partial + ((int64_t)blockIdx.y * p.M + 32 * t + m) * p.d_model + n0 + 4 * c4) = sum;
+      *reinterpret_cast<float4*>(p.partial + ((int64_t)slice * p.M + 32 * t + m) * p.d_model + n0 + 4 * c4) = sum;
     }
   }
 }
@@ -632,9 +782,28 @@ int ffn_k_splits(int d_model, int d_ff) {
   return ks < 1 ? 1 : ks;
 }
 
+namespace {
+// d_ff up to which the gate / up walk takes the split kernel: with 16 channels per workgroup that is two
+// rounds of 256 workgroups (at 8192 it is 2 - 7 % faster than the other walk, at 12000 9 % slower).  Eight
+// channels where that is one round at most.
+constexpr int kSplitUpTo = 8192, kSplitEightUpTo = 2048;
+
+template <int RC>
+void launch_split(const FfnParams& p, hipStream_t st) {
+  const dim3 grid(p.d_ff / RC);
+  if (p.M <= 8) hipLaunchKernelGGL((ffn_gate_up_split_kernel<RC, 1>), grid, dim3(kGuThreads), 0, st, p);
+  else if (p.M <= 16) hipLaunchKernelGGL((ffn_gate_up_split_kernel<RC, 2>), grid, dim3(kGuThreads), 0, st, p);
+  else if (p.M <= 32) hipLaunchKernelGGL((ffn_gate_up_split_kernel<RC, 4>), grid, dim3(kGuThreads), 0, st, p);
+  else hipLaunchKernelGGL((ffn_gate_up_split_kernel<RC, 8>), grid, dim3(kGuThreads), 0, st, p);
+}
+}  // namespace
+
 hipError_t launch_sparse_ffn(const FfnParams& p, hipStream_t st) {
   const dim3 gu(p.d_ff / kTileRows);
-  if (p.fused_walk) {
+  if (p.fused_walk && p.d_ff <= kSplitUpTo) {
+    if (p.d_ff <= kSplitEightUpTo) launch_split<8>(p, st);
+    else launch_split<16>(p, st);
+  } else if (p.fused_walk) {
     const int tiles = (p.d_ff + p.tile_rows - 1) / p.tile_rows;
     if (p.M <= 32) hipLaunchKernelGGL(ffn_gate_up_fused_kernel<1>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
     else hipLaunchKernelGGL(ffn_gate_up_fused_kernel<2>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
@@ -644,7 +813,7 @@ hipError_t launch_sparse_ffn(const FfnParams& p, hipStream_t st) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 gd(p.d_model / kDnCols, p.k_splits);
+  const dim3 gd(p.d_model / kDnCols * p.k_splits);
   if (p.M <= 32) hipLaunchKernelGGL(ffn_down_kernel<1>, gd, dim3(kDnThreads), 0, st, p);
   else hipLaunchKernelGGL(ffn_down_kernel<2>, gd, dim3(kDnThreads), 0, st, p);
   e = hipGetLastError();

@@ -19,7 +19,7 @@ struct FfnParams {
   const float* b_down;      // fp32 [d_model] or NULL
   void* y;                  // bf16 [M][d_model]
   uint64_t* active;         // [d_ff] or NULL
-  void* h_up;               // bf16 [64][d_ff]: h * up per token, zero where the token does not use the channel
+  void* h_up;               // bf16 [d_ff / 16][32 or 64 tokens][16]: h * up per token, zero where the token does not use the channel
   uint8_t* rowany;          // [d_ff]: nonzero = the channel is used by some token
   float* partial;           // fp32 [k_splits][M][d_model]
   int32_t M, d_model, d_ff, act, k_splits;
