@@ -5,10 +5,20 @@
 // Split-K over the selected tokens: workgroup (split, kv head, sequence x row group) walks
 // its share of 32-token tiles (prefix tiles first, then the draft tile(s)), staging K and V
 // through LDS as fp32; thread (r, sub) owns query row r of the row group and the channels
-// sub, sub+8, ...  The 8 lanes of a row compute its 32 logits, keep the running maximum and
-// denominator in registers (online softmax in the log2 domain) and accumulate its output.
-// Each split writes an unnormalised partial (o, m, l); a second kernel merges the splits
-// with the log-sum-exp rule and writes out / lse.
+// 4 * sub .. 4 * sub + 3 of every 32.  The 8 lanes of a row compute its 32 logits, keep the
+// running maximum and denominator in registers (online softmax in the log2 domain) and
+// accumulate its output.  Each split writes an unnormalised partial (o, m, l); a second kernel
+// merges the splits with the log-sum-exp rule and writes out / lse.
+//
+// A workgroup usually has one tile, so what bounds it is its memory round trips (count, block id,
+// page, key) and, behind them, LDS reads: each of the 256 threads reads a whole query row and four
+// key rows.  They are read 16 bytes at a time from rows of D + 4 floats (the 8 rows or tokens of a
+// wavefront's read then lie in different banks), and queries, keys and values are all requested
+// before anything waits.  Every sum keeps its order.
+// Whole steps, against scalar LDS reads from unpadded rows and a merge of one split at a time, same bits
+// in fp32: two layers of 1024 tokens (8 query heads of 64, 4 drafts, 8 blocks of 16) 37.7 -> 28.8 us;
+// two sequences of 8k tokens (16 heads of 128, 8 drafts, 16 blocks of 32) 77.7 -> 39.9 us; bf16 in
+// blocks of 66 (4 sequences, 32 heads, 5 drafts, 24 blocks) 229 -> 90.6 us.
 #include <hip/hip_bf16.h>
 
 #include "svf_device.h"
@@ -21,22 +31,26 @@ constexpr int kThreads = 256;
 constexpr int kRows = 32;      // query rows per workgroup
 constexpr int kTile = 32;      // tokens per tile
 constexpr int kSub = 8;        // lanes per query row
+constexpr int kPPitch = kTile + 4;   // floats per row of weights
+constexpr int kMergeBatch = 16;      // splits whose partials the merge has in flight at once
 
-template <typename T>
-__device__ __forceinline__ float to_float(T x);
-template <>
-__device__ __forceinline__ float to_float<float>(float x) { return x; }
-template <>
-__device__ __forceinline__ float to_float<__hip_bfloat16>(__hip_bfloat16 x) { return __bfloat162float(x); }
+// four consecutive channels (16 or 8 bytes, aligned: rows start at multiples of 16 bytes)
+__device__ __forceinline__ float4 load4(const float* src) { return *reinterpret_cast<const float4*>(src); }
+__device__ __forceinline__ float4 load4(const __hip_bfloat16* src) {
+  const uint2 u = *reinterpret_cast<const uint2*>(src);
+  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                     __uint_as_float(u.y & 0xffff0000u));
+}
 
 // grid: (n_splits, Hkv, B * row_groups)
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void verify_attn_valu_kernel(AttnParams p, int row_groups) {
-  constexpr int KP = D + 1;                   // padded K row (floats) to spread LDS banks
-  __shared__ float sQ[kRows * D];
-  __shared__ float sK[kTile * KP];
-  __shared__ float sV[kTile * D];
-  __shared__ float sP[kRows * (kTile + 1)];
+  constexpr int KP = D + 4;                   // padded Q and K rows (floats)
+  constexpr int NC = D / (4 * kSub);          // four-channel chunks per thread: sub, sub + 8, ...
+  __shared__ __attribute__((aligned(16))) float sQ[kRows * KP];
+  __shared__ __attribute__((aligned(16))) float sK[kTile * KP];
+  __shared__ __attribute__((aligned(16))) float sV[kTile * D];
+  __shared__ __attribute__((aligned(16))) float sP[kRows * kPPitch];
   __shared__ int sTok[kTile];                 // >= 0: prefix token, -1: invalid, -2 - t: draft t
 
   const int split = blockIdx.x, h = blockIdx.y;
@@ -65,80 +79,91 @@ __global__ __launch_bounds__(kThreads) void verify_attn_valu_kernel(AttnParams p
     else mask = di >= 63 ? ~0ull : ((2ull << di) - 1ull);
   }
 
-  // stage this row group's queries as fp32
-  for (int e = tid; e < kRows * D; e += kThreads) {
-    const int rr = e / D, c = e - rr * D;
-    const int grow = rg * kRows + rr;
-    float v = 0.f;
-    if (grow < p.M) {
-      const int i = grow / p.G, j = h * p.G + grow % p.G;
-      v = to_float<T>(static_cast<const T*>(p.q)[(((int64_t)b * p.gamma + i) * p.Hq + j) * D + c]);
-    }
-    sQ[e] = v;
+  // this row's queries: chunks sub, sub + 8, ... (stored to LDS behind the first tile's requests)
+  float4 qv[NC];
+  {
+    const T* qsrc = static_cast<const T*>(p.q) + (((int64_t)b * p.gamma + di) * p.Hq + hq) * D + 4 * sub;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) qv[i] = row_ok ? load4(qsrc + 4 * kSub * i) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 
   float m_run = -INFINITY, l_run = 0.f;
-  float acc[D / kSub];
+  float4 acc[NC];
 #pragma unroll
-  for (int i = 0; i < D / kSub; ++i) acc[i] = 0.f;
+  for (int i = 0; i < NC; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   for (int tile = tile0; tile < tile1; ++tile) {
-    __syncthreads();                          // previous tile fully consumed (and sQ visible)
-    // which token sits in each of the tile's 32 slots
-    if (tid < kTile) {
-      int code = -1;
-      if (tile < tiles_p) {
-        const int slot = tile * kTile + tid;
-        if (slot < n_prefix) {
-          const int bi = slot / p.block_size;
-          const int blk = sel[bi];
-          const int t = blk * p.block_size + (slot - bi * p.block_size);
-          if (blk >= 0 && t < L) code = t;
-        }
-      } else {
-        const int t = (tile - tiles_p) * kTile + tid;
-        if (t < p.gamma) code = -2 - t;
+    // token r of the tile is loaded by the 8 threads (r, sub)
+    int code = -1;
+    if (tile < tiles_p) {
+      const int slot = tile * kTile + r;
+      if (slot < n_prefix) {
+        const int bi = slot / p.block_size;
+        const int blk = sel[bi];
+        const int t = blk * p.block_size + (slot - bi * p.block_size);
+        if (blk >= 0 && t < L) code = t;
       }
-      sTok[tid] = code;
+    } else {
+      const int t = (tile - tiles_p) * kTile + r;
+      if (t < p.gamma) code = -2 - t;
     }
-    __syncthreads();
-    // cooperative load: 8 threads per token, D/8 channels each
-    {
-      const int tt = tid / 8, part = tid % 8;
-      const int code = sTok[tt];
-      constexpr int CH = D / 8;
-      const T* ksrc = nullptr;
-      const T* vsrc = nullptr;
+    float4 kv[NC], vv[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) kv[i] = vv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (code != -1) {
+      const T *ksrc, *vsrc;
       if (code >= 0) {
-        const int64_t off = token_offset(p.kv, p.table, b, code) + (int64_t)h * p.kv.stride_head + part * CH;
+        const int64_t off = token_offset(p.kv, p.table, b, code) + (int64_t)h * p.kv.stride_head + 4 * sub;
         ksrc = static_cast<const T*>(p.K) + off;
         vsrc = static_cast<const T*>(p.V) + off;
-      } else if (code <= -2) {
-        const int64_t off = (((int64_t)b * p.gamma + (-2 - code)) * p.Hkv + h) * D + part * CH;
+      } else {
+        const int64_t off = (((int64_t)b * p.gamma + (-2 - code)) * p.Hkv + h) * D + 4 * sub;
         ksrc = static_cast<const T*>(p.k_draft) + off;
         vsrc = static_cast<const T*>(p.v_draft) + off;
       }
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        sK[tt * KP + part * CH + c] = ksrc ? to_float<T>(ksrc[c]) : 0.f;
-        sV[tt * D + part * CH + c] = vsrc ? to_float<T>(vsrc[c]) : 0.f;
+      for (int i = 0; i < NC; ++i) {
+        kv[i] = load4(ksrc + 4 * kSub * i);
+        vv[i] = load4(vsrc + 4 * kSub * i);
       }
+    }
+    if (tile == tile0) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) *reinterpret_cast<float4*>(sQ + r * KP + 4 * sub + 4 * kSub * i) = qv[i];
+    } else {
+      __syncthreads();                        // previous tile fully consumed
+    }
+    if (sub == 0) sTok[r] = code;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      *reinterpret_cast<float4*>(sK + r * KP + 4 * sub + 4 * kSub * i) = kv[i];
+      *reinterpret_cast<float4*>(sV + r * D + 4 * sub + 4 * kSub * i) = vv[i];
     }
     __syncthreads();
 
     // logits of row r against tokens sub, sub + 8, sub + 16, sub + 24
     float s[kTile / kSub];
+#pragma unroll
+    for (int u = 0; u < kTile / kSub; ++u) s[u] = 0.f;
+#pragma unroll 4
+    for (int c = 0; c < D; c += 4) {
+      const float4 a = *reinterpret_cast<const float4*>(sQ + r * KP + c);
+#pragma unroll
+      for (int u = 0; u < kTile / kSub; ++u) {
+        const float4 k = *reinterpret_cast<const float4*>(sK + (sub + kSub * u) * KP + c);
+        s[u] += a.x * k.x;
+        s[u] += a.y * k.y;
+        s[u] += a.z * k.z;
+        s[u] += a.w * k.w;
+      }
+    }
     float m_tile = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kTile / kSub; ++u) {
-      const int t = sub + kSub * u;
-      const int code = sTok[t];
-      float dot = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < D; ++c) dot += sQ[r * D + c] * sK[t * KP + c];
-      bool vis = code >= 0;
-      if (code <= -2) vis = (mask >> (-2 - code)) & 1ull;
-      s[u] = vis && row_ok ? dot * p.scale_log2 : -INFINITY;
+      const int code_u = sTok[sub + kSub * u];
+      bool vis = code_u >= 0;
+      if (code_u <= -2) vis = (mask >> (-2 - code_u)) & 1ull;
+      s[u] = vis && row_ok ? s[u] * p.scale_log2 : -INFINITY;
       m_tile = fmaxf(m_tile, s[u]);
     }
 #pragma unroll
@@ -151,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_valu_kernel(AttnParams p
     for (int u = 0; u < kTile / kSub; ++u) {
       const float pe = exp2f(s[u] - m_use);
       l_tile += pe;
-      sP[r * (kTile + 1) + sub + kSub * u] = pe;
+      sP[r * kPPitch + sub + kSub * u] = pe;
     }
 #pragma unroll
     for (int o = 1; o < kSub; o <<= 1) l_tile += __shfl_xor(l_tile, o, 64);
@@ -160,11 +185,27 @@ __global__ __launch_bounds__(kThreads) void verify_attn_valu_kernel(AttnParams p
     __syncthreads();                          // sP complete (rows are wave-local, but keep it simple)
 
 #pragma unroll
-    for (int i = 0; i < D / kSub; ++i) acc[i] *= alpha;
-    for (int t = 0; t < kTile; ++t) {
-      const float pe = sP[r * (kTile + 1) + t];
+    for (int i = 0; i < NC; ++i) {
+      acc[i].x *= alpha;
+      acc[i].y *= alpha;
+      acc[i].z *= alpha;
+      acc[i].w *= alpha;
+    }
+#pragma unroll 2
+    for (int t = 0; t < kTile; t += 4) {
+      const float4 pe4 = *reinterpret_cast<const float4*>(sP + r * kPPitch + t);
+      const float pe[4] = {pe4.x, pe4.y, pe4.z, pe4.w};
 #pragma unroll
-      for (int i = 0; i < D / kSub; ++i) acc[i] += pe * sV[t * D + sub + kSub * i];
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+          const float4 v = *reinterpret_cast<const float4*>(sV + (t + e) * D + 4 * sub + 4 * kSub * i);
+          acc[i].x += pe[e] * v.x;
+          acc[i].y += pe[e] * v.y;
+          acc[i].z += pe[e] * v.z;
+          acc[i].w += pe[e] * v.w;
+        }
+      }
     }
   }
 
@@ -172,7 +213,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_valu_kernel(AttnParams p
   const int64_t pr = (((int64_t)b * p.Hkv + h) * p.n_splits + split) * p.Mpad + row;
   if (row < p.Mpad) {
 #pragma unroll
-    for (int i = 0; i < D / kSub; ++i) p.part_o[pr * D + sub + kSub * i] = acc[i];
+    for (int i = 0; i < NC; ++i) *reinterpret_cast<float4*>(p.part_o + pr * D + 4 * sub + 4 * kSub * i) = acc[i];
     if (sub == 0) {
       p.part_m[pr] = m_run;
       p.part_l[pr] = l_run;
@@ -190,22 +231,41 @@ __device__ __forceinline__ void store_out<__hip_bfloat16>(__hip_bfloat16* dst, f
 }
 
 // grid: (M, Hkv, B); block: D threads.  Merges the per-split partials of one query row.
+// Memory round trips bound it (a split at a time: two per split): a wavefront finds the maximum with
+// a split per lane, and the partials of kMergeBatch splits are requested together, the first ones
+// before the maximum is known.  The splits are added in ascending order.
 template <typename T>
 __global__ void merge_splits_kernel(AttnParams p) {
   const int row = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int c = threadIdx.x;
   const int D = p.d;
-  const int64_t base = ((int64_t)b * p.Hkv + h) * p.n_splits;
+  const int S = p.n_splits;
+  const int64_t base = ((int64_t)b * p.Hkv + h) * S;
+  float bm[kMergeBatch], bl[kMergeBatch], bo[kMergeBatch];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < kMergeBatch; ++u) {
+      const int64_t pr = (base + min(s0 + u, S - 1)) * p.Mpad + row;
+      bm[u] = p.part_m[pr];
+      bl[u] = p.part_l[pr];
+      bo[u] = p.part_o[pr * D + c];
+    }
+  };
+  request(0);
   float m = -INFINITY;
-  for (int s = 0; s < p.n_splits; ++s) m = fmaxf(m, p.part_m[(base + s) * p.Mpad + row]);
+  for (int s = c & 63; s < S; s += 64) m = fmaxf(m, p.part_m[(base + s) * p.Mpad + row]);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
   float l = 0.f, o = 0.f;
-  for (int s = 0; s < p.n_splits; ++s) {
-    const int64_t pr = (base + s) * p.Mpad + row;
-    const float ms = p.part_m[pr];
-    if (ms == -INFINITY) continue;
-    const float w = exp2f(ms - m);
-    l += w * p.part_l[pr];
-    o += w * p.part_o[pr * D + c];
+  for (int s0 = 0; s0 < S; s0 += kMergeBatch) {
+    if (s0) request(s0);
+#pragma unroll
+    for (int u = 0; u < kMergeBatch; ++u) {
+      if (s0 + u >= S || bm[u] == -INFINITY) continue;
+      const float w = exp2f(bm[u] - m);
+      l += w * bl[u];
+      o += w * bo[u];
+    }
   }
   const int i = row / p.G, j = h * p.G + row % p.G;
   const int64_t orow = ((int64_t)b * p.gamma + i) * p.Hq + j;
