@@ -22,7 +22,7 @@ namespace {
 
 struct Failed {};                      // a Python error is set
 
-enum Kind : uint8_t { kShape, kTensor, kInt };
+enum Kind : uint8_t { kShape, kTensor, kInt, kNumber };   // kNumber: whatever int() takes
 
 struct Param {
   const char* name;
@@ -36,7 +36,7 @@ struct Param {
 struct Args {
   static constexpr int kMost = 20;
   void* ptr[kMost] = {};               // tensors and shapes
-  int64_t num[kMost] = {};             // integers; for tensors the number of bytes
+  int64_t num[kMost] = {};             // integers; for tensors the number of elements (a workspace is bytes)
   PyObject* obj[kMost] = {};
   Py_buffer view[2];
   int views = 0;
@@ -54,8 +54,12 @@ void take(const Signature& s, int i, PyObject* o, Args& a) {
   const Param& p = s.params[i];
   a.obj[i] = o;
   switch (p.kind) {
+    case kNumber:
     case kInt: {
-      const int64_t v = PyLong_AsLongLong(o);
+      PyObject* whole = p.kind == kNumber && !PyLong_Check(o) ? PyNumber_Long(o) : nullptr;
+      if (p.kind == kNumber && !PyLong_Check(o) && !whole) throw Failed{};
+      const int64_t v = PyLong_AsLongLong(whole ? whole : o);
+      Py_XDECREF(whole);
       if (v == -1 && PyErr_Occurred()) throw Failed{};
       if (v != (int32_t)v) {
         PyErr_Format(PyExc_OverflowError, "%s(): %s does not fit a 32-bit integer", s.where, p.name);
@@ -76,7 +80,7 @@ void take(const Signature& s, int i, PyObject* o, Args& a) {
       if (THPVariable_Check(o)) {
         const at::Tensor& t = THPVariable_Unpack(o);
         a.ptr[i] = t.data_ptr();
-        a.num[i] = (int64_t)t.nbytes();
+        a.num[i] = t.numel();
         return;
       }
       PyErr_Format(PyExc_TypeError, "%s(): %s must be a tensor or None", s.where, p.name);
@@ -163,7 +167,7 @@ const Shape* shape_of(const Signature& s, const Args& a, int i) {
 Param shape(const char* n) { return {n, kShape, false, 0}; }
 Param tensor(const char* n) { return {n, kTensor, false, 0}; }
 Param tensor_or_none(const char* n) { return {n, kTensor, true, 0}; }
-Param integer(const char* n) { return {n, kInt, false, 0}; }
+Param number(const char* n) { return {n, kNumber, false, 0}; }
 Param integer(const char* n, int64_t v) { return {n, kInt, true, v}; }
 
 // One function: its signature and the call of the C entry point with the parsed arguments.
@@ -224,7 +228,7 @@ SVF_CALL(svf_verify_step,
          rc = svf_verify_step(sh, (int)a.num[1], a.ptr[2], F32(3), a.ptr[4], a.ptr[5], I32(6), I32(7),
                               a.ptr[8], a.ptr[9], U64(10), static_cast<int32_t*>(a.ptr[11]), static_cast<int32_t*>(a.ptr[12]),
                               a.ptr[13], static_cast<float*>(a.ptr[15]), WS(14), st),
-         shape("shape"), integer("mode"), tensor("q"), tensor("reps"), tensor("K"), tensor("V"), tensor("block_table"),
+         shape("shape"), number("mode"), tensor("q"), tensor("reps"), tensor("K"), tensor("V"), tensor("block_table"),
          tensor("seq_lens"), tensor("k_draft"), tensor("v_draft"), tensor("draft_mask"), tensor("sel_idx"), tensor("sel_cnt"),
          tensor("out"), tensor("ws"), tensor_or_none("lse"))
 
@@ -256,7 +260,7 @@ SVF_CALL(svf_moe_skip,
          const int64_t* d = sizes_of(s, a, 0, 2); void* st = stream(); NoGil free;
          rc = svf_moe_skip(F32(0), (int32_t)d[0], (int32_t)d[1], (int32_t)a.num[1], F32(2), static_cast<int32_t*>(a.ptr[3]),
                            static_cast<uint32_t*>(a.ptr[4]), st),
-         tensor("w"), integer("m"), tensor("beta"), tensor("n_skip"), tensor("keep_mask"))
+         tensor("w"), number("m"), tensor("beta"), tensor("n_skip"), tensor("keep_mask"))
 
 SVF_CALL(svf_accept_resample,
          const int64_t* d = sizes_of(s, a, 0, 3); void* st = stream(); NoGil free;
