@@ -891,7 +891,7 @@ def main():
                                   f"max-abs vs GPU {worst:.2e}; near-tie blocks excused {near_ties}"}
 
     value_us = ms_step * 1e3
-    if cfg.dtype != "bf16" or cfg.d != 128:
+    if cfg.dtype != "bf16":
         kernel_name = "verify_attn_valu_kernel"
     elif cfg.gamma * (cfg.Hq // cfg.Hkv) > 64:     # more than two groups of 32 query rows per KV head
         kernel_name = "verify_attn_mfma_rows_kernel (reuse layer, split merge inside)"
