@@ -128,12 +128,12 @@ struct AttnParams {
   uint64_t* epochs;            // [groups]
   int32_t slice_rows;          // rows of a row group that one workgroup merges: ceil(32 / min(n_splits, 16))
   int32_t B, gamma, Hq, Hkv, G, d, M, Mpad, block_size, k_blocks, n_splits, mask_per_batch, max_seq_len;
-  int32_t split_stride;        // splits per pair that the partials have room for (>= n_splits)
-  int32_t share_splits;        // the launch may share the splits out by the pairs' counts
   int32_t block_shift;         // log2(block_size) if a power of two, else -1
   uint64_t g_magic;            // floor(2^32 / G) + 1: n / G == (n * g_magic) >> 32 for n, G < 65536
   uint64_t hkv_magic;          // the same for Hkv
   float scale_log2;            // sm_scale * log2(e)
+  int32_t split_stride;        // splits per pair that the partials have room for (>= n_splits)
+  int32_t share_splits;        // the launch may share the splits out by the pairs' counts
 };
 
 // Prefix length of sequence b, clamped to what the shape allows so that a corrupt length
@@ -258,7 +258,7 @@ struct AttnPlan {
   int32_t split_stride;      // splits per pair that the partials have room for
   bool share_splits;         // see mfma_shared_splits
   int32_t slice_rows;        // rows of a row group one workgroup merges: ceil(32 / min(n_splits, 16))
-  bool mfma;                 // bf16: matrix-core kernel; otherwise the vector-ALU kernel
+  bool mfma;                 // bf16 (see mfma_supported): matrix-core kernel; otherwise the vector-ALU kernel
   bool fused_select;         // anchor layers retrieve inside the attention kernel
   bool gather;               // the shape can use a gather list
   int32_t gather_groups;     // entries per (sequence, KV head): a whole number of 32-token tiles

@@ -1337,9 +1337,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int S = p.n_splits;                                           // splits of this pair
   const int rg = blockIdx.z;
   if (MODE == kResolve && !kOneTile && p.share_splits) {   // (with one tile per wavefront as planned they are not shared out)
-    if (!share_out_splits(p, pairs, threadIdx.x & 63, gridDim.z, pair, split, S)) return;
+    if (!share_out_splits(p, pairs, threadIdx.x & 63, gridDim.z, pair, split, S) || split >= S) return;
   }
-  if (pair >= pairs || split >= S) return;
+  if (pair >= pairs) return;                                    // (split < n_splits by the grid otherwise)
   const int group = rg * pairs + pair;                          // index of the group's ticket
   const int b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32), h = pair - b * p.Hkv;   // pair / Hkv
 
