@@ -196,7 +196,7 @@ int svf_verify_attn_static_ws(const svf_shape_t* shape, const void* q, const voi
  *   SVF_STEP_ANCHOR call on this `ws`, contents unchanged (K, V, q, the drafts and the outputs
  *   may differ: the layers of one verification step share their page table).  A broken promise
  *   gives attention over the anchor call's rows, never an access outside the pools it was built
- *   for.  Shapes that have no gather list (anything but bf16 with block and page
+ *   for.  Shapes that have no gather list (anything but bf16 with d = 128 and block and page
  *   sizes that are multiples of four, or more than 1024 kept blocks) take the SVF_STEP_REUSE path.
  * Any other mode: SVF_ERR_SHAPE.
  */

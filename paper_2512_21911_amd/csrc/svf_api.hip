@@ -120,11 +120,13 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   pl.off_m = off;
   pl.off_l = off + pairs * pl.split_stride * pl.Mpad * sizeof(float);
   off += align_up((pl.mfma ? 4 : 2) * pairs * pl.split_stride * pl.Mpad * sizeof(float));
-  pl.gather = pl.mfma && s.k_blocks <= kMaxGatherBlocks;
-  pl.fused_select = pl.gather && nb_max_of(s) <= kMaxGatherBlocks;
-  pl.gather_groups = pl.gather ? (int32_t)(((int64_t)s.k_blocks * s.block_size + 31) / 32 * 8) : 0;
+  // (no gather list at d = 64: SVF_STEP_REUSE_GATHER promises to rely on its arguments alone there)
+  const bool listed = pl.mfma && s.k_blocks <= kMaxGatherBlocks;
+  pl.gather = listed && s.d == 128;
+  pl.fused_select = listed && nb_max_of(s) <= kMaxGatherBlocks;
+  pl.gather_groups = listed ? (int32_t)(((int64_t)s.k_blocks * s.block_size + 31) / 32 * 8) : 0;
   pl.off_gather = off;
-  off += align_up(pairs * (size_t)pl.gather_groups * sizeof(uint64_t));
+  off += align_up(pl.gather ? pairs * (size_t)pl.gather_groups * sizeof(uint64_t) : 0);
   // key exchange of the in-kernel retrieval: per (pair, row group)
   pl.off_xkeys = off;
   off += align_up(pl.fused_select ? pl.groups * (size_t)nb_max_of(s) * sizeof(uint64_t) : 0);
@@ -410,7 +412,7 @@ static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void*
     p.reps = reps_to_select_from;
     p.sel_idx_out = const_cast<int32_t*>(sel_idx);
     p.sel_cnt_out = const_cast<int32_t*>(sel_cnt);
-    p.gather_out = reinterpret_cast<uint64_t*>(w + pl.off_gather);
+    p.gather_out = pl.gather ? reinterpret_cast<uint64_t*>(w + pl.off_gather) : nullptr;
     p.gather = nullptr;
   }
   p.B = shape->B;

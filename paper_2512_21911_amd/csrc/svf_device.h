@@ -117,7 +117,7 @@ struct AttnParams {
   const float* reps;           // [B][Hkv][nb_max][d]
   int32_t* sel_idx_out;        // [B][Hkv][k_blocks]
   int32_t* sel_cnt_out;        // [B][Hkv]
-  uint64_t* gather_out;        // [B][Hkv][gather_groups]
+  uint64_t* gather_out;        // [B][Hkv][gather_groups] (NULL at d = 64)
   int32_t nb_max, n_sink, n_local;
   // exchange of block keys between the workgroups of a (pair, row group): one 64-bit word per
   // block (key in the low half, the call's tag in the high half)
@@ -261,7 +261,7 @@ struct AttnPlan {
   bool mfma;                 // bf16 (see mfma_supported): matrix-core kernel; otherwise the vector-ALU kernel
   bool fused_select;         // anchor layers retrieve inside the attention kernel
   bool gather;               // the shape can use a gather list
-  int32_t gather_groups;     // entries per (sequence, KV head): a whole number of 32-token tiles
+  int32_t gather_groups;     // groups of four slots per (sequence, KV head): a whole number of 32-token tiles
   size_t off_o, off_m, off_l, off_tickets, off_gather, off_xkeys, off_epochs, bytes;
   size_t groups;             // (sequence, KV head, row group) triples: entries of tickets / epochs
 };

@@ -316,9 +316,6 @@ __device__ __forceinline__ void load_query_fragments(bf16x8 (&qf)[8], const void
   asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qf[i]) : "v"(row), "n"((i) * 32) : "memory")
   SVF_QFRAG(0); SVF_QFRAG(1); SVF_QFRAG(2); SVF_QFRAG(3);
   SVF_QFRAG(4); SVF_QFRAG(5); SVF_QFRAG(6); SVF_QFRAG(7);
-}
-__device__ __forceinline__ void load_query_fragments(bf16x8 (&qf)[4], const void* row) {
-  SVF_QFRAG(0); SVF_QFRAG(1); SVF_QFRAG(2); SVF_QFRAG(3);
 #undef SVF_QFRAG
 }
 __device__ __forceinline__ u32x2 load8_plain(const void* p) {
@@ -338,10 +335,6 @@ __device__ __forceinline__ void query_fragments_arrived(bf16x8 (&qf)[8]) {
   asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7])
                :
                : "memory");
-}
-
-__device__ __forceinline__ void query_fragments_arrived(bf16x8 (&qf)[4]) {
-  asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]) : : "memory");
 }
 
 // One 32-token tile against the workgroup's 32 query rows.  stage: LDS address of the stage;
@@ -1295,6 +1288,7 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
 // LDS; the workgroups of a pair repeat this work (they share an XCD, so the representatives
 // come out of its L2 after the first), which costs less than two more launches.  The result is
 // written to sel_idx / sel_cnt and, tile by tile, to the gather list for the layers that reuse it.
+// (At D = 64 there is no list: SVF_STEP_REUSE_GATHER relies on nothing but its arguments there.)
 // kOneTile: no wavefront has more than one tile of the cache (the launcher knows).  Then only
 // wavefronts 0 .. 3 compute: wavefront w takes its own tile and, after a barrier, the tile that
 // wavefront w + 4 (same SIMD) has fetched into its stage - the second wavefront of a SIMD gets its
@@ -1434,7 +1428,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   if (MODE != kSelect) {
     const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
                                  (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
-    if (MODE == kGather) {
+    if constexpr (MODE == kGather) {
       // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
       // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
       if (computes) load_query_fragments(qf, qrow);
@@ -1503,8 +1497,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     __syncthreads();                 // the last reads of the staged page table and the query rows are done
   } else if (MODE == kGather) {
     // everything requested ahead of the query fragments (and of an early draft tile), or everything
-    // (an even count: with one load more in than needed where the number is odd)
-    if (kOneTile && computes) wait_vmcnt_upto24((D / 16 + early_draft_loads) & ~1); else wait_vmcnt_upto24(early_draft_loads & ~1);
+    if (kOneTile && computes) wait_vmcnt_upto24(D / 16 + early_draft_loads); else wait_vmcnt_upto24(early_draft_loads);
     front_loads_arrived(gent_raw, rmask_raw, cnt_raw, epoch_raw);
     epoch_word = (uint64_t)epoch_raw[0] | ((uint64_t)epoch_raw[1] << 32);
     if (gent_wanted) gent = (uint64_t)gent_raw[0] | ((uint64_t)gent_raw[1] << 32);
@@ -1639,7 +1632,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     if (split == p.n_splits - 1 && rg == 0) publish_selection(p, s_sel, cnt, pair, tid);
     const int tc = gw + (lane >> 3) * NW - tiles_d;
     const int e = tc * 8 + (lane & 7);
-    if (rg == 0 && lane < 8 * kMaxTiles && tc >= 0 && e < p.gather_groups)
+    if (D == 128 && rg == 0 && lane < 8 * kMaxTiles && tc >= 0 && e < p.gather_groups)
       p.gather_out[(int64_t)pair * p.gather_groups + e] = gent;
   }
   if (!p.draft_mask) rmask = qi >= 63 ? ~0ull : ((2ull << qi) - 1ull);     // linear causal drafts
@@ -1666,7 +1659,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   } else if (MODE == kGather) {
     wait_vmcnt<0>();
   }
-  if (MODE == kGather && computes) query_fragments_arrived(qf);
+  if constexpr (MODE == kGather)
+    if (computes) query_fragments_arrived(qf);
   // (the word comes back behind this wavefront's tile, which it waits for anyway)
   uint64_t where = 0;
   if (counts_xcds && wave == kWaves - 1 && lane == 0)
@@ -2147,7 +2141,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     __syncthreads();                 // the last reads of the staged page table are done
     // for the layers that reuse this retrieval (s_sel is not a stage): stored in front of the tile loop
     if (split == S - 1 && zs == 0) publish_selection(p, s_sel, cnt, pair, tid);
-    if (e_ok && zs == 0) p.gather_out[(int64_t)pair * p.gather_groups + e_u] = gent;
+    if (D == 128 && e_ok && zs == 0) p.gather_out[(int64_t)pair * p.gather_groups + e_u] = gent;
   } else {
     if (MODE != kGather) cnt_raw = p.sel_cnt[pair + vzero];
     cnt = __builtin_amdgcn_readfirstlane(min(max(cnt_raw, 0), p.k_blocks));
@@ -2559,7 +2553,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
     const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds),
                     (unsigned)((row_groups + kWaves - 1) / kWaves));
     if (p.reps) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kSelect>), grid, dim3(kThreads), 0, st, p, pairs);
-    else if (p.gather) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kGather>), grid, dim3(kThreads), 0, st, p, pairs);
+    else if (D == 128 && p.gather) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<128, kGather>), grid, dim3(kThreads), 0, st, p, pairs);
     else hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kResolve>), grid, dim3(kThreads), 0, st, p, pairs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_splits <= kMaxSplitsMergedInKernel) return e;
@@ -2573,13 +2567,13 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
   const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits;
-#define SVF_LAUNCH_ATTN(MODE)                                                                              \
+#define SVF_LAUNCH_ATTN(DIM, MODE)                                                                         \
   do {                                                                                                     \
-    if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<D, MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
-    else hipLaunchKernelGGL((verify_attn_mfma_kernel<D, MODE, false>), grid, dim3(kThreads), 0, st, p, pairs);          \
+    if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
+    else hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, false>), grid, dim3(kThreads), 0, st, p, pairs);          \
   } while (0)
-  if (p.reps) SVF_LAUNCH_ATTN(kSelect);
-  else if (p.gather) SVF_LAUNCH_ATTN(kGather);
+  if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
+  else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
   else {
     if (p.share_splits) {
       // as planned: n_splits rows of the grid.  Shared out: one share per compute unit and one more per
@@ -2589,7 +2583,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
       if (y < p.n_splits + 1) y = p.n_splits + 1;
       grid = dim3((unsigned)x, (unsigned)y, (unsigned)row_groups);
     }
-    SVF_LAUNCH_ATTN(kResolve);
+    SVF_LAUNCH_ATTN(D, kResolve);
   }
 #undef SVF_LAUNCH_ATTN
   return hipGetLastError();

@@ -2,8 +2,11 @@
 partials), against the CPU oracle, at the sizes where their tiles, splits and row groups have edges,
 and bit for bit whatever the workgroups' waits for each other do."""
 import pytest
+import torch
 
-from svf_harness import full_parity
+import paper_2512_21911_amd as S
+import workloads as W
+from svf_harness import DeviceRun, full_parity, to_gpu
 from test_gpu_parity import same_bits_whatever_the_wait, small
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +38,19 @@ def test_d64(name):
 @pytest.mark.parametrize("name", ["ragged_tail_contiguous", "several_tiles_per_wavefront", "rows_tree24"])
 def test_d64_same_bits_whatever_the_workgroups_wait_for_each_other(name):
     same_bits_whatever_the_wait(D64[name])
+
+
+@pytest.mark.parametrize("name", ["ragged_tail_contiguous", "several_tiles_per_wavefront", "rows_tree24"])
+def test_d64_gather_mode_relies_on_its_arguments_alone(name):
+    """A selection that no anchor call made, a workspace that no call has used: SVF_STEP_REUSE_GATHER of a
+    shape without a gather list is SVF_STEP_REUSE, bit for bit."""
+    cfg = D64[name]
+    run = DeviceRun(cfg, to_gpu(W.make_layer(cfg)))
+    run.block_reps().score_select().verify_step(S.SVF_STEP_REUSE).sync()
+    out, lse = run.out.clone(), run.lse.clone()
+    run.ws = S.new_workspace(run.shape)
+    run.out.fill_(float("nan"))
+    run.lse.fill_(float("nan"))
+    run.verify_step(S.SVF_STEP_REUSE_GATHER).sync()
+    assert torch.equal(run.out.view(torch.int16), out.view(torch.int16))
+    assert torch.equal(run.lse.view(torch.int32), lse.view(torch.int32))
