@@ -1208,53 +1208,57 @@ struct TileInfo {
 // that no wavefront gets more than kMaxTiles tiles; the rest of the grid leaves.  Every workgroup works
 // the shares out for itself, from the same counts.  Neighbouring shares go to one XCD.
 // Where every count is the per-head rule's own, min(k_blocks, blocks of the sequence), nothing is
-// changed: the step modes must then add up in the same order.
-// Returns false if this workgroup has no part.
+// changed: the step modes must then add up in the same order, and the planned grid is the faster one.  To find
+// that out each wavefront looks at 32 pairs and leaves their tiles in LDS.  kLoadsFirst: while the planned pair's
+// front loads are on their way, which costs nothing where the counts are even (0.4 us per launch otherwise).
+// kPairsFirst: before any other load, where the plan has more workgroups than shares can be needed: if the
+// counts differ, the rest of them leave one after the other behind the others' work (0.5 - 0.9 us per launch sooner).
+// Even counts, svf_verify_attn of 4 x 8 pairs with 128 blocks of 64: 55.3 us by the kernel that knows the plan
+// only, 55.6 so; 68.3 with the grid laid out for the most shares there can be.
 // (4 sequences, 8 heads, 256 kept blocks of 64 among them, most of them in one or two heads: 63 us as
-// planned, 19 us so.)
+// planned, 19 us so.  A count per workgroup for its own pair only, splits cut to its tiles: 36 us; the long
+// lists' workgroups then share an XCD's 32 compute units.)
+constexpr int kAsPlanned = 0, kLoadsFirst = 1, kPairsFirst = 2;
 constexpr int kShareChunks = 4;              // pairs this handles: 64 per chunk
 constexpr int kMaxSharedSplits = 32;         // splits of one pair: two batches of sixteen in the merge
-__device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs, int lane, int row_groups, int& pair,
-                                                 int& split, int& S) {
-  int cnt[kShareChunks], L[kShareChunks], tiles[kShareChunks];
-#pragma unroll
-  for (int c = 0; c < kShareChunks; ++c) {
-    cnt[c] = L[c] = 0;
-    if (c * 64 < pairs) {
-      const int i = min(c * 64 + lane, pairs - 1);
-      cnt[c] = p.sel_cnt[i];
-      L[c] = p.seq_lens[(uint32_t)(((uint64_t)(uint32_t)i * p.hkv_magic) >> 32)];
-    }
-  }
-  const int tiles_d = (p.gamma + kTile - 1) / kTile;
-  bool uneven = false;
+constexpr int kUneven = (int)0x80000000;     // flag beside a pair's tiles: the count is not the per-head rule's
+static_assert(kShareChunks * 64 == kWaves * 32, "a wavefront looks at 32 pairs");
+
+// Counts (lanes 0 .. 31) and sequence lengths (lanes 32 .. 63) of this wavefront's 32 pairs.
+__device__ __forceinline__ int load_pair_counts(const AttnParams& p, int pairs, int wave, int lane) {
+  const int i = min(wave * 32 + (lane & 31), pairs - 1);
+  const int32_t* const len = p.seq_lens + (uint32_t)(((uint64_t)(uint32_t)i * p.hkv_magic) >> 32);
+  return *(lane < 32 ? p.sel_cnt + i : len);
+}
+__device__ __forceinline__ void leave_pair_tiles(const AttnParams& p, int pairs, int loaded, int wave, int lane, int* tiles) {
+  const int L = __shfl(loaded, (lane & 31) + 32, 64);
+  if (lane >= 32) return;
+  const int cnt = min(max(loaded, 0), p.k_blocks);
+  const bool uneven = cnt < p.k_blocks && cnt * p.block_size < min(L, p.max_seq_len);
+  const int n = (p.gamma + kTile - 1) / kTile + (cnt * p.block_size + kTile - 1) / kTile;
+  tiles[wave * 32 + lane] = wave * 32 + lane < pairs ? n | (uneven ? kUneven : 0) : 0;
+}
+// This workgroup's pair, its split and the pair's number of splits; false if it has no part.
+// The grid holds all shares: of W workgroups per row group, W - pairs (256 / row_groups at most) are shared
+// out.  Where a tile is then worth 1 / 32 of a share or more, a pair gets at most one split more than its share
+// rounded down; where it is worth less, the least, ceil(tiles / 32) <= n_splits.
+__device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs, int lane, int row_groups,
+                                                 const int (&tiles)[kShareChunks], int& pair, int& split, int& S) {
   int total = 0;
 #pragma unroll
-  for (int c = 0; c < kShareChunks; ++c) {
-    tiles[c] = 0;
-    if (c * 64 < pairs) {
-      const int n = min(max(cnt[c], 0), p.k_blocks);
-      uneven = uneven || (n < p.k_blocks && n * p.block_size < min(L[c], p.max_seq_len));
-      if (c * 64 + lane < pairs) tiles[c] = tiles_d + (n * p.block_size + kTile - 1) / kTile;
-      total += __builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)tiles[c]), 63);
-    }
-  }
+  for (int c = 0; c < kShareChunks; ++c)
+    if (c * 64 < pairs) total += __builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(tiles[c] & ~kUneven)), 63);
   const int id = blockIdx.y * gridDim.x + blockIdx.x;
-  if (!__any(uneven)) {
-    // (gridDim.x is a multiple of kXcds)
-    split = blockIdx.y;
-    pair = blockIdx.x;
-    return split < S && pair < pairs;
-  }
-  const float per_tile = (float)(256 / row_groups) / (float)total;
+  const float per_tile = (float)min(256 / row_groups, (int)(gridDim.x * gridDim.y) - pairs) / (float)total;
   int s[kShareChunks], incl[kShareChunks], shares = 0;
 #pragma unroll
   for (int c = 0; c < kShareChunks; ++c) {
     s[c] = incl[c] = 0;
     if (c * 64 < pairs) {
-      const int most = min((tiles[c] + kWaves - 1) / kWaves, p.split_stride);
-      const int least = (tiles[c] + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
-      if (c * 64 + lane < pairs) s[c] = max(max(min((int)((float)tiles[c] * per_tile), most), least), 1);
+      const int n = tiles[c] & ~kUneven;
+      const int most = min((n + kWaves - 1) / kWaves, p.split_stride);
+      const int least = (n + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
+      if (c * 64 + lane < pairs) s[c] = max(max(min((int)((float)n * per_tile), most), least), 1);
       incl[c] = shares + (int)wave_inclusive_sum((uint32_t)s[c]);
       shares = __builtin_amdgcn_readlane(incl[c], 63);
     }
@@ -1275,8 +1279,7 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
   return true;
 }
 
-// grid: x = kXcds * n_splits, y = ceil(pairs / kXcds), z = row groups; pairs = B * Hkv.  (kResolve with
-// share_splits: x = pairs rounded up to a multiple of kXcds, y = as many as the shares can need.)
+// grid: x = kXcds * n_splits, y = ceil(pairs / kXcds), z = row groups; pairs = B * Hkv.
 // Workgroups are handed to the XCDs round-robin in x-fastest order and gridDim.x is a multiple
 // of kXcds, so blockIdx.x mod kXcds names the XCD: all splits and all row groups of a pair
 // share it (the second reader of a pair's K/V finds them in that XCD's L2).
@@ -1296,7 +1299,8 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
 // cost is its instruction count: 0.5 instead of 1.0 us), four wavefronts instead of eight load
 // query fragments, and the tiles that arrive last are computed by wavefronts that have the SIMD
 // to themselves.  Also (MODE kGather): which of the up-front loads go out first, see below.
-template <int D, int MODE, bool kOneTile>
+// SHARE: see share_out_splits.
+template <int D, int MODE, bool kOneTile, int SHARE = kAsPlanned>
 __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p, int pairs) {
   // one stage per wavefront, plus one for draft tile 0 (its owner then streams its cache tile
   // at the same time); after the main loop stage w becomes wavefront w's fp32 output buffer
@@ -1330,41 +1334,51 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int pair = blockIdx.y * kXcds + blockIdx.x % kXcds;
   int S = p.n_splits;                                           // splits of this pair
   const int rg = blockIdx.z;
-  if (MODE == kResolve && !kOneTile && p.share_splits) {   // (with one tile per wavefront as planned they are not shared out)
-    if (!share_out_splits(p, pairs, threadIdx.x & 63, gridDim.z, pair, split, S) || split >= S) return;
-  }
-  if (pair >= pairs) return;                                    // (split < n_splits by the grid otherwise)
-  const int group = rg * pairs + pair;                          // index of the group's ticket
-  const int b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32), h = pair - b * p.Hkv;   // pair / Hkv
-
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
+  static_assert(SHARE == kAsPlanned || (MODE == kResolve && !kOneTile), "shared out by the kernel that resolves its tiles one after the other");
+  const bool planned = pair < pairs;                            // (split < n_splits by the grid)
+  if (SHARE == kAsPlanned && !planned) return;
+  int pair_counts = 0;
+  if (SHARE != kAsPlanned) {
+    pair_counts = load_pair_counts(p, pairs, wave, lane);
+    pair = min(pair, pairs - 1);                                // (its loads are valid, whatever comes of it)
+  }
+  int group, b, h;                                              // index of the group's ticket, pair / Hkv, pair % Hkv
+  auto place_pair = [&]() {
+    group = rg * pairs + pair;
+    b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32);
+    h = pair - b * p.Hkv;
+  };
+  place_pair();
+
   const int l32 = lane & 31, g = lane >> 5;
   const int row0 = rg * 32;
-  const int NW = kWaves * S;
-  const int gw = split * kWaves + wave;
+  int NW = kWaves * S;
+  int gw = split * kWaves + wave;
   constexpr int kSlices = kOneTile ? kWaves / 2 : kWaves;      // wavefronts that compute
-  const bool computes = wave < kSlices;                         // (wave-uniform)
+  const bool computes = !kOneTile || wave < kSlices;            // (wave-uniform)
   // Draft tile 0 has a stage of its own, of which only the four-token groups that hold a draft
   // are fetched (two of eight for eight drafts: 4 load instructions instead of 32).  The V rows
   // of the other groups must still be finite (their weights are zero, and 0 x NaN is not): the
   // wavefront that owns the tile clears them now, before it has any load in flight.  What the K
   // rows hold does not matter: the scores of slots without a token are replaced.
-  if (gw == 0) {
+  auto clear_draft_stage = [&]() {
+    if (gw != 0) return;
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int k = 0; k < kTileBytes / 1024; ++k)
       *reinterpret_cast<u32x4*>(smem + kWaves * kStageBytes<D> + (D == 128 ? kTileBytes : 0) + k * 1024 + lane * 16) = zero;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  }
+  };
+  if (SHARE == kAsPlanned) clear_draft_stage();
   const int tiles_d = (p.gamma + kTile - 1) / kTile;           // draft tiles come first
 
   const char* Kc = static_cast<const char*>(p.K);
   const char* Vc = static_cast<const char*>(p.V);
   const char* Kd = static_cast<const char*>(p.k_draft);
   const char* Vd = static_cast<const char*>(p.v_draft);
-  const int32_t* __restrict__ sel_g = p.sel_idx + (int64_t)pair * p.k_blocks;
 
   // ---- this lane's query row as B operands (issued first: vector loads complete in order, so
   // a wait for these must not have the K/V stream in front of it), and the row's draft mask ----
@@ -1379,7 +1393,6 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   RetrievalLoads<D> rl;
   if (MODE == kSelect)
     rl = issue_retrieval_loads<D>(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
-  const int32_t* const table_row = p.table + (int64_t)b * p.kv.max_pages;
   // With a gather list the tile loads wait for nothing but their gather entries.  Where a
   // wavefront has one tile (kOneTile) the entries (with the draft mask and the pair's block
   // count) go out ahead of the query fragments, which may then arrive while the tile is on its
@@ -1425,17 +1438,13 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     qpiece = *reinterpret_cast<const u32x4*>(static_cast<const __hip_bfloat16*>(p.q) +
                                              (((int64_t)b * p.gamma + ri) * p.Hq + h * p.G + rj) * D + tid % kQChunks * 8);
   }
-  if (MODE != kSelect) {
-    const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
-                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
-    if constexpr (MODE == kGather) {
-      // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
-      // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
-      if (computes) load_query_fragments(qf, qrow);
-    } else if (computes) {
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
-    }
+  auto query_row = [&]() {
+    return static_cast<const __hip_bfloat16*>(p.q) + (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
+  };
+  if constexpr (MODE == kGather) {
+    // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
+    // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
+    if (computes) load_query_fragments(qf, query_row());
   }
   if (MODE == kGather && !kOneTile) request_entries();
   // Draft tile 0 into its own stage, by its owner, ahead of everything that depends on the kept
@@ -1461,20 +1470,55 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   };
   // (with a gather list: now, without waiting for the entries)
   if (MODE == kGather && gw == 0) request_draft_tile();
-  if (MODE != kGather && p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
-
-  int L = 0;
-  if (MODE != kGather) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
+  // what a wavefront without a gather list knows its tiles from (raw: nothing here waits)
+  int L = 0, cnt = 0;
+  // the group's epoch word: this call's tag (for the key exchange of a retrieval and for the
+  // split partials) is its low half plus one, its high half the wait budget
+  uint64_t epoch_word = 0;
+  auto load_front = [&]() {
+    if (MODE == kResolve && computes) {
+      const __hip_bfloat16* qrow = query_row();
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+    }
+    if (MODE != kGather && p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
+    if (MODE != kGather) L = p.seq_lens[b + vzero];
+    if (MODE == kResolve) {
+      epoch_word = p.epochs[group + vzero];
+      cnt = p.sel_cnt[pair + vzero];
+    }
+  };
+  if (SHARE != kPairsFirst) load_front();
+  if (SHARE != kAsPlanned) {
+    int* const pair_tiles = reinterpret_cast<int*>(&sm_m[0][0]);      // (free until the stream has ended)
+    static_assert(sizeof(sm_m) >= kShareChunks * 64 * sizeof(int), "a word per pair");
+    leave_pair_tiles(p, pairs, pair_counts, wave, lane, pair_tiles);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    int tiles_of[kShareChunks], flags = 0;
+#pragma unroll
+    for (int c = 0; c < kShareChunks; ++c) flags |= tiles_of[c] = pair_tiles[c * 64 + lane];
+    if (__any(flags < 0)) {
+      if (!share_out_splits(p, pairs, lane, gridDim.z, tiles_of, pair, split, S)) return;
+      place_pair();
+      NW = kWaves * S;
+      gw = split * kWaves + wave;
+      if (SHARE == kLoadsFirst) load_front();
+    } else if (!planned) {
+      return;
+    }
+    if (SHARE == kPairsFirst) load_front();
+  }
+  if (SHARE != kAsPlanned) clear_draft_stage();
+  const int32_t* __restrict__ sel_g = p.sel_idx + (int64_t)pair * p.k_blocks;
+  const int32_t* const table_row = p.table + (int64_t)b * p.kv.max_pages;
+  if (MODE != kGather) L = min(max(L, 0), p.max_seq_len);
   if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
   if (MODE == kSelect && tid < 32 * kQChunks) {
     const int r = tid / kQChunks;
     *reinterpret_cast<u32x4*>(q_stage + r * (D * 2) + ((tid % kQChunks ^ (r & (kQChunks - 1))) << 4)) = qpiece;
   }
-  int cnt;
-  // the group's epoch word: this call's tag (for the key exchange of a retrieval and for the
-  // split partials) is its low half plus one, its high half the wait budget
-  uint64_t epoch_word = 0;
-  if (MODE == kResolve) epoch_word = p.epochs[group + vzero];
   if (MODE == kSelect) {
     epoch_word = rl.epoch_word;
     const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, group, tid, lane, wave, [&]() {
@@ -1504,7 +1548,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     if (p.draft_mask) rmask = (uint64_t)rmask_raw[0] | ((uint64_t)rmask_raw[1] << 32);
     cnt = __builtin_amdgcn_readfirstlane(min(max((int)cnt_raw, 0), p.k_blocks));
   } else {
-    cnt = __builtin_amdgcn_readfirstlane(min(max(p.sel_cnt[pair + vzero], 0), p.k_blocks));
+    cnt = __builtin_amdgcn_readfirstlane(min(max(cnt, 0), p.k_blocks));
   }
   const int n_prefix = cnt * p.block_size;
   const int tiles = tiles_d + (n_prefix + kTile - 1) / kTile;
@@ -2458,8 +2502,8 @@ int mfma_splits(const svf_shape_t& s) {
 }
 
 // Splits a pair may be given where the launch shares them out by the pairs' counts (share_out_splits), or
-// 0 where it uses mfma_splits for every pair: with one tile per wavefront as planned there is nothing to
-// gain, and the shares are worked out for up to 64 kShareChunks pairs.  The partials it takes are held to
+// 0 where it uses mfma_splits for every pair: with one tile per wavefront or one split per pair as planned there
+// is nothing to share out, and the shares are worked out for up to 64 kShareChunks pairs.  The partials it takes are held to
 // 8 MB, which keeps small workspaces small.
 int mfma_shared_splits(const svf_shape_t& s) {
   const int M = s.gamma * (s.Hq / s.Hkv);
@@ -2467,7 +2511,7 @@ int mfma_shared_splits(const svf_shape_t& s) {
   const int64_t pairs = (int64_t)s.B * s.Hkv;
   const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
   const int64_t cover = (256 + pairs * row_groups - 1) / (pairs * row_groups);
-  if (pairs > 64 * kShareChunks || tiles - 1 <= kWaves * cover) return 0;
+  if (pairs > 64 * kShareChunks || tiles - 1 <= kWaves * cover || mfma_splits(s) == 1) return 0;
   const int64_t most = (tiles + kWaves - 1) / kWaves < kMaxSharedSplits ? (tiles + kWaves - 1) / kWaves : kMaxSharedSplits;
   const int64_t n = mfma_splits(s);
   const int64_t room = ((int64_t)8 << 20) / (pairs * row_groups * 32 * kRowBytes);
@@ -2562,7 +2606,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
                        advance_tags);
     return hipGetLastError();
   }
-  dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds), (unsigned)row_groups);
+  const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds), (unsigned)row_groups);
   // one tile per wavefront (the owner of draft tile 0 streams a second one beside it)?  The same
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
@@ -2574,17 +2618,11 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
   else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
-  else {
-    if (p.share_splits) {
-      // as planned: n_splits rows of the grid.  Shared out: one share per compute unit and one more per
-      // pair for the least share, or the least shares alone (n_splits per pair where all are full)
-      const int64_t x = (pairs + kXcds - 1) / kXcds * kXcds;
-      int64_t y = (256 / row_groups + 2 * (int64_t)pairs + kXcds + x - 1) / x;
-      if (y < p.n_splits + 1) y = p.n_splits + 1;
-      grid = dim3((unsigned)x, (unsigned)y, (unsigned)row_groups);
-    }
-    SVF_LAUNCH_ATTN(D, kResolve);
-  }
+  else if (p.share_splits && (int64_t)grid.x * grid.y <= 256 / row_groups + pairs)
+    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
+  else if (p.share_splits)
+    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kPairsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
+  else SVF_LAUNCH_ATTN(D, kResolve);
 #undef SVF_LAUNCH_ATTN
   return hipGetLastError();
 }

@@ -69,3 +69,38 @@ def test_attention_over_lists_of_different_lengths(counts, d):
             assert torch.equal(run.out.view(torch.int16), out0.view(torch.int16)), f"polls={polls}"
     out_ref, lse_ref = oracle_attn(cfg, x, idx, cnt)
     check_attn(cfg, run.out, run.lse, out_ref, lse_ref)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=3, Hq=6, Hkv=3, gamma=5, T=8192, k_blocks=250),                       # 9 pairs: no multiple of eight
+    dict(B=5, Hq=40, Hkv=5, gamma=5, T=2400, k_blocks=70, d=64),                 # 40 rows: two row groups
+    dict(B=13, Hq=10, Hkv=5, gamma=3, T=1600, k_blocks=50),                      # 65 pairs: the second chunk holds one
+    dict(B=9, Hq=90, Hkv=15, gamma=6, T=1500, k_blocks=44, d=64),                # 135 pairs, two row groups
+    dict(B=16, Hq=16, Hkv=16, gamma=4, T=1600, k_blocks=50, d=64),               # 256 pairs, all four chunks
+], ids=lambda kw: f"{kw['B']}x{kw['Hkv']}")
+def test_shared_out_splits_over_many_pairs(kw):
+    """Counts drawn per pair (empty, short, all that fits): every chunk of 64 pairs, the padded pairs of the grid
+    and both row groups, against the oracle; then every count the per-head rule's: the planned splits,
+    the bits of the step that reuses the selection through its gather list."""
+    cfg = small_bf16(block_size=32, page_size=16, min_len=kw["T"] - 200, **kw)
+    x = W.make_layer(cfg)
+    run = DeviceRun(cfg, to_gpu(x))
+    rng = np.random.default_rng(cfg.B)
+    idx = np.full((cfg.B, cfg.Hkv, cfg.k_blocks), -1, dtype=np.int32)
+    lens = x["seq_lens"].tolist()
+    for b in range(cfg.B):
+        nb = min(-(-lens[b] // 32), cfg.k_blocks)
+        for h in range(cfg.Hkv):
+            c = int(rng.choice([0, 1, 3, 9, nb, rng.integers(1, nb + 1)]))
+            idx[b, h, :c] = np.sort(rng.choice(nb, c, replace=False))
+    cnt = (idx >= 0).sum(-1).astype(np.int32)
+    idx, cnt = torch.from_numpy(idx), torch.from_numpy(cnt)
+    for _ in range(2):
+        run.out.fill_(float("nan"))
+        run.verify_attn(sel_idx=idx.cuda(), sel_cnt=cnt.cuda()).sync()
+    check_attn(cfg, run.out, run.lse, *oracle_attn(cfg, x, idx, cnt))
+    run.block_reps().verify_step(S.SVF_STEP_ANCHOR).verify_step(S.SVF_STEP_REUSE_GATHER).sync()
+    out = run.out.clone()
+    run.out.fill_(float("nan"))
+    run.verify_attn().sync()
+    assert torch.equal(run.out.view(torch.int16), out.view(torch.int16))
