@@ -333,27 +333,28 @@ __device__ __forceinline__ void finish_channels(const FfnParams& p, int lane, in
 // (Wavefronts that split the model dimension with two private stages of 128 each kept 64 KB in flight at
 // most, fetched x from L2 into registers and added four partial tiles at the end.  14336 x 4096: 40.6 -> 38.2 us,
 // 6.1 TB/s, for 8 tokens; 51.4 -> 40.8 us for 60, of which 10 for the order of the chunks, see `first`.)
-//   One workgroup per compute unit, so the tile height p.tile_rows <= 32 is chosen such that the
+//   One workgroup per compute unit, so the tile height tile_rows <= 32 is chosen such that the
 //   workgroups fill whole rounds; the rows of the 32-row matrix-core tile past it repeat its last
 //   row, and a tile that would reach past d_ff is moved back to end there (the channels it shares with
 //   the tile before it are that tile's to write: workgroups add in different orders).
 constexpr int kWalkK = 64;                               // model dimensions per chunk
 constexpr int kWalkRow = kWalkK * 2;                     // 128 bytes
 constexpr int kWalkTile = kTileRows * kWalkRow;          // 4 KB: one wavefront's rows, or 32 tokens of x
-template <int NT> constexpr int kWalkStage = (kGuWaves + NT) * kWalkTile;
-template <int NT> constexpr int kWalkStages = NT == 1 ? 7 : 6;
-template <int NT> constexpr int kWalkLoads = 4 + NT;     // load instructions of a wavefront per chunk
+// XT: 32-token pieces of x in a stage, NT per chunk
+template <int XT> constexpr int kWalkStage = (kGuWaves + XT) * kWalkTile;
+template <int XT> constexpr int kWalkStages = XT == 1 ? 7 : 6;
+template <int XT> constexpr int kWalkLoads = 4 + XT;     // load instructions of a wavefront per stage
 
-// Waits until this wavefront's loads of all but `chunks` (0 .. 5) chunks have landed.
-template <int NT>
-__device__ __forceinline__ void wait_walk(int chunks) {
-  switch (chunks) {
+// Waits until this wavefront's loads of all but `stages` (0 .. 5) stages have landed.
+template <int XT>
+__device__ __forceinline__ void wait_walk(int stages) {
+  switch (stages) {
     case 0: wait_vmcnt<0>(); break;
-    case 1: wait_vmcnt<kWalkLoads<NT>>(); break;
-    case 2: wait_vmcnt<2 * kWalkLoads<NT>>(); break;
-    case 3: wait_vmcnt<3 * kWalkLoads<NT>>(); break;
-    case 4: wait_vmcnt<4 * kWalkLoads<NT>>(); break;
-    default: wait_vmcnt<5 * kWalkLoads<NT>>(); break;
+    case 1: wait_vmcnt<kWalkLoads<XT>>(); break;
+    case 2: wait_vmcnt<2 * kWalkLoads<XT>>(); break;
+    case 3: wait_vmcnt<3 * kWalkLoads<XT>>(); break;
+    case 4: wait_vmcnt<4 * kWalkLoads<XT>>(); break;
+    default: wait_vmcnt<5 * kWalkLoads<XT>>(); break;
   }
 }
 
@@ -367,46 +368,53 @@ __device__ __forceinline__ void fragments_wait(u32x4 (&f)[4]) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : : "memory");
 }
 
-// grid: (ceil(ceil(d_ff / tile_rows) / 2)); block: 256
-template <int NT>
+// TILES = 2 as above.  TILES = 1 (up to 32 tokens): one channel tile per workgroup, for hidden sizes whose
+// pairs of tiles fill their rounds badly; a stage then holds two chunks, wavefronts 0 and 1 walk the
+// even ones and 2 and 3 the odd ones (d_model is a multiple of two chunks), and the two sums are added last.
+// grid: (ceil(ceil(d_ff / tile_rows) / TILES)); block: 256
+template <int NT, int TILES>
 __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams p) {
-  constexpr int RS = 32 * NT + 1;                        // row stride of the [matrix tile][channel][token] sums
-  constexpr int S = kWalkStages<NT>;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[S * kWalkStage<NT>];
-  static_assert(kGuWaves * kTileRows * RS * 4 <= S * kWalkStage<NT>, "the sums fit the stages");
+  constexpr int KP = 2 / TILES;                          // chunks per stage
+  constexpr int XT = NT * KP;
+  constexpr int RS = 32 * NT + 1;                        // row stride of the [wavefront][channel][token] sums
+  constexpr int S = kWalkStages<XT>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[S * kWalkStage<XT>];
+  static_assert(kGuWaves * kTileRows * RS * 4 <= S * kWalkStage<XT>, "the sums fit the stages");
   static_assert(S - 2 <= 5, "wait_walk");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int l32 = lane & 31, g = lane >> 5;
-  const int R = p.tile_rows;
-  const int n_chunks = p.d_model / kWalkK;
-  // wavefront w: tile w / 2 of the workgroup's two, gate (even) or up (odd) matrix
-  const int c0 = min((blockIdx.x * 2 + (wave >> 1)) * R, p.d_ff - R);
+  const int R = p.walk.tile_rows;
+  const int n_steps = p.d_model / (kWalkK * KP);         // stages to walk
+  // wavefront w: gate (even) or up (odd) matrix; tile w / 2 of the workgroup's two, or chunk w / 2 of a stage
+  const int half = wave >> 1;
+  const int c0 = min((blockIdx.x * TILES + (TILES == 2 ? half : 0)) * R, p.d_ff - R);
   // (a tile's and x's offsets fit 32 bits: at most 64 rows of 2 MB)
   const uint32_t row_bytes = (uint32_t)p.d_model * 2u;
   const char* const w_tile = static_cast<const char*>((wave & 1) ? p.w_up : p.w_gate) + (int64_t)c0 * row_bytes;
   // load n of a tile brings rows 8n .. 8n + 7, eight lanes per row
-  uint32_t w_off[4], x_off[NT];
+  uint32_t w_off[4], x_off[XT];
   const int lrow = lane >> 3, lcol = lane & 7;
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
     const int r = 8 * n + lrow;
     w_off[n] = (uint32_t)min(r, R - 1) * row_bytes + (uint32_t)((lcol ^ ((r >> 1) & 7)) << 4);
   }
-  // x: wavefront w brings loads w NT .. w NT + NT - 1 of its 4 NT (tokens past the last repeat it)
+  // x: wavefront w brings loads w XT .. w XT + XT - 1 of the stage's 4 XT, those of chunk w / 2 where there
+  // are two (tokens past the last repeat it)
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int r = 8 * (wave * NT + t) + lrow;
+  for (int t = 0; t < XT; ++t) {
+    const int r = 8 * ((wave * XT + t) % (4 * NT)) + lrow;
     x_off[t] = (uint32_t)min(r, p.M - 1) * row_bytes + (uint32_t)((lcol ^ ((r >> 1) & 7)) << 4);
   }
   // Workgroups start at different chunks: a chunk of x lies in rows d_model apart, a power of two as a
   // rule, which is few memory channels, and the 32 compute units of an XCD would all ask them at once.
-  const int first = (int)((blockIdx.x / 8) % 32 * (uint32_t)n_chunks / 32);
+  const int first = (int)((blockIdx.x / 8) % 32 * (uint32_t)n_steps / 32);
   auto request = [&](int i, unsigned char* st) {
     const int k = i + first;
-    uint32_t koff = (uint32_t)(k >= n_chunks ? k - n_chunks : k) * kWalkRow;
+    uint32_t koff = (uint32_t)((k >= n_steps ? k - n_steps : k) * KP + (TILES == 1 ? half : 0)) * kWalkRow;
     asm volatile("" : "+s"(koff));                       // (a scalar of its own: no per-lane pointers advanced in every round)
     const char* wb = w_tile + koff;
     const char* xb = static_cast<const char*>(p.x) + koff;
@@ -414,9 +422,9 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams
     for (int n = 0; n < 4; ++n)
       __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(wb + w_off[n]), FFN_LDS_PTR(st + wave * kWalkTile + n * 1024), 16, 0, 2);
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < XT; ++t)
       __builtin_amdgcn_global_load_lds(FFN_GLOBAL_PTR(xb + x_off[t]),
-                                       FFN_LDS_PTR(st + kGuWaves * kWalkTile + (wave * NT + t) * 1024), 16, 0, 0);
+                                       FFN_LDS_PTR(st + kGuWaves * kWalkTile + (wave * XT + t) * 1024), 16, 0, 0);
   };
 
   floatx16 acc[NT];
@@ -428,19 +436,20 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams
   const uint32_t lds = (uint32_t)(uintptr_t)FFN_LDS_PTR(smem);
   const uint32_t kx = (uint32_t)((g ^ ((l32 >> 1) & 7)) << 4);
   const uint32_t frag = lds + (uint32_t)l32 * kWalkRow;
-  for (int i = 0; i < min(S - 1, n_chunks); ++i) request(i, smem + i * kWalkStage<NT>);
-  int st = 0;                                            // stage of chunk i
-  for (int i = 0; i < n_chunks; ++i) {
-    wait_walk<NT>(min(S - 2, n_chunks - 1 - i));
+  const uint32_t x_piece = (uint32_t)(kGuWaves + (TILES == 1 ? half : 0)) * kWalkTile;
+  for (int i = 0; i < min(S - 1, n_steps); ++i) request(i, smem + i * kWalkStage<XT>);
+  int st = 0;                                            // stage of step i
+  for (int i = 0; i < n_steps; ++i) {
+    wait_walk<XT>(min(S - 2, n_steps - 1 - i));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     const int prev = st == 0 ? S - 1 : st - 1;
-    if (i + S - 1 < n_chunks) request(i + S - 1, smem + prev * kWalkStage<NT>);
-    uint32_t base = frag + (uint32_t)st * kWalkStage<NT>;
+    if (i + S - 1 < n_steps) request(i + S - 1, smem + prev * kWalkStage<XT>);
+    uint32_t base = frag + (uint32_t)st * kWalkStage<XT>;
     u32x4 wf[4], xf[NT][4];
     read_fragments(wf, base + (uint32_t)wave * kWalkTile, kx);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) read_fragments(xf[t], base + (uint32_t)(kGuWaves + t) * kWalkTile, kx);
+    for (int t = 0; t < NT; ++t) read_fragments(xf[t], base + x_piece + (uint32_t)t * kWalkTile, kx);
     fragments_wait(wf);
 #pragma unroll
     for (int t = 0; t < NT; ++t) fragments_wait(xf[t]);
@@ -462,14 +471,19 @@ __global__ __launch_bounds__(kGuThreads) void ffn_gate_up_fused_kernel(FfnParams
       sums[(wave * kTileRows + 8 * (v >> 2) + 4 * g + (v & 3)) * RS + l32 + 32 * t] = acc[t][v];
   __syncthreads();
   const int quads = R / 4;                               // groups of four channels per tile
-  for (int q0 = wave * kSide<NT>; q0 < 2 * quads; q0 += kGuWaves * kSide<NT>) {
+  for (int q0 = wave * kSide<NT>; q0 < TILES * quads; q0 += kGuWaves * kSide<NT>) {
     const int q = q0 + (NT == 1 ? g : 0);
-    const int tile = q >= quads ? 1 : 0, c = q < 2 * quads ? 4 * (q - tile * quads) : 0;
-    const int nominal = (blockIdx.x * 2 + tile) * R;
+    const int tile = TILES == 2 && q >= quads ? 1 : 0, c = q < TILES * quads ? 4 * (q - tile * quads) : 0;
+    const int nominal = (blockIdx.x * TILES + tile) * R;
     const int ch = min(nominal, p.d_ff - R) + c;
     const float* zg = sums + (2 * tile * kTileRows + c) * RS;
-    finish_channels<NT>(p, lane, ch, q < 2 * quads && ch >= nominal, [&](int j, int m) { return zg[j * RS + m]; },
-                        [&](int j, int m) { return zg[(kTileRows + j) * RS + m]; });
+    auto sum = [&](int row, int m) {                     // (TILES = 1: the even and the odd chunks')
+      float z = zg[row * RS + m];
+      if (TILES == 1) z += zg[(2 * kTileRows + row) * RS + m];
+      return z;
+    };
+    finish_channels<NT>(p, lane, ch, q < TILES * quads && ch >= nominal, [&](int j, int m) { return sum(j, m); },
+                        [&](int j, int m) { return sum(kTileRows + j, m); });
   }
 }
 
@@ -759,18 +773,26 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(FfnParams p) {
 
 }  // namespace
 
-// Channels per tile of the fused walk: one workgroup per compute unit runs at a time, so the
-// cost is (rounds of 256 workgroups) x (rows per tile); the largest multiple of four that
-// minimises it.
-int ffn_fused_tile_rows(int d_ff) {
-  const int per_wg = 2;                                   // channel tiles per workgroup
-  int best = kTileRows;
-  int64_t best_cost = -1;
-  for (int r = kTileRows; r >= 16; r -= 4) {
-    const int64_t wgs = ((d_ff + r - 1) / r + per_wg - 1) / per_wg;
-    const int64_t cost = ((wgs + 255) / 256) * r;
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = r; }
-  }
+namespace {
+// (rounds of 256 workgroups, one per compute unit) x (channels per workgroup of `tiles` tiles of r rows): what the
+// busiest compute unit reads
+int64_t busiest_channels(int d_ff, int r, int tiles) {
+  const int64_t wgs = ((d_ff + r - 1) / r + tiles - 1) / tiles;
+  return (wgs + 255) / 256 * r * tiles;
+}
+}  // namespace
+
+// Channels per tile (a multiple of four) and tiles per workgroup of the fused walk: the fewest channels on the
+// busiest compute unit; of equals the larger tile, then two tiles, which share x.  One tile per workgroup for up
+// to 32 tokens only (the stages have no room for two chunks of more).  Whole layer, d_model 2560, 8 tokens: 8192
+// channels in single tiles of 32 33.2 us, in pairs of 16 36.8 us.
+FfnWalk ffn_fused_walk(int d_ff, int M) {
+  FfnWalk best = {kTileRows, 2};
+  for (int tiles = 2; tiles >= (M <= 32 ? 1 : 2); --tiles)
+    for (int r = kTileRows; r >= 16; r -= 4) {
+      const int64_t cost = busiest_channels(d_ff, r, tiles), least = busiest_channels(d_ff, best.tile_rows, best.tiles);
+      if (cost < least || (cost == least && r > best.tile_rows)) best = {r, tiles};
+    }
   return best;
 }
 
@@ -783,10 +805,17 @@ int ffn_k_splits(int d_model, int d_ff) {
 }
 
 namespace {
-// d_ff up to which the gate / up walk takes the split kernel: with 16 channels per workgroup that is two
-// rounds of 256 workgroups (at 8192 it is 2 - 7 % faster than the other walk, at 12000 9 % slower).  Eight
-// channels where that is one round at most.
-constexpr int kSplitUpTo = 8192, kSplitEightUpTo = 2048;
+// Channels per workgroup of the split kernel, or 0: the fused walk.  Eight where that is one round of 256
+// workgroups at most.  Sixteen up to one round for up to 32 tokens: behind that a second one that is mostly
+// idle is slower than the fused walk's single round of tiles of 20 - 32 channels (whole layer, d_model 4096,
+// 8 / 32 tokens: 4608 channels 34.4 / 38.7 us split, 30.0 / 32.3 us fused; 6144: 37.8 / 42.9 and 34.8 / 37.1),
+// and a full one hardly better (8192: 43.3 against 44.5 us; d_model 2560: 34.5 against 33.2).  Up to two
+// rounds for more tokens, where the fused walk takes two tiles per workgroup (at 8192 channels 2 - 7 %
+// faster than it, at 12000 9 % slower).
+int split_channels(const FfnParams& p) {
+  if (p.d_ff <= 2048) return 8;
+  return p.d_ff <= (p.M <= 32 ? 4096 : 8192) ? 16 : 0;
+}
 
 template <int RC>
 void launch_split(const FfnParams& p, hipStream_t st) {
@@ -800,13 +829,16 @@ void launch_split(const FfnParams& p, hipStream_t st) {
 
 hipError_t launch_sparse_ffn(const FfnParams& p, hipStream_t st) {
   const dim3 gu(p.d_ff / kTileRows);
-  if (p.fused_walk && p.d_ff <= kSplitUpTo) {
-    if (p.d_ff <= kSplitEightUpTo) launch_split<8>(p, st);
+  const int split = p.fused_walk ? split_channels(p) : 0;
+  if (split) {
+    if (split == 8) launch_split<8>(p, st);
     else launch_split<16>(p, st);
   } else if (p.fused_walk) {
-    const int tiles = (p.d_ff + p.tile_rows - 1) / p.tile_rows;
-    if (p.M <= 32) hipLaunchKernelGGL(ffn_gate_up_fused_kernel<1>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
-    else hipLaunchKernelGGL(ffn_gate_up_fused_kernel<2>, dim3((tiles + 1) / 2), dim3(kGuThreads), 0, st, p);
+    const int tiles = (p.d_ff + p.walk.tile_rows - 1) / p.walk.tile_rows;
+    const dim3 grid((tiles + p.walk.tiles - 1) / p.walk.tiles);
+    if (p.walk.tiles == 1) hipLaunchKernelGGL((ffn_gate_up_fused_kernel<1, 1>), grid, dim3(kGuThreads), 0, st, p);
+    else if (p.M <= 32) hipLaunchKernelGGL((ffn_gate_up_fused_kernel<1, 2>), grid, dim3(kGuThreads), 0, st, p);
+    else hipLaunchKernelGGL((ffn_gate_up_fused_kernel<2, 2>), grid, dim3(kGuThreads), 0, st, p);
   } else {
     if (p.M <= 32) hipLaunchKernelGGL(ffn_gate_up_kernel<1>, gu, dim3(kGuThreads), 0, st, p);
     else hipLaunchKernelGGL(ffn_gate_up_kernel<2>, gu, dim3(kGuThreads), 0, st, p);

@@ -9,6 +9,11 @@
 
 namespace svf {
 
+// The fused walk's channels per tile (<= 32) and tiles per workgroup (1 or 2).
+struct FfnWalk {
+  int32_t tile_rows, tiles;
+};
+
 struct FfnParams {
   const void* x;            // bf16 [M][d_model]
   const void* w_gate;       // bf16 [d_ff][d_model]
@@ -24,13 +29,13 @@ struct FfnParams {
   float* partial;           // fp32 [k_splits][M][d_model]
   int32_t M, d_model, d_ff, act, k_splits;
   int32_t fused_walk;       // gate and up matrices walked together (every row of W_up is read)
-  int32_t tile_rows;        // channels per tile of the fused walk (<= 32)
+  FfnWalk walk;
   float tau;
 };
 
 // Slices of the hidden dimension the down projection is cut into (partial sums in the workspace).
 int ffn_k_splits(int d_model, int d_ff);
-int ffn_fused_tile_rows(int d_ff);
+FfnWalk ffn_fused_walk(int d_ff, int M);
 hipError_t launch_sparse_ffn(const FfnParams& p, hipStream_t st);
 
 }  // namespace svf
