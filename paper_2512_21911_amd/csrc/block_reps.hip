@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void block_reps_kernel(RepsParams p, int 
 // channel are added in the order of tl.
 // One block of 64 tokens, 8 heads of 128 channels, bf16: 6.1 - 8.4 -> 4.8 - 5.9 us for 1 to 16
 // blocks with contiguous pages, 17.6 - 22.6 -> 5.4 - 7.5 us for 1 to 16 blocks of each of 4 sequences in
-// pages of 16 tokens (keys out of memory).
+// pages of 16 tokens (keys out of memory).  Where it does not pay: few_is_faster.
 // grid: (blocks in range, B, Hkv); block: kThreads
 constexpr int kFewBytes = 32768;
 constexpr int kFewWorkgroups = 512;
@@ -257,19 +257,32 @@ void launch_for(const RepsParams& p, dim3 grid, int cols, int cpb, int tok_par, 
 
 }  // namespace
 
+namespace {
+// Is the launch of few blocks (one workgroup per head) the faster one?  It must fit: at most two workgroups per
+// compute unit, one head's keys of a block within the stage (d * tok_par items stay within red[]: cols = Hkv d / N
+// >= d / 8, so tok_par <= 2048 / d).  Then it depends on what each is bound by (both measured over 850 shapes:
+// 1 - 16 heads, blocks of 16 - 256 tokens, both types, one or four sequences, keys out of memory).  The wide kernel
+// takes 3 us and a trip to memory per four tokens of a thread, 0.75 us, or 2.4 with a page table
+// (the key's address is a trip of its own); this one 3.6 us (paged 5), its stage filled and summed from
+// LDS, 0.4 us per KB of bf16 (0.35 of fp32), and up to 1 us more with two workgroups per compute unit.
+// In tenths of a microsecond; the constants are such that no shape is slower than with the wide kernel (which
+// takes 4.5 us for 128 tokens of one head of 128 channels, this one 11) and at most 11 % of what can be had is left.
+bool few_is_faster(const RepsParams& p, int dtype, int B, int tok_par) {
+  const int64_t workgroups = (int64_t)p.n_blocks * B * p.Hkv, channels = (int64_t)p.block_size * p.d;
+  if (workgroups > kFewWorkgroups || channels * (dtype == SVF_F32 ? 4 : 2) > kFewBytes) return false;
+  const int64_t trips = (p.block_size + 4 * tok_par - 1) / (4 * tok_par);
+  const int64_t wide = p.kv.page_size > 0 ? 22 * trips - 24 : 8 * trips - 12;      // beyond what both take
+  return wide > channels * (dtype == SVF_F32 ? 7 : 4) / 1024 + workgroups / 51;
+}
+}  // namespace
+
 hipError_t launch_block_reps(const RepsParams& p, int dtype, int B, hipStream_t st) {
   if (p.n_blocks <= 0) return hipSuccess;
   const int N = dtype == SVF_F32 ? 4 : 8;
   const int cols = p.Hkv * p.d / N;
   const int cpb = cols < kThreads ? cols : kThreads;
   const int tok_par = kThreads / cpb;
-  // Few blocks: at most two workgroups per compute unit there (one sequence, 64 tokens of 8 heads: 64 blocks 6.5
-  // against 8.5 us, 128 blocks 11.4 against 9.1), a block whose keys of one head fit the stage, and more tokens
-  // per thread of the wide kernel than its four loads take at once (32 tokens of 4 heads of 64 channels, eight
-  // token lanes: one trip there, 3.2 against 3.9 us).  d * tok_par items stay within red[]:
-  // cols = Hkv d / N >= d / 8, so tok_par <= 2048 / d.
-  if ((int64_t)p.n_blocks * B * p.Hkv <= kFewWorkgroups && p.block_size > 4 * tok_par &&
-      (int64_t)p.block_size * p.d * (16 / N) <= kFewBytes) {
+  if (few_is_faster(p, dtype, B, tok_par)) {
     const dim3 few(p.n_blocks, B, p.Hkv);
     if (dtype == SVF_F32) launch_few<float>(p, few, tok_par, st);
     else launch_few<__hip_bfloat16>(p, few, tok_par, st);
