@@ -22,6 +22,7 @@ int mfma_rows_splits(const svf_shape_t& s);
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr size_t kStaticScratchBytes = (size_t)16 << 20;   // svf_verify_attn_static_ws
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -83,6 +84,8 @@ int check_ws(const svf_shape_t* s, const void* ws, size_t ws_bytes) {
 
 int hip_code(hipError_t e) { return e == hipSuccess ? SVF_OK : SVF_ERR_HIP; }
 
+void lay_out(const svf_shape_t& s, AttnPlan& pl);
+
 }  // namespace
 
 // Workspace layout: [tickets | partial o | partial m, l / records | gather list | exchanged keys | epoch words],
@@ -103,9 +106,23 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
     if (want < 1) want = 1;
     pl.n_splits = (int)want;
   }
+  const size_t pairs = (size_t)s.B * s.Hkv;
   const int shared = pl.mfma && !mfma_rows_mode(s) ? mfma_shared_splits(s) : 0;
   pl.share_splits = shared > 0;
-  pl.split_stride = shared > 0 ? shared : pl.n_splits;
+  pl.split_stride = pl.n_splits;
+  lay_out(s, pl);
+  if (shared > pl.n_splits) {
+    // more splits for a pair as long as a workspace that fits the static array without them still does
+    const size_t now = pl.bytes + scores_bytes(s), per_split = pairs * pl.Mpad * (s.d * (s.d == 128 ? 2 : 4) + 16);
+    const size_t room = now <= kStaticScratchBytes ? (kStaticScratchBytes - now) / per_split : shared;
+    pl.split_stride = pl.n_splits + (int)(room < (size_t)(shared - pl.n_splits) ? room : shared - pl.n_splits);
+    lay_out(s, pl);
+  }
+  return pl;
+}
+
+namespace {
+void lay_out(const svf_shape_t& s, AttnPlan& pl) {
   const size_t pairs = (size_t)s.B * s.Hkv;
   pl.groups = pairs * (pl.Mpad / 32);
   pl.slice_rows = (32 + (pl.n_splits < 16 ? pl.n_splits : 16) - 1) / (pl.n_splits < 16 ? pl.n_splits : 16);
@@ -133,10 +150,7 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   pl.off_epochs = off;
   off += align_up(pl.groups * sizeof(uint64_t));
   pl.bytes = off;
-  return pl;
 }
-
-namespace {
 
 // high half of every group's epoch word: 0 (default wait budget) or the caller's number of polls plus one
 __global__ void set_wait_polls_kernel(uint64_t* epochs, size_t n, uint32_t high_half) {
@@ -455,7 +469,6 @@ int svf_verify_attn(const svf_shape_t* shape, const void* q, const void* K, cons
 // ---- the entry point that allocates nothing ---------------------------------------------------------
 // Its workspace is this array (one copy per GPU, held until the process ends).  In host code the
 // array's name is only a stand-in: the device address comes from hipGetSymbolAddress, once per device.
-constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -497,14 +510,18 @@ int svf_verify_attn_static_ws(const svf_shape_t* shape, const void* q, const voi
   if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(k_draft) || misaligned(v_draft) ||
       misaligned(out))
     return SVF_ERR_SHAPE;
-  // a shape whose workspace does not fit the array is refused
-  if (svf_workspace_bytes(shape) > kStaticScratchBytes) return SVF_ERR_WORKSPACE;
+  // A shape whose workspace does not fit the array is refused; at d = 64 the vector-ALU kernel, which needs
+  // a fraction of it, takes what does not fit with the matrix-core kernel's splits.
+  const bool allow_mfma = svf_workspace_bytes(shape) <= kStaticScratchBytes;
+  if (!allow_mfma &&
+      (shape->d != 64 || plan_attn(*shape, false).bytes + scores_bytes(*shape) > kStaticScratchBytes))
+    return SVF_ERR_WORKSPACE;
   void* ws = static_scratch(&rc);
   if (!ws) return rc;
   // The array keeps what the last call left, of whatever shape: everything the kernels expect to
   // find zero (arrival words, call counters, exchanged keys, and the tagged records, whose tags
   // restart with the counters) is cleared first, by a fill kernel on the caller's stream.
-  const AttnPlan pl = plan_attn(*shape);
+  const AttnPlan pl = plan_attn(*shape, allow_mfma);
   ZeroRanges zr;
   zr.off[0] = pl.off_tickets;
   zr.bytes[0] = pl.off_o - pl.off_tickets;
@@ -515,8 +532,9 @@ int svf_verify_attn_static_ws(const svf_shape_t* shape, const void* q, const voi
   hipLaunchKernelGGL(zero_ranges_kernel, dim3(64), dim3(256), 0, static_cast<hipStream_t>(stream),
                      static_cast<char*>(ws), zr);
   if (hipGetLastError() != hipSuccess) return SVF_ERR_HIP;
+  // (its size has been checked above, against the plan of the kernel at hand)
   return verify_attn_impl(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask_or_null, sel_idx,
-                          sel_cnt, out, lse_or_null, ws, kStaticScratchBytes, stream, false);
+                          sel_cnt, out, lse_or_null, ws, SIZE_MAX, stream, false, nullptr, allow_mfma);
 }
 
 // ---- diagnostics (include/svf_diag.h) ---------------------------------------------------------------

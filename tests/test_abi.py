@@ -230,3 +230,25 @@ def test_rules_validate_before_launching():
     assert L.svf_accept_resample(*args, 2, 4, 0, ok, ok, None) == -2
     assert L.svf_accept_resample(*args, 2, 4, 524289, ok, ok, None) == -2
 
+
+
+STATIC_WS = [      # served before d = 64 went to the matrix cores and before splits could be shared out
+    dict(B=8, Hq=32, Hkv=8, gamma=4, k_blocks=512, block_size=64, max_seq_len=32768, d=64),
+    dict(B=32, Hq=32, Hkv=8, gamma=4, k_blocks=128, block_size=64, max_seq_len=32768, d=64),
+    dict(B=16, Hq=32, Hkv=32, gamma=4, k_blocks=32, block_size=64, max_seq_len=32768, d=64),
+    dict(B=16, Hq=16, Hkv=16, gamma=8, k_blocks=64, block_size=16, max_seq_len=131072, d=128),
+]
+
+
+@pytest.mark.parametrize("kw", STATIC_WS, ids=lambda kw: f"{kw['B']}x{kw['Hkv']}x{kw['d']}")
+def test_static_workspace_serves_what_fits(kw):
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the pointers are not memory: for a process without a GPU, where an accepted call cannot launch")
+    T, Hkv, d = kw["max_seq_len"], kw["Hkv"], kw["d"]
+    sh = good_shape(**kw, page_size=0, max_pages_per_seq=0, kv_strides=(T * Hkv * d, Hkv * d, d))
+    rc = S.lib().svf_verify_attn_static_ws(ctypes.byref(sh), *([ctypes.c_void_p(0x10000)] * 12), None)
+    assert rc == -7                                         # accepted, and no device to launch on
+    assert d == 64 or S.svf_workspace_bytes(sh) <= S.svf_static_workspace_bytes()
+    huge = good_shape(**dict(kw, B=256), page_size=0, max_pages_per_seq=0, kv_strides=(T * Hkv * d, Hkv * d, d))
+    assert S.lib().svf_verify_attn_static_ws(ctypes.byref(huge), *([ctypes.c_void_p(0x10000)] * 12), None) == -6
