@@ -3,7 +3,7 @@
 Every function here has the name of the C entry point it calls (include/svf.h) and does no
 arithmetic of its own.  Tensors are torch CUDA tensors used purely as device memory; work is
 enqueued on torch's current stream.  A missing library is an error: there is no fallback path.
-The calls a program makes in every step go through the native module _svf_calls
+The calls a program makes in every step (NATIVE_CALLS) go through the native module _svf_calls
 (csrc/py_calls.cpp: a call through ctypes costs about as much host time as the launch takes on the
 GPU); the others go through ctypes.
 """
@@ -162,22 +162,31 @@ def _check(rc: int, where: str):
         raise SvfError(rc, where)
 
 
-def _native_call(name: str):
-    """The function of that name in the native calls module.  Before the module has been built (this
-    package is imported to build it) a stand-in that loads it, or raises, when it is called."""
-    try:
-        from . import _svf_calls
-        return getattr(_svf_calls, name)
-    except ImportError:
-        pass
+# The functions of the native calls module.  It is loaded when the first of them is asked for, not when this
+# package is imported: loading it maps libsvf.so, and a program that imports the package to build the library must
+# not be left with the one that was there before.
+NATIVE_CALLS = ("svf_block_reps", "svf_score_select", "svf_verify_attn", "svf_verify_attn_static_ws", "svf_verify_step",
+                "svf_block_summaries", "svf_retrieve", "svf_sparse_ffn", "svf_moe_skip", "svf_accept_resample")
 
-    def load_and_call(*args, **kwargs):
-        lib()                                             # raises if the library itself is missing
-        if not os.path.exists(CALLS_PATH):
-            raise RuntimeError(f"{CALLS_PATH} is missing: build it with __graft_entry__.build() "
-                               "or `python -m paper_2512_21911_amd.build`")
-        from . import _svf_calls
-        return getattr(_svf_calls, name)(*args, **kwargs)
+
+def _native_calls():
+    lib()                                                 # raises if the library itself is missing
+    if not os.path.exists(CALLS_PATH):
+        raise RuntimeError(f"{CALLS_PATH} is missing: build it with __graft_entry__.build() "
+                           "or `python -m paper_2512_21911_amd.build`")
+    from . import _svf_calls
+    return _svf_calls
+
+
+def __getattr__(name: str):
+    if name not in NATIVE_CALLS:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    if os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH):
+        globals()[name] = getattr(_native_calls(), name)
+        return globals()[name]
+
+    def load_and_call(*args, **kwargs):                   # nothing is built yet: the call itself raises
+        return getattr(_native_calls(), name)(*args, **kwargs)
 
     load_and_call.__name__ = name
     return load_and_call
@@ -229,24 +238,6 @@ def new_workspace(shape: SvfShape, device="cuda") -> torch.Tensor:
     return ws
 
 
-# svf_block_reps(shape, K, block_table, seq_lens, reps, first_block=0, n_blocks=-1)
-svf_block_reps = _native_call("svf_block_reps")
-
-
-# svf_score_select(shape, q, reps, seq_lens, sel_idx, sel_cnt, ws, scores=None)
-svf_score_select = _native_call("svf_score_select")
-
-
-# svf_verify_attn(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt, out, ws,
-#     lse=None)
-svf_verify_attn = _native_call("svf_verify_attn")
-
-
-# svf_verify_attn_static_ws(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx, sel_cnt,
-#     out, lse=None)
-svf_verify_attn_static_ws = _native_call("svf_verify_attn_static_ws")
-
-
 SVF_KERNEL_AUTO, SVF_KERNEL_VECTOR_ALU = 0, 1
 
 
@@ -283,11 +274,6 @@ SVF_STEP_REUSE, SVF_STEP_ANCHOR, SVF_STEP_REUSE_GATHER = 0, 1, 2
 def svf_workspace_set_wait_polls(shape, ws, polls):
     _check(lib().svf_workspace_set_wait_polls(ctypes.byref(shape), _ptr(ws), ws.numel(), int(polls), _stream()),
            "svf_workspace_set_wait_polls")
-
-
-# svf_verify_step(shape, mode, q, reps, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask, sel_idx,
-#     sel_cnt, out, ws, lse=None)
-svf_verify_step = _native_call("svf_verify_step")
 
 
 # ---- retrieval analytics (argument marshalling only) ------------------------------------------
@@ -334,16 +320,6 @@ def svf_topk_anchors(J, K):
     return [int(out[i]) for i in range(int(K))]
 
 
-# ---- retrieval variants (argument marshalling only) -------------------------------------------
-
-# svf_block_summaries(shape, retrieval, K, block_table, seq_lens, summaries, first_block=0, n_blocks=-1)
-svf_block_summaries = _native_call("svf_block_summaries")
-
-
-# svf_retrieve(shape, retrieval, q, summaries, seq_lens, sel_idx, sel_cnt, ws, scores=None)
-svf_retrieve = _native_call("svf_retrieve")
-
-
 # ---- sparse feed-forward verification (argument marshalling only) ------------------------------
 
 def make_ffn_shape(*, M, d_model, d_ff, act="silu", tau=0.0, walk=SVF_FFN_WALK_AUTO) -> SvfFfnShape:
@@ -362,23 +338,10 @@ def new_ffn_workspace(shape: SvfFfnShape, device="cuda") -> torch.Tensor:
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
-# svf_sparse_ffn(shape, x, w_gate, w_up, w_down_t, y, ws, b_gate=None, b_up=None, b_down=None, active=None)
-svf_sparse_ffn = _native_call("svf_sparse_ffn")
-
-
 # ---- expert skipping, acceptance / resampling (argument marshalling only) -----------------------
-
-# svf_moe_skip(w, m, beta, n_skip, keep_mask)
-svf_moe_skip = _native_call("svf_moe_skip")
-
 
 def svf_moe_calibrate(w_cal, beta, ws=None):
     T, k = w_cal.shape
     if ws is None:
         ws = torch.empty(int(lib().svf_moe_calibrate_workspace_bytes(T, k)), dtype=torch.uint8, device=w_cal.device)
     _check(lib().svf_moe_calibrate(_ptr(w_cal), T, k, _ptr(beta), _ptr(ws), ws.numel(), _stream()), "svf_moe_calibrate")
-
-
-# svf_accept_resample(p_target, p_draft, draft_tokens, u_accept, u_resample, n_accepted, resampled)
-svf_accept_resample = _native_call("svf_accept_resample")
-

@@ -252,3 +252,24 @@ def test_static_workspace_serves_what_fits(kw):
     assert d == 64 or S.svf_workspace_bytes(sh) <= S.svf_static_workspace_bytes()
     huge = good_shape(**dict(kw, B=256), page_size=0, max_pages_per_seq=0, kv_strides=(T * Hkv * d, Hkv * d, d))
     assert S.lib().svf_verify_attn_static_ws(ctypes.byref(huge), *([ctypes.c_void_p(0x10000)] * 12), None) == -6
+
+
+def test_importing_the_package_maps_no_library():
+    """A process that imports the package to build the library must not be left with the one built before."""
+    import subprocess
+    import sys
+    code = """
+import paper_2512_21911_amd as S
+mapped = lambda: [n for n in ('libsvf.so', '_svf_calls.so') if n in open('/proc/self/maps').read()]
+from paper_2512_21911_amd.build import LIB_PATH
+assert not mapped(), mapped()
+assert 'svf_verify_step' in dir(S) and 'svf_verify_step' in S.__all__
+call = S.svf_verify_step
+assert len(mapped()) == 2 and call is S.svf_verify_step and call is S.binding.svf_verify_step
+try:
+    S.svf_no_such_call
+except AttributeError:
+    print('done')
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "done" in r.stdout, r.stderr
