@@ -175,6 +175,7 @@ def _native_calls():
         raise RuntimeError(f"{CALLS_PATH} is missing: build it with __graft_entry__.build() "
                            "or `python -m paper_2512_21911_amd.build`")
     from . import _svf_calls
+    _svf_calls.set_structures(SvfShape, SvfRetrieval, SvfFfnShape)
     return _svf_calls
 
 

@@ -273,3 +273,23 @@ except AttributeError:
 """
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "done" in r.stdout, r.stderr
+
+
+def test_native_calls_take_the_structure_they_name_and_no_other():
+    import inspect
+    N = [None] * 6
+    for call, args in ((S.svf_retrieve, (good_shape(), good_shape(), *N)),
+                       (S.svf_retrieve, (bytes(200), S.SvfRetrieval(), *N)),
+                       (S.svf_block_summaries, (S.SvfRetrieval(), S.SvfRetrieval(), *N[:4])),
+                       (S.svf_sparse_ffn, (good_shape(), *N)),
+                       (S.svf_block_reps, (S.SvfFfnShape(), *N[:4])),
+                       (S.svf_block_reps, (None, *N[:4]))):
+        with pytest.raises(TypeError, match="must be a Svf"):
+            call(*args)
+    with pytest.raises(AttributeError):                     # neither a tensor nor anything with its data_ptr()
+        S.svf_block_reps(good_shape(), 3.0, None, None, None)
+    with pytest.raises(TypeError, match="missing required argument: 'reps'"):
+        S.svf_block_reps(good_shape(), None, None, None)
+    assert str(inspect.signature(S.svf_block_reps)) == ("(shape, K, block_table, seq_lens, reps, first_block=0, "
+                                                        "n_blocks=-1)")
+    assert list(inspect.signature(S.svf_verify_step).parameters)[-2:] == ["ws", "lse"]
