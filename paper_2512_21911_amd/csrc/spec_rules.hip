@@ -187,10 +187,8 @@ __device__ __forceinline__ void sum_chunks(const float* pt, const float* pd, int
   const int whole = max(min(c_end, V / kChunk) - c_begin, 0) / 4;
   const float* pt_lane = pt + (int64_t)c_begin * kChunk + 4 * lane;
   const float* pd_lane = pd + (int64_t)c_begin * kChunk + 4 * lane;
-  // (unconditional: past the last group it is requested again, so that the loop has no branch
-  // between a request and its use, which would make every wait a wait for everything in flight)
   auto request = [&](int g, ChunkLoads& q) {
-    const int at = min(g, whole - 1) * (4 * kChunk);
+    const int at = g * (4 * kChunk);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       q.a[u] = load4(pt_lane + at + u * kChunk);
@@ -201,18 +199,28 @@ __device__ __forceinline__ void sum_chunks(const float* pt, const float* pd, int
 #pragma unroll
     for (int u = 0; u < 4; ++u) sum_chunk(c_begin + 4 * g + u, residual4_of(q.a[u], q.d[u], FROM_TARGET));
   };
-  if (whole > 0) {
-    ChunkLoads q0, q1;
+  // (no branch between a request and its use inside the loop, which would make every wait a wait for
+  // everything in flight, and no request behind the last group: the barrier that follows would wait for it, 1 us
+  // of 9.6 for the 64 sequences of 32 000 tokens, whose wavefronts have two groups)
+  ChunkLoads q0, q1;
+  if (whole >= 2) {
     request(0, q0);
     request(1, q1);
     int g = 0;
-    for (; g + 1 < whole; g += 2) {
+    for (; g + 3 < whole; g += 2) {
       sum_up(g, q0);
       request(g + 2, q0);
       sum_up(g + 1, q1);
       request(g + 3, q1);
     }
-    if (g < whole) sum_up(g, q0);
+    sum_up(g, q0);
+    const bool third = g + 3 == whole;
+    if (third) request(g + 2, q0);
+    sum_up(g + 1, q1);
+    if (third) sum_up(g + 2, q0);
+  } else if (whole == 1) {
+    request(0, q0);
+    sum_up(0, q0);
   }
   for (int c = c_begin + 4 * whole; c < c_end; ++c) sum_chunk(c, residual4(pt, pd, c * kChunk + 4 * lane, V, FROM_TARGET));
 }
@@ -222,9 +230,11 @@ __device__ __forceinline__ void sum_chunks(const float* pt, const float* pd, int
 // the chunks of its contiguous share, the chunk sums are scanned by the workgroup, and the chunk the
 // target mass falls in is walked by one wavefront.  The intervals [lower, upper) are built so that
 // one's upper bound is the next one's lower bound bit for bit: exactly one chunk and one lane match.
-// Bound by what one compute unit can take in (64 bytes a clock) and, with many rejected sequences, by
-// HBM.  The next four chunks are always on their way while four are summed (with eight requested,
-// waited for and summed in turn: 19.9 us for 64 sequences of 129 280 tokens, so 17.2 us).
+// Bound: some 6.5 us that do not depend on the vocabulary (launch, the gamma tests, the scan, the walk), then
+// what one compute unit takes in: one sequence 8.2 us at 32 000 tokens and 13.4 at 129 280, 62 bytes a clock in
+// between.  64 sequences (48 rejected): 8.5 and 18.1 us, 34 bytes a clock and unit, 4 TB/s together.  The next
+// four chunks are always on their way while four are summed (with eight requested, waited for and summed in
+// turn: 8.7 and 22.2 us for the 64).
 __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __restrict__ p_target,
                                                              const float* __restrict__ p_draft,
                                                              const int32_t* __restrict__ draft_tokens,

@@ -137,3 +137,17 @@ def test_same_bits_on_repeated_calls():
     for _ in range(3):
         b = gpu_accept(x)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("ragged", [0, 77, -3])
+@pytest.mark.parametrize("per_wave", [1, 4, 5, 8, 11, 12, 16, 20, 23])
+def test_every_number_of_chunk_groups(per_wave, ragged):
+    """Chunks of 256 tokens per wavefront around whole groups of four: none, one, two, three
+    and more (a group on its way while one is summed), with and without chunks left over; targets
+    from the first to the last token, of the residual and, where it is zero everywhere, of p_target."""
+    x = WR.acceptance_inputs(8, 1, 4096 * per_wave + ragged, seed=per_wave)
+    x["u_accept"].fill_(1.0)
+    x["u_resample"] = torch.tensor([0.0, 0.01, 0.2, 0.4, 0.6, 0.8, 0.97, 0.999])
+    check_accept(x)
+    x["p_draft"] = x["p_target"].clone()
+    check_accept(x)
