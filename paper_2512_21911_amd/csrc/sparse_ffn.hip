@@ -331,8 +331,8 @@ __device__ __forceinline__ void finish_channels(const FfnParams& p, int lane, in
 // the one before, whose stage takes the next request.  x is shared by the four wavefronts, and a
 // wavefront has its tile's whole sum: nothing is added up afterwards.
 // (Wavefronts that split the model dimension with two private stages of 128 each kept 64 KB in flight at
-// most, fetched x from L2 into registers and added four partial tiles at the end.  14336 x 4096: 40.6 -> 38.2 us,
-// 6.1 TB/s, for 8 tokens; 51.4 -> 40.8 us for 60, of which 10 for the order of the chunks, see `first`.)
+// most, fetched x from L2 into registers and added four partial tiles at the end.  14336 x 4096: 40.6 -> 39.0 us,
+// 6.0 TB/s, for 8 tokens; 51.4 -> 43.0 us for 60, where the order of the chunks matters, see `first`.)
 //   One workgroup per compute unit, so the tile height tile_rows <= 32 is chosen such that the
 //   workgroups fill whole rounds; the rows of the 32-row matrix-core tile past it repeat its last
 //   row, and a tile that would reach past d_ff is moved back to end there (the channels it shares with
