@@ -1334,31 +1334,25 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int pair = blockIdx.y * kXcds + blockIdx.x % kXcds;
   int S = p.n_splits;                                           // splits of this pair
   const int rg = blockIdx.z;
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
   static_assert(SHARE == kAsPlanned || (MODE == kResolve && !kOneTile), "shared out by the kernel that resolves its tiles one after the other");
   const bool planned = pair < pairs;                            // (split < n_splits by the grid)
   if (SHARE == kAsPlanned && !planned) return;
-  int pair_counts = 0;
-  if (SHARE != kAsPlanned) {
-    pair_counts = load_pair_counts(p, pairs, wave, lane);
-    pair = min(pair, pairs - 1);                                // (its loads are valid, whatever comes of it)
-  }
-  int group, b, h;                                              // index of the group's ticket, pair / Hkv, pair % Hkv
-  auto place_pair = [&]() {
-    group = rg * pairs + pair;
-    b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32);
-    h = pair - b * p.Hkv;
-  };
-  place_pair();
+  if (SHARE != kAsPlanned) pair = min(pair, pairs - 1);         // (its loads are valid, whatever comes of it)
+  int group = rg * pairs + pair;                                // index of the group's ticket
+  int b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32), h = pair - b * p.Hkv;   // pair / Hkv
 
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  int pair_counts = 0;
+  if (SHARE != kAsPlanned) pair_counts = load_pair_counts(p, pairs, wave, lane);
   const int l32 = lane & 31, g = lane >> 5;
   const int row0 = rg * 32;
   int NW = kWaves * S;
   int gw = split * kWaves + wave;
   constexpr int kSlices = kOneTile ? kWaves / 2 : kWaves;      // wavefronts that compute
-  const bool computes = !kOneTile || wave < kSlices;            // (wave-uniform)
+  // (wave-uniform; said to be true where the pairs' counts are waited for with the query loads behind them in flight)
+  const bool computes = SHARE != kAsPlanned || wave < kSlices;
   // Draft tile 0 has a stage of its own, of which only the four-token groups that hold a draft
   // are fetched (two of eight for eight drafts: 4 load instructions instead of 32).  The V rows
   // of the other groups must still be finite (their weights are zero, and 0 x NaN is not): the
@@ -1379,6 +1373,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const char* Vc = static_cast<const char*>(p.V);
   const char* Kd = static_cast<const char*>(p.k_draft);
   const char* Vd = static_cast<const char*>(p.v_draft);
+  const int32_t* __restrict__ sel_g = p.sel_idx + (int64_t)pair * p.k_blocks;
 
   // ---- this lane's query row as B operands (issued first: vector loads complete in order, so
   // a wait for these must not have the K/V stream in front of it), and the row's draft mask ----
@@ -1393,6 +1388,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   RetrievalLoads<D> rl;
   if (MODE == kSelect)
     rl = issue_retrieval_loads<D>(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
+  const int32_t* table_row = p.table + (int64_t)b * p.kv.max_pages;
   // With a gather list the tile loads wait for nothing but their gather entries.  Where a
   // wavefront has one tile (kOneTile) the entries (with the draft mask and the pair's block
   // count) go out ahead of the query fragments, which may then arrive while the tile is on its
@@ -1438,13 +1434,17 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     qpiece = *reinterpret_cast<const u32x4*>(static_cast<const __hip_bfloat16*>(p.q) +
                                              (((int64_t)b * p.gamma + ri) * p.Hq + h * p.G + rj) * D + tid % kQChunks * 8);
   }
-  auto query_row = [&]() {
-    return static_cast<const __hip_bfloat16*>(p.q) + (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
-  };
-  if constexpr (MODE == kGather) {
-    // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
-    // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
-    if (computes) load_query_fragments(qf, query_row());
+  if (MODE != kSelect && SHARE != kPairsFirst) {
+    const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
+                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
+    if constexpr (MODE == kGather) {
+      // issued by hand: the fragments are in once at most one tile's loads are outstanding (see
+      // below), which the compiler's own bookkeeping would turn into a full wait inside the loop
+      if (computes) load_query_fragments(qf, qrow);
+    } else if (computes) {
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+    }
   }
   if (MODE == kGather && !kOneTile) request_entries();
   // Draft tile 0 into its own stage, by its owner, ahead of everything that depends on the kept
@@ -1470,26 +1470,28 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   };
   // (with a gather list: now, without waiting for the entries)
   if (MODE == kGather && gw == 0) request_draft_tile();
-  // what a wavefront without a gather list knows its tiles from (raw: nothing here waits)
-  int L = 0, cnt = 0;
+  if (MODE != kGather && SHARE != kPairsFirst && p.draft_mask)
+    rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
+
+  int L = 0;
+  if (MODE != kGather && SHARE == kAsPlanned) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
+  if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
+  if (MODE == kSelect && tid < 32 * kQChunks) {
+    const int r = tid / kQChunks;
+    *reinterpret_cast<u32x4*>(q_stage + r * (D * 2) + ((tid % kQChunks ^ (r & (kQChunks - 1))) << 4)) = qpiece;
+  }
+  int cnt;
   // the group's epoch word: this call's tag (for the key exchange of a retrieval and for the
   // split partials) is its low half plus one, its high half the wait budget
   uint64_t epoch_word = 0;
-  auto load_front = [&]() {
-    if (MODE == kResolve && computes) {
-      const __hip_bfloat16* qrow = query_row();
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
-    }
-    if (MODE != kGather && p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
-    if (MODE != kGather) L = p.seq_lens[b + vzero];
-    if (MODE == kResolve) {
+  if (MODE == kResolve && SHARE == kAsPlanned) epoch_word = p.epochs[group + vzero];
+  if constexpr (SHARE != kAsPlanned) {
+    auto load_pair = [&]() {                             // (raw: nothing here waits)
+      L = p.seq_lens[b + vzero];
       epoch_word = p.epochs[group + vzero];
       cnt = p.sel_cnt[pair + vzero];
-    }
-  };
-  if (SHARE != kPairsFirst) load_front();
-  if (SHARE != kAsPlanned) {
+    };
+    if (SHARE == kLoadsFirst) load_pair();
     int* const pair_tiles = reinterpret_cast<int*>(&sm_m[0][0]);      // (free until the stream has ended)
     static_assert(sizeof(sm_m) >= kShareChunks * 64 * sizeof(int), "a word per pair");
     leave_pair_tiles(p, pairs, pair_counts, wave, lane, pair_tiles);
@@ -1499,25 +1501,29 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     int tiles_of[kShareChunks], flags = 0;
 #pragma unroll
     for (int c = 0; c < kShareChunks; ++c) flags |= tiles_of[c] = pair_tiles[c * 64 + lane];
-    if (__any(flags < 0)) {
+    const bool uneven = __any(flags < 0);
+    if (uneven) {
       if (!share_out_splits(p, pairs, lane, gridDim.z, tiles_of, pair, split, S)) return;
-      place_pair();
+      group = rg * pairs + pair;
+      b = (int)(((uint64_t)(uint32_t)pair * p.hkv_magic) >> 32);
+      h = pair - b * p.Hkv;
+      sel_g = p.sel_idx + (int64_t)pair * p.k_blocks;
+      table_row = p.table + (int64_t)b * p.kv.max_pages;
       NW = kWaves * S;
       gw = split * kWaves + wave;
-      if (SHARE == kLoadsFirst) load_front();
     } else if (!planned) {
       return;
     }
-    if (SHARE == kPairsFirst) load_front();
-  }
-  if (SHARE != kAsPlanned) clear_draft_stage();
-  const int32_t* __restrict__ sel_g = p.sel_idx + (int64_t)pair * p.k_blocks;
-  const int32_t* const table_row = p.table + (int64_t)b * p.kv.max_pages;
-  if (MODE != kGather) L = min(max(L, 0), p.max_seq_len);
-  if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
-  if (MODE == kSelect && tid < 32 * kQChunks) {
-    const int r = tid / kQChunks;
-    *reinterpret_cast<u32x4*>(q_stage + r * (D * 2) + ((tid % kQChunks ^ (r & (kQChunks - 1))) << 4)) = qpiece;
+    if (SHARE == kPairsFirst || uneven) {
+      const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
+                                   (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
+#pragma unroll
+      for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+      if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
+      load_pair();
+    }
+    L = min(max(L, 0), p.max_seq_len);
+    clear_draft_stage();
   }
   if (MODE == kSelect) {
     epoch_word = rl.epoch_word;
@@ -1548,7 +1554,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     if (p.draft_mask) rmask = (uint64_t)rmask_raw[0] | ((uint64_t)rmask_raw[1] << 32);
     cnt = __builtin_amdgcn_readfirstlane(min(max((int)cnt_raw, 0), p.k_blocks));
   } else {
-    cnt = __builtin_amdgcn_readfirstlane(min(max(cnt, 0), p.k_blocks));
+    cnt = __builtin_amdgcn_readfirstlane(min(max(SHARE == kAsPlanned ? p.sel_cnt[pair + vzero] : cnt, 0), p.k_blocks));
   }
   const int n_prefix = cnt * p.block_size;
   const int tiles = tiles_d + (n_prefix + kTile - 1) / kTile;
