@@ -517,7 +517,7 @@ def sffn(args):
                      "achieved": head["GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(head["GBps"] / HBM_PEAK_GBPS, 4),
                      # FETCH_SIZE + WRITE_SIZE of the three kernels, scaled (profiles/sparse_ffn_dense8b_hbm_traffic.md)
-                     "traffic": 339.5e6 if cfg.name == "ffn3_dense_8b" else None,
+                     "traffic": 332.5e6 if cfg.name == "ffn3_dense_8b" else None,
                      "algorithmic_bytes_per_launch": head["algorithmic_bytes"], "avg_launch_us": head["us_per_layer"]},
         "cpu_baseline": {"value": round(wall * 1e6 * cfg.M / len(toks), 1), "unit": "us/layer",
                          "cores": max(1, int(round(cpu_t / max(wall, 1e-9)))), "kind": "oracle",

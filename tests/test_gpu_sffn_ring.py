@@ -26,8 +26,8 @@ def same_bits_each_time(M, d_model, d_ff):
 @pytest.mark.parametrize("M", [1, 32, 33, 64])
 @pytest.mark.parametrize("d_model,d_ff", [(128, 32), (384, 64), (512, 544), (896, 8224), (256, 14368)])
 def test_ring(d_model, d_ff, M):
-    """Hidden sizes whose tile is cut below 32 channels, with a last tile moved back and an odd number of tiles:
-    every channel is written once."""
+    """Few chunks and few channels (split kernel), then hidden sizes whose tile is cut below 32 channels, with a last
+    tile moved back and an odd number of tiles: every channel is written once."""
     same_bits_each_time(M, d_model, d_ff)
 
 
