@@ -1,10 +1,11 @@
 // Expert skipping of the sparse mixture of experts (Sec. 3.5, Eq. 15-16) and acceptance /
 // resampling of the draft tokens (Sec. 2.1, Eq. 2-3): small, latency-bound kernels.
 //
-//   moe kernels   32 lanes per token, lane j holds the weight of the token's j-th expert.  A
-//                 lane's rank (weights below it, equal weights by position) comes from k shuffles;
-//                 the weights are put in rank order in LDS and every lane adds its prefix
-//                 sequentially in ascending order (the order the sums are defined in).
+//   moe kernels   sixteen lanes per token (32 for more than sixteen experts), lane j holds the
+//                 weight of the token's j-th expert.  A lane's rank (weights below it, equal
+//                 weights by position) comes from k broadcasts; the weights move to their rank's
+//                 lane and every lane adds its prefix sequentially in ascending order (the order
+//                 the sums are defined in).
 //   median        one workgroup per skip size: 4-pass radix select over the tokens' ratios
 //                 (positive floats order like their bit patterns), twice when T is even.
 //   accept        one workgroup per sequence: the gamma acceptance tests in one wavefront, then,
@@ -18,65 +19,96 @@
 
 namespace {
 
-constexpr int kMoeThreads = 256;
-constexpr int kTokPerBlock = kMoeThreads / 32;
+// The kernel is a chain: launch, one round trip for weights and thresholds, some hundred dependent
+// instructions.  Hence small workgroups, everything requested at once, loops of a length known at
+// compile time, and broadcasts inside a row of sixteen lanes by an operand modifier (a shuffle is a
+// trip through LDS).  256 tokens of 8, 16, 32 experts: 2.3, 2.5, 3.5 us a call (2.0 is an empty launch),
+// against 2.7, 3.3, 4.5 with 32 lanes per token, loops of run-time length, the sorted weights in LDS, and the
+// thresholds loaded behind the sums; 65 536 tokens of 8: 6.1 against 8.7 us.
+constexpr int kMoeThreads = 64;
 
-// Rank of lane j's weight among the token's k weights and the token's sorted prefix sums.
-// Returns this lane's rank; prefix (sum of the weights of rank <= lane) and total through refs.
-__device__ __forceinline__ int rank_and_prefix(float w, int j, int k, float* sorted, float& prefix, float& total) {
-  int rank = 0;
-  const int base = (threadIdx.x & 63) & ~31;             // first lane of this token in the wavefront
-  for (int l = 0; l < k; ++l) {
-    const float o = __shfl(w, base + l, 64);
-    rank += (o < w || (o == w && l < j)) ? 1 : 0;
-  }
-  if (j < k) sorted[rank] = w;
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  float s = 0.f, tot = 0.f;
-  for (int l = 0; l < k; ++l) {
-    tot += sorted[l];
-    if (l == j) s = tot;
-  }
-  prefix = s;
-  total = tot;
-  return rank;
+// Lane L of a token's lanes, to all of them (LANES = 16: a row of the wavefront).
+template <int LANES, int L>
+__device__ __forceinline__ float token_lane(float x) {
+  if constexpr (LANES == 16)
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, true));   // row_newbcast:L
+  else
+    return __shfl(x, ((int)threadIdx.x & ~(LANES - 1)) + L, 64);
 }
 
-// grid: ceil(T / 8); block: 256
+// Weights of lanes 0 .. L that come before lane j's in ascending order (equal weights: by position).
+template <int LANES, int L>
+__device__ __forceinline__ int rank_upto(float w, int j) {
+  const float o = token_lane<LANES, L>(w);
+  const int r = (o < w || (o == w && L < j)) ? 1 : 0;
+  if constexpr (L > 0) return r + rank_upto<LANES, L - 1>(w, j);
+  else return r;
+}
+// total: sorted[0] + ... + sorted[L], added in that order; prefix: lane j's sum up to its own.
+template <int LANES, int L>
+__device__ __forceinline__ void sums_upto(float sorted, int j, float& prefix, float& total) {
+  if constexpr (L > 0) sums_upto<LANES, L - 1>(sorted, j, prefix, total);
+  total += token_lane<LANES, L>(sorted);
+  if (L == j) prefix = total;
+}
+
+// Rank of lane j's weight among the token's k <= KMAX weights and the token's sorted prefix sums:
+// prefix = sum of the weights of rank <= j.  Lanes j >= k take part with a weight that comes behind
+// all others and count nothing in the sums (adding zero to them changes no bit).
+template <int KMAX>
+struct MoeToken {
+  static constexpr int kLanes = KMAX <= 16 ? 16 : 32;
+  static constexpr int kPerWorkgroup = kMoeThreads / kLanes;
+  int rank;
+  float prefix, total;
+  __device__ __forceinline__ MoeToken(float w, int j, int k) {
+    const float mine = j < k ? w : INFINITY;
+    rank = rank_upto<kLanes, KMAX - 1>(mine, j);
+    // (a lane past KMAX counts KMAX at most and writes behind the k lanes that are read)
+    const int to = ((int)threadIdx.x & ~(kLanes - 1)) + (j < KMAX ? rank : j);
+    float sorted = __int_as_float(__builtin_amdgcn_ds_permute(4 * to, __float_as_int(mine)));
+    if (j >= k) sorted = 0.f;
+    prefix = total = 0.f;
+    sums_upto<kLanes, KMAX - 1>(sorted, j, prefix, total);
+  }
+};
+
+// grid: ceil(T / tokens per workgroup)
+template <int KMAX>
 __global__ __launch_bounds__(kMoeThreads) void moe_skip_kernel(const float* __restrict__ w, int T, int k, int m,
                                                                const float* __restrict__ beta, int32_t* n_skip,
                                                                uint32_t* keep_mask) {
-  __shared__ float sorted[kTokPerBlock][32];
-  const int j = threadIdx.x & 31, tl = threadIdx.x >> 5;
-  const int t = blockIdx.x * kTokPerBlock + tl;
+  typedef MoeToken<KMAX> Token;
+  const int j = threadIdx.x & (Token::kLanes - 1), tl = threadIdx.x / Token::kLanes;
+  const int t = blockIdx.x * Token::kPerWorkgroup + tl;
   const bool live = t < T;
-  const float wj = (live && j < k) ? w[(int64_t)t * k + j] : 0.f;
-  float prefix, total;
-  const int rank = rank_and_prefix(wj, j, k, sorted[tl], prefix, total);
+  // (both requested before either is waited for, from addresses that are valid in every lane)
+  const float wj = w[(int64_t)min(t, T - 1) * k + min(j, k - 1)];
+  const float bj = beta[min(j, m - 1)];
+  const Token tok(wj, j, k);
   // lane j looks at skip size i = j + 1
-  const bool ok = live && j < m && prefix / total < beta[j];
-  const uint64_t b = __ballot(ok);
-  const uint32_t mine = (uint32_t)(b >> ((threadIdx.x & 32) ? 32 : 0));
+  const bool ok = live && j < m && tok.prefix / tok.total < bj;
+  const int at = (threadIdx.x & 63) & ~(Token::kLanes - 1);
+  constexpr uint32_t kAll = Token::kLanes == 32 ? 0xffffffffu : 0xffffu;
+  const uint32_t mine = (uint32_t)(__ballot(ok) >> at) & kAll;
   const int skip = mine ? 32 - __builtin_clz(mine) : 0;
-  const uint64_t kb = __ballot(live && j < k && rank >= skip);
+  const uint32_t keep = (uint32_t)(__ballot(live && j < k && tok.rank >= skip) >> at) & kAll;
   if (live && j == 0) {
     n_skip[t] = skip;
-    keep_mask[t] = (uint32_t)(kb >> ((threadIdx.x & 32) ? 32 : 0));
+    keep_mask[t] = keep;
   }
 }
 
-// ratios[i-1][t] = r_i of token t; grid: ceil(T / 8)
+// ratios[i-1][t] = r_i of token t; grid: ceil(T / tokens per workgroup)
+template <int KMAX>
 __global__ __launch_bounds__(kMoeThreads) void moe_ratios_kernel(const float* __restrict__ w, int T, int k,
                                                                  float* ratios) {
-  __shared__ float sorted[kTokPerBlock][32];
-  const int j = threadIdx.x & 31, tl = threadIdx.x >> 5;
-  const int t = blockIdx.x * kTokPerBlock + tl;
-  const bool live = t < T;
-  const float wj = (live && j < k) ? w[(int64_t)t * k + j] : 0.f;
-  float prefix, total;
-  rank_and_prefix(wj, j, k, sorted[tl], prefix, total);
-  if (live && j < k - 1) ratios[(int64_t)j * T + t] = prefix / total;
+  typedef MoeToken<KMAX> Token;
+  const int j = threadIdx.x & (Token::kLanes - 1), tl = threadIdx.x / Token::kLanes;
+  const int t = blockIdx.x * Token::kPerWorkgroup + tl;
+  const float wj = w[(int64_t)min(t, T - 1) * k + min(j, k - 1)];
+  const Token tok(wj, j, k);
+  if (t < T && j < k - 1) ratios[(int64_t)j * T + t] = tok.prefix / tok.total;
 }
 
 // The value of 0-based rank `rank` (ascending) among vals[0 .. T): radix select on the bit patterns
@@ -126,7 +158,7 @@ __global__ __launch_bounds__(256) void moe_median_kernel(const float* __restrict
 constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / 64;
 constexpr int kChunk = 256;                               // tokens per chunk: four per lane
-constexpr int kMaxChunks = 2 * kAccThreads;               // two chunk sums per thread in the scan
+constexpr int kMaxChunks = 2048;                          // sixteen segments of the scan
 
 // Inclusive prefix sum over the 64 lanes with cross-lane operand moves only (no trip through LDS
 // per step): shifts by 1, 2, 4, 8 inside each row of 16 lanes (lanes without a source add zero),
@@ -225,35 +257,78 @@ __device__ __forceinline__ void sum_chunks(const float* pt, const float* pd, int
   for (int c = c_begin + 4 * whole; c < c_end; ++c) sum_chunk(c, residual4(pt, pd, c * kChunk + 4 * lane, V, FROM_TARGET));
 }
 
+// The scan of the chunk sums by one wavefront.  128 sums make a segment, two per lane; a lane's pair,
+// the lanes of a segment and the segments are added in this order, so that the intervals
+// [lower, upper) of pairs are built from the same sums wherever they are formed: one's upper bound is
+// the next one's lower bound bit for bit, and exactly one pair holds the target.
+struct ChunkScan {
+  float total;
+  float before;                        // lane s: sum of the segments in front of segment s
+  __device__ __forceinline__ void sum_up(const float* csum, int n_chunks, int lane) {
+    const int segments = (n_chunks + 127) / 128;
+    float run = 0.f;
+    before = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < segments; ++s) {
+      const float2 c = *reinterpret_cast<const float2*>(csum + 128 * s + 2 * lane);
+      const float incl = wave_inclusive_sum_f(c.x + c.y, lane);
+      if (lane == s) before = run;
+      run += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(incl), 63));
+    }
+    total = run;
+  }
+  // The chunk that holds the target and the sum in front of it; the last chunk and zero where rounding (a
+  // target that is not below the total) leaves it outside every interval.
+  __device__ __forceinline__ int find(const float* csum, int n_chunks, float target, int lane, float& base) const {
+    const int segments = (n_chunks + 127) / 128;
+    base = 0.f;
+    const uint64_t from = __ballot(lane < segments && before <= target);
+    if (!from) return n_chunks - 1;
+    const int s = 63 - __builtin_clzll(from);              // (the sums do not decrease)
+    const float in_front = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(before), s));
+    const float2 c = *reinterpret_cast<const float2*>(csum + 128 * s + 2 * lane);
+    const float incl = wave_inclusive_sum_f(c.x + c.y, lane);
+    const float prev = __shfl_up(incl, 1, 64);
+    const float upper = in_front + incl, lower = lane == 0 ? in_front : in_front + prev;
+    const uint64_t hit = __ballot(lower <= target && target < upper);
+    if (!hit) return n_chunks - 1;
+    const bool second = !(target < lower + c.x);
+    const int l = __builtin_ctzll(hit);
+    base = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(second ? lower + c.x : lower), l));
+    return min(__builtin_amdgcn_readlane(2 * (64 * s + lane) + (second ? 1 : 0), l), n_chunks - 1);
+  }
+};
+
 // grid: (B); block: 1024.  The vocabulary is cut into chunks of 256 consecutive tokens (a lane holds
 // four, so a wavefront reads a chunk as one contiguous kilobyte per distribution); wavefront w sums
-// the chunks of its contiguous share, the chunk sums are scanned by the workgroup, and the chunk the
-// target mass falls in is walked by one wavefront.  The intervals [lower, upper) are built so that
+// the chunks of its contiguous share; one wavefront scans the chunk sums and walks the chunk the
+// target mass falls in.  The intervals [lower, upper) are built so that
 // one's upper bound is the next one's lower bound bit for bit: exactly one chunk and one lane match.
-// Bound: some 6.5 us that do not depend on the vocabulary (launch, the gamma tests, the scan, the walk), then
-// what one compute unit takes in: one sequence 8.2 us at 32 000 tokens and 13.4 at 129 280, 62 bytes a clock in
-// between.  64 sequences (48 rejected): 8.5 and 18.1 us, 34 bytes a clock and unit, 4 TB/s together.  The next
-// four chunks are always on their way while four are summed (with eight requested, waited for and summed in
-// turn: 8.7 and 22.2 us for the 64).
+// Bound: 3.4 us that do not depend on the vocabulary (launch, the gamma tests, the scan, the walk), then
+// what one compute unit takes in: one sequence 5.2 us at 32 000 tokens and 12.9 at 129 280, 45 bytes a clock.
+// 64 sequences, all rejected: 7.0 and 21.9 us, 3.6 TB/s together.  The next four chunks are always on their way
+// while four are summed.  With the scan by the whole workgroup and the choice of chunk and token handed on through
+// LDS and barriers: 4.2 (1 000 tokens), 6.2 and 13.5 us for one sequence, 8.0 and 22.0 for the 64.
 __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __restrict__ p_target,
                                                              const float* __restrict__ p_draft,
                                                              const int32_t* __restrict__ draft_tokens,
                                                              const float* __restrict__ u_accept,
                                                              const float* __restrict__ u_resample, int gamma, int V,
                                                              int32_t* n_accepted, int32_t* resampled) {
-  __shared__ float csum[kMaxChunks];
-  __shared__ float wave_sum[kAccWaves];
-  __shared__ int sh_n, sh_pick, sh_chunk;
-  __shared__ float sh_total, sh_base;
+  __shared__ __attribute__((aligned(8))) float csum[kMaxChunks];
+  __shared__ int sh_n, sh_again;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t seq = (int64_t)b * gamma;
+  const float u_r = u_resample[b];
+  for (int i = tid; i < kMaxChunks; i += kAccThreads) csum[i] = 0.f;
   if (wave == 0) {
     bool rejected = false;
     if (lane < gamma) {
+      const float u = u_accept[seq + lane];
       const int x = min(max(draft_tokens[seq + lane], 0), V - 1);
       const float pt = p_target[(seq + lane) * V + x], pd = p_draft[(seq + lane) * V + x];
       const float alpha = pd > 0.f ? fminf(1.0f, pt / pd) : 1.0f;                 // Eq. 2
-      rejected = !(u_accept[seq + lane] < alpha);
+      rejected = !(u < alpha);
     }
     const uint64_t rj = __ballot(rejected);
     if (lane == 0) sh_n = rj ? __builtin_ctzll(rj) : gamma;
@@ -269,64 +344,46 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __rest
   const int n_chunks = (V + kChunk - 1) / kChunk;
   const int cpw = (n_chunks + kAccWaves - 1) / kAccWaves;
   const int c_begin = wave * cpw, c_end = min(c_begin + cpw, n_chunks);
-  bool from_target = false;
-  float total = 0.f;
-  for (int round = 0; round < 2; ++round) {
-    if (tid == 0) { sh_chunk = n_chunks - 1; sh_base = 0.f; sh_pick = V - 1; }
-    for (int i = tid; i < kMaxChunks; i += kAccThreads) csum[i] = 0.f;
-    __syncthreads();
-    if (from_target) sum_chunks<true>(pt, pd, V, c_begin, c_end, lane, csum);
-    else sum_chunks<false>(pt, pd, V, c_begin, c_end, lane, csum);
-    __syncthreads();
-    // scan of the chunk sums: thread t takes chunks 2t and 2t + 1
-    const float s0 = csum[2 * tid], s1 = csum[2 * tid + 1];
-    const float incl = wave_inclusive_sum_f(s0 + s1, lane);
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-    float before = 0.f;
-    for (int w2 = 0; w2 < wave; ++w2) before += wave_sum[w2];
-    const float prev = __shfl_up(incl, 1, 64);
-    const float upper = before + incl;
-    const float lower = lane == 0 ? before : before + prev;
-    if (tid == kAccThreads - 1) sh_total = upper;
-    __syncthreads();
-    total = sh_total;
-    if (total > 0.f || from_target) {
-      const float target = u_resample[b] * total;
-      if (lower <= target && target < upper) {
-        const bool second = !(target < lower + s0);
-        sh_chunk = min(2 * tid + (second ? 1 : 0), n_chunks - 1);
-        sh_base = second ? lower + s0 : lower;
-      }
-      break;
-    }
-    from_target = true;                                   // the distributions coincide: resample from p_theta
-    __syncthreads();
-  }
+  sum_chunks<false>(pt, pd, V, c_begin, c_end, lane, csum);
   __syncthreads();
+  // What is left is a chain of short steps, by one wavefront: handed from step to step through LDS and a
+  // barrier they cost several times what they compute.
+  ChunkScan scan;
   if (wave == 0) {
-    const float target = u_resample[b] * total;
-    const int v = sh_chunk * kChunk + 4 * lane;
-    const float base = sh_base;
-    // (if rounding leaves the target just outside every lane's interval: the chunk's last token)
-    if (lane == 0) sh_pick = min((sh_chunk + 1) * kChunk, V) - 1;
-    const float4 r = residual4(pt, pd, v, V, from_target);
-    const float incl = wave_inclusive_sum_f(((r.x + r.y) + r.z) + r.w, lane);
-    const float prev = __shfl_up(incl, 1, 64);
-    const float upper = base + incl;
-    float c = lane == 0 ? base : base + prev;
-    if (c <= target && target < upper) {
-      int pick = v + 3;
-      c += r.x;
-      if (c > target) pick = v;
-      else if ((c += r.y) > target) pick = v + 1;
-      else if ((c += r.z) > target) pick = v + 2;
-      sh_pick = min(pick, V - 1);
-    }
+    scan.sum_up(csum, n_chunks, lane);
+    if (lane == 0) sh_again = scan.total > 0.f ? 0 : 1;
   }
   __syncthreads();
-  if (tid == 0) { n_accepted[b] = n; resampled[b] = sh_pick; }
+  const bool from_target = sh_again != 0;                 // the distributions coincide: resample from p_theta
+  if (from_target) {
+    sum_chunks<true>(pt, pd, V, c_begin, c_end, lane, csum);
+    __syncthreads();
+    if (wave == 0) scan.sum_up(csum, n_chunks, lane);
+  }
+  if (wave != 0) return;
+  const float target = u_r * scan.total;
+  float base;
+  const int chunk = scan.find(csum, n_chunks, target, lane, base);
+  const int v = chunk * kChunk + 4 * lane;
+  const float4 r = residual4(pt, pd, v, V, from_target);
+  const float incl = wave_inclusive_sum_f(((r.x + r.y) + r.z) + r.w, lane);
+  const float prev = __shfl_up(incl, 1, 64);
+  const float upper = base + incl;
+  float c = lane == 0 ? base : base + prev;
+  const uint64_t hit = __ballot(c <= target && target < upper);
+  int mine = v + 3;
+  c += r.x;
+  if (c > target) mine = v;
+  else if ((c += r.y) > target) mine = v + 1;
+  else if ((c += r.z) > target) mine = v + 2;
+  // (if rounding leaves the target just outside every lane's interval: the chunk's last token)
+  int pick = min((chunk + 1) * kChunk, V) - 1;
+  if (hit) pick = min(__builtin_amdgcn_readlane(mine, __builtin_ctzll(hit)), V - 1);
+  if (lane == 0) { n_accepted[b] = n; resampled[b] = pick; }
 }
+
+template <int KMAX>
+dim3 moe_grid(int T) { return dim3((unsigned)((T + MoeToken<KMAX>::kPerWorkgroup - 1) / MoeToken<KMAX>::kPerWorkgroup)); }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
@@ -339,8 +396,10 @@ int svf_moe_skip(const float* w, int32_t T, int32_t k, int32_t m, const float* b
   if (!w || !beta || !n_skip || !keep_mask) return SVF_ERR_NULL;
   if (T < 1 || k < 2 || k > 32) return SVF_ERR_SHAPE;
   if (m < 1 || m >= k) return SVF_ERR_BUDGET;
-  hipLaunchKernelGGL(moe_skip_kernel, dim3((T + kTokPerBlock - 1) / kTokPerBlock), dim3(kMoeThreads), 0,
-                     static_cast<hipStream_t>(stream), w, T, k, m, beta, n_skip, keep_mask);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (k <= 8) hipLaunchKernelGGL(moe_skip_kernel<8>, moe_grid<8>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
+  else if (k <= 16) hipLaunchKernelGGL(moe_skip_kernel<16>, moe_grid<16>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
+  else hipLaunchKernelGGL(moe_skip_kernel<32>, moe_grid<32>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
   return hipGetLastError() == hipSuccess ? SVF_OK : SVF_ERR_HIP;
 }
 
@@ -357,8 +416,9 @@ int svf_moe_calibrate(const float* w_cal, int32_t T, int32_t k, float* beta, voi
     return SVF_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* ratios = static_cast<float*>(ws);
-  hipLaunchKernelGGL(moe_ratios_kernel, dim3((T + kTokPerBlock - 1) / kTokPerBlock), dim3(kMoeThreads), 0, st, w_cal,
-                     T, k, ratios);
+  if (k <= 8) hipLaunchKernelGGL(moe_ratios_kernel<8>, moe_grid<8>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
+  else if (k <= 16) hipLaunchKernelGGL(moe_ratios_kernel<16>, moe_grid<16>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
+  else hipLaunchKernelGGL(moe_ratios_kernel<32>, moe_grid<32>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
   if (hipGetLastError() != hipSuccess) return SVF_ERR_HIP;
   hipLaunchKernelGGL(moe_median_kernel, dim3(k - 1), dim3(256), 0, st, ratios, T, beta);
   return hipGetLastError() == hipSuccess ? SVF_OK : SVF_ERR_HIP;

@@ -151,3 +151,32 @@ def test_every_number_of_chunk_groups(per_wave, ragged):
     check_accept(x)
     x["p_draft"] = x["p_target"].clone()
     check_accept(x)
+
+
+@pytest.mark.parametrize("k", [2, 7, 8, 9, 15, 16, 17, 31, 32])
+def test_skipping_at_every_group_of_lanes(k):
+    """Expert counts on both sides of every kernel's lanes per token, token counts around its
+    workgroups, weights with many ties.  The weights are multiples of 1/64, so all sums are exact: the ratios
+    are one rounding away from the oracle's, and thresholds between two multiples leave no near-ties."""
+    g = torch.Generator().manual_seed(k)
+    for T in (1, 2, 3, 4, 5, 257):
+        w = torch.randint(1, 9, (T, k), generator=g).float() / 64
+        beta = [(i + 1) / k - 1e-4 for i in range(k - 1)]
+        for m in sorted({1, k // 2, k - 1}):
+            n_ref, keep_ref = R.moe_skip(w.numpy(), np.asarray(beta), m)
+            n, keep = gpu_skip(w, beta, m)
+            r = R.skip_ratios(w.numpy())
+            assert np.abs(r[:, :m] - np.asarray(beta)[None, :m]).min() > 1e-6
+            assert (n == n_ref).all() and (keep == keep_ref).all()
+
+
+@pytest.mark.parametrize("V", [32767, 32768, 32769, 65537, 524288])
+def test_targets_around_the_segments_of_the_scan(V):
+    """128 chunks of 256 tokens are one segment of the scan: targets at its ends."""
+    x = WR.acceptance_inputs(4, 1, V, seed=V % 97)
+    x["u_accept"].fill_(1.0)
+    cdf = np.cumsum(np.maximum(x["p_target"].double().numpy() - x["p_draft"].double().numpy(), 0)[:, 0], axis=1)
+    last = min(32767, V - 1)
+    x["u_resample"] = torch.tensor([0.0, 0.5 * (cdf[1, last - 1] + cdf[1, last]) / cdf[1, -1],
+                                    0.999 * cdf[2, last] / cdf[2, -1], 0.9999], dtype=torch.float32).clamp(max=0.9999999)
+    check_accept(x)
