@@ -73,7 +73,7 @@ def parse():
     ap.add_argument("--profile-only", default="", help="run only this many steps of the timed loop (for rocprofv3)")
     ap.add_argument("--mfma-vs-valu", action="store_true",
                     help="time the attention of the configuration's layers with the matrix-core kernel and with the "
-                         "vector-ALU kernel (svf_diag_verify_attn) instead of the step; with --profile-only N just run "
+                         "fp32 kernel (the vector ALU's rate; svf_diag_verify_attn) instead of the step; with --profile-only N just run "
                          "N passes of each for the profiler")
     ap.add_argument("--analytics", action="store_true",
                     help="time the retrieval analytics (per-draft block sets, overlap, Jaccard) instead of the step")
@@ -91,8 +91,8 @@ def parse():
 
 def mfma_vs_valu(args):
     """The attention launch of every layer of the configuration (blocks already selected) with the kernel
-    svf_verify_attn picks for the shape (matrix cores for bf16, d = 128) and with the vector-ALU kernel
-    forced, each as one captured HIP graph over independent layers.  One JSON line."""
+    svf_verify_attn picks for the shape (bf16 matrix cores for bf16) and with the kernel in fp32 arithmetic
+    (at the vector ALU's rate) forced, each as one captured HIP graph over independent layers.  One JSON line."""
     import numpy as np
     import torch
     import paper_2512_21911_amd as S
@@ -892,7 +892,7 @@ def main():
 
     value_us = ms_step * 1e3
     if cfg.dtype != "bf16":
-        kernel_name = "verify_attn_valu_kernel"
+        kernel_name = "verify_attn_f32_kernel"
     elif cfg.gamma * (cfg.Hq // cfg.Hkv) > 64:     # more than two groups of 32 query rows per KV head
         kernel_name = "verify_attn_mfma_rows_kernel (reuse layer, split merge inside)"
     else:

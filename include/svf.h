@@ -173,7 +173,7 @@ int svf_verify_attn(const svf_shape_t* shape, const void* q, const void* K, cons
  * synchronise; it enqueues one small fill kernel ahead of the attention kernels (the array keeps
  * the last call's contents, of whatever shape).  A shape whose svf_workspace_bytes exceeds the
  * array: SVF_ERR_WORKSPACE, nothing enqueued; but at d = 64 in bf16 such a shape is served by the
- * vector-ALU kernel as long as that one's workspace (svf_diag.h's kernel 1, usually a few MB) fits:
+ * fp32 kernel as long as that one's workspace (svf_diag.h's kernel 1, usually a few MB) fits:
  * the same arithmetic in another order of the sums, the bits of svf_diag_verify_attn.  All calls on one GPU share that GPU's array:
  * calls that overlap in time on one GPU (different streams, different threads) race; order them.
  */

@@ -1,8 +1,8 @@
 /*
  * libsvf diagnostics - not part of the method's boundary (include/svf.h is).
  *
- * svf_verify_attn picks its kernel from the shape: the matrix-core kernel for bf16 with head
- * dimension 128, the vector-ALU kernel otherwise.  For measuring that choice (the packed query
+ * svf_verify_attn picks its kernel from the shape: the bf16 matrix-core kernel for bf16, the kernel
+ * in fp32 arithmetic (at the vector ALU's rate) for fp32 and for odd block or page sizes.  For measuring that choice (the packed query
  * rows per KV head, gamma x G of them, are few: whether the matrix cores pay at that size is a
  * question for the profiler) the call below runs the same attention (Sec. 3.1 / 3.3, same
  * arguments, same result within the output tolerance) with the kernel named by the caller.
@@ -18,7 +18,7 @@ extern "C" {
 #endif
 
 #define SVF_KERNEL_AUTO 0        /* what svf_verify_attn would run                       */
-#define SVF_KERNEL_VECTOR_ALU 1  /* the vector-ALU kernel whatever the shape (and its merge launch) */
+#define SVF_KERNEL_VECTOR_ALU 1  /* the fp32 kernel whatever the shape                   */
 
 /* Workspace bytes svf_diag_verify_attn needs for `kernel` (>= svf_workspace_bytes; 0 if invalid). */
 size_t svf_diag_workspace_bytes(const svf_shape_t* shape, int kernel);

@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libsvf.so")
 CALLS_PATH = os.path.join(PKG_DIR, "_svf_calls.so")
 
-SOURCES = ["svf_api.hip", "block_reps.hip", "score_select.hip", "verify_attn_valu.hip", "verify_attn_mfma.hip",
+SOURCES = ["svf_api.hip", "block_reps.hip", "score_select.hip", "verify_attn_f32.hip", "verify_attn_mfma.hip",
            "analytics.hip", "retrieval_variants.hip", "sparse_ffn.hip", "svf_ffn_api.hip", "spec_rules.hip"]
 
 HIPCC_FLAGS = [
@@ -26,7 +26,7 @@ HIPCC_FLAGS = [
 
 # Kernels that must not use scratch memory (a private segment makes every dispatch slower, and an
 # array the compiler moved there turns register accesses into memory round trips).
-NO_SCRATCH = ("verify_attn_mfma_kernel", "verify_attn_mfma_rows_kernel", "retrieve_only_kernel")
+NO_SCRATCH = ("verify_attn_mfma_kernel", "verify_attn_mfma_rows_kernel", "retrieve_only_kernel", "verify_attn_f32_kernel")
 
 
 def hipcc_path() -> str:

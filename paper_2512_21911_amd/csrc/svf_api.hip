@@ -10,7 +10,9 @@
 
 namespace svf {
 
-hipError_t launch_verify_attn_valu(const AttnParams& p, int dtype, hipStream_t st);
+hipError_t launch_verify_attn_f32(const AttnParams& p, int dtype, hipStream_t st);
+int f32_splits(const svf_shape_t& s);
+bool f32_retrieves(const svf_shape_t& s);
 hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st);
 hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st);
 bool mfma_supported(const svf_shape_t& s);
@@ -99,18 +101,22 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   if (pl.mfma) {
     pl.n_splits = mfma_rows_mode(s) ? mfma_rows_splits(s) : mfma_splits(s);
   } else {
-    const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + 31) / 32 + (s.gamma + 31) / 32;
-    const int64_t groups = (int64_t)s.B * s.Hkv * (pl.Mpad / 32);
-    int64_t want = (512 + groups - 1) / groups;          // aim at ~2 workgroups per compute unit
-    if (want > tiles) want = tiles;
-    if (want < 1) want = 1;
-    pl.n_splits = (int)want;
+    pl.n_splits = f32_splits(s);
   }
   const size_t pairs = (size_t)s.B * s.Hkv;
   const int shared = pl.mfma && !mfma_rows_mode(s) ? mfma_shared_splits(s) : 0;
   pl.share_splits = shared > 0;
   pl.split_stride = pl.n_splits;
   lay_out(s, pl);
+  if (!pl.mfma && pl.bytes + scores_bytes(s) > kStaticScratchBytes) {
+    // fewer splits where that makes the workspace fit the static array
+    const size_t per_split = pairs * pl.Mpad * (s.d + 2) * sizeof(float);
+    const size_t others = pl.bytes + scores_bytes(s) - pl.n_splits * per_split;      // (with what aligning them added)
+    if (others + per_split <= kStaticScratchBytes) {
+      pl.n_splits = pl.split_stride = (int)((kStaticScratchBytes - others) / per_split);
+      lay_out(s, pl);
+    }
+  }
   if (shared > pl.n_splits) {
     // more splits for a pair as long as a workspace that fits the static array without them still does
     const size_t now = pl.bytes + scores_bytes(s), per_split = pairs * pl.Mpad * (s.d * (s.d == 128 ? 2 : 4) + 16);
@@ -129,18 +135,18 @@ void lay_out(const svf_shape_t& s, AttnPlan& pl) {
   size_t off = 0;
   pl.off_tickets = off;
   off += align_up(pl.groups * kTicketWords * sizeof(uint64_t));
-  // partial outputs: fp32 (vector-ALU kernel, matrix-core kernels at d = 64) or bf16 (d = 128) per split and row
+  // partial outputs: fp32 (fp32 kernel, bf16 matrix-core kernels at d = 64) or bf16 (d = 128) per split and row
   pl.off_o = off;
   off += align_up(pairs * pl.split_stride * pl.Mpad * s.d * (pl.mfma && s.d == 128 ? sizeof(uint16_t) : sizeof(float)));
-  // maxima and denominators: two fp32 arrays for the vector-ALU kernel; 16 bytes per split and row
-  // for the matrix-core kernels (a tagged record)
+  // (maximum, denominator) per split and row: two floats for the fp32 kernel, 16 bytes for the bf16
+  // matrix-core kernels (a tagged record)
   pl.off_m = off;
-  pl.off_l = off + pairs * pl.split_stride * pl.Mpad * sizeof(float);
   off += align_up((pl.mfma ? 4 : 2) * pairs * pl.split_stride * pl.Mpad * sizeof(float));
   // (no gather list at d = 64: SVF_STEP_REUSE_GATHER promises to rely on its arguments alone there)
   const bool listed = pl.mfma && s.k_blocks <= kMaxGatherBlocks;
   pl.gather = listed && s.d == 128;
   pl.fused_select = listed && nb_max_of(s) <= kMaxGatherBlocks;
+  pl.f32_retrieves = !pl.mfma && f32_retrieves(s);
   pl.gather_groups = listed ? (int32_t)(((int64_t)s.k_blocks * s.block_size + 31) / 32 * 8) : 0;
   pl.off_gather = off;
   off += align_up(pl.gather ? pairs * (size_t)pl.gather_groups * sizeof(uint64_t) : 0);
@@ -407,7 +413,6 @@ static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void*
   p.tickets = reinterpret_cast<uint64_t*>(w + pl.off_tickets);
   p.part_o = reinterpret_cast<float*>(w + pl.off_o);
   p.part_m = reinterpret_cast<float*>(w + pl.off_m);
-  p.part_l = reinterpret_cast<float*>(w + pl.off_l);
   p.part_rec = reinterpret_cast<uint32_t*>(p.part_m);
   p.gather = (use_gather && pl.gather) ? reinterpret_cast<const uint64_t*>(w + pl.off_gather) : nullptr;
   p.gather_groups = pl.gather_groups;
@@ -422,7 +427,7 @@ static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void*
   p.xkeys = reinterpret_cast<uint64_t*>(w + pl.off_xkeys);
   p.epochs = reinterpret_cast<uint64_t*>(w + pl.off_epochs);
   p.slice_rows = pl.slice_rows;
-  if (reps_to_select_from && pl.fused_select) {
+  if (reps_to_select_from && (pl.fused_select || pl.f32_retrieves)) {
     p.reps = reps_to_select_from;
     p.sel_idx_out = const_cast<int32_t*>(sel_idx);
     p.sel_cnt_out = const_cast<int32_t*>(sel_cnt);
@@ -454,7 +459,7 @@ static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void*
   p.scale_log2 = scale * 1.4426950408889634f;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (pl.mfma) return hip_code(launch_verify_attn_mfma(p, st));
-  return hip_code(launch_verify_attn_valu(p, shape->dtype, st));
+  return hip_code(launch_verify_attn_f32(p, shape->dtype, st));
 }
 
 int svf_verify_attn(const svf_shape_t* shape, const void* q, const void* K, const void* V,
@@ -510,7 +515,7 @@ int svf_verify_attn_static_ws(const svf_shape_t* shape, const void* q, const voi
   if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(k_draft) || misaligned(v_draft) ||
       misaligned(out))
     return SVF_ERR_SHAPE;
-  // A shape whose workspace does not fit the array is refused; at d = 64 the vector-ALU kernel, which needs
+  // A shape whose workspace does not fit the array is refused; at d = 64 the fp32 kernel, which needs
   // a fraction of it, takes what does not fit with the matrix-core kernel's splits.
   const bool allow_mfma = svf_workspace_bytes(shape) <= kStaticScratchBytes;
   if (!allow_mfma &&
@@ -604,7 +609,8 @@ int svf_verify_step(const svf_shape_t* shape, int mode, const void* q, const flo
     return SVF_ERR_SHAPE;
   rc = check_ws(shape, ws, ws_bytes);
   if (rc) return rc;
-  if (do_select && plan_attn(*shape).fused_select)
+  const AttnPlan pl = plan_attn(*shape);
+  if (do_select && (pl.fused_select || pl.f32_retrieves))
     return verify_attn_impl(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask_or_null, sel_idx,
                             sel_cnt, out, lse_or_null, ws, ws_bytes, stream, false, reps);
   if (do_select) {

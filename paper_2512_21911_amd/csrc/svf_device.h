@@ -96,14 +96,13 @@ struct AttnParams {
   const int32_t* sel_cnt;
   void* out;
   float* lse;                  // may be null
-  // split partials.  Vector-ALU kernel: fp32 unnormalised outputs [B][Hkv][S][Mpad][d] with their
-  // running maxima (log2 domain) and denominators in part_m / part_l.  Matrix-core kernels: outputs
+  // split partials.  fp32 kernel: fp32 unnormalised outputs [B][Hkv][S][Mpad][d] with their running
+  // maxima (log2 domain) and denominators side by side in part_m.  bf16 matrix-core kernels: outputs
   // normalised by their own denominator, [B][Hkv][S][Mpad] rows of 256 bytes (d = 128: rounded to
   // bf16, d = 64: fp32) in part_o, and 16-byte records (maximum, tag, denominator, tag) in part_rec, valid for the call
   // whose tag both halves carry.  part_m and part_rec name the same region.
   float* part_o;
-  float* part_m;               // [B][Hkv][S][Mpad]
-  float* part_l;               // [B][Hkv][S][Mpad]
+  float* part_m;               // [B][Hkv][S][Mpad][2]
   uint32_t* part_rec;          // [B][Hkv][S][Mpad][4]
   // per (pair, row group) eight 64-bit words: [0], [1] arrival word of calls with an even / odd
   // tag (bits 15:0 arrivals, bits 31:16 slices given up), [2] arrival counter of the kernels that
@@ -258,11 +257,12 @@ struct AttnPlan {
   int32_t split_stride;      // splits per pair that the partials have room for
   bool share_splits;         // see mfma_shared_splits
   int32_t slice_rows;        // rows of a row group one workgroup merges: ceil(32 / min(n_splits, 16))
-  bool mfma;                 // bf16 (see mfma_supported): matrix-core kernel; otherwise the vector-ALU kernel
-  bool fused_select;         // anchor layers retrieve inside the attention kernel
+  bool mfma;                 // bf16 (see mfma_supported): bf16 matrix-core kernel; otherwise the fp32 kernel
+  bool fused_select;         // anchor layers retrieve inside the attention kernel (bf16 matrix-core kernel)
+  bool f32_retrieves;        // the same for the fp32 kernel
   bool gather;               // the shape can use a gather list
   int32_t gather_groups;     // groups of four slots per (sequence, KV head): a whole number of 32-token tiles
-  size_t off_o, off_m, off_l, off_tickets, off_gather, off_xkeys, off_epochs, bytes;
+  size_t off_o, off_m, off_tickets, off_gather, off_xkeys, off_epochs, bytes;
   size_t groups;             // (sequence, KV head, row group) triples: entries of tickets / epochs
 };
 AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma = true);
