@@ -403,7 +403,7 @@ def variants(args):
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": "cfg3_long_batch_32k", "B": cfg.B, "Hq": cfg.Hq, "Hkv": cfg.Hkv, "d": cfg.d, "T": cfg.T,
                    "block_size": cfg.block_size, "n_total_blocks": n_total, "launch": "stream"},
-        "roofline": {"bound": "hbm", "kernel": "variant_scores_kernel + select_global_kernel",
+        "roofline": {"bound": "hbm", "kernel": "retrieve_kernel",
                      "achieved": round(alg / (us_head * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(alg / (us_head * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None,
                      "algorithmic_bytes_per_launch": alg, "avg_launch_us": round(us_head, 3)},

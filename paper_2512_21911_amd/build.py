@@ -13,7 +13,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libsvf.so")
 CALLS_PATH = os.path.join(PKG_DIR, "_svf_calls.so")
 
 SOURCES = ["svf_api.hip", "block_reps.hip", "score_select.hip", "verify_attn_f32.hip", "verify_attn_mfma.hip",
-           "analytics.hip", "retrieval_variants.hip", "sparse_ffn.hip", "svf_ffn_api.hip", "spec_rules.hip"]
+           "analytics.hip", "retrieve.hip", "sparse_ffn.hip", "svf_ffn_api.hip", "spec_rules.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",

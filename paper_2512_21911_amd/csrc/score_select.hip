@@ -1,10 +1,8 @@
-// Block scores and the shared top-N block set (Sec. 3.1, Eq. 5 and the selection rule;
-// Sec. 2.2: the first draft token's query retrieves for every draft token).
+// Block scores of every draft token (retrieval analytics, Sec. 2.2), and the selection over scores in memory:
+// behind them, and for the retrieval of more blocks than one workgroup's LDS holds (retrieve.hip).
 //
-// Two kernels.
-//   scores:  wide, HBM-bound pass over the fp32 representatives.  A group of d/4 lanes owns
-//            one block: float4 loads, fp32 dot with the group-mean first-draft query,
-//            reduction inside the lane group.
+//   scores:  wide, HBM-bound pass over the fp32 representatives.  Eight lanes own one block: float4
+//            loads, fp32 dot with the group-mean queries, reduction inside the lane group.
 //   select:  one workgroup per (sequence, KV head).  Scores become order-preserving 32-bit
 //            keys (forced sink/local blocks get the maximum key); a 4-pass radix select over
 //            LDS histograms (bins scanned with a wavefront prefix sum) finds the key of the
@@ -24,56 +22,9 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kKeysPerThread = 8;      // selection keys a thread keeps in registers
 constexpr int kPasses = 4;              // blocks scored per lane group in the scores kernel
 
-// grid: (ceil(nb_max / (kPasses * blocks per pass)), Hkv, B)
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void block_scores_kernel(SelectParams p) {
-  constexpr int LPB = kScoreLanes;           // lanes per block
-  constexpr int NCH = D / (4 * LPB);         // 16-byte chunks per lane: sub, sub + 8, ...
-  constexpr int BPW = kThreads / LPB;        // blocks per workgroup pass
-  __shared__ __attribute__((aligned(16))) float q0[D];
-
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int G = p.Hq / p.Hkv;
-  const int sub = threadIdx.x % LPB;
-
-  // All loads go out before anything waits, so that the query and the representatives share one
-  // memory round trip.  First draft token's query: channel threadIdx.x mod D of the group's heads
-  // (loaded by every thread, used by the first D); representative rows unconditionally (rows past
-  // the sequence's last block exist in the buffer; their result is discarded).
-  const T* qch = static_cast<const T*>(p.q) + ((int64_t)b * p.gamma * p.Hq + (int64_t)h * G) * D + threadIdx.x % D;
-  const QueryHeads<T> qh = load_query_heads<T>(qch, G, D);
-  float4 r[kPasses][NCH];
-  int jj[kPasses];
-#pragma unroll
-  for (int u = 0; u < kPasses; ++u) {
-    const int j = (blockIdx.x * kPasses + u) * BPW + threadIdx.x / LPB;
-    jj[u] = j;
-    const int jc = j < p.nb_max ? j : p.nb_max - 1;
-    const float* row = p.reps + (((int64_t)b * p.Hkv + h) * p.nb_max + jc) * D + sub * 4;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) r[u][i] = *reinterpret_cast<const float4*>(row + i * 4 * LPB);
-  }
-
-  // averaged over the query heads of this KV head
-  if (threadIdx.x < D) q0[threadIdx.x] = mean_query_channel<T>(qh, qch, G, D);
-  const int L = clamped_len(p.seq_lens, b, p.max_seq_len);
-  const int nb = (L + p.block_size - 1) / p.block_size;
-  __syncthreads();
-
-  float4 qv[NCH];
-#pragma unroll
-  for (int i = 0; i < NCH; ++i) qv[i] = *reinterpret_cast<const float4*>(q0 + sub * 4 + i * 4 * LPB);
-#pragma unroll
-  for (int u = 0; u < kPasses; ++u) {
-    const float v = block_score<NCH>(r[u], qv);
-    if (sub == 0 && jj[u] < p.nb_max)
-      p.scores[((int64_t)b * p.Hkv + h) * p.nb_max + jj[u]] = jj[u] < nb ? v + 0.0f : 0.0f;
-  }
-}
-
 // Scores of every draft token's query (Sec. 2.2: retrieval "based on their respective query
 // values"), one pass over the representatives: the rows a thread holds are scored against the
-// gamma mean queries in LDS, with the arithmetic of the kernel above (query 0 gives the same bits).
+// gamma mean queries in LDS, with the arithmetic of the retrieval kernels (query 0 gives the same bits).
 // grid: (ceil(nb_max / (kPasses * blocks per pass)) * ceil(gamma / kDraftsPerGroup), Hkv, B): a
 // workgroup scores its rows against one group of drafts (the rows' other readers find them in L2);
 // scores [B][gamma][Hkv][nb_max]
@@ -257,33 +208,18 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectParams p) {
 
 }  // namespace
 
-hipError_t launch_score_select(const SelectParams& p, int dtype, hipStream_t st) {
-  hipError_t e = launch_scores_only(p, dtype, st);
-  if (e != hipSuccess) return e;
-  return launch_select_only(p, st);
-}
-
-// The scores alone (p.nq = 1: the first draft token's; otherwise every draft token's).
-hipError_t launch_scores_only(const SelectParams& p, int dtype, hipStream_t st) {
+hipError_t launch_select_per_draft(const SelectParams& p, int dtype, hipStream_t st) {
   const int bpw = kPasses * (kThreads / kScoreLanes);
-  dim3 g1((p.nb_max + bpw - 1) / bpw, p.Hkv, p.B);
-  if (p.nq > 1) {
-    g1.x *= (unsigned)((p.gamma + kDraftsPerGroup - 1) / kDraftsPerGroup);
-    if (dtype == SVF_F32) {
-      if (p.d == 64) hipLaunchKernelGGL((block_scores_all_kernel<float, 64>), g1, dim3(kThreads), 0, st, p);
-      else hipLaunchKernelGGL((block_scores_all_kernel<float, 128>), g1, dim3(kThreads), 0, st, p);
-    } else {
-      if (p.d == 64) hipLaunchKernelGGL((block_scores_all_kernel<__hip_bfloat16, 64>), g1, dim3(kThreads), 0, st, p);
-      else hipLaunchKernelGGL((block_scores_all_kernel<__hip_bfloat16, 128>), g1, dim3(kThreads), 0, st, p);
-    }
-  } else if (dtype == SVF_F32) {
-    if (p.d == 64) hipLaunchKernelGGL((block_scores_kernel<float, 64>), g1, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((block_scores_kernel<float, 128>), g1, dim3(kThreads), 0, st, p);
+  const dim3 grid((unsigned)((p.nb_max + bpw - 1) / bpw) * (unsigned)((p.gamma + kDraftsPerGroup - 1) / kDraftsPerGroup), p.Hkv, p.B);
+  if (dtype == SVF_F32) {
+    if (p.d == 64) hipLaunchKernelGGL((block_scores_all_kernel<float, 64>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((block_scores_all_kernel<float, 128>), grid, dim3(kThreads), 0, st, p);
   } else {
-    if (p.d == 64) hipLaunchKernelGGL((block_scores_kernel<__hip_bfloat16, 64>), g1, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((block_scores_kernel<__hip_bfloat16, 128>), g1, dim3(kThreads), 0, st, p);
+    if (p.d == 64) hipLaunchKernelGGL((block_scores_all_kernel<__hip_bfloat16, 64>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((block_scores_all_kernel<__hip_bfloat16, 128>), grid, dim3(kThreads), 0, st, p);
   }
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_select_only(p, st);
 }
 
 // The selection alone, over scores that are already in p.scores.

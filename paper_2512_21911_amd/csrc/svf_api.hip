@@ -288,6 +288,65 @@ int svf_block_reps(const svf_shape_t* shape, const void* K, const int32_t* block
   return block_reps_impl(shape, K, block_table, seq_lens, first_block, n_blocks, reps, stream, 0, 0);
 }
 
+// What a retrieval call hands to its kernels; the rule is the caller's to fill in.
+static VariantParams retrieval_params(const svf_shape_t& s, const AttnPlan& pl, const void* q, const void* summaries,
+                                      const int32_t* seq_lens, int32_t* sel_idx, int32_t* sel_cnt, float* scores_or_null, void* ws) {
+  VariantParams v{};
+  v.q = q;
+  v.summaries = summaries;
+  v.seq_lens = seq_lens;
+  v.scores = scores_or_null ? scores_or_null : reinterpret_cast<float*>(static_cast<char*>(ws) + pl.bytes);
+  v.sel_idx = sel_idx;
+  v.sel_cnt = sel_cnt;
+  v.B = s.B;
+  v.gamma = s.gamma;
+  v.Hq = s.Hq;
+  v.Hkv = s.Hkv;
+  v.d = s.d;
+  v.block_size = s.block_size;
+  v.nb_max = nb_max_of(s);
+  v.k_blocks = s.k_blocks;
+  v.n_sink = s.n_sink;
+  v.n_local = s.n_local;
+  v.max_seq_len = s.max_seq_len;
+  v.tickets = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + pl.off_tickets);
+  v.kv = layout_of(s);
+  v.gather_groups = pl.gather_groups;
+  return v;
+}
+
+// One launch, or, where the keys of a selection do not fit a workgroup's LDS, the scores and then a selection
+// that reads them again in every pass.
+static int retrieve(VariantParams v, int dtype, hipStream_t st) {
+  if (retrieve_selects(v.all_heads ? v.Hkv : 1, v.nb_max)) return hip_code(launch_retrieve(v, dtype, st));
+  v.tickets = nullptr;
+  const hipError_t e = launch_retrieve(v, dtype, st);
+  if (e != hipSuccess) return SVF_ERR_HIP;
+  if (v.all_heads) return hip_code(launch_select_global(v, st));
+  SelectParams p{};
+  p.seq_lens = v.seq_lens;
+  p.scores = v.scores;
+  p.sel_idx = v.sel_idx;
+  p.sel_cnt = v.sel_cnt;
+  p.B = v.B;
+  p.gamma = v.gamma;
+  p.Hq = v.Hq;
+  p.Hkv = v.Hkv;
+  p.d = v.d;
+  p.block_size = v.block_size;
+  p.nb_max = v.nb_max;
+  p.k_blocks = v.k_blocks;
+  p.n_sink = v.n_sink;
+  p.n_local = v.n_local;
+  p.max_seq_len = v.max_seq_len;
+  p.nq = 1;
+  p.gather = v.gather;
+  p.table = v.table;
+  p.kv = v.kv;
+  p.gather_groups = v.gather_groups;
+  return hip_code(launch_select_only(p, st));
+}
+
 // block_table given (or the cache unpaged) and with_gather: the selection also leaves its gather
 // list in the workspace
 static int score_select_impl(const svf_shape_t* shape, const void* q, const float* reps,
@@ -338,35 +397,12 @@ static int score_select_impl(const svf_shape_t* shape, const void* q, const floa
       return hip_code(launch_retrieve_only(a, static_cast<hipStream_t>(stream)));
     }
   }
-  SelectParams p;
-  p.q = q;
-  p.reps = reps;
-  p.seq_lens = seq_lens;
-  p.scores = scores_or_null ? scores_or_null
-                            : reinterpret_cast<float*>(static_cast<char*>(ws) + plan_attn(*shape).bytes);
-  p.sel_idx = sel_idx;
-  p.sel_cnt = sel_cnt;
-  p.B = shape->B;
-  p.gamma = shape->gamma;
-  p.Hq = shape->Hq;
-  p.Hkv = shape->Hkv;
-  p.d = shape->d;
-  p.block_size = shape->block_size;
-  p.nb_max = nb_max_of(*shape);
-  p.k_blocks = shape->k_blocks;
-  p.n_sink = shape->n_sink;
-  p.n_local = shape->n_local;
-  p.max_seq_len = shape->max_seq_len;
   const AttnPlan pl = plan_attn(*shape);
-  p.nq = 1;
-  p.masks = nullptr;
-  p.mask_words = 0;
-  p.gather = nullptr;
-  p.table = block_table;
-  p.kv = layout_of(*shape);
-  p.gather_groups = pl.gather_groups;
-  if (with_gather && pl.gather) p.gather = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + pl.off_gather);
-  return hip_code(launch_score_select(p, shape->dtype, static_cast<hipStream_t>(stream)));
+  VariantParams v = retrieval_params(*shape, pl, q, reps, seq_lens, sel_idx, sel_cnt, scores_or_null, ws);
+  v.mean_query = 1;
+  v.table = block_table;
+  if (with_gather && pl.gather) v.gather = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + pl.off_gather);
+  return retrieve(v, shape->dtype, static_cast<hipStream_t>(stream));
 }
 
 int svf_score_select(const svf_shape_t* shape, const void* q, const float* reps,
@@ -669,7 +705,7 @@ int svf_select_per_draft(const svf_shape_t* shape, const void* q, const float* r
   p.table = nullptr;
   p.kv = layout_of(*shape);
   p.gather_groups = 0;
-  return hip_code(launch_score_select(p, shape->dtype, static_cast<hipStream_t>(stream)));
+  return hip_code(launch_select_per_draft(p, shape->dtype, static_cast<hipStream_t>(stream)));
 }
 
 int svf_masks_from_selection(const svf_shape_t* shape, const int32_t* sel_idx, const int32_t* sel_cnt,
@@ -770,55 +806,14 @@ int svf_retrieve(const svf_shape_t* shape, const svf_retrieval_t* retrieval, con
   if (misaligned(q) || misaligned(summaries)) return SVF_ERR_SHAPE;
   rc = check_ws(shape, ws, ws_bytes);
   if (rc) return rc;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  float* scores = scores_or_null ? scores_or_null
-                                 : reinterpret_cast<float*>(static_cast<char*>(ws) + plan_attn(*shape).bytes);
-  VariantParams v;
-  v.q = q;
-  v.summaries = summaries;
-  v.seq_lens = seq_lens;
-  v.scores = scores;
-  v.sel_idx = sel_idx;
-  v.sel_cnt = sel_cnt;
-  v.B = shape->B;
-  v.gamma = shape->gamma;
-  v.Hq = shape->Hq;
-  v.Hkv = shape->Hkv;
-  v.d = shape->d;
-  v.block_size = shape->block_size;
-  v.nb_max = nb_max_of(*shape);
-  v.k_blocks = shape->k_blocks;
-  v.n_sink = shape->n_sink;
-  v.n_local = shape->n_local;
-  v.max_seq_len = shape->max_seq_len;
+  VariantParams v = retrieval_params(*shape, plan_attn(*shape), q, summaries, seq_lens, sel_idx, sel_cnt, scores_or_null, ws);
+  v.mean_query = default_scores(r);
   v.minmax = r.summary == SVF_SUMMARY_MINMAX;
   v.summary_bf16 = r.summary_dtype == SVF_BF16;
   v.group_max = r.group_rule == SVF_GROUP_MAX;
+  v.all_heads = r.budget_rule == SVF_BUDGET_GLOBAL;
   v.n_total = r.n_total;
-  // the main path's own kernels wherever the rule is the main path's (same bits as svf_score_select)
-  SelectParams p;
-  p.q = q;
-  p.reps = static_cast<const float*>(summaries);
-  p.seq_lens = seq_lens;
-  p.scores = scores;
-  p.sel_idx = sel_idx;
-  p.sel_cnt = sel_cnt;
-  p.B = v.B; p.gamma = v.gamma; p.Hq = v.Hq; p.Hkv = v.Hkv; p.d = v.d;
-  p.block_size = v.block_size; p.nb_max = v.nb_max; p.k_blocks = v.k_blocks;
-  p.n_sink = v.n_sink; p.n_local = v.n_local; p.max_seq_len = v.max_seq_len;
-  p.nq = 1;
-  p.masks = nullptr;
-  p.mask_words = 0;
-  p.gather = nullptr;
-  p.table = nullptr;
-  p.kv = layout_of(*shape);
-  p.gather_groups = 0;
-  hipError_t e;
-  if (default_scores(r)) e = launch_scores_only(p, shape->dtype, st);
-  else e = launch_variant_scores(v, shape->dtype, st);
-  if (e != hipSuccess) return SVF_ERR_HIP;
-  if (r.budget_rule == SVF_BUDGET_PER_HEAD) return hip_code(launch_select_only(p, st));
-  return hip_code(launch_select_global(v, st));
+  return retrieve(v, shape->dtype, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

@@ -220,10 +220,9 @@ __device__ __forceinline__ float mean_query_channel(const QueryHeads<T>& h, cons
   return s / (float)G;
 }
 
-// Retrieval variants (retrieval_variants.hip): scores of the first draft token per query head
-// against mean-key or min/max summaries (fp32 or bf16), combined per KV head by mean or maximum;
-// kept blocks per KV head (the selection kernel of score_select.hip) or over all KV heads of a
-// sequence.
+// Retrieval (retrieve.hip): scores of the first draft token's mean query, or per query head against
+// mean-key or min/max summaries (fp32 or bf16), combined per KV head by mean or maximum; kept blocks
+// per KV head or over all KV heads of a sequence.
 struct VariantParams {
   const void* q;            // [B][gamma][Hq][d]
   const void* summaries;
@@ -233,15 +232,24 @@ struct VariantParams {
   int32_t* sel_cnt;         // [B][Hkv]
   int32_t B, gamma, Hq, Hkv, d, block_size, nb_max, k_blocks, n_sink, n_local, max_seq_len;
   int32_t minmax, summary_bf16, group_max, n_total;
+  int32_t mean_query;       // the main path's rule: one query, the mean over the query heads
+  int32_t all_heads;        // one selection of n_total pairs per sequence instead of k_blocks per KV head
+  uint64_t* tickets;        // AttnParams::tickets (the counter of a group's first word of its kind); NULL: the scores alone
+  // optional gather list (per KV head only; NULL: none) and the cache addressing it needs
+  uint64_t* gather;
+  const int32_t* table;
+  KvLayout kv;
+  int32_t gather_groups;
 };
-hipError_t launch_variant_scores(const VariantParams& p, int dtype, hipStream_t st);
+// Whether one workgroup selects among this many KV heads' blocks.
+bool retrieve_selects(int heads, int nb_max);
+hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st);
 hipError_t launch_select_global(const VariantParams& p, hipStream_t st);
-hipError_t launch_scores_only(const SelectParams& p, int dtype, hipStream_t st);
 hipError_t launch_select_only(const SelectParams& p, hipStream_t st);
 
 // Launchers (each validates nothing: the C ABI layer has already done so).
 hipError_t launch_block_reps(const RepsParams& p, int dtype, int B, hipStream_t st);
-hipError_t launch_score_select(const SelectParams& p, int dtype, hipStream_t st);
+hipError_t launch_select_per_draft(const SelectParams& p, int dtype, hipStream_t st);
 // retrieval analytics (analytics.hip)
 hipError_t launch_masks_from_selection(const int32_t* sel_idx, const int32_t* sel_cnt, uint64_t* masks, int pairs,
                                        int k_blocks, int mask_words, hipStream_t st);
