@@ -26,9 +26,9 @@
 // that is faster than two launches for it (f32_retrieves).
 // us per anchor / reuse call, against a kernel that staged tiles in LDS for the vector ALU, with a merge
 // launch behind it and two retrieval launches in front: 1024 tokens, 8 query heads of 64, 4 drafts 19.7 / 11.6
-// -> 10.0 / 7.7; 6160 tokens, 4 heads of 128, 8 drafts 21.9 / 13.4 -> 13.5 / 8.9; one sequence of 32k, 32 heads of
-// 128, 8 drafts 46.2 / 35.6 -> 27.4 / 22.9; bf16 in blocks of 66 (4 sequences, 32 heads, 5 drafts, 24 blocks)
-// 50.4 / 40.7 -> 42.6 / 34.9.
+// -> 10.0 / 7.7; 6160 tokens, 4 heads of 128, 8 drafts 21.9 / 13.4 -> 13.5 / 8.9; four sequences of 32k, 32 heads of
+// 128, 8 drafts 66.2 / 52.9 -> 41.1 / 31.5; bf16 in blocks of 66 (4 sequences, 32 heads, 5 drafts, 24 blocks)
+// 51.4 / 41.3 -> 28.1 / 24.4.
 #include <hip/hip_bf16.h>
 #include <math.h>
 
@@ -477,11 +477,13 @@ int64_t groups_of(const svf_shape_t& s) {
 
 // Splits per (sequence, KV head, row group).  A unit is a tile for sixteen rows; a workgroup has four SIMDs.
 // Eight splits are merged in one trip to memory (2 us with the exchange), so few units spread over eight
-// workgroups, or as many as there are tiles, rather than queue in one; four units are as fast in one
-// workgroup.  Behind that a workgroup takes eight units, and the splits grow with the square root once the
-// trips of the merge cost what the units save, up to two workgroups per compute unit.  us per call, d = 64 and
-// d = 128: 9 units 7.4 / 8.4 (2 splits 8.1 / 9.2; one 9.1 / 11.1), 17 units 7.8 / 9.1 (16 splits 8.3 / 9.4), 258 units
-// (d = 128) 22.9 with 24 splits, 25.6 with 33; 2049 units 30.8 with 68, 45 with 257.
+// workgroups, or as many as there are tiles, rather than queue in one (also with sixteen wavefronts there);
+// four units are as fast in one workgroup.  Behind that a workgroup takes eight units, and the splits grow with the
+// square root once the trips of the merge cost what the units save.  Never more than one round of 256 workgroups: a
+// compute unit's registers hold one at a time, and a second round that is half full costs a whole one.  us per call,
+// d = 64 and d = 128: 9 units 7.4 / 8.4 (2 splits 8.1 / 9.2; one 9.1 / 11.1), 17 units 7.8 / 9.1 (16 splits 8.3 / 9.4),
+// 258 units (d = 128) 22.9 with 24 splits, 25.6 with 33; 2049 units 30.8 with 68, 45 with 257; 8 pairs of 1026 units 35.5
+// with 32 splits, 50.7 with 49; 32 pairs of 129 units (d = 128) 31.5 with 8, 43.9 with 16.
 int f32_splits(const svf_shape_t& s) {
   const int64_t units = units_of(s), groups = groups_of(s);
   if (units <= 4) return 1;
@@ -490,15 +492,14 @@ int f32_splits(const svf_shape_t& s) {
   const int64_t root = (int64_t)ceil(1.5 * sqrt((double)units));
   if (want > 16 && want > root) want = root > 16 ? root : 16;
   if (want > tiles) want = tiles;
-  const int64_t most = groups < 512 ? 512 / groups : 1;
+  const int64_t most = groups < 256 ? 256 / groups : 1;
   return (int)(want < most ? want : most);
 }
 
 // Whether anchor layers retrieve inside the attention kernel, every workgroup for itself.  One round of
-// workgroups reads a pair's representatives (512 KB at most) faster than two more launches are made, also if
-// all splits read the same ones: 8 pairs x 24 splits, 1024 blocks 31.2 us against 35.3, 512 blocks 27.4 against
-// 33.7.  Several rounds do that one after the other: 512 workgroups 26.1 against 31.5 us with 32 KB each, 30.4 and
-// 31.5 with 64 KB, 35.7 and 32.1 with 128 KB.
+// workgroups reads a pair's representatives (512 KB at most) faster than another launch is made, also if
+// all splits read the same ones.  Several rounds (256 groups and more) do that one after the other: 512
+// workgroups 26.1 against 31.5 us with 32 KB each, 30.4 and 31.5 with 64 KB, 35.7 and 32.1 with 128 KB.
 bool f32_retrieves(const svf_shape_t& s) {
   const int64_t nb = ((int64_t)s.max_seq_len + s.block_size - 1) / s.block_size;
   const int64_t workgroups = groups_of(s) * f32_splits(s);
