@@ -20,6 +20,7 @@ int mfma_splits(const svf_shape_t& s);
 int mfma_shared_splits(const svf_shape_t& s);
 bool mfma_rows_mode(const svf_shape_t& s);
 int mfma_rows_splits(const svf_shape_t& s);
+int mfma_select_splits(const svf_shape_t& s);
 
 namespace {
 
@@ -390,7 +391,7 @@ static int score_select_impl(const svf_shape_t* shape, const void* q, const floa
       a.Mpad = pl.Mpad;
       a.block_size = shape->block_size;
       a.k_blocks = shape->k_blocks;
-      a.n_splits = pl.n_splits;
+      a.n_splits = mfma_select_splits(*shape);
       a.max_seq_len = shape->max_seq_len;
       a.g_magic = (1ull << 32) / (uint64_t)a.G + 1ull;
       a.hkv_magic = (1ull << 32) / (uint64_t)a.Hkv + 1ull;

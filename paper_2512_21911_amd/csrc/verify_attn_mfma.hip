@@ -2398,9 +2398,28 @@ bool mfma_supported(const svf_shape_t& s) {
          s.Hq < 65536;
 }
 
+// Splits of a group such that all workgroups of the launch are resident at once, if the least number of
+// splits `lo` allows that, else `want`.  Workgroups hold half of a compute unit's LDS or more (one per
+// compute unit at D = 128, two at D = 64), and all splits and groups of a pair go to one XCD of 32 compute
+// units: with 48 pairs in six splits an XCD gets 36 workgroups, and the four that wait for a free place cost a
+// whole second round.  Fewer splits with another tile for some wavefronts cost far less.  us per reuse / anchor
+// launch at D = 128, `want` splits (256 compute units over the groups, rounded up) and as many as fit:
+//   24 pairs of 4096 tokens, 32 rows: 11 splits 25.5 / 37.6, 10 splits 16.7 / 19.0
+//   48 pairs of 1728 tokens, 32 rows: 6 splits 23.8 / 29.9, 5 splits 15.9 / 18.1; 92 rows: 27.3 / 35.8 and 17.7 / 21.3
+//   28 pairs of 1088 tokens, 64 rows: 5 splits 17.7 / 23.4, 4 splits 11.4 / 14.4
+//   96 pairs of 512 tokens, 64 rows: 2 splits 22.3 / 28.3, 1 split 12.0 / 14.9
+// (over 130 shapes of 1 - 112 pairs that did not fit: 1.2 - 4.5 times as fast, none slower; 1024 blocks scored by
+// one workgroup instead of two: 24.5 us instead of 42.0.)
+static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64_t want, int64_t lo) {
+  const int64_t places = s.d == 64 ? 64 : 32;            // workgroups that an XCD holds
+  const int64_t fit = places / (((int64_t)s.B * s.Hkv + kXcds - 1) / kXcds * groups_per_pair);
+  return want > fit && fit >= lo && fit >= 1 ? fit : want;
+}
+
 // Splits per (sequence, KV head, row group): enough workgroups to cover the 256 compute units,
-// at most kMaxTiles tiles per wavefront, at least one tile per wavefront.
-int mfma_splits(const svf_shape_t& s) {
+// at most kMaxTiles tiles per wavefront, at least one tile per wavefront.  `sharing`: of the retrieval alone, whose
+// workgroups are small.
+static int tile_splits(const svf_shape_t& s, bool sharing) {
   const int M = s.gamma * (s.Hq / s.Hkv);
   const int64_t groups = (int64_t)s.B * s.Hkv * ((M + 31) / 32);
   const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
@@ -2409,12 +2428,13 @@ int mfma_splits(const svf_shape_t& s) {
   int64_t want = (256 + groups - 1) / groups;
   if (want > hi) want = hi;
   if (want < lo) want = lo;
-  return (int)want;
+  return (int)(sharing ? want : one_round_splits(s, (M + 31) / 32, want, lo));
 }
+int mfma_splits(const svf_shape_t& s) { return tile_splits(s, false); }
 
 // Splits a pair may be given where the launch shares them out by the pairs' counts (share_out_splits), or
-// 0 where it uses mfma_splits for every pair: with one tile per wavefront or one split per pair as planned there
-// is nothing to share out, and the shares are worked out for up to 64 kShareChunks pairs.  The partials it takes are held to
+// 0 where it uses mfma_splits for every pair: with one tile per wavefront (but for what one_round_splits changes) or one
+// split per pair as planned there is nothing to share out, and the shares are worked out for up to 64 kShareChunks pairs.  The partials it takes are held to
 // 8 MB, which keeps small workspaces small.
 int mfma_shared_splits(const svf_shape_t& s) {
   const int M = s.gamma * (s.Hq / s.Hkv);
@@ -2438,7 +2458,7 @@ bool mfma_rows_mode(const svf_shape_t& s) {
 
 // Splits per (sequence, KV head, set of eight row groups) of the rows kernel: cover the compute
 // units; at least one tile and at most kMaxRowTiles tiles per workgroup.
-int mfma_rows_splits(const svf_shape_t& s) {
+static int row_splits(const svf_shape_t& s, bool sharing) {
   const int M = s.gamma * (s.Hq / s.Hkv);
   const int row_groups = (M + 31) / 32;
   const int64_t groups = (int64_t)s.B * s.Hkv * ((row_groups + kWaves - 1) / kWaves);
@@ -2447,8 +2467,12 @@ int mfma_rows_splits(const svf_shape_t& s) {
   int64_t want = (256 + groups - 1) / groups;
   if (want > tiles) want = tiles;
   if (want < lo) want = lo;
-  return (int)want;
+  return (int)(sharing ? want : one_round_splits(s, (row_groups + kWaves - 1) / kWaves, want, lo));
 }
+int mfma_rows_splits(const svf_shape_t& s) { return row_splits(s, false); }
+
+// Workgroups per (sequence, KV head) that share the scoring of the retrieval alone.
+int mfma_select_splits(const svf_shape_t& s) { return mfma_rows_mode(s) ? row_splits(s, true) : tile_splits(s, true); }
 
 // The retrieval of kSelect without the attention behind it (the stand-alone block selection of a
 // shape the retrieving attention kernel handles): the workgroups of a (sequence, KV head) share
