@@ -9,7 +9,7 @@
 //           own a block, 16 channels each (d = 128), fixed order of the arithmetic; the summaries are read
 //           once whatever the number of query heads.
 //   select  top-N over the blocks of a KV head, or over all (KV head, block) pairs of a sequence (Eq. 6
-//           counts its budget over the H KV heads), by the workgroup that is the last of its KV head (or
+//           counts its budget over the H KV heads), up to 8192 of them by the workgroup that is the last of its KV head (or
 //           sequence) to have stored its scores: radix select over keys in registers, then one ordered
 //           compaction.
 //
@@ -31,8 +31,8 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kBlocksPerPass = kThreads / kScoreLanes;
 constexpr int kPasses = 1;             // blocks per lane group
 constexpr int kHeadsPerRound = 8;      // query heads staged in LDS at a time
-constexpr int kKeys = 8;               // keys per thread of one selection
-constexpr int kMaxKeys = kKeys * kThreads;
+constexpr int kKeys = 8;               // keys per thread of a selection in the launch that scores
+constexpr int kManyKeys = 32;          // ... of one in a launch of its own
 constexpr int kMaxHeads = 256;         // KV heads of one selection
 
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -59,11 +59,21 @@ __device__ __forceinline__ float bound_score(const float4 (&mn)[NCH], const floa
 // How a block is scored (VariantParams::mean_query, minmax, group_max).
 enum Rule { kMeanQuery, kMeanOfHeads, kMaxOfHeads, kBoundMeanOfHeads, kBoundMaxOfHeads };
 
-struct Scratch {
-  uint32_t hist[4][256];
+// What a selection over KEYS keys per thread needs in LDS.
+// COPIES of a digit's histogram: lanes l, l + COPIES, ... count in one of them (a bin of all of them in different banks).
+template <int COPIES>
+struct Counts {
+  static constexpr int kCopies = COPIES, kStride = COPIES == 1 ? 256 : 260;
+  uint32_t hist[4][COPIES * kStride];
   uint32_t low[kWaves], high[kWaves], top[kWaves];   // of a wavefront's keys: smallest, largest below the top key, top keys
-  uint32_t seg[kMaxKeys / 64];           // larger keys (low half) and equal keys of 64 consecutive keys
+};
+// (With many keys per thread, the adds to the few bins that most scores share are what a digit takes: 32 768 pairs
+// 55.4 us a retrieval with one copy, 51.7 with two, 49.8 with four, 49.6 with eight.)
+template <int KEYS>
+struct Scratch : Counts<KEYS <= 8 ? 1 : 4> {
+  uint32_t seg[KEYS * kWaves];           // larger keys (low half) and equal keys of 64 consecutive keys
   uint32_t head_rank[kMaxHeads + 1];     // kept pairs in front of a head's first
+  int32_t sel[kMaxGatherBlocks];         // kept block ids, for the gather list
 };
 
 constexpr uint32_t kTopKey = 0xffffffffu;  // of a block that is always kept
@@ -91,8 +101,14 @@ __device__ __forceinline__ uint32_t wave_extreme(uint32_t x) {
 // One digit of the radix select: finds the bin of hist that the need-th largest key lies in.  Every wavefront scans
 // the 256 bins for itself, lane l bins 255 - 4l (in .w) down to 252 - 4l (in .x).  need becomes what is still wanted
 // from inside the bin; true if that is all of it.
-__device__ __forceinline__ bool pick_bin(const uint32_t (&hist)[256], int lane, uint32_t& need, uint32_t& bin_out) {
-  const uint4 hq = *reinterpret_cast<const uint4*>(&hist[252 - 4 * lane]);
+template <int COPIES, int STRIDE>
+__device__ __forceinline__ bool pick_bin(const uint32_t (&hist)[COPIES * STRIDE], int lane, uint32_t& need, uint32_t& bin_out) {
+  uint4 hq = *reinterpret_cast<const uint4*>(&hist[252 - 4 * lane]);
+#pragma unroll
+  for (int c = 1; c < COPIES; ++c) {
+    const uint4 other = *reinterpret_cast<const uint4*>(&hist[c * STRIDE + 252 - 4 * lane]);
+    hq.x += other.x; hq.y += other.y; hq.z += other.z; hq.w += other.w;
+  }
   const uint32_t own = hq.x + hq.y + hq.z + hq.w;
   const uint32_t incl = wave_inclusive_sum(own);
   uint32_t run = incl - own;
@@ -117,7 +133,8 @@ __device__ __forceinline__ bool pick_bin(const uint32_t (&hist)[256], int lane, 
 // One key per thread (N <= 1024): the digits are the key's bytes.  Scores share their sign and most of their
 // exponent, so the first byte tells few of them apart, and a wavefront's adds to one bin go one lane at a
 // time: the lanes that share the first lane's bin are counted with one add.
-__device__ __forceinline__ uint32_t threshold_of(uint32_t key, Scratch* sc, int N, uint32_t keep_n, int tid, int lane, uint32_t& need) {
+template <typename Counts>
+__device__ __forceinline__ uint32_t threshold_of(uint32_t key, Counts* sc, int N, uint32_t keep_n, int tid, int lane, uint32_t& need) {
   uint32_t prefix = 0;
   need = keep_n;
 #pragma unroll
@@ -135,7 +152,7 @@ __device__ __forceinline__ uint32_t threshold_of(uint32_t key, Scratch* sc, int 
     }
     __syncthreads();
     uint32_t picked;
-    const bool whole = pick_bin(sc->hist[pass], lane, need, picked);
+    const bool whole = pick_bin<Counts::kCopies, Counts::kStride>(sc->hist[pass], lane, need, picked);
     prefix |= picked << shift;
     if (whole) {
       need = kAllEqual;
@@ -147,11 +164,12 @@ __device__ __forceinline__ uint32_t threshold_of(uint32_t key, Scratch* sc, int 
 // Several keys per thread (thread t: keys t, t + 1024, ...): the digits are taken from the top of the keys' range,
 // which saves one or two of them and spreads the adds, and costs a pass and a barrier: four sequences of 4096
 // keys 13.4 -> 12.3 us a call, one of 8192 keys 17.2 -> 15.2 (32 heads of 512 keys 9.0 -> 9.1).
-__device__ __forceinline__ uint32_t threshold_of(const uint32_t (&key)[kKeys], Scratch* sc, int N, uint32_t keep_n, int tid, int lane,
+template <int KEYS, typename Counts>
+__device__ __forceinline__ uint32_t threshold_of(const uint32_t (&key)[KEYS], Counts* sc, int N, uint32_t keep_n, int tid, int lane,
                                                  int wave, uint32_t& need) {
   uint32_t low = kTopKey, high = 0u, top = 0u;           // (top keys stand apart, or the range would be all there is)
 #pragma unroll
-  for (int u = 0; u < kKeys; ++u) {
+  for (int u = 0; u < KEYS; ++u) {
     if (u * kThreads >= N) break;                        // (uniform)
     const bool in = u * kThreads + tid < N, is_top = in && key[u] == kTopKey;
     top += (uint32_t)__popcll(__ballot(is_top));
@@ -183,15 +201,15 @@ __device__ __forceinline__ uint32_t threshold_of(const uint32_t (&key)[kKeys], S
     const int width = min(shift, 8);
     shift -= width;
 #pragma unroll
-    for (int u = 0; u < kKeys; ++u) {
+    for (int u = 0; u < KEYS; ++u) {
       if (u * kThreads >= N) break;
       const uint32_t rel = key[u] - low;
       if (u * kThreads + tid < N && key[u] != kTopKey && (uint64_t)(rel ^ prefix) >> (shift + width) == 0)
-        atomicAdd(&sc->hist[pass][(rel >> shift) & ((1u << width) - 1u)], 1u);
+        atomicAdd(&sc->hist[pass][lane % Counts::kCopies * Counts::kStride + ((rel >> shift) & ((1u << width) - 1u))], 1u);
     }
     __syncthreads();
     uint32_t picked;
-    const bool whole = pick_bin(sc->hist[pass], lane, need, picked);
+    const bool whole = pick_bin<Counts::kCopies, Counts::kStride>(sc->hist[pass], lane, need, picked);
     prefix |= picked << shift;
     if (whole) {
       need = kAllEqual;
@@ -200,6 +218,139 @@ __device__ __forceinline__ uint32_t threshold_of(const uint32_t (&key)[kKeys], S
     if (shift == 0) break;
   }
   return low + prefix;
+}
+
+// What is selected from: `heads` KV heads from h0 on of sequence b, nb blocks each.  Pair i = h * nb + j is block j of
+// head h0 + h; thread t holds the keys of pairs t, t + 1024, ...
+struct Pairs {
+  int b, h0, heads, nb, L, N;
+  uint32_t per_nb;                       // 2^32 / nb, rounded up: i / nb == (i * per_nb) >> 32 (exact: i, nb <= 32768)
+  __device__ __forceinline__ Pairs(const VariantParams& p, int b_, int h, int L_, int nb_)
+      : b(b_), h0(p.all_heads ? 0 : h), heads(p.all_heads ? p.Hkv : 1), nb(nb_), L(L_), N(heads * nb_),
+        per_nb(nb_ > 1 ? 0xffffffffu / (uint32_t)nb_ + 1u : 0u) {}
+  __device__ __forceinline__ int head_of(int i) const { return heads == 1 ? 0 : (nb > 1 ? (int)__umulhi((uint32_t)i, per_nb) : i); }
+};
+// Keys of the scores in memory, all in flight at once.
+template <int KEYS>
+__device__ __forceinline__ void load_keys(const VariantParams& p, const Pairs& all, uint32_t (&key)[KEYS], int tid) {
+  const float* const from = p.scores + ((int64_t)all.b * p.Hkv + all.h0) * p.nb_max;
+  float v[KEYS];
+  int j[KEYS];
+#pragma unroll
+  for (int u = 0; u < KEYS; ++u) {
+    if (u * kThreads >= all.N) break;                    // (uniform)
+    const int i = min(u * kThreads + tid, all.N - 1), h = all.head_of(i);
+    j[u] = i - h * all.nb;
+    v[u] = __hip_atomic_load(from + (int64_t)h * p.nb_max + j[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+#pragma unroll
+  for (int u = 0; u < KEYS; ++u) {
+    if (u * kThreads >= all.N) break;
+    key[u] = (j[u] < p.n_sink || j[u] >= all.nb - p.n_local) ? kTopKey : score_key(v[u]);
+  }
+}
+
+__device__ __forceinline__ uint32_t pairs_kept(const VariantParams& p, int N) { return (uint32_t)min(N, p.all_heads ? p.n_total : p.k_blocks); }
+
+// The selection by the whole workgroup, and all that is written of it.  sc->hist is zero and sc->head_rank is
+// keep_n up to [heads] (heads behind the last pair, an empty sequence: all), with a barrier since.
+template <int KEYS>
+__device__ __forceinline__ void select_kept(const VariantParams& p, const Pairs& all, uint32_t (&key)[KEYS], Scratch<KEYS>* sc, int tid, int lane,
+                                            int wave) {
+  const int N = all.N, heads = all.heads;
+  const uint32_t keep_n = pairs_kept(p, N);
+  uint32_t need = 0, tau = kTopKey;
+  if (keep_n > 0)
+    tau = N <= kThreads ? threshold_of(key[0], sc, N, keep_n, tid, lane, need) : threshold_of<KEYS>(key, sc, N, keep_n, tid, lane, wave, need);
+  const bool all_equal = need == kAllEqual;              // (a selection that cuts through equal keys is rare)
+
+  // Per 64 keys the number of larger and of equal ones, and one scan over them (neither sum exceeds 32768): a
+  // key's rank among the kept ones is then known, and with it, at the pairs that begin a head, where that
+  // head's list starts.
+  auto look = [&](int u, uint64_t& gt, uint64_t& eq) {
+    const bool in = u * kThreads + tid < N;
+    gt = __ballot(in && (all_equal ? key[u] >= tau : key[u] > tau));
+    eq = all_equal ? 0ull : __ballot(in && key[u] == tau);
+  };
+#pragma unroll
+  for (int u = 0; u < KEYS; ++u) {
+    if (u * kThreads >= N) break;
+    uint64_t gt, eq;
+    look(u, gt, eq);
+    if (lane == 0) sc->seg[u * kWaves + wave] = (uint32_t)__popcll(gt) | ((uint32_t)__popcll(eq) << 16);
+  }
+  __syncthreads();
+  // (every wavefront scans them for itself: lane l holds segments kPer l .. kPer l + kPer - 1, and of their sums
+  // keeps the one in front of the segment that the wavefront's own are: u * kWaves + wave)
+  constexpr int kPer = KEYS * kWaves / 64;
+  static_assert(kWaves % kPer == 0, "a wavefront's segments have the same place in every lane");
+  uint32_t in_front;
+  {
+    const int segments = (N + kThreads - 1) / kThreads * kWaves;
+    uint32_t sum = 0, before = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (i == wave % kPer) before = sum;
+      sum += kPer * lane + i < segments ? sc->seg[kPer * lane + i] : 0u;
+    }
+    in_front = wave_inclusive_sum(sum) - sum + before;
+  }
+  uint32_t rank[KEYS];
+  uint32_t kept = 0;                                       // bit u
+  static_assert(KEYS <= 32, "a bit per key");
+#pragma unroll
+  for (int u = 0; u < KEYS; ++u) {
+    if (u * kThreads >= N) break;
+    uint64_t gt, eq;
+    look(u, gt, eq);
+    const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)in_front, (u * kWaves + wave) / kPer);
+    rank[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(gt >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)gt, s & 0xffffu));
+    bool keep = (gt >> lane) & 1ull;
+    if (!all_equal) {
+      const uint32_t eq_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, s >> 16));
+      rank[u] += min(eq_before, need);
+      keep |= ((eq >> lane) & 1ull) && eq_before < need;
+    }
+    if (keep) kept |= 1u << u;
+    const int i = u * kThreads + tid, h = all.head_of(i);
+    if (heads > 1 && i < N && i == h * all.nb) sc->head_rank[h] = rank[u];
+  }
+  if (heads > 1) __syncthreads();
+  int32_t* const out = p.sel_idx + ((int64_t)all.b * p.Hkv + all.h0) * p.k_blocks;
+#pragma unroll
+  for (int u = 0; u < KEYS; ++u) {
+    if (u * kThreads >= N) break;
+    if (!((kept >> u) & 1u)) continue;
+    const int i = u * kThreads + tid, h = all.head_of(i);
+    const uint32_t pos = heads == 1 ? rank[u] : rank[u] - sc->head_rank[h];
+    if (pos < (uint32_t)p.k_blocks) out[(int64_t)h * p.k_blocks + pos] = i - h * all.nb;
+    if (heads == 1 && pos < (uint32_t)kMaxGatherBlocks) sc->sel[pos] = i;
+  }
+  for (int h = wave; h < heads; h += kWaves) {
+    const int cnt = heads == 1 ? (int)keep_n : min((int)(sc->head_rank[h + 1] - sc->head_rank[h]), p.k_blocks);
+    for (int i = cnt + lane; i < p.k_blocks; i += 64) out[(int64_t)h * p.k_blocks + i] = -1;
+    if (lane == 0) p.sel_cnt[(int64_t)all.b * p.Hkv + all.h0 + h] = cnt;
+  }
+  // Gather list: where the K row of every fourth selected-token slot sits in the pool, and how many of its
+  // four slots hold a real token (block and page sizes are multiples of four, so the four slots share a block
+  // and a page).
+  if (p.gather) {                                        // (one KV head at a time)
+    __syncthreads();
+    uint64_t* const gl = p.gather + ((int64_t)all.b * p.Hkv + all.h0) * p.gather_groups;
+    for (int e = tid; e < p.gather_groups; e += kThreads) {
+      const int slot0 = 4 * e, bi = slot0 / p.block_size;
+      uint64_t entry = 0;
+      if (bi < (int)keep_n) {
+        const int tok0 = sc->sel[bi] * p.block_size + (slot0 - bi * p.block_size);
+        const int nv = min(max(all.L - tok0, 0), 4);
+        if (nv > 0) {
+          const int64_t off = (token_offset(p.kv, p.table, all.b, tok0) + (int64_t)all.h0 * p.kv.stride_head) * 2;
+          entry = ((uint64_t)off & kGatherOffsetMask) | ((uint64_t)nv << kGatherCountShift);
+        }
+      }
+      gl[e] = entry;
+    }
+  }
 }
 
 // grid: (ceil(nb_max / 128), Hkv, B)
@@ -212,15 +363,14 @@ __global__ __launch_bounds__(kThreads) void retrieve_kernel(VariantParams p) {
   constexpr int ROWS = MINMAX ? 2 : 1;
   __shared__ __attribute__((aligned(16))) float qs[RULE == kMeanQuery ? 1 : kHeadsPerRound][D];
   __shared__ uint32_t s_keys[kPasses * kBlocksPerPass];   // (one workgroup alone) the keys as they are formed
-  __shared__ __attribute__((aligned(16))) Scratch s_scratch;
-  __shared__ int32_t s_sel[kMaxGatherBlocks];            // kept block ids, for the gather list
+  __shared__ __attribute__((aligned(16))) Scratch<kKeys> s_scratch;
   __shared__ int s_last;
 
   const int b = blockIdx.z;
   const int tid = threadIdx.x, sub = tid % LPB;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = p.Hq / p.Hkv;
-  Scratch* const sc = &s_scratch;
+  Scratch<kKeys>* const sc = &s_scratch;
   const bool alone = gridDim.x == 1 && (!p.all_heads || p.Hkv == 1);   // one workgroup scores all it selects from
   int L, nb;
   {
@@ -293,11 +443,7 @@ __global__ __launch_bounds__(kThreads) void retrieve_kernel(VariantParams p) {
   if (!p.tickets) return;                                // the scores alone
 
   // ---- the last workgroup of the KV head (or of the sequence) selects ----
-  const int h0 = p.all_heads ? 0 : blockIdx.y, heads = p.all_heads ? p.Hkv : 1;
-  const int N = heads * nb;
-  // head of pair i: a multiplication by 2^32 / nb, rounded up (exact: i, nb <= 8192)
-  const uint32_t per_nb = nb > 1 ? 0xffffffffu / (uint32_t)nb + 1u : 0u;
-  auto head_of = [&](int i) { return heads == 1 ? 0 : (nb > 1 ? (int)__umulhi((uint32_t)i, per_nb) : i); };
+  const Pairs all(p, b, blockIdx.y, L, nb);
   uint32_t key[kKeys];
 #pragma unroll
   for (int u = 0; u < kKeys; ++u) key[u] = 0u;
@@ -305,122 +451,39 @@ __global__ __launch_bounds__(kThreads) void retrieve_kernel(VariantParams p) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's scores have been acknowledged
     __syncthreads();
     if (tid == 0) {
-      uint64_t* const arrivals = p.tickets + ((int64_t)b * p.Hkv + h0) * kTicketWords + 2;
-      const uint64_t of = (uint64_t)gridDim.x * heads;
+      uint64_t* const arrivals = p.tickets + ((int64_t)b * p.Hkv + all.h0) * kTicketWords + 2;
+      const uint64_t of = (uint64_t)gridDim.x * all.heads;
       const uint64_t prev = __hip_atomic_fetch_add(arrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       s_last = prev == of - 1;
       if (s_last) __hip_atomic_store(arrivals, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (!s_last) return;
-    // scores of pair i = h * nb + j, all in flight at once
-    const float* const from = p.scores + ((int64_t)b * p.Hkv + h0) * p.nb_max;
-    float v[kKeys];
-    int j[kKeys];
-#pragma unroll
-    for (int u = 0; u < kKeys; ++u) {
-      if (u * kThreads >= N) break;                      // (uniform)
-      const int i = min(u * kThreads + tid, N - 1), h = head_of(i);
-      j[u] = i - h * nb;
-      v[u] = __hip_atomic_load(from + (int64_t)h * p.nb_max + j[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-#pragma unroll
-    for (int u = 0; u < kKeys; ++u) {
-      if (u * kThreads >= N) break;
-      key[u] = (j[u] < p.n_sink || j[u] >= nb - p.n_local) ? kTopKey : score_key(v[u]);
-    }
+    load_keys<kKeys>(p, all, key, tid);
   }
-  const uint32_t keep_n = (uint32_t)min(N, p.all_heads ? p.n_total : p.k_blocks);
-  if (tid <= heads) sc->head_rank[tid] = keep_n;          // heads behind the last pair (an empty sequence: all)
+  if (tid <= all.heads) sc->head_rank[tid] = pairs_kept(p, all.N);
   __syncthreads();
-  if (alone && tid < N) key[0] = s_keys[tid];
-  uint32_t need = 0, tau = kTopKey;
-  if (keep_n > 0)
-    tau = N <= kThreads ? threshold_of(key[0], sc, N, keep_n, tid, lane, need) : threshold_of(key, sc, N, keep_n, tid, lane, wave, need);
-  const bool all_equal = need == kAllEqual;              // (a selection that cuts through equal keys is rare)
+  if (alone && tid < all.N) key[0] = s_keys[tid];
+  select_kept<kKeys>(p, all, key, sc, tid, lane, wave);
+}
 
-  // Per 64 keys the number of larger and of equal ones, and one scan over them (neither sum exceeds 8192): a
-  // key's rank among the kept ones is then known, and with it, at the pairs that begin a head, where that
-  // head's list starts.
-  auto look = [&](int u, uint64_t& gt, uint64_t& eq) {
-    const bool in = u * kThreads + tid < N;
-    gt = __ballot(in && (all_equal ? key[u] >= tau : key[u] > tau));
-    eq = all_equal ? 0ull : __ballot(in && key[u] == tau);
-  };
-#pragma unroll
-  for (int u = 0; u < kKeys; ++u) {
-    if (u * kThreads >= N) break;
-    uint64_t gt, eq;
-    look(u, gt, eq);
-    if (lane == 0) sc->seg[u * kWaves + wave] = (uint32_t)__popcll(gt) | ((uint32_t)__popcll(eq) << 16);
-  }
+// The selection in a launch of its own, over scores in memory: pairs that do not fit the registers of the kernel
+// above (whose 8 keys per thread leave room for two workgroups on a compute unit).  us per retrieval with the scores'
+// launch, against a selection that reads the scores again in every pass: one budget over 8 x 1025 pairs 36.7 -> 19.9,
+// 8 x 2048 41.4 -> 28.3, 8 x 4096 72.8 -> 46.9, 128 x 200 284 -> 45; per head, 8 heads of 9000 blocks 65 -> 23, of
+// 32 768 231 -> 61.
+// grid: (1, B) or (Hkv, B)
+__global__ __launch_bounds__(kThreads) void select_kept_kernel(VariantParams p) {
+  __shared__ __attribute__((aligned(16))) Scratch<kManyKeys> s_scratch;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int L = clamped_len(p.seq_lens, blockIdx.y, p.max_seq_len);
+  const Pairs all(p, blockIdx.y, blockIdx.x, L, (L + p.block_size - 1) / p.block_size);
+  uint32_t key[kManyKeys];
+  for (int i = tid; i < (int)(sizeof(s_scratch.hist) / 4); i += kThreads) (&s_scratch.hist[0][0])[i] = 0;
+  if (tid <= all.heads) s_scratch.head_rank[tid] = pairs_kept(p, all.N);
+  load_keys<kManyKeys>(p, all, key, tid);
   __syncthreads();
-  static_assert(kMaxKeys / 64 == 128, "two segments per lane");
-  // (every wavefront scans them for itself; lane l: the counts in front of segments 2l and 2l + 1)
-  uint32_t in_front, own_first;
-  {
-    const int segments = (N + kThreads - 1) / kThreads * kWaves;
-    const uint32_t c0 = 2 * lane < segments ? sc->seg[2 * lane] : 0u, c1 = 2 * lane + 1 < segments ? sc->seg[2 * lane + 1] : 0u;
-    in_front = wave_inclusive_sum(c0 + c1) - (c0 + c1);
-    own_first = c0;
-  }
-  uint32_t rank[kKeys];
-  uint32_t kept = 0;                                       // bit u
-#pragma unroll
-  for (int u = 0; u < kKeys; ++u) {
-    if (u * kThreads >= N) break;
-    uint64_t gt, eq;
-    look(u, gt, eq);
-    const int seg = u * kWaves + wave;
-    uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)in_front, seg >> 1);
-    if (seg & 1) s += (uint32_t)__builtin_amdgcn_readlane((int)own_first, seg >> 1);
-    rank[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(gt >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)gt, s & 0xffffu));
-    bool keep = (gt >> lane) & 1ull;
-    if (!all_equal) {
-      const uint32_t eq_before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, s >> 16));
-      rank[u] += min(eq_before, need);
-      keep |= ((eq >> lane) & 1ull) && eq_before < need;
-    }
-    if (keep) kept |= 1u << u;
-    const int i = u * kThreads + tid, h = head_of(i);
-    if (heads > 1 && i < N && i == h * nb) sc->head_rank[h] = rank[u];
-  }
-  if (heads > 1) __syncthreads();
-  int32_t* const out = p.sel_idx + ((int64_t)b * p.Hkv + h0) * p.k_blocks;
-#pragma unroll
-  for (int u = 0; u < kKeys; ++u) {
-    if (u * kThreads >= N) break;
-    if (!((kept >> u) & 1u)) continue;
-    const int i = u * kThreads + tid, h = head_of(i);
-    const uint32_t pos = heads == 1 ? rank[u] : rank[u] - sc->head_rank[h];
-    if (pos < (uint32_t)p.k_blocks) out[(int64_t)h * p.k_blocks + pos] = i - h * nb;
-    if (heads == 1 && pos < (uint32_t)kMaxGatherBlocks) s_sel[pos] = i;
-  }
-  for (int h = wave; h < heads; h += kWaves) {
-    const int cnt = heads == 1 ? (int)keep_n : min((int)(sc->head_rank[h + 1] - sc->head_rank[h]), p.k_blocks);
-    for (int i = cnt + lane; i < p.k_blocks; i += 64) out[(int64_t)h * p.k_blocks + i] = -1;
-    if (lane == 0) p.sel_cnt[(int64_t)b * p.Hkv + h0 + h] = cnt;
-  }
-  // Gather list: where the K row of every fourth selected-token slot sits in the pool, and how many of its
-  // four slots hold a real token (block and page sizes are multiples of four, so the four slots share a block
-  // and a page).
-  if (p.gather) {                                        // (one KV head at a time)
-    __syncthreads();
-    uint64_t* const gl = p.gather + ((int64_t)b * p.Hkv + h0) * p.gather_groups;
-    for (int e = tid; e < p.gather_groups; e += kThreads) {
-      const int slot0 = 4 * e, bi = slot0 / p.block_size;
-      uint64_t entry = 0;
-      if (bi < (int)keep_n) {
-        const int tok0 = s_sel[bi] * p.block_size + (slot0 - bi * p.block_size);
-        const int nv = min(max(L - tok0, 0), 4);
-        if (nv > 0) {
-          const int64_t off = (token_offset(p.kv, p.table, b, tok0) + (int64_t)h0 * p.kv.stride_head) * 2;
-          entry = ((uint64_t)off & kGatherOffsetMask) | ((uint64_t)nv << kGatherCountShift);
-        }
-      }
-      gl[e] = entry;
-    }
-  }
+  select_kept<kManyKeys>(p, all, key, &s_scratch, tid, lane, wave);
 }
 
 template <typename QT, typename RT, int D>
@@ -442,7 +505,7 @@ void launch_d(const VariantParams& p, hipStream_t st) {
   else launch_rule<QT, RT, 128>(p, st);
 }
 
-// ---- more pairs than a workgroup's LDS holds ----------------------------------------------------
+// ---- more pairs than a workgroup's registers hold ------------------------------------------------
 constexpr int kGThreads = 1024;
 constexpr int kGWaves = kGThreads / 64;
 
@@ -550,7 +613,11 @@ __global__ __launch_bounds__(kGThreads) void select_global_kernel(VariantParams 
 
 }  // namespace
 
-bool retrieve_selects(int heads, int nb_max) { return heads <= kMaxHeads && (int64_t)heads * nb_max <= kMaxKeys; }
+Selection selection_of(int heads, int nb_max) {
+  const int64_t pairs = (int64_t)heads * nb_max;
+  if (heads > kMaxHeads || pairs > kManyKeys * kThreads) return kSelectRereads;
+  return pairs <= kKeys * kThreads ? kSelectWithScores : kSelectFromRegisters;
+}
 
 hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st) {
   if (dtype == SVF_F32) {
@@ -560,6 +627,11 @@ hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st) {
     if (p.summary_bf16) launch_d<__hip_bfloat16, __hip_bfloat16>(p, st);
     else launch_d<__hip_bfloat16, float>(p, st);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_select_kept(const VariantParams& p, hipStream_t st) {
+  hipLaunchKernelGGL(select_kept_kernel, dim3(p.all_heads ? 1 : p.Hkv, p.B), dim3(kThreads), 0, st, p);
   return hipGetLastError();
 }
 

@@ -316,13 +316,15 @@ static VariantParams retrieval_params(const svf_shape_t& s, const AttnPlan& pl, 
   return v;
 }
 
-// One launch, or, where the keys of a selection do not fit a workgroup's LDS, the scores and then a selection
-// that reads them again in every pass.
+// One launch, or, where there are more keys than the scoring workgroups have registers for, the scores and then the
+// selection.
 static int retrieve(VariantParams v, int dtype, hipStream_t st) {
-  if (retrieve_selects(v.all_heads ? v.Hkv : 1, v.nb_max)) return hip_code(launch_retrieve(v, dtype, st));
+  const Selection how = selection_of(v.all_heads ? v.Hkv : 1, v.nb_max);
+  if (how == kSelectWithScores) return hip_code(launch_retrieve(v, dtype, st));
   v.tickets = nullptr;
   const hipError_t e = launch_retrieve(v, dtype, st);
   if (e != hipSuccess) return SVF_ERR_HIP;
+  if (how == kSelectFromRegisters) return hip_code(launch_select_kept(v, st));
   if (v.all_heads) return hip_code(launch_select_global(v, st));
   SelectParams p{};
   p.seq_lens = v.seq_lens;

@@ -241,9 +241,12 @@ struct VariantParams {
   KvLayout kv;
   int32_t gather_groups;
 };
-// Whether one workgroup selects among this many KV heads' blocks.
-bool retrieve_selects(int heads, int nb_max);
+// How one workgroup selects among this many KV heads' blocks: in the launch that scores, its keys in
+// registers; in a launch of its own, the same; reading the scores again in every pass.
+enum Selection { kSelectWithScores, kSelectFromRegisters, kSelectRereads };
+Selection selection_of(int heads, int nb_max);
 hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st);
+hipError_t launch_select_kept(const VariantParams& p, hipStream_t st);
 hipError_t launch_select_global(const VariantParams& p, hipStream_t st);
 hipError_t launch_select_only(const SelectParams& p, hipStream_t st);
 
