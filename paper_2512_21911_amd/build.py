@@ -27,7 +27,7 @@ HIPCC_FLAGS = [
 # Kernels that must not use scratch memory (a private segment makes every dispatch slower, and an
 # array the compiler moved there turns register accesses into memory round trips).
 NO_SCRATCH = ("verify_attn_mfma_kernel", "verify_attn_mfma_rows_kernel", "retrieve_only_kernel", "verify_attn_f32_kernel",
-              "retrieve_kernel", "select_kept_kernel")
+              "retrieve_kernel")
 
 
 def hipcc_path() -> str:

@@ -1,4 +1,4 @@
-// Retrieval: block scores and the kept blocks, in one launch (Sec. 3.1, Eq. 5 and the selection rule), with
+// Retrieval: block scores and the kept blocks, in one launch or two (Sec. 3.1, Eq. 5 and the selection rule), with
 // one rule of Sec. 3.1 exchanged where the caller asks for it.
 //
 //   scores  the first draft token's score of every block: with the query averaged over the query heads of
@@ -9,9 +9,9 @@
 //           own a block, 16 channels each (d = 128), fixed order of the arithmetic; the summaries are read
 //           once whatever the number of query heads.
 //   select  top-N over the blocks of a KV head, or over all (KV head, block) pairs of a sequence (Eq. 6
-//           counts its budget over the H KV heads), up to 8192 of them by the workgroup that is the last of its KV head (or
-//           sequence) to have stored its scores: radix select over keys in registers, then one ordered
-//           compaction.
+//           counts its budget over the H KV heads), by the workgroup that is the last of its KV head
+//           (or sequence) to have stored its scores, or in a launch of its own (selection_of): radix select over
+//           keys in registers, then one ordered compaction.
 //
 // What bounds it: latency.  The summaries are a few MB; the rest is a chain of launch, query, scores, exchange,
 // three or four radix digits of one barrier each, compaction.  128 blocks per workgroup, so that many compute
@@ -28,11 +28,13 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kBlocksPerPass = kThreads / kScoreLanes;
-constexpr int kPasses = 1;             // blocks per lane group
+constexpr int kScoreThreads = 256;     // of a launch that only scores
+constexpr int kScorePasses = 4;        // its blocks per lane group
+constexpr int kBlocksPerGroup = kThreads / kScoreLanes;   // blocks per workgroup that scores
+static_assert(kScorePasses * kScoreThreads == kThreads, "the same blocks per workgroup");
 constexpr int kHeadsPerRound = 8;      // query heads staged in LDS at a time
 constexpr int kKeys = 8;               // keys per thread of a selection in the launch that scores
-constexpr int kManyKeys = 32;          // ... of one in a launch of its own
+constexpr int kManyKeys = 32;          // the most in a launch of its own
 constexpr int kMaxHeads = 256;         // KV heads of one selection
 
 __device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -69,8 +71,8 @@ struct Counts {
 };
 // (With many keys per thread, the adds to the few bins that most scores share are what a digit takes: 32 768 pairs
 // 55.4 us a retrieval with one copy, 51.7 with two, 49.8 with four, 49.6 with eight.)
-template <int KEYS>
-struct Scratch : Counts<KEYS <= 8 ? 1 : 4> {
+template <int KEYS, int COPIES>
+struct Scratch : Counts<COPIES> {
   uint32_t seg[KEYS * kWaves];           // larger keys (low half) and equal keys of 64 consecutive keys
   uint32_t head_rank[kMaxHeads + 1];     // kept pairs in front of a head's first
   int32_t sel[kMaxGatherBlocks];         // kept block ids, for the gather list
@@ -220,45 +222,162 @@ __device__ __forceinline__ uint32_t threshold_of(const uint32_t (&key)[KEYS], Co
   return low + prefix;
 }
 
-// What is selected from: `heads` KV heads from h0 on of sequence b, nb blocks each.  Pair i = h * nb + j is block j of
-// head h0 + h; thread t holds the keys of pairs t, t + 1024, ...
-struct Pairs {
-  int b, h0, heads, nb, L, N;
-  uint32_t per_nb;                       // 2^32 / nb, rounded up: i / nb == (i * per_nb) >> 32 (exact: i, nb <= 32768)
-  __device__ __forceinline__ Pairs(const VariantParams& p, int b_, int h, int L_, int nb_)
-      : b(b_), h0(p.all_heads ? 0 : h), heads(p.all_heads ? p.Hkv : 1), nb(nb_), L(L_), N(heads * nb_),
-        per_nb(nb_ > 1 ? 0xffffffffu / (uint32_t)nb_ + 1u : 0u) {}
-  __device__ __forceinline__ int head_of(int i) const { return heads == 1 ? 0 : (nb > 1 ? (int)__umulhi((uint32_t)i, per_nb) : i); }
-};
-// Keys of the scores in memory, all in flight at once.
-template <int KEYS>
-__device__ __forceinline__ void load_keys(const VariantParams& p, const Pairs& all, uint32_t (&key)[KEYS], int tid) {
-  const float* const from = p.scores + ((int64_t)all.b * p.Hkv + all.h0) * p.nb_max;
-  float v[KEYS];
-  int j[KEYS];
-#pragma unroll
-  for (int u = 0; u < KEYS; ++u) {
-    if (u * kThreads >= all.N) break;                    // (uniform)
-    const int i = min(u * kThreads + tid, all.N - 1), h = all.head_of(i);
-    j[u] = i - h * all.nb;
-    v[u] = __hip_atomic_load(from + (int64_t)h * p.nb_max + j[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-#pragma unroll
-  for (int u = 0; u < KEYS; ++u) {
-    if (u * kThreads >= all.N) break;
-    key[u] = (j[u] < p.n_sink || j[u] >= all.nb - p.n_local) ? kTopKey : score_key(v[u]);
-  }
-}
+// PART: what a launch does.  Scores and selection, by the workgroup that arrives last; or the one or the other.
+enum Part { kBoth, kScoresOnly, kSelectionOnly };
 
-__device__ __forceinline__ uint32_t pairs_kept(const VariantParams& p, int N) { return (uint32_t)min(N, p.all_heads ? p.n_total : p.k_blocks); }
+// The scores alone take four blocks per lane group of a quarter of the threads: as many bytes on their way with fewer
+// wavefronts, which pays where the workgroups come in rounds.  A selection alone, us per retrieval with the scores'
+// launch, against one that reads the scores again in every pass: one budget over 8 x 1025 pairs 36.7 -> 19.9,
+// 8 x 2048 41.4 -> 28.3, 8 x 4096 72.8 -> 46.9, 128 x 200 284 -> 45; per head, 8 heads of 9000 blocks 65 -> 23, of
+// 32 768 231 -> 61.
+// grid: (ceil(nb_max / 128), Hkv, B); the selection alone: (1, 1 for all heads or Hkv, B)
+template <typename QT, typename RT, int D, int RULE, int PART, int KEYS>
+__global__ __launch_bounds__(PART == kScoresOnly ? kScoreThreads : kThreads) void retrieve_kernel(VariantParams p) {
+  constexpr int kOwnThreads = PART == kScoresOnly ? kScoreThreads : kThreads;
+  constexpr int kPasses = PART == kScoresOnly ? kScorePasses : 1;      // blocks per lane group
+  constexpr int kBlocksPerPass = kOwnThreads / kScoreLanes;
+  constexpr int LPB = kScoreLanes;
+  constexpr int NCH = D / (4 * LPB);
+  constexpr bool MINMAX = RULE == kBoundMeanOfHeads || RULE == kBoundMaxOfHeads;
+  constexpr bool GMAX = RULE == kMaxOfHeads || RULE == kBoundMaxOfHeads;
+  constexpr int ROWS = MINMAX ? 2 : 1;
+  __shared__ __attribute__((aligned(16))) float qs[RULE == kMeanQuery ? 1 : kHeadsPerRound][D];
+  __shared__ uint32_t s_keys[kBlocksPerGroup];            // (one workgroup alone) the keys as they are formed
+  __shared__ __attribute__((aligned(16))) Scratch<KEYS, PART == kBoth ? 1 : 4> s_scratch;
+  __shared__ int s_last;
 
-// The selection by the whole workgroup, and all that is written of it.  sc->hist is zero and sc->head_rank is
-// keep_n up to [heads] (heads behind the last pair, an empty sequence: all), with a barrier since.
-template <int KEYS>
-__device__ __forceinline__ void select_kept(const VariantParams& p, const Pairs& all, uint32_t (&key)[KEYS], Scratch<KEYS>* sc, int tid, int lane,
-                                            int wave) {
-  const int N = all.N, heads = all.heads;
-  const uint32_t keep_n = pairs_kept(p, N);
+  const int b = blockIdx.z;
+  const int tid = threadIdx.x, sub = tid % LPB;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = p.Hq / p.Hkv;
+  auto* const sc = &s_scratch;
+  const bool alone = gridDim.x == 1 && (!p.all_heads || p.Hkv == 1);   // one workgroup scores all it selects from
+  int L, nb;
+  if constexpr (PART != kSelectionOnly) {
+    // All loads go out before anything waits.  Summaries unconditionally (rows past the sequence's last block
+    // exist in the buffer; their result is discarded).
+    const int h = blockIdx.y;
+    float4 r[kPasses][ROWS][NCH];
+    int jj[kPasses];
+    const QT* const q0 = static_cast<const QT*>(p.q) + ((int64_t)b * p.gamma * p.Hq + (int64_t)h * G) * D;
+    QueryHeads<QT> qh;
+    if constexpr (RULE == kMeanQuery) qh = load_query_heads<QT>(q0 + tid % D, G, D);
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) {
+      const int j = (blockIdx.x * kPasses + u) * kBlocksPerPass + tid / LPB;
+      jj[u] = j;
+      const RT* row = static_cast<const RT*>(p.summaries) + ((((int64_t)b * p.Hkv + h) * p.nb_max + min(j, p.nb_max - 1)) * ROWS) * D + sub * 4;
+#pragma unroll
+      for (int w = 0; w < ROWS; ++w)
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) r[u][w][i] = load4(row + w * D + i * 4 * LPB);
+    }
+    L = clamped_len(p.seq_lens, b, p.max_seq_len);
+    nb = (L + p.block_size - 1) / p.block_size;
+    if constexpr (PART == kBoth)
+      for (int i = tid; i < 4 * 256; i += kThreads) (&sc->hist[0][0])[i] = 0;
+
+    float acc[kPasses];
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u) acc[u] = GMAX ? -__builtin_inff() : 0.f;
+    if constexpr (RULE == kMeanQuery) {
+      if (tid < D) qs[0][tid] = mean_query_channel<QT>(qh, q0 + tid % D, G, D);
+      __syncthreads();
+      float4 qv[NCH];
+#pragma unroll
+      for (int i = 0; i < NCH; ++i) qv[i] = *reinterpret_cast<const float4*>(&qs[0][sub * 4 + i * 4 * LPB]);
+#pragma unroll
+      for (int u = 0; u < kPasses; ++u) acc[u] = block_score<NCH>(r[u][0], qv);
+    } else {
+      for (int g0 = 0; g0 < G; g0 += kHeadsPerRound) {
+        const int ng = min(kHeadsPerRound, G - g0);
+        if (g0 > 0) __syncthreads();                      // the round before has been read
+        for (int idx = tid; idx < ng * D; idx += kOwnThreads) (&qs[0][0])[idx] = query_value(q0[(int64_t)g0 * D + idx]);
+        __syncthreads();
+        for (int g = 0; g < ng; ++g) {
+          float4 qv[NCH];
+#pragma unroll
+          for (int i = 0; i < NCH; ++i) qv[i] = *reinterpret_cast<const float4*>(&qs[g][sub * 4 + i * 4 * LPB]);
+#pragma unroll
+          for (int u = 0; u < kPasses; ++u) {
+            float s;
+            if constexpr (MINMAX) s = bound_score<NCH>(r[u][0], r[u][ROWS - 1], qv);
+            else s = block_score<NCH>(r[u][0], qv);
+            acc[u] = GMAX ? fmaxf(acc[u], s) : acc[u] + s;
+          }
+        }
+      }
+      if constexpr (!GMAX) {
+#pragma unroll
+        for (int u = 0; u < kPasses; ++u) acc[u] = acc[u] / (float)G;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kPasses; ++u)
+      if (sub == 0 && jj[u] < p.nb_max) {
+        const float v = jj[u] < nb ? acc[u] + 0.0f : 0.0f;
+        float* const to = p.scores + ((int64_t)b * p.Hkv + h) * p.nb_max + jj[u];
+        if constexpr (PART == kScoresOnly) {
+          *to = v;
+          continue;
+        }
+        // (write-through: the workgroup that selects may run on another XCD)
+        __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (alone) s_keys[jj[u]] = (jj[u] < p.n_sink || jj[u] >= nb - p.n_local) ? kTopKey : score_key(v);
+      }
+  } else {
+    L = clamped_len(p.seq_lens, b, p.max_seq_len);
+    nb = (L + p.block_size - 1) / p.block_size;
+    for (int i = tid; i < (int)(sizeof(sc->hist) / 4); i += kThreads) (&sc->hist[0][0])[i] = 0;
+  }
+  if constexpr (PART == kScoresOnly) return;
+
+  // ---- the last workgroup of the KV head (or of the sequence) selects ----
+  const int h0 = p.all_heads ? 0 : blockIdx.y, heads = p.all_heads ? p.Hkv : 1;
+  const int N = heads * nb;
+  // head of pair i: a multiplication by 2^32 / nb, rounded up (exact: i, nb <= 32768)
+  const uint32_t per_nb = nb > 1 ? 0xffffffffu / (uint32_t)nb + 1u : 0u;
+  auto head_of = [&](int i) { return heads == 1 ? 0 : (nb > 1 ? (int)__umulhi((uint32_t)i, per_nb) : i); };
+  uint32_t key[KEYS];
+  if constexpr (PART == kBoth) {
+#pragma unroll
+    for (int u = 0; u < KEYS; ++u) key[u] = 0u;
+  }
+  if (PART == kSelectionOnly || !alone) {
+    if constexpr (PART == kBoth) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's scores have been acknowledged
+      __syncthreads();
+      if (tid == 0) {
+        uint64_t* const arrivals = p.tickets + ((int64_t)b * p.Hkv + h0) * kTicketWords + 2;
+        const uint64_t of = (uint64_t)gridDim.x * heads;
+        const uint64_t prev = __hip_atomic_fetch_add(arrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = prev == of - 1;
+        if (s_last) __hip_atomic_store(arrivals, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      if (!s_last) return;
+    }
+    // scores of pair i = h * nb + j, all in flight at once
+    const float* const from = p.scores + ((int64_t)b * p.Hkv + h0) * p.nb_max;
+    float v[KEYS];
+    int j[KEYS];
+#pragma unroll
+    for (int u = 0; u < KEYS; ++u) {
+      if (u * kThreads >= N) break;                      // (uniform)
+      const int i = min(u * kThreads + tid, N - 1), h = head_of(i);
+      j[u] = i - h * nb;
+      v[u] = __hip_atomic_load(from + (int64_t)h * p.nb_max + j[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int u = 0; u < KEYS; ++u) {
+      if (u * kThreads >= N) continue;
+      key[u] = (j[u] < p.n_sink || j[u] >= nb - p.n_local) ? kTopKey : score_key(v[u]);
+    }
+  }
+  const uint32_t keep_n = (uint32_t)min(N, p.all_heads ? p.n_total : p.k_blocks);
+  if (tid <= heads) sc->head_rank[tid] = keep_n;          // heads behind the last pair (an empty sequence: all)
+  __syncthreads();
+  if (PART == kBoth && alone && tid < N) key[0] = s_keys[tid];
   uint32_t need = 0, tau = kTopKey;
   if (keep_n > 0)
     tau = N <= kThreads ? threshold_of(key[0], sc, N, keep_n, tid, lane, need) : threshold_of<KEYS>(key, sc, N, keep_n, tid, lane, wave, need);
@@ -312,39 +431,39 @@ __device__ __forceinline__ void select_kept(const VariantParams& p, const Pairs&
       keep |= ((eq >> lane) & 1ull) && eq_before < need;
     }
     if (keep) kept |= 1u << u;
-    const int i = u * kThreads + tid, h = all.head_of(i);
-    if (heads > 1 && i < N && i == h * all.nb) sc->head_rank[h] = rank[u];
+    const int i = u * kThreads + tid, h = head_of(i);
+    if (heads > 1 && i < N && i == h * nb) sc->head_rank[h] = rank[u];
   }
   if (heads > 1) __syncthreads();
-  int32_t* const out = p.sel_idx + ((int64_t)all.b * p.Hkv + all.h0) * p.k_blocks;
+  int32_t* const out = p.sel_idx + ((int64_t)b * p.Hkv + h0) * p.k_blocks;
 #pragma unroll
   for (int u = 0; u < KEYS; ++u) {
     if (u * kThreads >= N) break;
     if (!((kept >> u) & 1u)) continue;
-    const int i = u * kThreads + tid, h = all.head_of(i);
+    const int i = u * kThreads + tid, h = head_of(i);
     const uint32_t pos = heads == 1 ? rank[u] : rank[u] - sc->head_rank[h];
-    if (pos < (uint32_t)p.k_blocks) out[(int64_t)h * p.k_blocks + pos] = i - h * all.nb;
+    if (pos < (uint32_t)p.k_blocks) out[(int64_t)h * p.k_blocks + pos] = i - h * nb;
     if (heads == 1 && pos < (uint32_t)kMaxGatherBlocks) sc->sel[pos] = i;
   }
   for (int h = wave; h < heads; h += kWaves) {
     const int cnt = heads == 1 ? (int)keep_n : min((int)(sc->head_rank[h + 1] - sc->head_rank[h]), p.k_blocks);
     for (int i = cnt + lane; i < p.k_blocks; i += 64) out[(int64_t)h * p.k_blocks + i] = -1;
-    if (lane == 0) p.sel_cnt[(int64_t)all.b * p.Hkv + all.h0 + h] = cnt;
+    if (lane == 0) p.sel_cnt[(int64_t)b * p.Hkv + h0 + h] = cnt;
   }
   // Gather list: where the K row of every fourth selected-token slot sits in the pool, and how many of its
   // four slots hold a real token (block and page sizes are multiples of four, so the four slots share a block
   // and a page).
   if (p.gather) {                                        // (one KV head at a time)
     __syncthreads();
-    uint64_t* const gl = p.gather + ((int64_t)all.b * p.Hkv + all.h0) * p.gather_groups;
+    uint64_t* const gl = p.gather + ((int64_t)b * p.Hkv + h0) * p.gather_groups;
     for (int e = tid; e < p.gather_groups; e += kThreads) {
       const int slot0 = 4 * e, bi = slot0 / p.block_size;
       uint64_t entry = 0;
       if (bi < (int)keep_n) {
         const int tok0 = sc->sel[bi] * p.block_size + (slot0 - bi * p.block_size);
-        const int nv = min(max(all.L - tok0, 0), 4);
+        const int nv = min(max(L - tok0, 0), 4);
         if (nv > 0) {
-          const int64_t off = (token_offset(p.kv, p.table, all.b, tok0) + (int64_t)all.h0 * p.kv.stride_head) * 2;
+          const int64_t off = (token_offset(p.kv, p.table, b, tok0) + (int64_t)h0 * p.kv.stride_head) * 2;
           entry = ((uint64_t)off & kGatherOffsetMask) | ((uint64_t)nv << kGatherCountShift);
         }
       }
@@ -353,156 +472,28 @@ __device__ __forceinline__ void select_kept(const VariantParams& p, const Pairs&
   }
 }
 
-// grid: (ceil(nb_max / 128), Hkv, B)
 template <typename QT, typename RT, int D, int RULE>
-__global__ __launch_bounds__(kThreads) void retrieve_kernel(VariantParams p) {
-  constexpr int LPB = kScoreLanes;
-  constexpr int NCH = D / (4 * LPB);
-  constexpr bool MINMAX = RULE == kBoundMeanOfHeads || RULE == kBoundMaxOfHeads;
-  constexpr bool GMAX = RULE == kMaxOfHeads || RULE == kBoundMaxOfHeads;
-  constexpr int ROWS = MINMAX ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) float qs[RULE == kMeanQuery ? 1 : kHeadsPerRound][D];
-  __shared__ uint32_t s_keys[kPasses * kBlocksPerPass];   // (one workgroup alone) the keys as they are formed
-  __shared__ __attribute__((aligned(16))) Scratch<kKeys> s_scratch;
-  __shared__ int s_last;
-
-  const int b = blockIdx.z;
-  const int tid = threadIdx.x, sub = tid % LPB;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int G = p.Hq / p.Hkv;
-  Scratch<kKeys>* const sc = &s_scratch;
-  const bool alone = gridDim.x == 1 && (!p.all_heads || p.Hkv == 1);   // one workgroup scores all it selects from
-  int L, nb;
-  {
-    // All loads go out before anything waits.  Summaries unconditionally (rows past the sequence's last block
-    // exist in the buffer; their result is discarded).
-    const int h = blockIdx.y;
-    float4 r[kPasses][ROWS][NCH];
-    int jj[kPasses];
-    const QT* const q0 = static_cast<const QT*>(p.q) + ((int64_t)b * p.gamma * p.Hq + (int64_t)h * G) * D;
-    QueryHeads<QT> qh;
-    if constexpr (RULE == kMeanQuery) qh = load_query_heads<QT>(q0 + tid % D, G, D);
-#pragma unroll
-    for (int u = 0; u < kPasses; ++u) {
-      const int j = (blockIdx.x * kPasses + u) * kBlocksPerPass + tid / LPB;
-      jj[u] = j;
-      const RT* row = static_cast<const RT*>(p.summaries) + ((((int64_t)b * p.Hkv + h) * p.nb_max + min(j, p.nb_max - 1)) * ROWS) * D + sub * 4;
-#pragma unroll
-      for (int w = 0; w < ROWS; ++w)
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) r[u][w][i] = load4(row + w * D + i * 4 * LPB);
-    }
-    L = clamped_len(p.seq_lens, b, p.max_seq_len);
-    nb = (L + p.block_size - 1) / p.block_size;
-    for (int i = tid; i < 4 * 256; i += kThreads) (&sc->hist[0][0])[i] = 0;
-
-    float acc[kPasses];
-#pragma unroll
-    for (int u = 0; u < kPasses; ++u) acc[u] = GMAX ? -__builtin_inff() : 0.f;
-    if constexpr (RULE == kMeanQuery) {
-      if (tid < D) qs[0][tid] = mean_query_channel<QT>(qh, q0 + tid % D, G, D);
-      __syncthreads();
-      float4 qv[NCH];
-#pragma unroll
-      for (int i = 0; i < NCH; ++i) qv[i] = *reinterpret_cast<const float4*>(&qs[0][sub * 4 + i * 4 * LPB]);
-#pragma unroll
-      for (int u = 0; u < kPasses; ++u) acc[u] = block_score<NCH>(r[u][0], qv);
-    } else {
-      for (int g0 = 0; g0 < G; g0 += kHeadsPerRound) {
-        const int ng = min(kHeadsPerRound, G - g0);
-        if (g0 > 0) __syncthreads();                      // the round before has been read
-        for (int idx = tid; idx < ng * D; idx += kThreads) (&qs[0][0])[idx] = query_value(q0[(int64_t)g0 * D + idx]);
-        __syncthreads();
-        for (int g = 0; g < ng; ++g) {
-          float4 qv[NCH];
-#pragma unroll
-          for (int i = 0; i < NCH; ++i) qv[i] = *reinterpret_cast<const float4*>(&qs[g][sub * 4 + i * 4 * LPB]);
-#pragma unroll
-          for (int u = 0; u < kPasses; ++u) {
-            float s;
-            if constexpr (MINMAX) s = bound_score<NCH>(r[u][0], r[u][ROWS - 1], qv);
-            else s = block_score<NCH>(r[u][0], qv);
-            acc[u] = GMAX ? fmaxf(acc[u], s) : acc[u] + s;
-          }
-        }
-      }
-      if constexpr (!GMAX) {
-#pragma unroll
-        for (int u = 0; u < kPasses; ++u) acc[u] = acc[u] / (float)G;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kPasses; ++u)
-      if (sub == 0 && jj[u] < p.nb_max) {
-        const float v = jj[u] < nb ? acc[u] + 0.0f : 0.0f;
-        // (write-through: the workgroup that selects may run on another XCD)
-        __hip_atomic_store(p.scores + ((int64_t)b * p.Hkv + h) * p.nb_max + jj[u], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (alone) s_keys[jj[u]] = (jj[u] < p.n_sink || jj[u] >= nb - p.n_local) ? kTopKey : score_key(v);
-      }
-  }
-  if (!p.tickets) return;                                // the scores alone
-
-  // ---- the last workgroup of the KV head (or of the sequence) selects ----
-  const Pairs all(p, b, blockIdx.y, L, nb);
-  uint32_t key[kKeys];
-#pragma unroll
-  for (int u = 0; u < kKeys; ++u) key[u] = 0u;
-  if (!alone) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's scores have been acknowledged
-    __syncthreads();
-    if (tid == 0) {
-      uint64_t* const arrivals = p.tickets + ((int64_t)b * p.Hkv + all.h0) * kTicketWords + 2;
-      const uint64_t of = (uint64_t)gridDim.x * all.heads;
-      const uint64_t prev = __hip_atomic_fetch_add(arrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = prev == of - 1;
-      if (s_last) __hip_atomic_store(arrivals, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!s_last) return;
-    load_keys<kKeys>(p, all, key, tid);
-  }
-  if (tid <= all.heads) sc->head_rank[tid] = pairs_kept(p, all.N);
-  __syncthreads();
-  if (alone && tid < all.N) key[0] = s_keys[tid];
-  select_kept<kKeys>(p, all, key, sc, tid, lane, wave);
+void launch_kernel(const VariantParams& p, bool select, hipStream_t st) {
+  const dim3 grid((p.nb_max + kBlocksPerGroup - 1) / kBlocksPerGroup, p.Hkv, p.B);
+  if (select) hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, RULE, kBoth, kKeys>), grid, dim3(kThreads), 0, st, p);
+  else hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, RULE, kScoresOnly, kKeys>), grid, dim3(kScoreThreads), 0, st, p);
 }
-
-// The selection in a launch of its own, over scores in memory: pairs that do not fit the registers of the kernel
-// above (whose 8 keys per thread leave room for two workgroups on a compute unit).  us per retrieval with the scores'
-// launch, against a selection that reads the scores again in every pass: one budget over 8 x 1025 pairs 36.7 -> 19.9,
-// 8 x 2048 41.4 -> 28.3, 8 x 4096 72.8 -> 46.9, 128 x 200 284 -> 45; per head, 8 heads of 9000 blocks 65 -> 23, of
-// 32 768 231 -> 61.
-// grid: (1, B) or (Hkv, B)
-__global__ __launch_bounds__(kThreads) void select_kept_kernel(VariantParams p) {
-  __shared__ __attribute__((aligned(16))) Scratch<kManyKeys> s_scratch;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int L = clamped_len(p.seq_lens, blockIdx.y, p.max_seq_len);
-  const Pairs all(p, blockIdx.y, blockIdx.x, L, (L + p.block_size - 1) / p.block_size);
-  uint32_t key[kManyKeys];
-  for (int i = tid; i < (int)(sizeof(s_scratch.hist) / 4); i += kThreads) (&s_scratch.hist[0][0])[i] = 0;
-  if (tid <= all.heads) s_scratch.head_rank[tid] = pairs_kept(p, all.N);
-  load_keys<kManyKeys>(p, all, key, tid);
-  __syncthreads();
-  select_kept<kManyKeys>(p, all, key, &s_scratch, tid, lane, wave);
-}
-
 template <typename QT, typename RT, int D>
-void launch_rule(const VariantParams& p, hipStream_t st) {
-  const dim3 grid((p.nb_max + kPasses * kBlocksPerPass - 1) / (kPasses * kBlocksPerPass), p.Hkv, p.B);
+void launch_rule(const VariantParams& p, bool select, hipStream_t st) {
   if (p.minmax) {
-    if (p.group_max) hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, kBoundMaxOfHeads>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, kBoundMeanOfHeads>), grid, dim3(kThreads), 0, st, p);
+    if (p.group_max) launch_kernel<QT, RT, D, kBoundMaxOfHeads>(p, select, st);
+    else launch_kernel<QT, RT, D, kBoundMeanOfHeads>(p, select, st);
   } else if (p.mean_query) {                               // (fp32 summaries)
-    hipLaunchKernelGGL((retrieve_kernel<QT, float, D, kMeanQuery>), grid, dim3(kThreads), 0, st, p);
+    launch_kernel<QT, float, D, kMeanQuery>(p, select, st);
   } else {
-    if (p.group_max) hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, kMaxOfHeads>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((retrieve_kernel<QT, RT, D, kMeanOfHeads>), grid, dim3(kThreads), 0, st, p);
+    if (p.group_max) launch_kernel<QT, RT, D, kMaxOfHeads>(p, select, st);
+    else launch_kernel<QT, RT, D, kMeanOfHeads>(p, select, st);
   }
 }
 template <typename QT, typename RT>
-void launch_d(const VariantParams& p, hipStream_t st) {
-  if (p.d == 64) launch_rule<QT, RT, 64>(p, st);
-  else launch_rule<QT, RT, 128>(p, st);
+void launch_d(const VariantParams& p, bool select, hipStream_t st) {
+  if (p.d == 64) launch_rule<QT, RT, 64>(p, select, st);
+  else launch_rule<QT, RT, 128>(p, select, st);
 }
 
 // ---- more pairs than a workgroup's registers hold ------------------------------------------------
@@ -613,25 +604,40 @@ __global__ __launch_bounds__(kGThreads) void select_global_kernel(VariantParams 
 
 }  // namespace
 
-Selection selection_of(int heads, int nb_max) {
-  const int64_t pairs = (int64_t)heads * nb_max;
-  if (heads > kMaxHeads || pairs > kManyKeys * kThreads) return kSelectRereads;
-  return pairs <= kKeys * kThreads ? kSelectWithScores : kSelectFromRegisters;
+// Scores and selection in one launch where the keys fit its workgroups and these are all resident at once, one for
+// each compute unit (two where they have nothing to wait for).  In rounds, wavefronts that have stored their scores hold
+// places until their workgroup has been counted: us of one launch and of two,
+//   256 workgroups: 32 heads of 1024 blocks 7.6 and 8.9, 8 heads of 4096 11.5 and 12.4; of one chunk: 5.9 and 8.0
+//   512: 64 heads of 1024 13.1 and 9.9, one budget over 16 x (8 x 512) 18.8 and 14.3; of one chunk: 512 heads 9.8 and 12.0
+//   1024: 256 heads of 512 24.5 and 17.1, 64 of 2048 30.0 and 19.4;  4096: 64 heads of 8192 122 and 56
+// More than 256 selections of few keys are the small workgroups of select_kernel (2048 keys in registers): 1024 heads of
+// 256 blocks 28 against 35 us here, 512 of 512 28.6 and 29.5, of 2048 113 and 111, of 4096 218 and 205.
+Selection selection_of(const VariantParams& p) {
+  const int heads = p.all_heads ? p.Hkv : 1;
+  const int64_t pairs = (int64_t)heads * p.nb_max, chunks = (p.nb_max + kBlocksPerGroup - 1) / kBlocksPerGroup;
+  if (heads > kMaxHeads || pairs > kManyKeys * kThreads) return kSelectFromMemory;
+  if (pairs <= kKeys * kThreads && chunks * p.Hkv * p.B <= (chunks * heads == 1 ? 512 : 256)) return kSelectWithScores;
+  return !p.all_heads && (int64_t)p.B * p.Hkv > 256 && p.nb_max <= 2048 ? kSelectFromMemory : kSelectFromRegisters;
 }
 
-hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st) {
+// The scores, and with `select` (kSelectWithScores) what is kept.
+hipError_t launch_retrieve(const VariantParams& p, int dtype, bool select, hipStream_t st) {
   if (dtype == SVF_F32) {
-    if (p.summary_bf16) launch_d<float, __hip_bfloat16>(p, st);
-    else launch_d<float, float>(p, st);
+    if (p.summary_bf16) launch_d<float, __hip_bfloat16>(p, select, st);
+    else launch_d<float, float>(p, select, st);
   } else {
-    if (p.summary_bf16) launch_d<__hip_bfloat16, __hip_bfloat16>(p, st);
-    else launch_d<__hip_bfloat16, float>(p, st);
+    if (p.summary_bf16) launch_d<__hip_bfloat16, __hip_bfloat16>(p, select, st);
+    else launch_d<__hip_bfloat16, float>(p, select, st);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_select_kept(const VariantParams& p, hipStream_t st) {
-  hipLaunchKernelGGL(select_kept_kernel, dim3(p.all_heads ? 1 : p.Hkv, p.B), dim3(kThreads), 0, st, p);
+  const int heads = p.all_heads ? p.Hkv : 1;
+  const dim3 grid(1, p.Hkv / heads, p.B);
+  if ((int64_t)heads * p.nb_max <= kKeys * kThreads)       // (types and rule are the scores')
+    hipLaunchKernelGGL((retrieve_kernel<float, float, 64, kMeanQuery, kSelectionOnly, kKeys>), grid, dim3(kThreads), 0, st, p);
+  else hipLaunchKernelGGL((retrieve_kernel<float, float, 64, kMeanQuery, kSelectionOnly, kManyKeys>), grid, dim3(kThreads), 0, st, p);
   return hipGetLastError();
 }
 

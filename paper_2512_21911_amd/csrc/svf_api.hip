@@ -316,14 +316,12 @@ static VariantParams retrieval_params(const svf_shape_t& s, const AttnPlan& pl, 
   return v;
 }
 
-// One launch, or, where there are more keys than the scoring workgroups have registers for, the scores and then the
-// selection.
-static int retrieve(VariantParams v, int dtype, hipStream_t st) {
-  const Selection how = selection_of(v.all_heads ? v.Hkv : 1, v.nb_max);
-  if (how == kSelectWithScores) return hip_code(launch_retrieve(v, dtype, st));
-  v.tickets = nullptr;
-  const hipError_t e = launch_retrieve(v, dtype, st);
+// One launch, or the scores and then the selection.
+static int retrieve(const VariantParams& v, int dtype, hipStream_t st) {
+  const Selection how = selection_of(v);
+  const hipError_t e = launch_retrieve(v, dtype, how == kSelectWithScores, st);
   if (e != hipSuccess) return SVF_ERR_HIP;
+  if (how == kSelectWithScores) return SVF_OK;
   if (how == kSelectFromRegisters) return hip_code(launch_select_kept(v, st));
   if (v.all_heads) return hip_code(launch_select_global(v, st));
   SelectParams p{};

@@ -234,18 +234,18 @@ struct VariantParams {
   int32_t minmax, summary_bf16, group_max, n_total;
   int32_t mean_query;       // the main path's rule: one query, the mean over the query heads
   int32_t all_heads;        // one selection of n_total pairs per sequence instead of k_blocks per KV head
-  uint64_t* tickets;        // AttnParams::tickets (the counter of a group's first word of its kind); NULL: the scores alone
+  uint64_t* tickets;        // AttnParams::tickets (the counter of a group's first word of its kind)
   // optional gather list (per KV head only; NULL: none) and the cache addressing it needs
   uint64_t* gather;
   const int32_t* table;
   KvLayout kv;
   int32_t gather_groups;
 };
-// How one workgroup selects among this many KV heads' blocks: in the launch that scores, its keys in
-// registers; in a launch of its own, the same; reading the scores again in every pass.
-enum Selection { kSelectWithScores, kSelectFromRegisters, kSelectRereads };
-Selection selection_of(int heads, int nb_max);
-hipError_t launch_retrieve(const VariantParams& p, int dtype, hipStream_t st);
+// How the kept blocks are selected: in the launch that scores, the keys in registers; in a launch of its own, the
+// same; in one that reads the scores of the keys it has no registers for again in every pass.
+enum Selection { kSelectWithScores, kSelectFromRegisters, kSelectFromMemory };
+Selection selection_of(const VariantParams& p);
+hipError_t launch_retrieve(const VariantParams& p, int dtype, bool select, hipStream_t st);
 hipError_t launch_select_kept(const VariantParams& p, hipStream_t st);
 hipError_t launch_select_global(const VariantParams& p, hipStream_t st);
 hipError_t launch_select_only(const SelectParams& p, hipStream_t st);

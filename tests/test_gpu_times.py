@@ -50,3 +50,8 @@ def test_one_budget_over_an_eighth_more_pairs():
     """8192 pairs are selected from in the launch that scores, 9216 behind it.  (16 and 21 us a call; 37 where
     the scores are read again in every pass.)"""
     assert us_per_retrieval(1, 8, 1152, 256) < 1.7 * us_per_retrieval(1, 8, 1024, 256)
+
+
+def test_retrieval_of_eight_times_the_heads():
+    """256 workgroups score and select in one launch, 2048 only score.  (9 and 30 us a call; 57 in one launch.)"""
+    assert us_per_retrieval(16, 8, 2048) < 4.5 * us_per_retrieval(2, 8, 2048)
