@@ -14,6 +14,8 @@
 //                 a scan of the chunk sums, and a walk of the one chunk the target falls in.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "svf.h"
 #include "svf_rules.h"
 
@@ -22,33 +24,43 @@ namespace {
 // The kernel is a chain: launch, one round trip for weights and thresholds, some hundred dependent
 // instructions.  Hence small workgroups, everything requested at once, loops of a length known at
 // compile time, and broadcasts inside a row of sixteen lanes by an operand modifier (a shuffle is a
-// trip through LDS).  256 tokens of 8, 16, 32 experts: 2.3, 2.5, 3.5 us a call (2.0 is an empty launch),
-// against 2.7, 3.3, 4.5 with 32 lanes per token, loops of run-time length, the sorted weights in LDS, and the
-// thresholds loaded behind the sums; 65 536 tokens of 8: 6.1 against 8.7 us.
+// trip through LDS).  256 tokens of 8, 16, 17, 32 experts: 2.3, 2.5, 2.8, 3.2 us a call (2.0 is an empty launch),
+// against 2.7, 3.3, 3.4, 4.5 with 32 lanes per token, loops of run-time length, the sorted weights in LDS, and the
+// thresholds loaded behind the sums; 65 536 tokens: 6.0, 6.6, 12.2, 16.3 against 8.8, 12.7, 13.2, 20.7 us (24.4 for 17
+// and 32 experts with shuffles in loops of 32).
 constexpr int kMoeThreads = 64;
 
-// Lane L of a token's lanes, to all of them (LANES = 16: a row of the wavefront).
-template <int LANES, int L>
-__device__ __forceinline__ float token_lane(float x) {
-  if constexpr (LANES == 16)
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, true));   // row_newbcast:L
-  else
-    return __shfl(x, ((int)threadIdx.x & ~(LANES - 1)) + L, 64);
-}
+// A value per lane of a token's 16 or 32 lanes, each of which can be had in all of them: 16 lanes are a row of the
+// wavefront; of 32, both rows hold the first row's values and the second row's.
+template <int LANES>
+struct TokenLanes {
+  float low, high;
+  __device__ __forceinline__ explicit TokenLanes(float x) : low(x), high(x) {
+    if constexpr (LANES == 32) {                         // (odd rows of the one against even rows of the other)
+      const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      low = __uint_as_float(rows[0]);
+      high = __uint_as_float(rows[1]);
+    }
+  }
+  template <int L>
+  __device__ __forceinline__ float lane() const {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(L < 16 ? low : high), 0x150 + (L & 15), 0xf, 0xf, true));   // row_newbcast
+  }
+};
 
-// Weights of lanes 0 .. L that come before lane j's in ascending order (equal weights: by position).
+// Weights of lanes 0 .. L that come before lane j's, w, in ascending order (equal weights: by position).
 template <int LANES, int L>
-__device__ __forceinline__ int rank_upto(float w, int j) {
-  const float o = token_lane<LANES, L>(w);
+__device__ __forceinline__ int rank_upto(const TokenLanes<LANES>& all, float w, int j) {
+  const float o = all.template lane<L>();
   const int r = (o < w || (o == w && L < j)) ? 1 : 0;
-  if constexpr (L > 0) return r + rank_upto<LANES, L - 1>(w, j);
+  if constexpr (L > 0) return r + rank_upto<LANES, L - 1>(all, w, j);
   else return r;
 }
 // total: sorted[0] + ... + sorted[L], added in that order; prefix: lane j's sum up to its own.
 template <int LANES, int L>
-__device__ __forceinline__ void sums_upto(float sorted, int j, float& prefix, float& total) {
+__device__ __forceinline__ void sums_upto(const TokenLanes<LANES>& sorted, int j, float& prefix, float& total) {
   if constexpr (L > 0) sums_upto<LANES, L - 1>(sorted, j, prefix, total);
-  total += token_lane<LANES, L>(sorted);
+  total += sorted.template lane<L>();
   if (L == j) prefix = total;
 }
 
@@ -63,13 +75,13 @@ struct MoeToken {
   float prefix, total;
   __device__ __forceinline__ MoeToken(float w, int j, int k) {
     const float mine = j < k ? w : INFINITY;
-    rank = rank_upto<kLanes, KMAX - 1>(mine, j);
+    rank = rank_upto<kLanes, KMAX - 1>(TokenLanes<kLanes>(mine), mine, j);
     // (a lane past KMAX counts KMAX at most and writes behind the k lanes that are read)
     const int to = ((int)threadIdx.x & ~(kLanes - 1)) + (j < KMAX ? rank : j);
     float sorted = __int_as_float(__builtin_amdgcn_ds_permute(4 * to, __float_as_int(mine)));
     if (j >= k) sorted = 0.f;
     prefix = total = 0.f;
-    sums_upto<kLanes, KMAX - 1>(sorted, j, prefix, total);
+    sums_upto<kLanes, KMAX - 1>(TokenLanes<kLanes>(sorted), j, prefix, total);
   }
 };
 
@@ -382,6 +394,15 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __rest
   if (lane == 0) { n_accepted[b] = n; resampled[b] = pick; }
 }
 
+// A kernel for k experts: the least KMAX that holds them (65 536 tokens of 17 experts: 16.5 us with KMAX = 32).
+template <typename Launch>
+void with_kmax(int k, Launch&& launch) {
+  if (k <= 8) launch(std::integral_constant<int, 8>());
+  else if (k <= 16) launch(std::integral_constant<int, 16>());
+  else if (k <= 20) launch(std::integral_constant<int, 20>());
+  else if (k <= 24) launch(std::integral_constant<int, 24>());
+  else launch(std::integral_constant<int, 32>());
+}
 template <int KMAX>
 dim3 moe_grid(int T) { return dim3((unsigned)((T + MoeToken<KMAX>::kPerWorkgroup - 1) / MoeToken<KMAX>::kPerWorkgroup)); }
 
@@ -397,9 +418,9 @@ int svf_moe_skip(const float* w, int32_t T, int32_t k, int32_t m, const float* b
   if (T < 1 || k < 2 || k > 32) return SVF_ERR_SHAPE;
   if (m < 1 || m >= k) return SVF_ERR_BUDGET;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (k <= 8) hipLaunchKernelGGL(moe_skip_kernel<8>, moe_grid<8>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
-  else if (k <= 16) hipLaunchKernelGGL(moe_skip_kernel<16>, moe_grid<16>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
-  else hipLaunchKernelGGL(moe_skip_kernel<32>, moe_grid<32>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
+  with_kmax(k, [&](auto kmax) {
+    hipLaunchKernelGGL(moe_skip_kernel<kmax>, moe_grid<kmax>(T), dim3(kMoeThreads), 0, st, w, T, k, m, beta, n_skip, keep_mask);
+  });
   return hipGetLastError() == hipSuccess ? SVF_OK : SVF_ERR_HIP;
 }
 
@@ -416,9 +437,9 @@ int svf_moe_calibrate(const float* w_cal, int32_t T, int32_t k, float* beta, voi
     return SVF_ERR_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* ratios = static_cast<float*>(ws);
-  if (k <= 8) hipLaunchKernelGGL(moe_ratios_kernel<8>, moe_grid<8>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
-  else if (k <= 16) hipLaunchKernelGGL(moe_ratios_kernel<16>, moe_grid<16>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
-  else hipLaunchKernelGGL(moe_ratios_kernel<32>, moe_grid<32>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
+  with_kmax(k, [&](auto kmax) {
+    hipLaunchKernelGGL(moe_ratios_kernel<kmax>, moe_grid<kmax>(T), dim3(kMoeThreads), 0, st, w_cal, T, k, ratios);
+  });
   if (hipGetLastError() != hipSuccess) return SVF_ERR_HIP;
   hipLaunchKernelGGL(moe_median_kernel, dim3(k - 1), dim3(256), 0, st, ratios, T, beta);
   return hipGetLastError() == hipSuccess ? SVF_OK : SVF_ERR_HIP;

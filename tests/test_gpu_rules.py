@@ -180,3 +180,21 @@ def test_targets_around_the_segments_of_the_scan(V):
     x["u_resample"] = torch.tensor([0.0, 0.5 * (cdf[1, last - 1] + cdf[1, last]) / cdf[1, -1],
                                     0.999 * cdf[2, last] / cdf[2, -1], 0.9999], dtype=torch.float32).clamp(max=0.9999999)
     check_accept(x)
+
+
+@pytest.mark.parametrize("k", [19, 20, 21, 24, 25])
+def test_skipping_at_the_kernels_of_32_lanes(k):
+    test_skipping_at_every_group_of_lanes(k)
+
+
+@pytest.mark.parametrize("k", [16, 17, 20, 24, 25, 32])
+def test_calibration_at_every_kernel(k):
+    """Thresholds of 7 and 64 tokens: the medians of the oracle's ratios.  (Sums of up to 32 fp32 values and a
+    division against fp64.)"""
+    g = torch.Generator().manual_seed(k)
+    for T in (7, 64):
+        w = torch.rand(T, k, generator=g) + 0.01
+        beta = torch.zeros(k - 1, device="cuda")
+        S.svf_moe_calibrate(w.cuda(), beta)
+        want = np.median(R.skip_ratios(w.numpy()), axis=0)
+        assert np.abs(beta.cpu().numpy() - want).max() <= 34 * 2 ** -24

@@ -55,3 +55,14 @@ def test_one_budget_over_an_eighth_more_pairs():
 def test_retrieval_of_eight_times_the_heads():
     """256 workgroups score and select in one launch, 2048 only score.  (9 and 30 us a call; 57 in one launch.)"""
     assert us_per_retrieval(16, 8, 2048) < 4.5 * us_per_retrieval(2, 8, 2048)
+
+
+def test_expert_skipping_of_one_expert_more():
+    """16 lanes per token up to 16 experts, 32 behind that.  (65 536 tokens: 6.5 us a call and, with
+    broadcasts through LDS, 24.)"""
+    def us(k):
+        w = torch.rand(65536, k, generator=torch.Generator().manual_seed(k)).cuda()
+        beta = torch.full((k - 1,), 0.5, device="cuda")
+        n, keep = (torch.zeros(65536, dtype=torch.int32, device="cuda") for _ in range(2))
+        return us_per_call(lambda: S.svf_moe_skip(w, 3, beta, n, keep))
+    assert us(17) < 2.5 * us(16)
