@@ -331,8 +331,6 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __rest
   __shared__ int sh_n, sh_again;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t seq = (int64_t)b * gamma;
-  const float u_r = u_resample[b];
-  for (int i = tid; i < kMaxChunks; i += kAccThreads) csum[i] = 0.f;
   if (wave == 0) {
     bool rejected = false;
     if (lane < gamma) {
@@ -356,6 +354,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_kernel(const float* __rest
   const int n_chunks = (V + kChunk - 1) / kChunk;
   const int cpw = (n_chunks + kAccWaves - 1) / kAccWaves;
   const int c_begin = wave * cpw, c_end = min(c_begin + cpw, n_chunks);
+  const float u_r = u_resample[b];
+  if (tid < (n_chunks + 127) / 128 * 128 - n_chunks) csum[n_chunks + tid] = 0.f;     // the rest of the scan's last segment
   sum_chunks<false>(pt, pd, V, c_begin, c_end, lane, csum);
   __syncthreads();
   // What is left is a chain of short steps, by one wavefront: handed from step to step through LDS and a
