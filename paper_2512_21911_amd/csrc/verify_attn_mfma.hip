@@ -1116,8 +1116,9 @@ struct TileInfo {
 // changed: the step modes must then add up in the same order, and the planned grid is the faster one.  To find
 // that out each wavefront looks at 32 pairs and leaves their tiles in LDS.  kLoadsFirst: while the planned pair's
 // front loads are on their way, which costs nothing where the counts are even (0.4 us per launch otherwise).
-// kPairsFirst: before any other load, where the plan has more workgroups than shares can be needed: if the
-// counts differ, the rest of them leave one after the other behind the others' work (0.5 - 0.9 us per launch sooner).
+// kPairsFirst: before any other load, where a plan that covers the compute units has more workgroups than shares can be
+// needed: if the counts differ, the rest of them leave, and nobody's loads wait for others that were not needed (0.5 - 1.1 us
+// per launch sooner, 0.2 later where the counts are even).
 // Even counts, svf_verify_attn of 4 x 8 pairs with 128 blocks of 64: 55.3 us by the kernel that knows the plan
 // only, 55.6 so; 68.3 with the grid laid out for the most shares there can be.
 // (4 sequences, 8 heads, 256 kept blocks of 64 among them, most of them in one or two heads: 63 us as
@@ -1144,9 +1145,13 @@ __device__ __forceinline__ void leave_pair_tiles(const AttnParams& p, int pairs,
   tiles[wave * 32 + lane] = wave * 32 + lane < pairs ? n | (uneven ? kUneven : 0) : 0;
 }
 // This workgroup's pair, its split and the pair's number of splits; false if it has no part.
-// The grid holds all shares: of W workgroups per row group, W - pairs (256 / row_groups at most) are shared
-// out.  Where a tile is then worth 1 / 32 of a share or more, a pair gets at most one split more than its share
+// The grid holds all shares: of W workgroups per row group all (256 / row_groups at most) are shared out, rounded down
+// for every pair; if what the short lists get in excess of their share (a split at least) makes that more than W, fewer, at
+// last W - pairs.
+// Where a tile is then worth 1 / 32 of a share or more, a pair gets at most one split more than its share
 // rounded down; where it is worth less, the least, ceil(tiles / 32) <= n_splits.
+// (W - pairs from the start, us per launch at D = 128, counts drawn about half of the plan's: 96 pairs of 1024 tokens 20.8 - 22.2
+// against 18.1 - 18.4 so, 48 of 2048 16.9 - 18.4 against 15.6 - 16.0, 28 of 4096 16.9 - 18.7 against 15.3 - 16.0.)
 __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs, int lane, int row_groups,
                                                  const int (&tiles)[kShareChunks], int& pair, int& split, int& S) {
   int total = 0;
@@ -1154,19 +1159,25 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
   for (int c = 0; c < kShareChunks; ++c)
     if (c * 64 < pairs) total += __builtin_amdgcn_readlane((int)wave_inclusive_sum((uint32_t)(tiles[c] & ~kUneven)), 63);
   const int id = blockIdx.y * gridDim.x + blockIdx.x;
-  const float per_tile = (float)min(256 / row_groups, (int)(gridDim.x * gridDim.y) - pairs) / (float)total;
+  const int W = gridDim.x * gridDim.y;
   int s[kShareChunks], incl[kShareChunks], shares = 0;
+#pragma unroll 1
+  for (int spare = 0;; spare = min(spare + (pairs + 3) / 4, pairs)) {
+    const float per_tile = (float)min(256 / row_groups, W - spare) / (float)total;
+    shares = 0;
 #pragma unroll
-  for (int c = 0; c < kShareChunks; ++c) {
-    s[c] = incl[c] = 0;
-    if (c * 64 < pairs) {
-      const int n = tiles[c] & ~kUneven;
-      const int most = min((n + kWaves - 1) / kWaves, p.split_stride);
-      const int least = (n + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
-      if (c * 64 + lane < pairs) s[c] = max(max(min((int)((float)n * per_tile), most), least), 1);
-      incl[c] = shares + (int)wave_inclusive_sum((uint32_t)s[c]);
-      shares = __builtin_amdgcn_readlane(incl[c], 63);
+    for (int c = 0; c < kShareChunks; ++c) {
+      s[c] = incl[c] = 0;
+      if (c * 64 < pairs) {
+        const int n = tiles[c] & ~kUneven;
+        const int most = min((n + kWaves - 1) / kWaves, p.split_stride);
+        const int least = (n + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
+        if (c * 64 + lane < pairs) s[c] = max(max(min((int)((float)n * per_tile), most), least), 1);
+        incl[c] = shares + (int)wave_inclusive_sum((uint32_t)s[c]);
+        shares = __builtin_amdgcn_readlane(incl[c], 63);
+      }
     }
+    if (shares <= W || spare == pairs) break;
   }
   const int per_xcd = (shares + kXcds - 1) / kXcds;
   const int mine = (id % kXcds) * per_xcd + id / kXcds;
@@ -1420,12 +1431,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       return;
     }
     if (SHARE == kPairsFirst || uneven) {
+      load_pair();                                       // (waited for first)
       const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
                                    (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
       if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
-      load_pair();
     }
     L = min(max(L, 0), p.max_seq_len);
     clear_draft_stage();
@@ -2553,7 +2564,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
   else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
-  else if (p.share_splits && (int64_t)grid.x * grid.y <= 256 / row_groups + pairs)
+  else if (p.share_splits && (int64_t)((255 + pairs * row_groups) / (pairs * row_groups)) * kXcds * grid.y <= 256 / row_groups + pairs)
     hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
   else if (p.share_splits)
     hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kPairsFirst>), grid, dim3(kThreads), 0, st, p, pairs);

@@ -104,3 +104,23 @@ def test_shared_out_splits_over_many_pairs(kw):
     run.out.fill_(float("nan"))
     run.verify_attn().sync()
     assert torch.equal(run.out.view(torch.int16), out.view(torch.int16))
+
+
+def test_shared_out_splits_that_do_not_fit_at_once():
+    """Many lists of one block beside a few full ones: a split for each of them is more than the grid holds beside the full
+    lists' shares of all of it, so fewer are shared out."""
+    cfg = small_bf16(B=12, Hq=32, Hkv=8, gamma=8, T=2100, k_blocks=32, block_size=32, page_size=16)
+    x = W.make_layer(cfg)
+    run = DeviceRun(cfg, to_gpu(x))
+    rng = np.random.default_rng(3)
+    idx = np.full((12, 8, 32), -1, dtype=np.int32)
+    for b in range(12):
+        for h in range(8):
+            c = 32 if (8 * b + h) % 3 == 0 else int(rng.integers(0, 2))
+            idx[b, h, :c] = np.sort(rng.choice(65, c, replace=False))
+    cnt = (idx >= 0).sum(-1).astype(np.int32)
+    idx, cnt = torch.from_numpy(idx), torch.from_numpy(cnt)
+    for _ in range(2):
+        run.out.fill_(float("nan"))
+        run.verify_attn(sel_idx=idx.cuda(), sel_cnt=cnt.cuda()).sync()
+    check_attn(cfg, run.out, run.lse, *oracle_attn(cfg, x, idx, cnt))
