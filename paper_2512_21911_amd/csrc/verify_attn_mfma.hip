@@ -2410,19 +2410,24 @@ bool mfma_supported(const svf_shape_t& s) {
 }
 
 // Splits of a group such that all workgroups of the launch are resident at once, if the least number of
-// splits `lo` allows that, else `want`.  Workgroups hold half of a compute unit's LDS or more (one per
-// compute unit at D = 128, two at D = 64), and all splits and groups of a pair go to one XCD of 32 compute
-// units: with 48 pairs in six splits an XCD gets 36 workgroups, and the four that wait for a free place cost a
+// splits `lo` allows that, else `want`.  A compute unit holds one workgroup: at D = 128 its LDS, at D = 64 its registers (144 - 150
+// vector registers make three wavefronts per SIMD, two workgroups would be four).  All splits and groups of a pair
+// go to one XCD of 32 compute units: with 48 pairs in six splits an XCD gets 36 workgroups, and the four that wait for a free place cost a
 // whole second round.  Fewer splits with another tile for some wavefronts cost far less.  us per reuse / anchor
 // launch at D = 128, `want` splits (256 compute units over the groups, rounded up) and as many as fit:
 //   24 pairs of 4096 tokens, 32 rows: 11 splits 25.5 / 37.6, 10 splits 16.7 / 19.0
 //   48 pairs of 1728 tokens, 32 rows: 6 splits 23.8 / 29.9, 5 splits 15.9 / 18.1; 92 rows: 27.3 / 35.8 and 17.7 / 21.3
 //   28 pairs of 1088 tokens, 64 rows: 5 splits 17.7 / 23.4, 4 splits 11.4 / 14.4
 //   96 pairs of 512 tokens, 64 rows: 2 splits 22.3 / 28.3, 1 split 12.0 / 14.9
-// (over 130 shapes of 1 - 112 pairs that did not fit: 1.2 - 4.5 times as fast, none slower; 1024 blocks scored by
+// and at D = 64:
+//   24 pairs of 4096 tokens, 32 rows: 11 splits 20.2 / 24.7, 10 splits 13.2 / 15.1
+//   48 pairs of 2048 tokens, 32 rows: 6 splits 20.6 / 26.1, 5 splits 13.0 / 14.8; 1728 tokens, 96 rows: 25.6 / 32.8 and 16.9 / 20.3
+//   28 pairs of 1088 tokens, 64 rows: 5 splits 15.6 / 20.5, 4 splits 10.1 / 12.2
+//   96 pairs of 512 tokens, 64 rows: 2 splits 21.3 / 26.4, 1 split 11.0 / 12.9
+// (D = 128, over 130 shapes of 1 - 112 pairs that did not fit: 1.2 - 4.5 times as fast, none slower; 1024 blocks scored by
 // one workgroup instead of two: 24.5 us instead of 42.0.)
 static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64_t want, int64_t lo) {
-  const int64_t places = s.d == 64 ? 64 : 32;            // workgroups that an XCD holds
+  const int64_t places = 32;                             // workgroups that an XCD holds
   const int64_t fit = places / (((int64_t)s.B * s.Hkv + kXcds - 1) / kXcds * groups_per_pair);
   return want > fit && fit >= lo && fit >= 1 ? fit : want;
 }

@@ -18,7 +18,11 @@ CASES = {
     "pairs_48_least_splits_do_not_fit": small(B=6, Hq=32, Hkv=8, gamma=10, T=2200, k_blocks=33, min_len=300),
     "rows_48_6_to_5": small(B=6, Hq=32, Hkv=8, gamma=20, tree_depth=5, T=600, k_blocks=8, min_len=100),
     "rows_1_pair_66_to_32": small(B=1, Hq=8, Hkv=1, gamma=12, T=2200, k_blocks=33),
-    "rows_3_pairs_d64_86_to_64": small(B=3, Hq=8, Hkv=1, d=64, gamma=12, T=4200, k_blocks=64),
+    "rows_3_pairs_d64_86_to_32": small(B=3, Hq=8, Hkv=1, d=64, gamma=12, T=4200, k_blocks=64),
+    "pairs_24_d64_11_to_10": small(B=3, Hq=8, Hkv=8, d=64, gamma=3, T=3000, k_blocks=44, min_len=900),
+    "pairs_20_d64_two_row_groups_7_to_5": small(B=5, Hq=16, Hkv=4, d=64, gamma=10, T=1800, k_blocks=27),
+    "pairs_80_d64_two_to_one": small(B=5, Hq=64, Hkv=16, d=64, gamma=9, T=600, k_blocks=8),
+    "rows_48_d64_6_to_5": small(B=6, Hq=32, Hkv=8, d=64, gamma=20, tree_depth=5, T=600, k_blocks=8, min_len=100),
 }
 
 
