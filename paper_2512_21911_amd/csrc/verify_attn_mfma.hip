@@ -2562,6 +2562,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
   const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits;
+  const int cover = (255 + pairs * row_groups) / (pairs * row_groups);       // splits that cover the compute units
 #define SVF_LAUNCH_ATTN(DIM, MODE)                                                                         \
   do {                                                                                                     \
     if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
@@ -2569,7 +2570,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
   else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
-  else if (p.share_splits && (int64_t)((255 + pairs * row_groups) / (pairs * row_groups)) * kXcds * grid.y <= 256 / row_groups + pairs)
+  else if (p.share_splits && (int64_t)(p.n_splits > cover ? p.n_splits : cover) * kXcds * grid.y <= 256 / row_groups + pairs)
     hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
   else if (p.share_splits)
     hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kPairsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
