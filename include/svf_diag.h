@@ -18,7 +18,8 @@ extern "C" {
 #endif
 
 #define SVF_KERNEL_AUTO 0        /* what svf_verify_attn would run                       */
-#define SVF_KERNEL_VECTOR_ALU 1  /* the fp32 kernel whatever the shape                   */
+#define SVF_KERNEL_VECTOR_ALU 1  /* the fp32 kernel whatever the shape (the name is older than
+                                    its matrix instructions, whose fp32 rate is the vector ALU's) */
 
 /* Workspace bytes svf_diag_verify_attn needs for `kernel` (>= svf_workspace_bytes; 0 if invalid). */
 size_t svf_diag_workspace_bytes(const svf_shape_t* shape, int kernel);

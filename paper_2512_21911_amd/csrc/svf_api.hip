@@ -110,7 +110,8 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   pl.split_stride = pl.n_splits;
   lay_out(s, pl);
   if (!pl.mfma && pl.bytes + scores_bytes(s) > kStaticScratchBytes) {
-    // fewer splits where that makes the workspace fit the static array
+    // fewer splits where that makes the workspace fit the static array (the block scores of some three to four million blocks
+    // leave little of it)
     const size_t per_split = pairs * pl.Mpad * (s.d + 2) * sizeof(float);
     const size_t others = pl.bytes + scores_bytes(s) - pl.n_splits * per_split;      // (with what aligning them added)
     if (others + per_split <= kStaticScratchBytes) {

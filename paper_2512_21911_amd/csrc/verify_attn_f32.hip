@@ -476,23 +476,27 @@ int64_t groups_of(const svf_shape_t& s) {
 }  // namespace
 
 // Splits per (sequence, KV head, row group).  A unit is a tile for sixteen rows; a workgroup has four SIMDs.
-// Eight splits are merged in one trip to memory (2 us with the exchange), so few units spread over eight
-// workgroups, or as many as there are tiles, rather than queue in one (also with sixteen wavefronts there);
-// four units are as fast in one workgroup.  Behind that a workgroup takes eight units, and the splits grow with the
-// square root once the trips of the merge cost what the units save.  Never more than one round of 256 workgroups: a
-// compute unit's registers hold one at a time, and a second round that is half full costs a whole one.  us per call,
+// Eight splits are merged in one trip to memory (2 us with the exchange), so the splits are a multiple of eight (or as
+// many as there are tiles), also for few units rather than let these queue in one workgroup (or in sixteen wavefronts
+// there); four units are as fast in one workgroup.  From 41 units on two trips pay, behind that the splits grow with
+// the square root.  Never more than 256 workgroups: a compute unit's registers hold one at a time at d = 128, and at
+// d = 64, where they hold two, a second one costs what its work saves; and where 16 splits would
+// fill the 256, 8 of them twice as long are the faster ones up to 80 units.  us per call,
 // d = 64 and d = 128: 9 units 7.4 / 8.4 (2 splits 8.1 / 9.2; one 9.1 / 11.1), 17 units 7.8 / 9.1 (16 splits 8.3 / 9.4),
-// 258 units (d = 128) 22.9 with 24 splits, 25.6 with 33; 2049 units 30.8 with 68, 45 with 257; 8 pairs of 1026 units 35.5
-// with 32 splits, 50.7 with 49; 32 pairs of 129 units (d = 128) 31.5 with 8, 43.9 with 16.
+// 66 units 8.7 / 12.8 with 16 splits, 9.0 / 13.7 with 8, 9.9 / 15.1 with 9; 130 units 10.0 / 15.3 with 16, 10.6 / 16.7 with 18;
+// 258 units 12.3 / 18.7 with 24, 12.8 / 20.0 with 25; 2049 units (d = 128) 30.8 with 68, 45 with 257; 8 pairs of 1026 units
+// 35.5 with 32 splits, 50.7 with 49; 32 pairs of 129 units (d = 128) 31.5 with 8, 43.9 with 16; of 258 units (d = 64)
+// 18.9 with 8, 19.2 with 16; 16 pairs of 258 units (d = 64) 14.7 with 16, 18.3 with 32; 16 row groups of 72 units 9.7 / 14.7
+// with 8, 10.1 / 15.5 with 16.
 int f32_splits(const svf_shape_t& s) {
   const int64_t units = units_of(s), groups = groups_of(s);
   if (units <= 4) return 1;
   const int64_t tiles = tiles_of(s);
-  int64_t want = (units + 7) / 8 > 8 ? (units + 7) / 8 : 8;
-  const int64_t root = (int64_t)ceil(1.5 * sqrt((double)units));
-  if (want > 16 && want > root) want = root > 16 ? root : 16;
+  const int64_t trips = (int64_t)(1.5 * sqrt((double)units) / 8);      // of the merge
+  int64_t want = units <= 40 ? 8 : 8 * (trips > 2 ? trips : 2);
   if (want > tiles) want = tiles;
   const int64_t most = groups < 256 ? 256 / groups : 1;
+  if (want > 8 && most <= 16 && units < 80) want = 8;
   return (int)(want < most ? want : most);
 }
 
