@@ -78,10 +78,11 @@ size_t scores_bytes(const svf_shape_t& s) {
   return align_up((size_t)s.B * s.Hkv * nb_max_of(s) * sizeof(float));
 }
 
-int check_ws(const svf_shape_t* s, const void* ws, size_t ws_bytes) {
+// (pl: the plan of shape s)
+int check_ws(const svf_shape_t& s, const AttnPlan& pl, const void* ws, size_t ws_bytes) {
   if (!ws) return SVF_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) % kAlign) return SVF_ERR_WORKSPACE;
-  if (ws_bytes < svf_workspace_bytes(s)) return SVF_ERR_WORKSPACE;
+  if (ws_bytes < pl.bytes + scores_bytes(s)) return SVF_ERR_WORKSPACE;
   return SVF_OK;
 }
 
@@ -246,10 +247,10 @@ int svf_workspace_init(void* ws, size_t ws_bytes, void* stream) {
 int svf_workspace_set_wait_polls(const svf_shape_t* shape, void* ws, size_t ws_bytes, int polls, void* stream) {
   int rc = check_shape(shape);
   if (rc) return rc;
-  rc = check_ws(shape, ws, ws_bytes);
+  const AttnPlan pl = plan_attn(*shape);
+  rc = check_ws(*shape, pl, ws, ws_bytes);
   if (rc) return rc;
   if (polls < -1 || polls > kMaxWaitPolls) return SVF_ERR_SHAPE;
-  const AttnPlan pl = plan_attn(*shape);
   uint64_t* epochs = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + pl.off_epochs);
   hipLaunchKernelGGL(set_wait_polls_kernel, dim3((unsigned)((pl.groups + 255) / 256)), dim3(256), 0,
                      static_cast<hipStream_t>(stream), epochs, pl.groups, polls < 0 ? 0u : (uint32_t)polls + 1u);
@@ -359,13 +360,13 @@ static int score_select_impl(const svf_shape_t* shape, const void* q, const floa
   if (rc) return rc;
   if (!q || !reps || !seq_lens || !sel_idx || !sel_cnt) return SVF_ERR_NULL;
   if (misaligned(q) || misaligned(reps)) return SVF_ERR_SHAPE;
-  rc = check_ws(shape, ws, ws_bytes);
+  const AttnPlan pl = plan_attn(*shape);
+  rc = check_ws(*shape, pl, ws, ws_bytes);
   if (rc) return rc;
   {
     // Shapes the retrieving attention kernel handles, when neither the scores nor a gather list
     // are asked for: its retrieval alone, one launch (the workgroups of a (sequence, KV head)
     // share the scoring), the same blocks bit for bit.
-    const AttnPlan pl = plan_attn(*shape);
     if (pl.fused_select && !scores_or_null && !with_gather) {
       char* w = static_cast<char*>(ws);
       AttnParams a{};
@@ -399,7 +400,6 @@ static int score_select_impl(const svf_shape_t* shape, const void* q, const floa
       return hip_code(launch_retrieve_only(a, static_cast<hipStream_t>(stream)));
     }
   }
-  const AttnPlan pl = plan_attn(*shape);
   VariantParams v = retrieval_params(*shape, pl, q, reps, seq_lens, sel_idx, sel_cnt, scores_or_null, ws);
   v.mean_query = 1;
   v.table = block_table;
@@ -414,25 +414,32 @@ int svf_score_select(const svf_shape_t* shape, const void* q, const float* reps,
                            false, nullptr);
 }
 
-// use_gather: the workspace holds the gather list of exactly this sel_idx / block_table / seq_lens
+// use_gather: the workspace holds the gather list of exactly this sel_idx / block_table / seq_lens.
+// checked: the shape's own plan, by a caller that has checked all arguments against it.
 static int verify_attn_impl(const svf_shape_t* shape, const void* q, const void* K, const void* V,
                             const int32_t* block_table, const int32_t* seq_lens, const void* k_draft,
                             const void* v_draft, const uint64_t* draft_mask_or_null, const int32_t* sel_idx,
                             const int32_t* sel_cnt, void* out, float* lse_or_null, void* ws, size_t ws_bytes,
                             void* stream, bool use_gather, const float* reps_to_select_from = nullptr,
-                            bool allow_mfma = true) {
-  int rc = check_shape(shape);
-  if (rc) return rc;
-  if (!q || !K || !V || !seq_lens || !k_draft || !v_draft || !sel_idx || !sel_cnt || !out ||
-      (shape->page_size > 0 && !block_table))
-    return SVF_ERR_NULL;
-  if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(k_draft) || misaligned(v_draft) ||
-      misaligned(out))
-    return SVF_ERR_SHAPE;
-  rc = check_ws(shape, ws, ws_bytes);
-  if (rc) return rc;
-  const AttnPlan pl = plan_attn(*shape, allow_mfma);
-  if (!allow_mfma && ws_bytes < pl.bytes) return SVF_ERR_WORKSPACE;
+                            bool allow_mfma = true, const AttnPlan* checked = nullptr) {
+  AttnPlan pl;
+  if (checked) {
+    pl = *checked;
+  } else {
+    int rc = check_shape(shape);
+    if (rc) return rc;
+    if (!q || !K || !V || !seq_lens || !k_draft || !v_draft || !sel_idx || !sel_cnt || !out ||
+        (shape->page_size > 0 && !block_table))
+      return SVF_ERR_NULL;
+    if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(k_draft) || misaligned(v_draft) ||
+        misaligned(out))
+      return SVF_ERR_SHAPE;
+    pl = plan_attn(*shape);
+    rc = check_ws(*shape, pl, ws, ws_bytes);
+    if (rc) return rc;
+    if (!allow_mfma) pl = plan_attn(*shape, false);
+    if (!allow_mfma && ws_bytes < pl.bytes) return SVF_ERR_WORKSPACE;
+  }
   char* w = static_cast<char*>(ws);
   AttnParams p;
   p.kv = layout_of(*shape);
@@ -602,10 +609,10 @@ __global__ void sum_fallbacks_kernel(const uint64_t* tickets, size_t groups, uin
 int svf_diag_wait_fallbacks(const svf_shape_t* shape, const void* ws, size_t ws_bytes, uint64_t* counts, void* stream) {
   int rc = check_shape(shape);
   if (rc) return rc;
-  rc = check_ws(shape, ws, ws_bytes);
+  const AttnPlan pl = plan_attn(*shape);
+  rc = check_ws(*shape, pl, ws, ws_bytes);
   if (rc) return rc;
   if (!counts) return SVF_ERR_NULL;
-  const AttnPlan pl = plan_attn(*shape);
   const uint64_t* tickets = reinterpret_cast<const uint64_t*>(static_cast<const char*>(ws) + pl.off_tickets);
   hipLaunchKernelGGL(sum_fallbacks_kernel, dim3(1), dim3(256), 0, static_cast<hipStream_t>(stream), tickets, pl.groups, counts);
   return hip_code(hipGetLastError());
@@ -645,19 +652,19 @@ int svf_verify_step(const svf_shape_t* shape, int mode, const void* q, const flo
   if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(k_draft) || misaligned(v_draft) ||
       misaligned(out) || (do_select && misaligned(reps)))
     return SVF_ERR_SHAPE;
-  rc = check_ws(shape, ws, ws_bytes);
-  if (rc) return rc;
   const AttnPlan pl = plan_attn(*shape);
+  rc = check_ws(*shape, pl, ws, ws_bytes);
+  if (rc) return rc;
   if (do_select && (pl.fused_select || pl.f32_retrieves))
     return verify_attn_impl(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask_or_null, sel_idx,
-                            sel_cnt, out, lse_or_null, ws, ws_bytes, stream, false, reps);
+                            sel_cnt, out, lse_or_null, ws, ws_bytes, stream, false, reps, true, &pl);
   if (do_select) {
     rc = score_select_impl(shape, q, reps, seq_lens, sel_idx, sel_cnt, nullptr, ws, ws_bytes, stream, true,
                            block_table);
     if (rc) return rc;
   }
   return verify_attn_impl(shape, q, K, V, block_table, seq_lens, k_draft, v_draft, draft_mask_or_null, sel_idx,
-                          sel_cnt, out, lse_or_null, ws, ws_bytes, stream, mode != SVF_STEP_REUSE);
+                          sel_cnt, out, lse_or_null, ws, ws_bytes, stream, mode != SVF_STEP_REUSE, nullptr, true, &pl);
 }
 
 // ---- retrieval analytics -------------------------------------------------------------------
@@ -806,9 +813,10 @@ int svf_retrieve(const svf_shape_t* shape, const svf_retrieval_t* retrieval, con
                             scores_or_null, ws, ws_bytes, stream);
   if (!q || !summaries || !seq_lens || !sel_idx || !sel_cnt) return SVF_ERR_NULL;
   if (misaligned(q) || misaligned(summaries)) return SVF_ERR_SHAPE;
-  rc = check_ws(shape, ws, ws_bytes);
+  const AttnPlan pl = plan_attn(*shape);
+  rc = check_ws(*shape, pl, ws, ws_bytes);
   if (rc) return rc;
-  VariantParams v = retrieval_params(*shape, plan_attn(*shape), q, summaries, seq_lens, sel_idx, sel_cnt, scores_or_null, ws);
+  VariantParams v = retrieval_params(*shape, pl, q, summaries, seq_lens, sel_idx, sel_cnt, scores_or_null, ws);
   v.mean_query = default_scores(r);
   v.minmax = r.summary == SVF_SUMMARY_MINMAX;
   v.summary_bf16 = r.summary_dtype == SVF_BF16;
