@@ -162,7 +162,7 @@ def mfma_vs_valu(args):
         raise SystemExit(f"bench --mfma-vs-valu: the two kernels disagree on the last layer (max-abs {diff:.3e})")
     bytes_ = W.algorithmic_bytes(cfg, x0["seq_lens"].cpu())["verify_attn"]
     M = cfg.gamma * (cfg.Hq // cfg.Hkv)
-    line = {"metric": f"verify-attn us/launch, matrix-core vs vector-ALU kernel ({cfg.name})",
+    line = {"metric": f"verify-attn us/launch, bf16 matrix-core vs fp32 kernel ({cfg.name})",
             "value": round(us[S.SVF_KERNEL_AUTO], 3), "unit": "us/launch", "n_gpus": 1, "steps": args.steps,
             "warmup": args.warmup, "ms_per_step": round(us[S.SVF_KERNEL_AUTO] * 1e-3, 6), "higher_is_better": False,
             "scaling": "weak", "vs_baseline": None, "dtype": cfg.dtype, "data": "synthetic",

@@ -1,5 +1,6 @@
 // Block scores of every draft token (retrieval analytics, Sec. 2.2), and the selection over scores in memory:
-// behind them, and for the retrieval of more blocks than one workgroup's registers hold (retrieve.hip).
+// behind them, and for the retrieval of many heads of few blocks, or of more blocks than a workgroup's registers hold
+// (selection_of in retrieve.hip).
 //
 //   scores:  wide, HBM-bound pass over the fp32 representatives.  Eight lanes own one block: float4
 //            loads, fp32 dot with the group-mean queries, reduction inside the lane group.
