@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -16,7 +17,7 @@ bool f32_retrieves(const svf_shape_t& s);
 hipError_t launch_verify_attn_mfma(const AttnParams& p, hipStream_t st);
 hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st);
 bool mfma_supported(const svf_shape_t& s);
-int mfma_splits(const svf_shape_t& s);
+int mfma_splits(const svf_shape_t& s, bool full);
 int mfma_shared_splits(const svf_shape_t& s);
 bool mfma_rows_mode(const svf_shape_t& s);
 int mfma_rows_splits(const svf_shape_t& s);
@@ -101,7 +102,7 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   pl.Mpad = (pl.M + 31) / 32 * 32;
   pl.mfma = allow_mfma && mfma_supported(s);
   if (pl.mfma) {
-    pl.n_splits = mfma_rows_mode(s) ? mfma_rows_splits(s) : mfma_splits(s);
+    pl.n_splits = mfma_rows_mode(s) ? mfma_rows_splits(s) : mfma_splits(s, false);
   } else {
     pl.n_splits = f32_splits(s);
   }
@@ -117,6 +118,16 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
     const size_t others = pl.bytes + scores_bytes(s) - pl.n_splits * per_split;      // (with what aligning them added)
     if (others + per_split <= kStaticScratchBytes) {
       pl.n_splits = pl.split_stride = (int)((kStaticScratchBytes - others) / per_split);
+      lay_out(s, pl);
+    }
+  }
+  if (pl.mfma && !mfma_rows_mode(s) && pl.bytes + scores_bytes(s) > kStaticScratchBytes) {
+    // the same for the tiles spread thinly
+    const int spread = pl.n_splits;
+    pl.n_splits = pl.split_stride = std::min(spread, mfma_splits(s, true));
+    lay_out(s, pl);
+    if (pl.bytes + scores_bytes(s) > kStaticScratchBytes) {
+      pl.n_splits = pl.split_stride = spread;
       lay_out(s, pl);
     }
   }

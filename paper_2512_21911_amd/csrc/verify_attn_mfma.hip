@@ -1215,9 +1215,13 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
 // cost is its instruction count: 0.5 instead of 1.0 us), four wavefronts instead of eight load
 // query fragments, and the tiles that arrive last are computed by wavefronts that have the SIMD
 // to themselves.  Also (MODE kGather): which of the up-front loads go out first, see below.
+// kThinTiles: the same where there are more splits than wavefronts need: tiles go to the splits in turn, instead of eight at a
+// time (which is 0.03 us per launch faster where all have eight).
 // SHARE: see share_out_splits.
-template <int D, int MODE, bool kOneTile, int SHARE = kAsPlanned>
+constexpr int kManyTiles = 0, kOneTilePerWave = 1, kThinTiles = 2;
+template <int D, int MODE, int TILES, int SHARE = kAsPlanned>
 __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p, int pairs) {
+  constexpr bool kOneTile = TILES != kManyTiles;
   // one stage per wavefront, plus one for draft tile 0 (its owner then streams its cache tile
   // at the same time); after the main loop stage w becomes wavefront w's fp32 output buffer
   __shared__ __attribute__((aligned(1024))) unsigned char smem[(kWaves + 1) * kStageBytes<D>];
@@ -1250,7 +1254,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int pair = blockIdx.y * kXcds + blockIdx.x % kXcds;
   int S = p.n_splits;                                           // splits of this pair
   const int rg = blockIdx.z;
-  static_assert(SHARE == kAsPlanned || (MODE == kResolve && !kOneTile), "shared out by the kernel that resolves its tiles one after the other");
+  static_assert(SHARE == kAsPlanned || (MODE == kResolve && TILES == kManyTiles), "shared out by the kernel that resolves its tiles one after the other");
   const bool planned = pair < pairs;                            // (split < n_splits by the grid)
   if (SHARE == kAsPlanned && !planned) return;
   if (SHARE != kAsPlanned) pair = min(pair, pairs - 1);         // (its loads are valid, whatever comes of it)
@@ -1265,7 +1269,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const int l32 = lane & 31, g = lane >> 5;
   const int row0 = rg * 32;
   int NW = kWaves * S;
-  int gw = split * kWaves + wave;
+  int gw = TILES == kThinTiles ? wave * S + split : split * kWaves + wave;
   constexpr int kSlices = kOneTile ? kWaves / 2 : kWaves;      // wavefronts that compute
   // (wave-uniform; said to be true where the pairs' counts are waited for with the query loads behind them in flight)
   const bool computes = SHARE != kAsPlanned || wave < kSlices;
@@ -2432,21 +2436,45 @@ static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64
   return want > fit && fit >= lo && fit >= 1 ? fit : want;
 }
 
-// Splits per (sequence, KV head, row group): enough workgroups to cover the 256 compute units,
-// at most kMaxTiles tiles per wavefront, at least one tile per wavefront.  `sharing`: of the retrieval alone, whose
-// workgroups are small.
-static int tile_splits(const svf_shape_t& s, bool sharing) {
-  const int M = s.gamma * (s.Hq / s.Hkv);
-  const int64_t groups = (int64_t)s.B * s.Hkv * ((M + 31) / 32);
-  const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
-  const int64_t lo = (tiles + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
-  const int64_t hi = (tiles - 1 + kWaves - 1) / kWaves > 0 ? (tiles - 1 + kWaves - 1) / kWaves : 1;
-  int64_t want = (256 + groups - 1) / groups;
-  if (want > hi) want = hi;
-  if (want < lo) want = lo;
-  return (int)(sharing ? want : one_round_splits(s, (M + 31) / 32, want, lo));
+// Splits per (sequence, KV head, row group): enough workgroups to cover the 256 compute units, at most kMaxTiles
+// tiles per wavefront, at least a tile or two per workgroup.  A compute unit takes 1 - 2 us to request eight tiles and
+// computes them four at a time, so a pair's tiles are spread thinly where there are units to spare: two to a
+// workgroup, up to sixteen splits (a merging thread's records are one poll, its chunks two batches of
+// eight; seventeen splits are a second pass over both), and one to a workgroup up to eight (one batch).  us per reuse / anchor launch,
+// D = 128, splits of a tile per wavefront -> these:
+//   8 pairs: 17 tiles 10.8 / 14.8 (2 splits) -> 7.3 / 10.6 (8); 33 tiles 8.8 / 12.2 (4) -> 7.5 / 10.9 (16); 65 tiles 9.4 / 13.0 (8)
+//   -> 8.8 / 12.2 (16); of 9 tiles 7.7 / 11.9 in one split, 7.2 / 10.8 in four, 7.1 / 10.3 in eight
+//   16 pairs of 33 tiles 9.6 / 13.3 (4) -> 8.0 / 11.8 (16); 32 pairs: 17 tiles 11.0 / 15.6 (2) -> 7.8 / 11.7 (8), 33 tiles 10.6 / 14.6 (4) -> 9.5 / 13.3
+//   (8); 64 pairs of 17 tiles 12.0 / 17.0 (2) -> 9.7 / 14.7 (4)
+// Nine to eleven splits cost the second batch and gain less than a tile per workgroup: 24 pairs of 33 tiles 8.9 / 12.5 with eight, 9.0 / 13.1
+// with ten, of 49 tiles 9.6 / 13.9 and 10.2 / 14.2.
+static int64_t tiles_of(const svf_shape_t& s) {
+  return ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
 }
-int mfma_splits(const svf_shape_t& s) { return tile_splits(s, false); }
+// full: a tile for every wavefront (the retrieval alone, whose workgroups share the scoring only, and plans that
+// have to be small)
+int mfma_splits(const svf_shape_t& s, bool full) {
+  const int row_groups = (s.gamma * (s.Hq / s.Hkv) + 31) / 32;
+  const int64_t groups = (int64_t)s.B * s.Hkv * row_groups;
+  const int64_t tiles = tiles_of(s);
+  const int64_t lo = (tiles + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
+  const int64_t filled = (tiles - 1 + kWaves - 1) / kWaves > 0 ? (tiles - 1 + kWaves - 1) / kWaves : 1;
+  int64_t most = filled;
+  if (!full) {
+    int64_t thin = tiles - 1 < 8 ? tiles - 1 : (tiles - 1) / 2;
+    if (thin < 8 && tiles > 8) thin = 8;
+    if (thin > 16) thin = 16;
+    if (most < thin) most = thin;
+  }
+  int64_t want = (256 + groups - 1) / groups;
+  if (want > most) want = most;
+  if (want < lo) want = lo;
+  if (!full) {
+    want = one_round_splits(s, row_groups, want, lo);
+    if (want > 8 && want < 12 && filled <= 8) want = 8;
+  }
+  return (int)want;
+}
 
 // Splits a pair may be given where the launch shares them out by the pairs' counts (share_out_splits), or
 // 0 where it uses mfma_splits for every pair: with one tile per wavefront (but for what one_round_splits changes) or one
@@ -2456,11 +2484,11 @@ int mfma_shared_splits(const svf_shape_t& s) {
   const int M = s.gamma * (s.Hq / s.Hkv);
   const int row_groups = (M + 31) / 32;
   const int64_t pairs = (int64_t)s.B * s.Hkv;
-  const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
+  const int64_t tiles = tiles_of(s);
   const int64_t cover = (256 + pairs * row_groups - 1) / (pairs * row_groups);
-  if (pairs > 64 * kShareChunks || tiles - 1 <= kWaves * cover || mfma_splits(s) == 1) return 0;
+  if (pairs > 64 * kShareChunks || tiles - 1 <= kWaves * cover || mfma_splits(s, false) == 1) return 0;
   const int64_t most = (tiles + kWaves - 1) / kWaves < kMaxSharedSplits ? (tiles + kWaves - 1) / kWaves : kMaxSharedSplits;
-  const int64_t n = mfma_splits(s);
+  const int64_t n = mfma_splits(s, false);
   const int64_t room = ((int64_t)8 << 20) / (pairs * row_groups * 32 * kRowBytes);
   return (int)(n > (most < room ? most : room) ? n : (most < room ? most : room));
 }
@@ -2478,7 +2506,7 @@ static int row_splits(const svf_shape_t& s, bool sharing) {
   const int M = s.gamma * (s.Hq / s.Hkv);
   const int row_groups = (M + 31) / 32;
   const int64_t groups = (int64_t)s.B * s.Hkv * ((row_groups + kWaves - 1) / kWaves);
-  const int64_t tiles = ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
+  const int64_t tiles = tiles_of(s);
   const int64_t lo = (tiles + kMaxRowTiles - 1) / kMaxRowTiles;
   int64_t want = (256 + groups - 1) / groups;
   if (want > tiles) want = tiles;
@@ -2488,7 +2516,7 @@ static int row_splits(const svf_shape_t& s, bool sharing) {
 int mfma_rows_splits(const svf_shape_t& s) { return row_splits(s, false); }
 
 // Workgroups per (sequence, KV head) that share the scoring of the retrieval alone.
-int mfma_select_splits(const svf_shape_t& s) { return mfma_rows_mode(s) ? row_splits(s, true) : tile_splits(s, true); }
+int mfma_select_splits(const svf_shape_t& s) { return mfma_rows_mode(s) ? row_splits(s, true) : mfma_splits(s, true); }
 
 // The retrieval of kSelect without the attention behind it (the stand-alone block selection of a
 // shape the retrieving attention kernel handles): the workgroups of a (sequence, KV head) share
@@ -2561,19 +2589,20 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   // one tile per wavefront (the owner of draft tile 0 streams a second one beside it)?  The same
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
-  const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits;
+  const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits, thin = tiles - 1 <= (int64_t)kWaves * (p.n_splits - 1);
   const int cover = (255 + pairs * row_groups) / (pairs * row_groups);       // splits that cover the compute units
-#define SVF_LAUNCH_ATTN(DIM, MODE)                                                                         \
-  do {                                                                                                     \
-    if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, true>), grid, dim3(kThreads), 0, st, p, pairs);  \
-    else hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, false>), grid, dim3(kThreads), 0, st, p, pairs);          \
+#define SVF_LAUNCH_ATTN(DIM, MODE)                                                                                                       \
+  do {                                                                                                                                   \
+    if (thin) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, kThinTiles>), grid, dim3(kThreads), 0, st, p, pairs);               \
+    else if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, kOneTilePerWave>), grid, dim3(kThreads), 0, st, p, pairs); \
+    else hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, kManyTiles>), grid, dim3(kThreads), 0, st, p, pairs);                    \
   } while (0)
   if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
   else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
   else if (p.share_splits && (int64_t)(p.n_splits > cover ? p.n_splits : cover) * kXcds * grid.y <= 256 / row_groups + pairs)
-    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
+    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, kManyTiles, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
   else if (p.share_splits)
-    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, false, kPairsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
+    hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, kManyTiles, kPairsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
   else SVF_LAUNCH_ATTN(D, kResolve);
 #undef SVF_LAUNCH_ATTN
   return hipGetLastError();

@@ -1,0 +1,32 @@
+"""Attention whose tiles are spread over more workgroups than their wavefronts would need, against the CPU oracle:
+one to three tiles per workgroup, splits without a tile, up to sixteen splits, two row groups, lists shorter than the
+plan, with all step modes on one workspace (full_parity() asks for the same blocks and the same bits)."""
+import pytest
+
+from svf_harness import full_parity
+from test_gpu_parity import small
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    "one_tile_and_the_draft": small(B=1, Hq=8, Hkv=2, gamma=2, T=200, block_size=32, k_blocks=1, page_size=0),
+    "draft_only_splits_empty": small(B=2, Hq=8, Hkv=2, gamma=3, T=300, k_blocks=4, min_len=1),
+    "nine_tiles_eight_splits": small(B=1, Hq=8, Hkv=8, gamma=4, T=900, k_blocks=4),
+    "seventeen_tiles_eight_splits": small(B=4, Hq=32, Hkv=8, gamma=8, T=1100, k_blocks=8),
+    "eighteen_tiles_nine_to_eight": small(B=3, Hq=8, Hkv=8, gamma=3, T=1100, block_size=32, k_blocks=17),
+    "33_tiles_sixteen_splits": small(B=1, Hq=32, Hkv=8, gamma=5, T=1500, k_blocks=16, page_size=0),
+    "34_tiles_seventeenth_split_not_taken": small(B=1, Hq=32, Hkv=8, gamma=5, T=1500, block_size=32, k_blocks=33),
+    "129_tiles_full_wavefronts": small(B=1, Hq=8, Hkv=2, gamma=3, T=4500, k_blocks=64),
+    "131_tiles_seventeen_splits": small(B=1, Hq=8, Hkv=2, gamma=3, T=4500, k_blocks=65),
+    "two_row_groups_sixteen_splits": small(B=1, Hq=32, Hkv=8, gamma=16, tree_depth=5, T=2000, k_blocks=17),
+    "two_draft_tiles": small(B=1, Hq=2, Hkv=2, gamma=40, tree_depth=5, T=900, k_blocks=6),
+    "ragged_lists_shorter_than_the_plan": small(B=4, Hq=8, Hkv=4, gamma=6, T=2500, k_blocks=20, min_len=40),
+    "d64_33_tiles": small(B=3, Hq=32, Hkv=8, d=64, gamma=7, T=1500, k_blocks=16, min_len=200),
+    "d64_seventeen_tiles_two_row_groups": small(B=1, Hq=32, Hkv=8, d=64, gamma=10, T=1100, k_blocks=8),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_thin_splits(name):
+    r = full_parity(CASES[name])
+    print(f"[thin splits] {name}: max_abs_err={r['max_abs_err']:.3e} near_ties={r['near_ties']}", flush=True)
