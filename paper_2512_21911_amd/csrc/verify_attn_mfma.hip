@@ -130,47 +130,68 @@ __device__ __forceinline__ u32x2 lds_read8_tr(uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
   return v;
 }
-// The eight transposing reads of one k-step of the second product.  Piece e = 2 nt + h is chunk
-// 4 nt + vc of the token rows vtok + 8 h (+ 16 KS2), at the swizzled position (4 nt + vc) ^ token.
-// With L = vc ^ (vtok & 3) (bits 0, 1), g = bit 2 of vtok and h = bit 3 of the token that is
-//   16 L + 64 ((nt & 1) ^ g) + 128 ((nt >> 1) ^ h),
-// and 64 ((nt & 1) ^ g) = 64 (nt & 1) + 64 g for even nt, 64 (nt & 1) - 64 g for odd nt: two
-// per-lane addresses (even / odd nt) and an immediate per piece, instead of an XOR and an addition
-// per piece in every tile.
-template <int E, int KS2>
-__device__ __forceinline__ u32x2 lds_read_vt_piece(uint32_t even, uint32_t odd) {
+// The eight transposing reads of one k-step of the second product: piece 2 nt + h is chunk 4 nt + vc of the token rows
+// vtok + 8 h (+ 16 KS2).  Where a V row's chunks sit: the four tokens that 16 lanes address, and the
+// eight of the wavefront's, would hit the same sixteen of 64 banks if a row's place were shifted by its
+// token within one group of four chunks; so the token's low two bits select the group.
+//   D = 128: chunk c of token t at c ^ 4 (t & 3): group nt ^ (t & 3), one address per nt (of), h and KS2 immediate.
+//   D = 64 (K and V share a row, and sixteen K rows must differ as well): at c ^ (4 (t & 3) + ((t >> 2) & 3)); h is bit 1 of
+//   t >> 2, which flips bit 1 of the place within the group: an address per (nt, h).
+// (With chunk c at c ^ (t & 15): 6.5 conflict cycles per transposing read, 57 % of the LDS cycles of a 60-node tree's launch.)
+struct VAddress { uint32_t at[4]; };                     // D = 128: of nt; D = 64: of 2 (nt - 2) + h
+template <int D>
+__device__ __forceinline__ VAddress v_address(uint32_t stage, int l32, int g) {
+  // This lane addresses, for piece h of a k-step, token 8*h + 4*g + q and the four channels
+  // 32*nt + 16*((lane/16)%2) + 4*(lane%4): chunk 4*nt + vc, half l32 % 2.
+  const uint32_t q = (uint32_t)((l32 & 15) >> 2), vc = (uint32_t)(2 * ((l32 >> 4) & 1) + ((l32 & 3) >> 1));
+  const uint32_t base = (4u * (uint32_t)g + q) * kRowBytes + ((uint32_t)(l32 & 1) << 3);
+  VAddress a;
+#pragma unroll
+  for (uint32_t i = 0; i < 4; ++i) {
+    if constexpr (D == 128) a.at[i] = stage + kTileBytes + (base + (vc << 4) + ((i ^ q) << 6));
+    else a.at[i] = stage + (base + ((vc ^ (uint32_t)g ^ (2u * (i & 1u))) << 4) + (((2u + (i >> 1)) ^ q) << 6));
+  }
+  return a;
+}
+template <int D, int E, int KS2>
+__device__ __forceinline__ u32x2 lds_read_vt_piece(const VAddress& a) {
   constexpr int nt = E >> 1, h = E & 1;
-  return lds_read8_tr<64 * (nt & 1) + 128 * ((nt >> 1) ^ h) + h * 8 * kRowBytes + KS2 * 16 * kRowBytes>((nt & 1) ? odd : even);
+  return lds_read8_tr<h * 8 * kRowBytes + KS2 * 16 * kRowBytes>(a.at[D == 128 ? nt : 2 * (nt - 2) + h]);
 }
 // Both k-steps at D = 64: the V row is chunks 8 .. 15, i.e. products nt = 2, 3; x[4 * KS2 + 2 * (nt - 2) + h].
-__device__ __forceinline__ void lds_read_vt64(u32x2 (&x)[8], uint32_t even, uint32_t odd) {
-  x[0] = lds_read_vt_piece<4, 0>(even, odd);
-  x[1] = lds_read_vt_piece<5, 0>(even, odd);
-  x[2] = lds_read_vt_piece<6, 0>(even, odd);
-  x[3] = lds_read_vt_piece<7, 0>(even, odd);
-  x[4] = lds_read_vt_piece<4, 1>(even, odd);
-  x[5] = lds_read_vt_piece<5, 1>(even, odd);
-  x[6] = lds_read_vt_piece<6, 1>(even, odd);
-  x[7] = lds_read_vt_piece<7, 1>(even, odd);
+__device__ __forceinline__ void lds_read_vt64(u32x2 (&x)[8], const VAddress& a) {
+  x[0] = lds_read_vt_piece<64, 4, 0>(a);
+  x[1] = lds_read_vt_piece<64, 5, 0>(a);
+  x[2] = lds_read_vt_piece<64, 6, 0>(a);
+  x[3] = lds_read_vt_piece<64, 7, 0>(a);
+  x[4] = lds_read_vt_piece<64, 4, 1>(a);
+  x[5] = lds_read_vt_piece<64, 5, 1>(a);
+  x[6] = lds_read_vt_piece<64, 6, 1>(a);
+  x[7] = lds_read_vt_piece<64, 7, 1>(a);
 }
 template <int KS2>
-__device__ __forceinline__ void lds_read_vt(u32x2 (&x)[8], uint32_t even, uint32_t odd) {
-  x[0] = lds_read_vt_piece<0, KS2>(even, odd);
-  x[1] = lds_read_vt_piece<1, KS2>(even, odd);
-  x[2] = lds_read_vt_piece<2, KS2>(even, odd);
-  x[3] = lds_read_vt_piece<3, KS2>(even, odd);
-  x[4] = lds_read_vt_piece<4, KS2>(even, odd);
-  x[5] = lds_read_vt_piece<5, KS2>(even, odd);
-  x[6] = lds_read_vt_piece<6, KS2>(even, odd);
-  x[7] = lds_read_vt_piece<7, KS2>(even, odd);
+__device__ __forceinline__ void lds_read_vt(u32x2 (&x)[8], const VAddress& a) {
+  x[0] = lds_read_vt_piece<128, 0, KS2>(a);
+  x[1] = lds_read_vt_piece<128, 1, KS2>(a);
+  x[2] = lds_read_vt_piece<128, 2, KS2>(a);
+  x[3] = lds_read_vt_piece<128, 3, KS2>(a);
+  x[4] = lds_read_vt_piece<128, 4, KS2>(a);
+  x[5] = lds_read_vt_piece<128, 5, KS2>(a);
+  x[6] = lds_read_vt_piece<128, 6, KS2>(a);
+  x[7] = lds_read_vt_piece<128, 7, KS2>(a);
+}
+// Place of chunk 0 of token t's K row (D = 64: and V row), in chunks; chunk c is at c ^ this.
+template <int D>
+__device__ __forceinline__ uint32_t k_swizzle(uint32_t t) {
+  return D == 128 ? t & 15u : ((t & 3u) << 2) | ((t >> 2) & 3u);
 }
 // Waits for all LDS reads; the registers pass through the statement so that no use of them can
 // be scheduled above the wait.
-template <typename T>
+template <int LEFT, typename T>
 __device__ __forceinline__ void lds_wait8(T (&r)[8]) {
-  asm volatile("s_waitcnt lgkmcnt(0)"
+  asm volatile("s_waitcnt lgkmcnt(%8)"
                : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7])
-               :
+               : "n"(LEFT)
                : "memory");
 }
 
@@ -183,9 +204,10 @@ __device__ __forceinline__ void lds_write4(uint32_t addr, uint32_t value) {
   asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(value) : "memory");
 }
 
-template <typename T>
+// (LEFT reads issued behind these may still be on their way: LDS answers in order)
+template <int LEFT, typename T>
 __device__ __forceinline__ void lds_wait4(T (&r)[4]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : : "memory");
+  asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "n"(LEFT) : "memory");
 }
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -294,17 +316,22 @@ __device__ __forceinline__ void row_lanes_from(uint32_t x, uint32_t (&out)[8]) {
   if constexpr (N > 0) row_lanes_from<B0, N - 1>(x, out);
 }
 
-// Requests the K and V rows of four tokens (sixteen lanes per token) into one kilobyte of a stage
-// (D = 128: one of its K part and one of its V part).  kb: K row of the group's first token (scalar),
-// dv: from there to the V row (scalar), off: this lane's token within the group in bytes, chunk: which
-// of the sixteen 16-byte chunks of the stage's row this lane fetches.  D = 64: chunks 8 .. 15 are the V row's.
+// Requests the K and V rows of tokens 4n .. 4n + 3 (sixteen lanes per token) into kilobyte n of a stage
+// (D = 128: of its K part and of its V part).  kb: K row of the group's first token (scalar), dv: from there to the V row
+// (scalar), off: this lane's token within the group in bytes, dst: the kilobyte.  Which of the row's sixteen 16-byte
+// chunks this lane fetches follows from where they sit (k_swizzle, VAddress): place lane % 16 of row 4n + lane / 16.
+struct LaneChunks {
+  uint32_t k, v;
+  __device__ __forceinline__ explicit LaneChunks(int lane) : k((uint32_t)((lane & 15) ^ (lane >> 4))), v((uint32_t)((lane & 15) ^ ((lane >> 4) << 2))) {}
+};
 template <int D>
-__device__ __forceinline__ void request_rows(const char* kb, int64_t dv, uint32_t off, uint32_t chunk, unsigned char* dst) {
+__device__ __forceinline__ void request_rows(const char* kb, int64_t dv, uint32_t off, LaneChunks c, int n, unsigned char* dst) {
   if constexpr (D == 128) {
-    const uint32_t o = off + (chunk << 4);
-    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + o), SVF_LDS_PTR(dst), 16, 0, 2);
-    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + dv + o), SVF_LDS_PTR(dst + kTileBytes), 16, 0, 2);
+    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + (off + ((c.k ^ (uint32_t)((4 * n) & 15)) << 4))), SVF_LDS_PTR(dst), 16, 0, 2);
+    __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + dv + (off + (c.v << 4))), SVF_LDS_PTR(dst + kTileBytes), 16, 0, 2);
   } else {
+    // (chunks 8 .. 15 are the V row's)
+    const uint32_t chunk = c.v ^ (uint32_t)(n & 3);
     const char* src = (chunk & 8u) ? kb + dv : kb;
     __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(src + (off + ((chunk & 7u) << 4))), SVF_LDS_PTR(dst), 16, 0, 2);
   }
@@ -351,36 +378,38 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
                                              float& l_run, floatx16 (&oacc)[D / 32]) {
   // K fragment of k-step ks: row l32, 16-byte chunk 2*ks + g at swizzled position
   const uint32_t kbase = stage + l32 * kRowBytes;
-  const uint32_t kx = (uint32_t)((g ^ (l32 & 15)) << 4);
+  const uint32_t kx = ((uint32_t)g ^ k_swizzle<D>((uint32_t)l32)) << 4;
   // V^T fragments by transposing reads: A row m (= lane mod 32) of the nt-th product is channel
   // 32 * nt + m; k-slot e of lane group g is token 8*(e/4) + 4*g + e%4 (+16 for the second k-step).
-  // This lane addresses, for piece h of a k-step, token 8*h + 4*g + (lane%16)/4 and the four
-  // channels 32*nt + 16*((lane/16)%2) + 4*(lane%4): 16-byte chunk 4*nt + vc, half vh.
-  const uint32_t vtok = (uint32_t)(4 * g + ((l32 & 15) >> 2));
-  const uint32_t vc = (uint32_t)(2 * ((l32 >> 4) & 1) + ((l32 & 3) >> 1));
-  const uint32_t vbase = stage + (D == 128 ? kTileBytes : 0) + vtok * kRowBytes + ((uint32_t)(l32 & 1) << 3);
-  const uint32_t vswz = (vc ^ (vtok & 3u)) << 4;
-  const uint32_t v_even = vbase + vswz + ((uint32_t)g << 6), v_odd = vbase + vswz - ((uint32_t)g << 6);
+  const VAddress va = v_address<D>(stage, l32, g);
 
   // S^T = K Q^T : token = lane mod 32 (A rows), query row = lane mod 32 (B columns)
   floatx16 sacc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+  // Every read is issued well ahead of what waits for it: the K fragments all at once, the V^T fragments
+  // (x0, x1: of the two k-steps, [2 * nt + h]; D = 64: both in x0) behind the products that free the K fragments' registers.
+  u32x4 kf[D / 64][4];
+  u32x2 x0[8], x1[8];
 #pragma unroll
-  for (int half = 0; half < D / 64; ++half) {
-    u32x4 kf[4];
-#pragma unroll
-    for (int k4 = 0; k4 < 4; ++k4) kf[k4] = lds_read16<0>(kbase + (kx ^ (uint32_t)((4 * half + k4) << 5)));
-    lds_wait4(kf);
+  for (int k = 0; k < D / 16; ++k) kf[k >> 2][k & 3] = lds_read16<0>(kbase + (kx ^ (uint32_t)(k << 5)));
+  auto scores = [&](int half) {
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4)
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[k4]), qf[4 * half + k4], sacc,
-                                                     0, 0, 0);
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[half][k4]), qf[4 * half + k4], sacc, 0, 0, 0);
+  };
+  if constexpr (D == 128) {
+    lds_wait4<4>(kf[0]);
+    scores(0);
+    lds_read_vt<0>(x0, va);
+    lds_wait4<8>(kf[D / 64 - 1]);
+    scores(D / 64 - 1);
+    lds_read_vt<1>(x1, va);
+  } else {
+    lds_read_vt64(x0, va);
+    lds_wait4<8>(kf[0]);
+    scores(0);
   }
-  // the V^T fragments of the first k-step: in flight while the softmax runs.  x[2 * nt + h]
-  u32x2 x[8];
-  if constexpr (D == 128) lds_read_vt<0>(x, v_even, v_odd);
-  else lds_read_vt64(x, v_even, v_odd);
 
   // online softmax; value v of a lane is token 8*(v/4) + 4*g + v%4 of the tile.
   // Invisible tokens drop out by setting their raw score to -inf (the scale is positive).
@@ -445,9 +474,9 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
   // group g is token 16*ks2 + 8*(e/4) + 4*g + e%4.  x[2*nt + h] holds k-slots 4*h .. 4*h+3.
 #pragma unroll
   for (int ks2 = 0; ks2 < 2; ++ks2) {
-    if constexpr (D == 128)
-      if (ks2 == 1) lds_read_vt<1>(x, v_even, v_odd);
-    if (D == 128 || ks2 == 0) lds_wait8(x);
+    u32x2 (&x)[8] = D == 128 && ks2 == 1 ? x1 : x0;
+    if (D == 128 && ks2 == 0) lds_wait8<8>(x);
+    else if (D == 128 || ks2 == 0) lds_wait8<0>(x);
 #pragma unroll
     for (int nt = 0; nt < D / 32; ++nt) {
       const int e = (D == 64 ? 4 * ks2 : 0) + 2 * nt;
@@ -1374,7 +1403,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   int early_draft_loads = 0;
   auto request_draft_tile = [&]() {
     const int er = lane >> 4;
-    const uint32_t ecx = (uint32_t)((lane & 15) ^ er);
+    const LaneChunks ec(lane);
     const uint32_t drow = (uint32_t)p.Hkv * (D * 2);
     const char* kd = Kd + (((int64_t)b * p.gamma) * p.Hkv + h) * (D * 2);
     const int64_t dvd = Vd - Kd;
@@ -1384,7 +1413,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       const int nvn = min(max(p.gamma - 4 * n, 0), 4);     // drafts in slots 4n .. 4n + 3 (uniform)
       if (nvn == 0) continue;
       const uint32_t off = (uint32_t)(4 * n + min(er, nvn - 1)) * drow;
-      request_rows<D>(kd, dvd, off, ecx ^ (uint32_t)((4 * n) & 15), xs + n * 1024);
+      request_rows<D>(kd, dvd, off, ec, n, xs + n * 1024);
       early_draft_loads += D == 128 ? 2 : 1;
     }
   };
@@ -1495,9 +1524,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     __hip_atomic_fetch_add(where_word, 1ull << (8 * xcc_id()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // per-lane parts of the load addresses: load n of a tile covers slots 4n .. 4n+3, sixteen lanes
-  // per slot; chunk swizzle: 16-byte chunk c of the row in slot s sits at position c ^ (s & 15)
+  // per slot
   const int lrow = lane >> 4;                              // row of this lane inside a load
-  const uint32_t cx = (uint32_t)((lane & 15) ^ lrow);     // chunk of load n: cx ^ (4n & 15)
+  const LaneChunks cx(lane);
   const uint32_t tok_bytes = (uint32_t)p.kv.stride_tok * 2u;
   const uint32_t drow_bytes = (uint32_t)p.Hkv * (D * 2);
   const int64_t dv_c = Vc - Kc, dv_d = Vd - Kd;
@@ -1575,7 +1604,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       // rows past the group's last valid row re-read that row
       const uint32_t last_off = (uint32_t)max(nvn - 1, 0) * (uint32_t)__builtin_amdgcn_readfirstlane((int)row_bytes);
       if (skip_void_groups && nvn == 0) continue;        // (wave-uniform)
-      request_rows<D>(kb, fd ? dv_d : dv_c, min(lrow_off, last_off), cx ^ (uint32_t)((4 * n) & 15), dst + n * 1024);
+      request_rows<D>(kb, fd ? dv_d : dv_c, min(lrow_off, last_off), cx, n, dst + n * 1024);
     }
     ti.valid = valid;
     return ti;
@@ -1983,7 +2012,7 @@ struct RowTileIssue {
   int64_t dv_c, dv_d;
   uint64_t gent;                 // lane u: gather entry of (u-th tile, this wavefront's group)
   int split, S, tiles_d, gamma, wave, lane;
-  uint32_t lrow, cx, tok_bytes, drow_bytes;
+  uint32_t lrow, tok_bytes, drow_bytes;
   uint32_t lrow_tok_off, lrow_draft_off;     // lrow x tok_bytes, lrow x drow_bytes
 };
 
@@ -2022,7 +2051,7 @@ __device__ __forceinline__ void issue_row_tile(const RowTileIssue& c, int i) {
   const uint32_t dt = 0u - (uint32_t)(t < c.tiles_d);          // (a draft tile: its rows lie drow_bytes apart)
   const uint32_t lrow_off = (c.lrow_draft_off & dt) | (c.lrow_tok_off & ~dt);
   const uint32_t off = min(lrow_off, (uint32_t)max(nv - 1, 0) * row_bytes);
-  request_rows<D>(kb, dv, off, c.cx ^ (uint32_t)((4 * c.wave) & 15), dst + c.wave * 1024);
+  request_rows<D>(kb, dv, off, LaneChunks(c.lane), c.wave, dst + c.wave * 1024);
 }
 
 template <int D, int MODE>
@@ -2144,7 +2173,6 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   n_my = __builtin_amdgcn_readfirstlane(n_my);             // (the same for the whole workgroup)
 
   const int lrow = lane >> 4;
-  const uint32_t cx = (uint32_t)((lane & 15) ^ lrow);
   const uint32_t tok_bytes = (uint32_t)p.kv.stride_tok * 2u;
   const uint32_t drow_bytes = (uint32_t)p.Hkv * (D * 2);
   const int64_t dv_c = Vc - Kc, dv_d = Vd - Kd;
@@ -2165,7 +2193,6 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   ic.wave = wave;
   ic.lane = lane;
   ic.lrow = (uint32_t)lrow;
-  ic.cx = cx;
   ic.tok_bytes = tok_bytes;
   ic.drow_bytes = drow_bytes;
   ic.lrow_tok_off = (uint32_t)lrow * tok_bytes;
