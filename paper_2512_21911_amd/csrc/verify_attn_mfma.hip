@@ -932,7 +932,10 @@ __device__ __forceinline__ RetrievalLoads<D> issue_retrieval_loads(const AttnPar
   // into addresses afterwards costs no further trip to memory
   R.table_row = p.table + (int64_t)b * p.kv.max_pages;
   R.table_in_lds = p.kv.page_size != 0 && p.kv.max_pages <= kTableLoads * kThreads;
-  R.share_scores = p.n_splits >= 2;
+// (up to 128 blocks everybody scores all of them: two rows of representatives per lane group cost less than the
+  // exchange.  us per anchor launch, 128 blocks: 32 pairs of 33 tiles 12.9 -> 12.7, 16 pairs of 80 rows 14.85 -> 14.2; 8 pairs and d = 64 the
+  // same; 256 blocks at d = 64: 10.4 -> 10.8)
+  R.share_scores = p.n_splits >= 2 && p.nb_max > 128;
   R.epoch_word = p.epochs[xgroup + vzero];
   R.rot = rot;
   R.table_wide = (p.kv.max_pages & 3) == 0 && (reinterpret_cast<uintptr_t>(p.table) & 15) == 0;
@@ -1258,7 +1261,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   __shared__ float sm_l[kWaves][32];
   __shared__ uint32_t sm_pair_valid[kWaves / 2];   // (kOneTile) what wavefront w + 4 fetched: valid slots,
   __shared__ int sm_pair_draft[kWaves / 2];        // draft base (-1: cache tile, -2: nothing)
-  __shared__ int sm_last;
+  __shared__ uint32_t sm_ticket;                   // once wavefront 0 has its ticket: slices left to the last arriver, and the top bit
   __shared__ int sm_own_ready;                     // wavefronts 0 .. 3 that have left their part of the own rows in LDS
   __shared__ int sm_one_xcd;                       // every workgroup of the group is known to run on this XCD
   __shared__ int32_t s_sel[MODE == kSelect ? kMaxSelectBlocks : 1];   // kept blocks, ascending
@@ -1727,7 +1730,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         mine[parked_index<D>(l32, nt * 8 + k * 2 + g)] =
             make_float4(oacc[nt][4 * k], oacc[nt][4 * k + 1], oacc[nt][4 * k + 2], oacc[nt][4 * k + 3]);
   }
-  if (tid == kMergeWave0 * 64) sm_own_ready = 0;
+  if (tid == kMergeWave0 * 64) {
+    sm_own_ready = 0;
+    sm_ticket = 0u;
+  }
   if (wave == kWaves - 1 && lane == 0)
     sm_one_xcd = counts_xcds && where == (uint64_t)S << (8 * xcc_id()) ? 1 : 0;
   __syncthreads();
@@ -1760,7 +1766,6 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   const int lo = split * R, hi = min(lo + R, 32);            // the workgroup's own slice (empty if lo >= 32)
   unsigned char* const own_o = x_stage;                     // [R][256 bytes], R <= 16
   float* const own_ml = reinterpret_cast<float*>(x_stage + 16 * kRowBytes);
-  uint64_t prev = 0;
   int64_t pr_rec = 0;
   float mw = -INFINITY, lw = 0.f;
   const int r = tid >> 3, c16 = tid & 7;                     // (wavefronts 0 .. 3) row, block of D / 8 channels
@@ -1864,12 +1869,19 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         if (one_xcd) store_l2_16(p.part_rec + pr_rec * 4, rec);
         else store_coherent16(p.part_rec + pr_rec * 4, rec);
       }
-      if (tid == 0) prev = __hip_atomic_fetch_add(arrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // The ticket, by a wavefront that has nothing else to do: what it says is known long before the merging wavefronts
+      // ask for it.  (All of the group's workgroups have taken theirs when the last one does: they have read the call counter.)
+      if (tid == 0) {
+        const uint64_t prev = __hip_atomic_fetch_add(arrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool last = (prev & 0xffffull) == (uint64_t)(S - 1);
+        const uint32_t word = 0x80000000u | (last ? (uint32_t)(prev >> 16) & 0xffffu : 0u);
+        asm volatile("ds_write_b32 %0, %1" : : "v"((uint32_t)(uintptr_t)SVF_LDS_PTR(&sm_ticket)), "v"(word) : "memory");
+        if (last) finish_call(p, group, tag);
+      }
     }
   }
-  if (single) return;
+  if (single || (wave != kMergeWave0 && wave != kMergeWave0 + 1)) return;      // (no barrier from here on)
 
-  const bool merger = wave == kMergeWave0 || wave == kMergeWave0 + 1;
   const int mt = tid - kMergeWave0 * 64;
   constexpr int WM = kWideMerge<D>;
   const bool ch4 = D == 64 || R <= 4;                        // 4 channels per merging thread, else 8
@@ -1882,7 +1894,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // polls for the records look at that counter as well
   const uint32_t ready = (uint32_t)(uintptr_t)SVF_LDS_PTR(&sm_own_ready);
   bool own_rows_in = false;
-  if (merger && prefetch) {
+  if (prefetch) {
     const int64_t g_row0 = (int64_t)pair * p.split_stride * p.Mpad + row0;
     if (ch4) {
       init_lane(L4, mt, lo, hi);
@@ -1892,7 +1904,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       records_in = !__any(L8.active) || poll_records(p, L8, g_row0 + L8.row, S, 0, tag, wait_polls, split, ready, 4u, &own_rows_in);
     }
   }
-  if (merger && !own_rows_in) {
+  if (!own_rows_in) {
     for (int it = 0; it < kLastResortPolls; ++it) {
       uint32_t n;
       asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(n) : "v"(ready) : "memory");
@@ -1902,10 +1914,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   }
   // Slices this wavefront still has to merge (bit x: slice x), the patience it has with them, and
   // whether the last attempt ran out of it.
-  uint32_t todo = (merger && lo < 32) ? 1u << split : 0u;
+  uint32_t todo = lo < 32 ? 1u << split : 0u;
   int budget = wait_polls;
   bool gave_up = false;
-  if (merger && prefetch) {
+  if (prefetch) {
     todo = 0u;
     if (!records_in) {
       gave_up = true;
@@ -1954,15 +1966,16 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       }
     }
     if (round == 0) {
-      __syncthreads();
-      if (tid == 0) {
-        const bool last = (prev & 0xffffull) == (uint64_t)(S - 1);
-        sm_last = last ? (int)((uint32_t)(prev >> 16) & 0xffffu) : 0;
-        if (last) finish_call(p, group, tag);
+      // (wavefront 0 waits for nobody)
+      uint32_t word = 0u;
+      for (int it = 0; it < kLastResortPolls && !(word >> 31); ++it) {
+        if (it) __builtin_amdgcn_s_sleep(1);
+        uint32_t w;
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(w) : "v"((uint32_t)(uintptr_t)SVF_LDS_PTR(&sm_ticket)) : "memory");
+        word = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
       }
-      __syncthreads();
       // (only in the last arriver, and only after a starved wait somewhere in the group)
-      todo = merger ? (uint32_t)sm_last : 0u;
+      todo = word & 0xffffu;
       budget = kLastResortPolls;
     }
   }
