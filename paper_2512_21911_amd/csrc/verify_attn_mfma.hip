@@ -2130,15 +2130,48 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     if (e_ok) gent = p.gather[(int64_t)pair * p.gather_groups + e_u];
     cnt_raw = p.sel_cnt[pair + vzero];
   }
-  bf16x8 qf[D / 16];
-  {
-    const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
-                                 (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
-  }
   uint64_t rmask = 0;
-  if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
+  auto load_mask = [&]() {
+    if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
+  };
+  if (MODE != kSelect) load_mask();
+  bf16x8 qf[D / 16];
+  // The wavefront's 32 query rows.  A fragment load takes 32 bytes of each row and costs the memory pipeline as much as
+  // four whole rows do, and there are 64 of them in a workgroup; so the rows come in whole, into stages that no tile needs
+  // yet, and the fragments are read from there.  (A retrieving workgroup takes them through registers, because its
+  // barriers would wait for loads that go to LDS, and behind its own scores, when their registers are free.)
+  // us per reuse / anchor launch: 32 pairs of 240 rows 22.0 / 26.3 -> 21.2 / 25.3, 8 pairs of 240 14.8 / 19.5 -> 14.5 / 18.4, 16 pairs of
+  // 320 14.2 / 18.0 -> 13.5 / 17.4, of 120 (d = 64) 12.5 / 16.0 -> 12.4 / 15.2.
+  constexpr int kQRow = D * 2, kQLanes = kQRow / 16, kQLoads = 32 * kQRow / 1024;      // bytes of a row, lanes that bring it, loads
+  unsigned char* const q_rows = smem + kRowStages * kStageBytes<D> - (kWaves - wave) * 32 * kQRow;
+  static_assert(kWaves * 32 * kQRow <= (kRowStages - kRowFirst) * kStageBytes<D>, "the first tiles' stages are theirs");
+  auto q_place = [&](int r) { return (uint32_t)(D == 128 ? r & 15 : (r >> 1) & 7); };       // chunk c of row r sits at c ^ this
+  u32x4 q_piece[kQLoads];
+  auto request_q = [&]() {
+    if (MODE == kSelect && !has_rows) return;            // (elsewhere a branch would make the wait for the gather entries a wait for the rows)
+    const __hip_bfloat16* const q0 = static_cast<const __hip_bfloat16*>(p.q) + ((int64_t)b * p.gamma * p.Hq + h * p.G) * D;
+#pragma unroll
+    for (int n = 0; n < kQLoads; ++n) {
+      const int r = n * (64 / kQLanes) + lane / kQLanes;
+      const uint32_t grow = (uint32_t)min(row0 + r, p.M - 1), i = (uint32_t)(((uint64_t)grow * p.g_magic) >> 32);
+      const uint32_t off = (i * (uint32_t)p.Hq + (grow - i * (uint32_t)p.G)) * (uint32_t)kQRow + (((uint32_t)(lane % kQLanes) ^ q_place(r)) << 4);
+      const char* const src = reinterpret_cast<const char*>(q0) + off;
+      if constexpr (MODE == kSelect) q_piece[n] = *reinterpret_cast<const u32x4*>(src);
+      else __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(src), SVF_LDS_PTR(q_rows + n * 1024), 16, 0, 0);
+    }
+  };
+  if (MODE != kSelect) request_q();
+  auto read_fragments = [&]() {
+    const uint32_t at = (uint32_t)(uintptr_t)SVF_LDS_PTR(q_rows) + (uint32_t)l32 * kQRow;
+    u32x4 f[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) f[ks] = lds_read16<0>(at + (((uint32_t)(2 * ks + g) ^ q_place(l32)) << 4));
+    if constexpr (D == 128) lds_wait8<0>(f);
+    else lds_wait4<0>(f);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, f[ks]);
+  };
+  if (MODE == kSelect) load_mask();
   int L = 0;
   if (MODE != kGather) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
   if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
@@ -2148,7 +2181,14 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   if (MODE != kSelect) epoch_word = p.epochs[xgroup + vzero];
   if (MODE == kSelect) {
     epoch_word = rl.epoch_word;
-    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, []() {});
+    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, request_q);
+    if (has_rows) {
+#pragma unroll
+      for (int n = 0; n < kQLoads; ++n) *reinterpret_cast<u32x4*>(q_rows + n * 1024 + lane * 16) = q_piece[n];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    read_fragments();
     L = rt.L;
     cnt = rt.cnt;
     if (e_ok) gent = gather_entry_of(p, s_sel, rt, rl, e_u, b, h);
@@ -2226,6 +2266,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile<D>(ic, issued);
   if (!p.draft_mask) rmask = qi >= 63 ? ~0ull : ((2ull << qi) - 1ull);
   if (!row_valid) rmask = 0;
+  if (MODE != kSelect) {
+    wait_row_tiles<D>(issued);                           // (the rows were requested in front of the tiles)
+    read_fragments();
+  }
 
   // Which slots of each tile hold a real token: wavefront w knows it for group w of every tile
   // (lane u: the workgroup's u-th tile); the groups' four-bit masks meet in LDS once, and lane u
