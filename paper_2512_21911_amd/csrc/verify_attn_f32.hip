@@ -157,13 +157,16 @@ __device__ __forceinline__ MergedChunk merge_chunk(const AttnParams& p, int64_t 
 }
 
 // grid: (n_splits, Hkv, B * row_groups)
-template <typename T, int D, bool SELECT>
+// SELECT: see f32_retrieves; kByWavefronts: up to kWaveSelectBlocks blocks.
+constexpr int kNoSelection = 0, kByWorkgroup = 1, kByWavefronts = 2;
+template <typename T, int D, int SELECT>
 __global__ __launch_bounds__(kThreads) void verify_attn_f32_kernel(AttnParams p, int row_groups) {
   constexpr int NJ = D / 16;                  // 16-channel steps of the first product
   constexpr int NH = D / 64;                  // four-channel pieces of a V row per lane
   constexpr int kPitch = D + 4;               // floats per parked row
   constexpr int NCH = D / (4 * kScoreLanes);  // four-channel pieces of a representative per lane
-  constexpr int kRetrievalBytes = (D + kMaxSelectBlocks + kTableEntries) * 4 + (int)sizeof(SelectScratch);
+  constexpr int kSelectBytes = SELECT == kByWavefronts ? sizeof(WaveSelectScratch) : sizeof(SelectScratch);
+  constexpr int kRetrievalBytes = (D + kMaxSelectBlocks + kTableEntries) * 4 + kSelectBytes;
   constexpr int kParkedBytes = kWaves * kHalf * kPitch * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[SELECT && kRetrievalBytes > kParkedBytes ? kRetrievalBytes : kParkedBytes];
   __shared__ float s_m[kWaves][kHalf], s_l[kWaves][kHalf];
@@ -192,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_f32_kernel(AttnParams p,
   const int di = row_ok ? row / p.G : 0;      // draft index of this lane's row
   const int hq = h * p.G + (row_ok ? row - di * p.G : 0);
   const int32_t* const table_row = p.table + (int64_t)b * p.kv.max_pages;
-  int32_t* const s_table = reinterpret_cast<int32_t*>(smem + (D + kMaxSelectBlocks) * 4 + sizeof(SelectScratch));
+  int32_t* const s_table = reinterpret_cast<int32_t*>(smem + (D + kMaxSelectBlocks) * 4 + kSelectBytes);
   const bool table_in_lds = SELECT && p.kv.page_size != 0 && p.kv.max_pages <= kTableEntries;
 
   const int tiles_d = (p.gamma + kTile - 1) / kTile;
@@ -257,7 +260,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_f32_kernel(AttnParams p,
     float* const s_q0 = reinterpret_cast<float*>(smem);
     uint32_t* const s_keys = reinterpret_cast<uint32_t*>(smem + D * 4);
     SelectScratch* const sc = reinterpret_cast<SelectScratch*>(smem + (D + kMaxSelectBlocks) * 4);
-    for (int i = tid; i < 4 * 256; i += kThreads) (&sc->hist[0][0])[i] = 0;
+    WaveSelectScratch* const wsc = reinterpret_cast<WaveSelectScratch*>(sc);
+    if constexpr (SELECT == kByWavefronts) clear_counts(wsc, tid);
+    else
+      for (int i = tid; i < 4 * 256; i += kThreads) (&sc->hist[0][0])[i] = 0;
     if (tid < D) s_q0[tid] = mean_query_channel<T>(heads, q0, p.G, D);
     __syncthreads();
     const int nb = (L + p.block_size - 1) / p.block_size;
@@ -279,7 +285,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_f32_kernel(AttnParams p,
         if (sub == 0 && j < nb) {
           const uint32_t key = (j < p.n_sink || j >= nb - p.n_local) ? 0xffffffffu : score_key(v + 0.0f);
           s_keys[j] = key;
-          atomicAdd(&sc->hist[0][key >> 24], 1u);
+          if constexpr (SELECT == kByWavefronts) count_key(wsc, key);
+          else atomicAdd(&sc->hist[0][key >> 24], 1u);
         }
       }
     }
@@ -289,8 +296,12 @@ __global__ __launch_bounds__(kThreads) void verify_attn_f32_kernel(AttnParams p,
         if (tid + u * kThreads < p.kv.max_pages) s_table[tid + u * kThreads] = table_own[u];
     }
     __syncthreads();
-    if (cnt > 0) workgroup_select(s_keys, sc, nb, cnt, s_sel, tid, lane, wave, true);
-    __syncthreads();
+    if constexpr (SELECT == kByWavefronts) {
+      if (cnt > 0) wave_select(s_keys, wsc, nb, cnt, s_sel, lane);
+    } else {
+      if (cnt > 0) workgroup_select(s_keys, sc, nb, cnt, s_sel, tid, lane, wave, true);
+      __syncthreads();
+    }
     if (split == 0 && rg == 0) {
       for (int i = tid; i < p.k_blocks; i += kThreads) p.sel_idx_out[(int64_t)pair * p.k_blocks + i] = i < cnt ? s_sel[i] : -1;
       if (tid == 0) p.sel_cnt_out[pair] = cnt;
@@ -458,8 +469,9 @@ template <typename T, int D>
 hipError_t launch(const AttnParams& p, hipStream_t st) {
   const int row_groups = p.Mpad / kRows;
   const dim3 grid(p.n_splits, p.Hkv, p.B * row_groups);
-  if (p.reps) hipLaunchKernelGGL((verify_attn_f32_kernel<T, D, true>), grid, dim3(kThreads), 0, st, p, row_groups);
-  else hipLaunchKernelGGL((verify_attn_f32_kernel<T, D, false>), grid, dim3(kThreads), 0, st, p, row_groups);
+  if (!p.reps) hipLaunchKernelGGL((verify_attn_f32_kernel<T, D, kNoSelection>), grid, dim3(kThreads), 0, st, p, row_groups);
+  else if (p.nb_max <= kWaveSelectBlocks) hipLaunchKernelGGL((verify_attn_f32_kernel<T, D, kByWavefronts>), grid, dim3(kThreads), 0, st, p, row_groups);
+  else hipLaunchKernelGGL((verify_attn_f32_kernel<T, D, kByWorkgroup>), grid, dim3(kThreads), 0, st, p, row_groups);
   return hipGetLastError();
 }
 
