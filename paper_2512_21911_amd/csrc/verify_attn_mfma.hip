@@ -64,6 +64,8 @@
 // bypassing loads are served).  Otherwise partials and records are written through to memory.
 #include <hip/hip_bf16.h>
 
+#include <type_traits>
+
 #include "svf_device.h"
 #include "svf_select.h"
 
@@ -82,7 +84,8 @@ constexpr int kRowBytes = 256;
 constexpr int kTileBytes = kTile * kRowBytes;          // 8 KB
 template <int D> constexpr int kStageBytes = D == 128 ? 2 * kTileBytes : kTileBytes;
 template <int D> constexpr int kTileLoads = D == 128 ? 16 : 8;   // load instructions of a tile
-constexpr int kScratchBytes = 16 * 1024;               // retrieval: one region for the scratch arrays, one for the page-table row
+// retrieval: a region for the scratch arrays, one for the page-table row, one for the query rows
+constexpr int kScratchBytes = 16 * 1024, kFewScratchBytes = 36 * 1024, kTableBytes = 16 * 1024;
 // A split's partial row is 256 bytes for both: D = 128 in bf16, D = 64 in fp32.
 constexpr int kMaxTiles = 4;         // tiles a wavefront may own (processed one after the other)
 constexpr int kXcds = 8;
@@ -855,6 +858,7 @@ constexpr int kResolve = 0;   // sel_idx / sel_cnt in memory, page table walked 
 constexpr int kGather = 1;    // gather list left behind by an earlier selection
 constexpr int kSelect = 2;    // the workgroup retrieves for itself (scores + top-N), builds its own
                               // gather entries, then as kGather
+constexpr int kSelectFew = 3; // kSelect of up to kWaveSelectBlocks blocks: every workgroup scores all of them, every wavefront selects
 constexpr int kTableLoads = 8;   // page-table entries a thread stages in LDS (rows up to 8 * kThreads pages)
 
 // ---- retrieval inside the attention kernel (anchor layers) ------------------------------------
@@ -918,7 +922,12 @@ __device__ __forceinline__ void load_score_batch(const AttnParams& p, const floa
   }
 }
 
-template <int D>
+// FEW: up to kWaveSelectBlocks blocks per sequence.  Two rows of representatives per lane group cost less than the exchange, and
+// wave_select has no barriers.  A kernel of its own: in one with the exchange and the workgroup's selection either way costs the
+// other's registers and instructions.  us per anchor launch, by the exchange and the workgroup -> so: 64 blocks, 8 pairs of 33 tiles 10.6 -> 9.3;
+// 128 blocks, 8 pairs of 33 tiles 11.0 -> 10.0, 32 pairs of 33 12.9 -> 11.8 and of 65 15.3 -> 14.4, 16 pairs of 80 rows 14.85 -> 13.5, 32 pairs at
+// d = 64 12.6 -> 11.7.  (256 blocks at d = 64 scored by everybody: 10.4 -> 10.8.)
+template <int D, bool FEW>
 __device__ __forceinline__ RetrievalLoads<D> issue_retrieval_loads(const AttnParams& p, int b, int h, int pair, int split,
                                                                 int xgroup, int rot, int tid, int vzero) {
   RetrievalLoads<D> R;
@@ -932,10 +941,7 @@ __device__ __forceinline__ RetrievalLoads<D> issue_retrieval_loads(const AttnPar
   // into addresses afterwards costs no further trip to memory
   R.table_row = p.table + (int64_t)b * p.kv.max_pages;
   R.table_in_lds = p.kv.page_size != 0 && p.kv.max_pages <= kTableLoads * kThreads;
-// (up to 128 blocks everybody scores all of them: two rows of representatives per lane group cost less than the
-  // exchange.  us per anchor launch, 128 blocks: 32 pairs of 33 tiles 12.9 -> 12.7, 16 pairs of 80 rows 14.85 -> 14.2; 8 pairs and d = 64 the
-  // same; 256 blocks at d = 64: 10.4 -> 10.8)
-  R.share_scores = p.n_splits >= 2 && p.nb_max > 128;
+  R.share_scores = !FEW && p.n_splits >= 2;
   R.epoch_word = p.epochs[xgroup + vzero];
   R.rot = rot;
   R.table_wide = (p.kv.max_pages & 3) == 0 && (reinterpret_cast<uintptr_t>(p.table) & 15) == 0;
@@ -975,26 +981,31 @@ struct Retrieved {
 };
 
 // Scores, exchange, selection.  On return s_sel[0 .. cnt) holds the kept blocks (ascending) and
-// every thread has passed the barrier behind the selection.  The scratch arrays live in stage 0
-// and the page-table row in stage 1 (stages 2 and up are the caller's); the caller must not stream
+// (FEW: for the wavefront that looks at it) every thread has passed the barrier behind the selection.  The scratch arrays
+// and the page-table row live at the front of the stages; the caller must not stream
 // into them before its own next barrier.  L_raw: the sequence length as loaded (per lane, not yet uniform).
 // meanwhile(): work of the caller's that may run behind the first barrier (what the caller wrote
 // to its stages before the call is visible there) while the other workgroups' keys are on their way.
-template <int D, typename Meanwhile>
+template <int D, bool FEW, typename Meanwhile>
 __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, RetrievalLoads<D>& R, unsigned char* smem,
                                                      int32_t* s_sel, int* s_exchange_failed, int L_raw, int pair,
                                                      int split, int xgroup, int tid, int lane, int wave,
                                                      Meanwhile&& meanwhile) {
-  int32_t* s_table = reinterpret_cast<int32_t*>(smem + kScratchBytes);
+  int32_t* s_table = reinterpret_cast<int32_t*>(smem + (FEW ? kFewScratchBytes : kScratchBytes));
   float* s_q0 = reinterpret_cast<float*>(smem);
   uint32_t* s_keys = reinterpret_cast<uint32_t*>(smem + D * 4);
-  SelectScratch* s_sc = reinterpret_cast<SelectScratch*>(smem + D * 4 + kMaxSelectBlocks * 4);
+  typedef typename std::conditional<FEW, WaveSelectScratch, SelectScratch>::type Counts;
+  constexpr int kKeys = FEW ? kWaveSelectBlocks : kMaxSelectBlocks;
+  Counts* s_sc = reinterpret_cast<Counts*>(smem + D * 4 + kKeys * 4);
+  static_assert(D * 4 + kKeys * 4 + sizeof(Counts) <= (FEW ? kFewScratchBytes : kScratchBytes), "the scratch arrays fit their region");
   const int sub = tid % kScoreLanes, jrow = tid / kScoreLanes;
   const float* rp = reps_lane_ptr<D>(p, pair, tid);
   uint64_t* const xk = p.xkeys + (int64_t)xgroup * p.nb_max;
 
   if (tid < D) s_q0[tid] = mean_query_channel<__hip_bfloat16>(R.q0h, R.q0ch, p.G, D);
-  for (int i = tid; i < 4 * 256; i += kThreads) (&s_sc->hist[0][0])[i] = 0;
+  if constexpr (FEW) clear_counts(s_sc, tid);
+  else
+    for (int i = tid; i < 4 * 256; i += kThreads) (&s_sc->hist[0][0])[i] = 0;
   if (tid == 0) *s_exchange_failed = 0;
   if (R.table_in_lds) {
     if (R.table_wide) {
@@ -1035,7 +1046,9 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
         if (sub == 0 && j < nb) {
           const uint32_t key = (j < p.n_sink || j >= nb - p.n_local) ? 0xffffffffu : score_key(v + 0.0f);
           s_keys[j] = key;
-          if (publish) {
+          if constexpr (FEW) {
+            count_key(s_sc, key);
+          } else if (publish) {
             __hip_atomic_store(xk + j, (uint64_t)key | ((uint64_t)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             atomicAdd(&s_sc->hist[0][key >> 24], 1u);
           }
@@ -1044,6 +1057,7 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
     }
   };
   bool score_alone = !R.share_scores;
+  if constexpr (!FEW)
   if (R.share_scores) {
     // this workgroup's share (nb <= 1024 = 16 passes, at least two splits: one batch), then
     // the others' keys: a key is valid once its word carries this call's tag.  The wait is
@@ -1088,8 +1102,9 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
   if (score_alone) {                                   // (the same for the whole workgroup)
     // (a starved exchange has left some keys counted: the selection counts for itself; everybody is
     // past the barrier behind the exchange, and the barrier below comes before the selection's adds)
-    if (R.share_scores)
-      for (int i = tid; i < 256; i += kThreads) s_sc->hist[0][i] = 0;
+    if constexpr (!FEW)
+      if (R.share_scores)
+        for (int i = tid; i < 256; i += kThreads) s_sc->hist[0][i] = 0;
     const bool loaded = !R.share_scores;               // the up-front batch was this one
     for (int f = 0; f * 64 < nb; f += kScoreBatch) {
       if (!(loaded && f == 0)) load_score_batch<D>(p, rp, jrow, f, 1, true, R.rot, R.r);
@@ -1097,8 +1112,12 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
     }
     __syncthreads();                                   // (after an exchange the barrier above has done this)
   }
-  if (out.cnt > 0) workgroup_select(s_keys, s_sc, nb, out.cnt, s_sel, tid, lane, wave, !score_alone);
-  __syncthreads();
+  if constexpr (FEW) {
+    if (out.cnt > 0) wave_select(s_keys, s_sc, nb, out.cnt, s_sel, lane);
+  } else {
+    if (out.cnt > 0) workgroup_select(s_keys, s_sc, nb, out.cnt, s_sel, tid, lane, wave, !score_alone);
+    __syncthreads();
+  }
   return out;
 }
 
@@ -1264,7 +1283,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   __shared__ uint32_t sm_ticket;                   // once wavefront 0 has its ticket: slices left to the last arriver, and the top bit
   __shared__ int sm_own_ready;                     // wavefronts 0 .. 3 that have left their part of the own rows in LDS
   __shared__ int sm_one_xcd;                       // every workgroup of the group is known to run on this XCD
-  __shared__ int32_t s_sel[MODE == kSelect ? kMaxSelectBlocks : 1];   // kept blocks, ascending
+  __shared__ int32_t s_sel[MODE >= kSelect ? kMaxSelectBlocks : 1];   // kept blocks, ascending
   __shared__ int s_exchange_failed;
 
   // The kernel arguments are read piecemeal further down, and every scalar-memory wait is a wait
@@ -1338,8 +1357,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   }
   // (retrieval only) what the retrieval needs goes out first, ahead of the query fragments
   RetrievalLoads<D> rl;
-  if (MODE == kSelect)
-    rl = issue_retrieval_loads<D>(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
+  if (MODE >= kSelect)
+    rl = issue_retrieval_loads<D, MODE == kSelectFew>(p, b, h, pair, split, group, (split + rg * p.n_splits) % kScoreBatch, tid, vzero);
   const int32_t* table_row = p.table + (int64_t)b * p.kv.max_pages;
   // With a gather list the tile loads wait for nothing but their gather entries.  Where a
   // wavefront has one tile (kOneTile) the entries (with the draft mask and the pair's block
@@ -1373,10 +1392,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // A retrieving workgroup has barriers ahead anyway: its 32 query rows come in once (16 bytes
   // per thread) and reach the wavefronts' registers through LDS (chunk c of row r at position
   // c ^ (r & 15)), instead of eight loads per lane in each of the eight wavefronts.
-  unsigned char* const q_stage = smem + 2 * kScratchBytes;
+  unsigned char* const q_stage = smem + (MODE == kSelectFew ? kFewScratchBytes : kScratchBytes) + kTableBytes;
   constexpr int kQChunks = D / 8;        // 16-byte chunks of a query row
   u32x4 qpiece = {0u, 0u, 0u, 0u};
-  if (MODE == kSelect && tid < 32 * kQChunks) {
+  if (MODE >= kSelect && tid < 32 * kQChunks) {
     const int r = tid / kQChunks, rrow = row0 + r;
     int ri = 0, rj = 0;
     if (rrow < p.M) {
@@ -1386,7 +1405,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     qpiece = *reinterpret_cast<const u32x4*>(static_cast<const __hip_bfloat16*>(p.q) +
                                              (((int64_t)b * p.gamma + ri) * p.Hq + h * p.G + rj) * D + tid % kQChunks * 8);
   }
-  if (MODE != kSelect && SHARE != kPairsFirst) {
+  if (MODE < kSelect && SHARE != kPairsFirst) {
     const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(p.q) +
                                  (((int64_t)b * p.gamma + qi) * p.Hq + h * p.G + qj) * D + g * 8;
     if constexpr (MODE == kGather) {
@@ -1427,8 +1446,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
 
   int L = 0;
   if (MODE != kGather && SHARE == kAsPlanned) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
-  if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
-  if (MODE == kSelect && tid < 32 * kQChunks) {
+  if (MODE >= kSelect) issue_first_score_batch(p, rl, pair, split, tid);
+  if (MODE >= kSelect && tid < 32 * kQChunks) {
     const int r = tid / kQChunks;
     *reinterpret_cast<u32x4*>(q_stage + r * (D * 2) + ((tid % kQChunks ^ (r & (kQChunks - 1))) << 4)) = qpiece;
   }
@@ -1479,9 +1498,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     L = min(max(L, 0), p.max_seq_len);
     clear_draft_stage();
   }
-  if (MODE == kSelect) {
+  if (MODE >= kSelect) {
     epoch_word = rl.epoch_word;
-    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, group, tid, lane, wave, [&]() {
+    const Retrieved rt = retrieve_blocks<D, MODE == kSelectFew>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, group, tid, lane, wave, [&]() {
       if (computes) {
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks)
@@ -1632,7 +1651,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // stream (their acknowledgements come back long before the first tile does; stored behind the
   // stream instead, an anchor launch took 0.14 us longer).  The workgroup with the least other work
   // publishes the selection (s_sel is not a stage).
-  if (MODE == kSelect) {
+  if (MODE >= kSelect) {
     if (split == p.n_splits - 1 && rg == 0) publish_selection(p, s_sel, cnt, pair, tid);
     const int tc = gw + (lane >> 3) * NW - tiles_d;
     const int e = tc * 8 + (lane & 7);
@@ -2073,7 +2092,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   // per (tile of the workgroup, four-token group): bit s set = slot s of the group holds a real token
   __shared__ __attribute__((aligned(8))) unsigned char s_group_valid[kMaxRowTiles][kWaves];
   __shared__ int sm_last;
-  __shared__ int32_t s_sel[MODE == kSelect ? kMaxSelectBlocks : 1];
+  __shared__ int32_t s_sel[MODE >= kSelect ? kMaxSelectBlocks : 1];
   __shared__ int s_exchange_failed;
 
   {
@@ -2115,8 +2134,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     qj = row - qi * p.G;
   }
   RetrievalLoads<D> rl;
-  if (MODE == kSelect)
-    rl = issue_retrieval_loads<D>(p, b, h, pair, split, xgroup, (split + zs * S) % kScoreBatch, tid, vzero);
+  if (MODE >= kSelect)
+    rl = issue_retrieval_loads<D, MODE == kSelectFew>(p, b, h, pair, split, xgroup, (split + zs * S) % kScoreBatch, tid, vzero);
   // gather entries: lane u holds (the workgroup's u-th tile, group = this wavefront).  With a gather
   // list they and the pair's block count are all the first tile requests wait for: they are loaded
   // ahead of the query fragments (loads come back in the order issued), and the first tiles are
@@ -2134,7 +2153,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   auto load_mask = [&]() {
     if (p.draft_mask) rmask = p.draft_mask[p.mask_per_batch ? (int64_t)b * p.gamma + qi : qi];
   };
-  if (MODE != kSelect) load_mask();
+  if (MODE < kSelect) load_mask();
   bf16x8 qf[D / 16];
   // The wavefront's 32 query rows.  A fragment load takes 32 bytes of each row and costs the memory pipeline as much as
   // four whole rows do, and there are 64 of them in a workgroup; so the rows come in whole, into stages that no tile needs
@@ -2148,7 +2167,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
   auto q_place = [&](int r) { return (uint32_t)(D == 128 ? r & 15 : (r >> 1) & 7); };       // chunk c of row r sits at c ^ this
   u32x4 q_piece[kQLoads];
   auto request_q = [&]() {
-    if (MODE == kSelect && !has_rows) return;            // (elsewhere a branch would make the wait for the gather entries a wait for the rows)
+    if (MODE >= kSelect && !has_rows) return;            // (elsewhere a branch would make the wait for the gather entries a wait for the rows)
     const __hip_bfloat16* const q0 = static_cast<const __hip_bfloat16*>(p.q) + ((int64_t)b * p.gamma * p.Hq + h * p.G) * D;
 #pragma unroll
     for (int n = 0; n < kQLoads; ++n) {
@@ -2156,11 +2175,11 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
       const uint32_t grow = (uint32_t)min(row0 + r, p.M - 1), i = (uint32_t)(((uint64_t)grow * p.g_magic) >> 32);
       const uint32_t off = (i * (uint32_t)p.Hq + (grow - i * (uint32_t)p.G)) * (uint32_t)kQRow + (((uint32_t)(lane % kQLanes) ^ q_place(r)) << 4);
       const char* const src = reinterpret_cast<const char*>(q0) + off;
-      if constexpr (MODE == kSelect) q_piece[n] = *reinterpret_cast<const u32x4*>(src);
+      if constexpr (MODE >= kSelect) q_piece[n] = *reinterpret_cast<const u32x4*>(src);
       else __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(src), SVF_LDS_PTR(q_rows + n * 1024), 16, 0, 0);
     }
   };
-  if (MODE != kSelect) request_q();
+  if (MODE < kSelect) request_q();
   auto read_fragments = [&]() {
     const uint32_t at = (uint32_t)(uintptr_t)SVF_LDS_PTR(q_rows) + (uint32_t)l32 * kQRow;
     u32x4 f[D / 16];
@@ -2171,28 +2190,35 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, f[ks]);
   };
-  if (MODE == kSelect) load_mask();
+  if (MODE >= kSelect) load_mask();
   int L = 0;
   if (MODE != kGather) L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
-  if (MODE == kSelect) issue_first_score_batch(p, rl, pair, split, tid);
+  if (MODE >= kSelect) issue_first_score_batch(p, rl, pair, split, tid);
   int cnt;
   // the group's epoch word: this call's tag is its low half plus one, its high half the wait budget
   uint64_t epoch_word = 0;
-  if (MODE != kSelect) epoch_word = p.epochs[xgroup + vzero];
-  if (MODE == kSelect) {
+  if (MODE < kSelect) epoch_word = p.epochs[xgroup + vzero];
+  if (MODE >= kSelect) {
     epoch_word = rl.epoch_word;
-    const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, request_q);
-    if (has_rows) {
+    const Retrieved rt = retrieve_blocks<D, MODE == kSelectFew>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, xgroup, tid, lane, wave, request_q);
+    auto keep_q = [&]() {
+      if (has_rows) {
 #pragma unroll
-      for (int n = 0; n < kQLoads; ++n) *reinterpret_cast<u32x4*>(q_rows + n * 1024 + lane * 16) = q_piece[n];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-    }
-    read_fragments();
+        for (int n = 0; n < kQLoads; ++n) *reinterpret_cast<u32x4*>(q_rows + n * 1024 + lane * 16) = q_piece[n];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+      read_fragments();
+    };
+    // (where the rows' place and the page table's overlap: behind the barrier below)
+    constexpr int kTableEnd = (MODE == kSelectFew ? kFewScratchBytes : kScratchBytes) + kTableBytes;
+    constexpr bool kRowsOverTable = kRowStages * kStageBytes<D> - kWaves * 32 * kQRow < kTableEnd;
+    if (!kRowsOverTable) keep_q();
     L = rt.L;
     cnt = rt.cnt;
     if (e_ok) gent = gather_entry_of(p, s_sel, rt, rl, e_u, b, h);
     __syncthreads();                 // the last reads of the staged page table are done
+    if (kRowsOverTable) keep_q();
     // for the layers that reuse this retrieval (s_sel is not a stage): stored in front of the tile loop
     if (split == S - 1 && zs == 0) publish_selection(p, s_sel, cnt, pair, tid);
     if (D == 128 && e_ok && zs == 0) p.gather_out[(int64_t)pair * p.gather_groups + e_u] = gent;
@@ -2266,7 +2292,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
     for (; issued < min(n_my, kRowFirst); ++issued) issue_row_tile<D>(ic, issued);
   if (!p.draft_mask) rmask = qi >= 63 ? ~0ull : ((2ull << qi) - 1ull);
   if (!row_valid) rmask = 0;
-  if (MODE != kSelect) {
+  if (MODE < kSelect) {
     wait_row_tiles<D>(issued);                           // (the rows were requested in front of the tiles)
     read_fragments();
   }
@@ -2610,9 +2636,9 @@ int mfma_select_splits(const svf_shape_t& s) { return mfma_rows_mode(s) ? row_sp
 // workgroup that finishes last moves the group's tag on.  No page table is touched (p.kv.page_size
 // must be 0 here) and no gather list is written.
 // grid: x = kXcds * n_splits, y = ceil(pairs / kXcds)
-template <int D>
+template <int D, bool FEW>
 __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, int pairs) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kScratchBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[FEW ? kFewScratchBytes : kScratchBytes];
   __shared__ int32_t s_sel[kMaxSelectBlocks];
   __shared__ int s_exchange_failed;
   {
@@ -2630,10 +2656,10 @@ __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, i
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  RetrievalLoads<D> rl = issue_retrieval_loads<D>(p, b, h, pair, split, pair, split % kScoreBatch, tid, vzero);
+  RetrievalLoads<D> rl = issue_retrieval_loads<D, FEW>(p, b, h, pair, split, pair, split % kScoreBatch, tid, vzero);
   const int L = clamped_len(p.seq_lens, b + vzero, p.max_seq_len);
   issue_first_score_batch(p, rl, pair, split, tid);
-  const Retrieved rt = retrieve_blocks<D>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, pair, tid, lane, wave, []() {});
+  const Retrieved rt = retrieve_blocks<D, FEW>(p, rl, smem, s_sel, &s_exchange_failed, L, pair, split, pair, tid, lane, wave, []() {});
   if (split == p.n_splits - 1) publish_selection(p, s_sel, rt.cnt, pair, tid);
   if (rl.share_scores && tid == 0) {
     // every workgroup that takes a ticket has read all the keys it needed
@@ -2649,8 +2675,13 @@ __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, i
 hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st) {
   const int pairs = p.B * p.Hkv;
   const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds));
-  if (p.d == 64) hipLaunchKernelGGL(retrieve_only_kernel<64>, grid, dim3(kThreads), 0, st, p, pairs);
-  else hipLaunchKernelGGL(retrieve_only_kernel<128>, grid, dim3(kThreads), 0, st, p, pairs);
+  if (p.nb_max <= kWaveSelectBlocks) {
+    if (p.d == 64) hipLaunchKernelGGL((retrieve_only_kernel<64, true>), grid, dim3(kThreads), 0, st, p, pairs);
+    else hipLaunchKernelGGL((retrieve_only_kernel<128, true>), grid, dim3(kThreads), 0, st, p, pairs);
+  } else {
+    if (p.d == 64) hipLaunchKernelGGL((retrieve_only_kernel<64, false>), grid, dim3(kThreads), 0, st, p, pairs);
+    else hipLaunchKernelGGL((retrieve_only_kernel<128, false>), grid, dim3(kThreads), 0, st, p, pairs);
+  }
   return hipGetLastError();
 }
 
@@ -2661,7 +2692,8 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   if (row_groups >= kRowsModeFrom) {
     const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds),
                     (unsigned)((row_groups + kWaves - 1) / kWaves));
-    if (p.reps) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kSelect>), grid, dim3(kThreads), 0, st, p, pairs);
+    if (p.reps && p.nb_max <= kWaveSelectBlocks) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kSelectFew>), grid, dim3(kThreads), 0, st, p, pairs);
+    else if (p.reps) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kSelect>), grid, dim3(kThreads), 0, st, p, pairs);
     else if (D == 128 && p.gather) hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<128, kGather>), grid, dim3(kThreads), 0, st, p, pairs);
     else hipLaunchKernelGGL((verify_attn_mfma_rows_kernel<D, kResolve>), grid, dim3(kThreads), 0, st, p, pairs);
     hipError_t e = hipGetLastError();
@@ -2683,7 +2715,8 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
     else if (one_tile) hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, kOneTilePerWave>), grid, dim3(kThreads), 0, st, p, pairs); \
     else hipLaunchKernelGGL((verify_attn_mfma_kernel<DIM, MODE, kManyTiles>), grid, dim3(kThreads), 0, st, p, pairs);                    \
   } while (0)
-  if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
+  if (p.reps && p.nb_max <= kWaveSelectBlocks) SVF_LAUNCH_ATTN(D, kSelectFew);
+  else if (p.reps) SVF_LAUNCH_ATTN(D, kSelect);
   else if (D == 128 && p.gather) SVF_LAUNCH_ATTN(128, kGather);      // (the list exists at d = 128 only)
   else if (p.share_splits && (int64_t)(p.n_splits > cover ? p.n_splits : cover) * kXcds * grid.y <= 256 / row_groups + pairs)
     hipLaunchKernelGGL((verify_attn_mfma_kernel<D, kResolve, kManyTiles, kLoadsFirst>), grid, dim3(kThreads), 0, st, p, pairs);
