@@ -369,9 +369,8 @@ __device__ __forceinline__ void query_fragments_arrived(bf16x8 (&qf)[8]) {
 }
 
 // One 32-token tile against the workgroup's 32 query rows.  stage: LDS address of the stage;
-// allowed: bit t set = token t of the tile is visible to this lane's row.  Register use is kept
-// low (two wavefronts share a SIMD): fragment addresses are recomputed, K fragments come in two
-// batches of four, the V rows of the second half reuse the registers of the first.
+// allowed: bit t set = token t of the tile is visible to this lane's row.  Fragment addresses are recomputed (two
+// wavefronts share a SIMD: 256 registers each).
 // D = 64: the softmax weights keep their 24 bits (the contract of that head dimension): they enter the
 // second product as the sum of three bf16 values, each the rounding of what the ones before it leave
 // (8 + 8 + 8 bits), and the partials stay in fp32; 16 MFMA per tile, as many as D = 128 has.
@@ -1057,7 +1056,7 @@ __device__ __forceinline__ Retrieved retrieve_blocks(const AttnParams& p, Retrie
     }
   };
   bool score_alone = !R.share_scores;
-  if constexpr (!FEW)
+  if constexpr (!FEW)                                  // (no exchange at all)
   if (R.share_scores) {
     // this workgroup's share (nb <= 1024 = 16 passes, at least two splits: one batch), then
     // the others' keys: a key is valid once its word carries this call's tag.  The wait is

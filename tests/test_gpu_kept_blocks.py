@@ -1,5 +1,5 @@
 """The kept blocks of an anchor layer where the selection changes its ways: numbers of blocks around a wavefront's keys,
-around the most that every workgroup scores for itself and, in fp32, every wavefront selects from (128), budgets from one
+around the most that every workgroup scores for itself and every wavefront selects from (128), budgets from one
 block to all, and scores that are exact, so that the expected set is (many ties, one value, neighbours in fp32, forced blocks)."""
 import numpy as np
 import pytest
