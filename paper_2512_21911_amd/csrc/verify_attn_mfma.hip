@@ -2554,11 +2554,15 @@ static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64
 // eight; seventeen splits are a second pass over both), and one to a workgroup up to eight (one batch).  us per reuse / anchor launch,
 // D = 128, splits of a tile per wavefront -> these:
 //   8 pairs: 17 tiles 10.8 / 14.8 (2 splits) -> 7.3 / 10.6 (8); 33 tiles 8.8 / 12.2 (4) -> 7.5 / 10.9 (16); 65 tiles 9.4 / 13.0 (8)
-//   -> 8.8 / 12.2 (16); of 9 tiles 7.7 / 11.9 in one split, 7.2 / 10.8 in four, 7.1 / 10.3 in eight
+//   -> 8.8 / 12.2 (16)
 //   16 pairs of 33 tiles 9.6 / 13.3 (4) -> 8.0 / 11.8 (16); 32 pairs: 17 tiles 11.0 / 15.6 (2) -> 7.8 / 11.7 (8), 33 tiles 10.6 / 14.6 (4) -> 9.5 / 13.3
 //   (8); 64 pairs of 17 tiles 12.0 / 17.0 (2) -> 9.7 / 14.7 (4)
 // Nine to eleven splits cost the second batch and gain less than a tile per workgroup: 24 pairs of 33 tiles 8.9 / 12.5 with eight, 9.0 / 13.1
 // with ten, of 49 tiles 9.6 / 13.9 and 10.2 / 14.2.
+// What one workgroup can take (up to nine tiles) stays with one at D = 128: a split's partial row is bf16 there, a single workgroup
+// rounds nothing but its result.  Nine tiles of 8 pairs are 7.7 / 11.9 in one split and 7.1 / 10.3 in eight, but the error against 64 bits
+// rises from 2.2e-4 to 2.6e-4 (rms); from two splits on, more of them make it smaller (1.42e-4 in four, 1.34e-4 in sixteen).  At
+// D = 64 the partials are fp32, and the line does not hold.
 static int64_t tiles_of(const svf_shape_t& s) {
   return ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
 }
@@ -2571,7 +2575,7 @@ int mfma_splits(const svf_shape_t& s, bool full) {
   const int64_t lo = (tiles + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
   const int64_t filled = (tiles - 1 + kWaves - 1) / kWaves > 0 ? (tiles - 1 + kWaves - 1) / kWaves : 1;
   int64_t most = filled;
-  if (!full) {
+  if (!full && (filled > 1 || s.d == 64)) {
     int64_t thin = tiles - 1 < 8 ? tiles - 1 : (tiles - 1) / 2;
     if (thin < 8 && tiles > 8) thin = 8;
     if (thin > 16) thin = 16;

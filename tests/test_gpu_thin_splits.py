@@ -1,9 +1,12 @@
 """Attention whose tiles are spread over more workgroups than their wavefronts would need, against the CPU oracle:
 one to three tiles per workgroup, splits without a tile, up to sixteen splits, two row groups, lists shorter than the
-plan, with all step modes on one workspace (full_parity() asks for the same blocks and the same bits)."""
+plan, with all step modes on one workspace (full_parity() asks for the same blocks and the same bits).  What one workgroup
+can take is rounded once."""
 import pytest
+import torch
 
-from svf_harness import full_parity
+import workloads as W
+from svf_harness import DeviceRun, full_parity, to_gpu
 from test_gpu_parity import small
 
 pytestmark = pytest.mark.gpu
@@ -11,7 +14,7 @@ pytestmark = pytest.mark.gpu
 CASES = {
     "one_tile_and_the_draft": small(B=1, Hq=8, Hkv=2, gamma=2, T=200, block_size=32, k_blocks=1, page_size=0),
     "draft_only_splits_empty": small(B=2, Hq=8, Hkv=2, gamma=3, T=300, k_blocks=4, min_len=1),
-    "nine_tiles_eight_splits": small(B=1, Hq=8, Hkv=8, gamma=4, T=900, k_blocks=4),
+    "nine_tiles_one_split": small(B=1, Hq=8, Hkv=8, gamma=4, T=900, k_blocks=4),
     "seventeen_tiles_eight_splits": small(B=4, Hq=32, Hkv=8, gamma=8, T=1100, k_blocks=8),
     "eighteen_tiles_nine_to_eight": small(B=3, Hq=8, Hkv=8, gamma=3, T=1100, block_size=32, k_blocks=17),
     "33_tiles_sixteen_splits": small(B=1, Hq=32, Hkv=8, gamma=5, T=1500, k_blocks=16, page_size=0),
@@ -21,6 +24,9 @@ CASES = {
     "two_row_groups_sixteen_splits": small(B=1, Hq=32, Hkv=8, gamma=16, tree_depth=5, T=2000, k_blocks=17),
     "two_draft_tiles": small(B=1, Hq=2, Hkv=2, gamma=40, tree_depth=5, T=900, k_blocks=6),
     "ragged_lists_shorter_than_the_plan": small(B=4, Hq=8, Hkv=4, gamma=6, T=2500, k_blocks=20, min_len=40),
+    "d64_one_tile_and_the_draft": small(B=1, Hq=8, Hkv=2, d=64, gamma=2, T=200, block_size=32, k_blocks=1, page_size=0),
+    "d64_draft_only_splits_empty": small(B=2, Hq=8, Hkv=2, d=64, gamma=3, T=300, k_blocks=4, min_len=1),
+    "d64_nine_tiles_eight_splits": small(B=1, Hq=8, Hkv=8, d=64, gamma=4, T=900, k_blocks=4),
     "d64_33_tiles": small(B=3, Hq=32, Hkv=8, d=64, gamma=7, T=1500, k_blocks=16, min_len=200),
     "d64_seventeen_tiles_two_row_groups": small(B=1, Hq=32, Hkv=8, d=64, gamma=10, T=1100, k_blocks=8),
 }
@@ -30,3 +36,23 @@ CASES = {
 def test_thin_splits(name):
     r = full_parity(CASES[name])
     print(f"[thin splits] {name}: max_abs_err={r['max_abs_err']:.3e} near_ties={r['near_ties']}", flush=True)
+
+
+@pytest.mark.parametrize("d, k_blocks", [(128, 1), (128, 2), (128, 4), (64, 1), (64, 4), (64, 16)])
+def test_short_lists_are_rounded_once(d, k_blocks):
+    """A query of zeros weighs every key alike: weights and their sum are exact, the output is the mean of the values,
+    and where nothing but the result is held in 16 bits it is off by half a bfloat16 step, plus n fp32 roundings."""
+    T = 64 * k_blocks
+    cfg = small(B=1, Hq=32, Hkv=8, d=d, gamma=4, T=T, k_blocks=k_blocks, page_size=0)
+    x = W.make_layer(cfg)
+    x["q"] = torch.zeros_like(x["q"])
+    run = DeviceRun(cfg, to_gpu(x)).block_reps().score_select().verify_attn(mask=None).sync()
+    length = int(x["seq_lens"][0])
+    v, vd = x["v_pool"][0, :length].double(), x["v_draft"][0].double()          # [T][Hkv][d], [gamma][Hkv][d]
+    for i in range(cfg.gamma):
+        keys = torch.cat([v, vd[:i + 1]])
+        mean = keys.mean(0)
+        half = 2.0 ** (torch.frexp(mean.float())[1].double() - 9)
+        bound = half + len(keys) * 2.0 ** -23 * keys.abs().mean(0)
+        got = run.out[0, i].double().cpu().view(cfg.Hkv, cfg.Hq // cfg.Hkv, d)
+        assert ((got - mean[:, None]).abs() <= bound[:, None]).all(), (i, d, k_blocks)
