@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       // D = 64: tiles to the splits in turn; eight at a time, the last split of a pair would have as little as one tile and the
       // others a second one for each wavefront.  D = 128, whose partial rows are bf16: eight at a time all the same, because a split
       // that outweighs the others is rounded like the result and adds little to its error; dealt in turn, 120 blocks of 128 over
-      // eight heads had 1.010e-4 (rms, against 64 bits) instead of 1.002e-4, and nine of twelve such shapes a little more than before
+      // eight heads had 1.010e-4 (rms, against 64 bits) instead of 1.002e-4, and eight of ten such shapes a little more than before
       // (four sequences, 256 blocks of 64 over eight heads: 18.0 us in turn, 18.9 so).
       gw = D == 64 ? wave * S + split : split * kWaves + wave;
     } else if (!planned) {
