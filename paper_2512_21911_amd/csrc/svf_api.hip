@@ -21,6 +21,7 @@ int mfma_splits(const svf_shape_t& s, bool full);
 int mfma_shared_splits(const svf_shape_t& s);
 bool mfma_rows_mode(const svf_shape_t& s);
 int mfma_rows_splits(const svf_shape_t& s);
+bool mfma_partials_f32(const svf_shape_t& s, int n_splits);
 int mfma_select_splits(const svf_shape_t& s);
 
 namespace {
@@ -133,7 +134,7 @@ AttnPlan plan_attn(const svf_shape_t& s, bool allow_mfma) {
   }
   if (shared > pl.n_splits) {
     // more splits for a pair as long as a workspace that fits the static array without them still does
-    const size_t now = pl.bytes + scores_bytes(s), per_split = pairs * pl.Mpad * (s.d * (s.d == 128 ? 2 : 4) + 16);
+    const size_t now = pl.bytes + scores_bytes(s), per_split = pairs * pl.Mpad * (s.d * (mfma_partials_f32(s, pl.n_splits) ? 4 : 2) + 16);
     const size_t room = now <= kStaticScratchBytes ? (kStaticScratchBytes - now) / per_split : shared;
     pl.split_stride = pl.n_splits + (int)(room < (size_t)(shared - pl.n_splits) ? room : shared - pl.n_splits);
     lay_out(s, pl);
@@ -149,9 +150,10 @@ void lay_out(const svf_shape_t& s, AttnPlan& pl) {
   size_t off = 0;
   pl.off_tickets = off;
   off += align_up(pl.groups * kTicketWords * sizeof(uint64_t));
-  // partial outputs: fp32 (fp32 kernel, bf16 matrix-core kernels at d = 64) or bf16 (d = 128) per split and row
+  // partial outputs per split and row: fp32, or bf16 (some plans of the bf16 matrix-core kernels)
   pl.off_o = off;
-  off += align_up(pairs * pl.split_stride * pl.Mpad * s.d * (pl.mfma && s.d == 128 ? sizeof(uint16_t) : sizeof(float)));
+  off += align_up(pairs * pl.split_stride * pl.Mpad * s.d *
+                  (pl.mfma && !mfma_partials_f32(s, pl.n_splits) ? sizeof(uint16_t) : sizeof(float)));
   // (maximum, denominator) per split and row: two floats for the fp32 kernel, 16 bytes for the bf16
   // matrix-core kernels (a tagged record)
   pl.off_m = off;

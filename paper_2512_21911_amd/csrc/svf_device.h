@@ -98,8 +98,8 @@ struct AttnParams {
   float* lse;                  // may be null
   // split partials.  fp32 kernel: fp32 unnormalised outputs [B][Hkv][S][Mpad][d] with their running
   // maxima (log2 domain) and denominators side by side in part_m.  bf16 matrix-core kernels: outputs
-  // normalised by their own denominator, [B][Hkv][S][Mpad] rows of 256 bytes (d = 128: rounded to
-  // bf16, d = 64: fp32) in part_o, and 16-byte records (maximum, tag, denominator, tag) in part_rec, valid for the call
+  // normalised by their own denominator, [B][Hkv][S][Mpad] rows in part_o (fp32 at d = 64 and where a plan
+  // spreads its tiles thinly, else rounded to bf16), and 16-byte records (maximum, tag, denominator, tag) in part_rec, valid for the call
   // whose tag both halves carry.  part_m and part_rec name the same region.
   float* part_o;
   float* part_m;               // [B][Hkv][S][Mpad][2]

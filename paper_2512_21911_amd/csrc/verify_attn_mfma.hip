@@ -43,8 +43,8 @@
 //
 // Merge.  The computing wavefronts combine through LDS (log-sum-exp rule).  With one split the
 // workgroup writes out / lse itself.  Otherwise every workgroup of a (pair, row group) stores a
-// partial (normalised output in bf16, (m, l) in fp32 inside a 16-byte record that carries the
-// call's tag twice) and then merges a slice of the rows itself: two of its wavefronts wait (a
+// partial (normalised output, see Partials, and (m, l) in fp32 inside a 16-byte record that carries the
+// call's tag twice) and then merges a slice of the rows itself: two or four of its wavefronts wait (a
 // bounded number of polls) until every record of the other splits' rows of that slice shows the
 // tag, fetch those partials (forming the weights while they are on their way), and sum in split
 // order, taking the own split from LDS.  No workgroup
@@ -86,7 +86,6 @@ template <int D> constexpr int kStageBytes = D == 128 ? 2 * kTileBytes : kTileBy
 template <int D> constexpr int kTileLoads = D == 128 ? 16 : 8;   // load instructions of a tile
 // retrieval: a region for the scratch arrays, one for the page-table row, one for the query rows
 constexpr int kScratchBytes = 16 * 1024, kFewScratchBytes = 36 * 1024, kTableBytes = 16 * 1024;
-// A split's partial row is 256 bytes for both: D = 128 in bf16, D = 64 in fp32.
 constexpr int kMaxTiles = 4;         // tiles a wavefront may own (processed one after the other)
 constexpr int kXcds = 8;
 constexpr float kRescaleGap = 8.0f;  // log2 units the running maximum may lag behind
@@ -492,10 +491,29 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
   }
 }
 
-// Value c of a 16-byte (or 8-byte) chunk of a partial row: bf16 at D = 128, fp32 at D = 64.
-template <int D, typename Chunk>
+// A split's partial row: bf16 at D = 128, fp32 at D = 64 and, at both, in plans whose tiles are spread thinly.  There a list
+// that one workgroup would have taken, and rounded once, is cut into as many partials as the plan has splits: in bf16 each of them
+// is rounded and their sum again (keys weighed alike, eight tiles over eight splits: 2.4e-4 instead of 1.7e-4 of error, rms).
+// The sixteen-byte pieces of an fp32 row of 128 channels lie as the combining threads hold them: piece 8j + c is channels
+// 16c + 4j .. 16c + 4j + 3 (eight threads of a row then store 128 bytes at once).
+// CH: channels per merging thread; kWaves: wavefronts that merge.
+template <int D_, bool F32_>
+struct Partials {
+  static constexpr int D = D_;
+  static constexpr bool kF32 = F32_;
+  static constexpr int kBytes = D * (kF32 ? 4 : 2);
+  static constexpr int kMergeWaves = kBytes == 512 ? 4 : 2;
+  static constexpr int kWide = kF32 ? 4 : 8;            // channels per thread with eight rows per pass
+  static __device__ __forceinline__ int channel(int piece, int ch) {      // first channel of a piece of ch channels
+    return kBytes == 512 ? 16 * (piece & 7) + 4 * (piece >> 3) : piece * ch;
+  }
+};
+template <int D> using UsualPartials = Partials<D, D == 64>;
+
+// Value c of a 16-byte (or 8-byte) chunk of a partial row.
+template <bool F32, typename Chunk>
 __device__ __forceinline__ float chunk_value(const Chunk& t, int c) {
-  if constexpr (D == 64) return __uint_as_float(t[c]);
+  if constexpr (F32) return __uint_as_float(t[c]);
   else return (c & 1) ? bf16_hi(t[c >> 1]) : bf16_lo(t[c >> 1]);
 }
 
@@ -547,7 +565,7 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, int64_t g_row,
       const float w = pm[u] != -INFINITY ? fast_exp2(pm[u] - mb) * pl[u] : 0.f;
       l_acc += w;
 #pragma unroll
-      for (int c = 0; c < CH; ++c) acc[c] += w * chunk_value<D>(t[u], c);
+      for (int c = 0; c < CH; ++c) acc[c] += w * chunk_value<D == 64>(t[u], c);
     }
     m_acc = mb;
   }
@@ -567,13 +585,13 @@ __device__ __forceinline__ void merge_splits(const AttnParams& p, int64_t g_row,
 }
 
 // ---- merging the splits of a group ----------------------------------------------------------------
-// A split's partial of a row is its output normalised by its own denominator (256 bytes) and a 16-byte
+// A split's partial of a row is its output normalised by its own denominator (Partials) and a 16-byte
 // record (maximum, tag, denominator, tag); the record is written after the output has been
 // acknowledged, so a record whose two tags are this call's vouches for the output beside it.
 // Merge rule (log-sum-exp), the same sums in the same order whoever computes them: splits in
 // order, in batches of eight, each batch brought to the running maximum.
-// The merging threads are two wavefronts (128 threads): CH channels per thread (4 or 8; at D = 64 always
-// 4), D / CH threads per row (at least sixteen), 4 or 8 rows per pass.
+// The merging threads are two wavefronts (four where a row is 512 bytes): CH channels per thread (4 or 8; of an fp32 row
+// always 4), D / CH threads per row (at least sixteen), 4 or 8 rows per pass.  PT: Partials.
 
 // Device-scope loads of what other workgroups have written through (they bypass the per-CU cache;
 // an L2 serves them, also for lines that a workgroup on another XCD has written through).  Issued
@@ -606,22 +624,20 @@ __device__ __forceinline__ void chunks_wait(T (&o)[8]) {
                :
                : "memory");
 }
-template <int CH, int D> struct ChunkOf;           // CH channels of a partial row
-template <> struct ChunkOf<4, 128> { typedef u32x2 type; };
-template <> struct ChunkOf<8, 128> { typedef u32x4 type; };
-template <> struct ChunkOf<4, 64> { typedef u32x4 type; };
-template <int D> constexpr int kWideMerge = D == 128 ? 8 : 4;   // channels per thread with eight rows per pass
+template <int CH, bool F32> struct ChunkOf;        // CH channels of a partial row
+template <> struct ChunkOf<4, false> { typedef u32x2 type; };
+template <> struct ChunkOf<8, false> { typedef u32x4 type; };
+template <> struct ChunkOf<4, true> { typedef u32x4 type; };
 
-constexpr int kMergeThreads = 128;          // wavefronts kMergeWave0 and kMergeWave0 + 1
-constexpr int kMergeWave0 = 4;
+constexpr int kMergeWave0 = 4;              // the first merging wavefront
 constexpr int kLastResortPolls = 1 << 16;   // for waits that are known to end: every writer has arrived
 
 // One merging thread's view of one pass over rows r0 .. r0 + rows per pass.
-template <int CH, int D>
+template <int CH, typename PT>
 struct MergeLane {
-  typedef typename ChunkOf<CH, D>::type Chunk;
-  static constexpr int kLanesPerRow = D / CH;                   // 32 or 16
-  static constexpr int kRowsPerPass = kMergeThreads / kLanesPerRow;
+  typedef typename ChunkOf<CH, PT::kF32>::type Chunk;
+  static constexpr int kLanesPerRow = PT::D / CH;               // 32 or 16
+  static constexpr int kRowsPerPass = PT::kMergeWaves * 64 / kLanesPerRow;
   int row;            // row of the row group (clamped to a valid one), cl: which CH channels
   int cl;
   bool active;        // the row is one of those to merge
@@ -639,7 +655,7 @@ struct MergeLane {
 };
 
 // This workgroup's own partial of the rows it merges, left in LDS by the threads that formed it:
-// [rows][256 bytes], then (maximum, denominator) per row.  own_split < 0: nothing is taken from LDS.
+// [rows][PT::kBytes], then (maximum, denominator) per row.  own_split < 0: nothing is taken from LDS.
 struct OwnRows {
   const unsigned char* o;
   const float* ml;
@@ -653,8 +669,8 @@ struct OwnRows {
 // watch / watched_for (optional): the LDS word at address `watch` is read along with every poll;
 // *watch_hit tells whether it was seen to hold `watched_for` (what the caller waits for next: by
 // the time the records are in, it has usually happened, and no further look is needed).
-template <int CH, int D>
-__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, D>& L, int64_t g_row, int S, int c0, uint32_t tag,
+template <int CH, typename PT>
+__device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, PT>& L, int64_t g_row, int S, int c0, uint32_t tag,
                                              int budget, int own_split, uint32_t watch = 0, uint32_t watched_for = 0,
                                              bool* watch_hit = nullptr) {
   const int sp = c0 + (L.cl & 15);
@@ -677,10 +693,10 @@ __device__ __forceinline__ bool poll_records(const AttnParams& p, MergeLane<CH, 
 // Requests the outputs of splits c0 + B0 .. c0 + B0 + 7 of the lane's row (past the last split: the
 // batch's first split again, weight 0 later; the own split's is fetched like the others even when
 // LDS holds it: one address chain, a step of one split's partial at a time).
-template <int CH, int D, int B0>
-__device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkOf<CH, D>::type (&t)[8], int pair, uint32_t voff,
+template <int CH, typename PT, int B0>
+__device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkOf<CH, PT::kF32>::type (&t)[8], int pair, uint32_t voff,
                                             int S, int c0) {
-  const uint64_t step = (uint64_t)p.Mpad * kRowBytes;
+  const uint64_t step = (uint64_t)p.Mpad * PT::kBytes;
   const uint64_t first = (uint64_t)(uintptr_t)p.part_o + ((uint64_t)pair * p.split_stride + (uint64_t)(c0 + B0)) * step;
   const int n = S - c0 - B0;                             // splits of this batch that exist (>= 1)
   uint64_t at = first;
@@ -696,8 +712,8 @@ __device__ __forceinline__ void fetch_batch(const AttnParams& p, typename ChunkO
 // are being fetched, and is free of branches, because the compiler does not know that the
 // registers of a hand-issued load are in flight (see merge_fetch_weigh).  m_before: the running
 // maximum in front of the batch.
-template <int CH, int D, int B0>
-__device__ __forceinline__ void batch_weights(MergeLane<CH, D>& L, int c0, const OwnRows& own, float m_before, float (&w)[8],
+template <int CH, typename PT, int B0>
+__device__ __forceinline__ void batch_weights(MergeLane<CH, PT>& L, int c0, const OwnRows& own, float m_before, float (&w)[8],
                                               float& fa, float& mb_out) {
   const int ou = own.split - c0 - B0;                  // (uniform) the own split's place in this batch
   const bool from_lds = ou >= 0 && ou < 8;
@@ -705,8 +721,8 @@ __device__ __forceinline__ void batch_weights(MergeLane<CH, D>& L, int c0, const
   // that split's record, its output in place of what is fetched (the reads are unconditional: own.o
   // and own.ml always point into LDS)
   const int orow = min(max(L.row - own.lo, 0), 31);
-  const typename ChunkOf<CH, D>::type oc =
-      *reinterpret_cast<const typename ChunkOf<CH, D>::type*>(own.o + orow * kRowBytes + L.cl * (int)sizeof(typename ChunkOf<CH, D>::type));
+  const typename ChunkOf<CH, PT::kF32>::type oc =
+      *reinterpret_cast<const typename ChunkOf<CH, PT::kF32>::type*>(own.o + orow * PT::kBytes + L.cl * (int)sizeof(typename ChunkOf<CH, PT::kF32>::type));
   const uint32_t om = __float_as_uint(own.ml[2 * orow]), ol = __float_as_uint(own.ml[2 * orow + 1]);
   L.own_chunk = (B0 == 0 || from_lds) ? oc : L.own_chunk;        // (the own split lies in one batch at most)
   const bool here = from_lds && (L.cl & 15) == B0 + ou;
@@ -729,8 +745,8 @@ __device__ __forceinline__ void batch_weights(MergeLane<CH, D>& L, int c0, const
   mb_out = mb;
 }
 
-template <int CH, int D, int B0>
-__device__ __forceinline__ void batch_accumulate(MergeLane<CH, D>& L, typename ChunkOf<CH, D>::type (&t)[8], int c0, const OwnRows& own,
+template <int CH, typename PT, int B0>
+__device__ __forceinline__ void batch_accumulate(MergeLane<CH, PT>& L, typename ChunkOf<CH, PT::kF32>::type (&t)[8], int c0, const OwnRows& own,
                                                  const float (&w)[8], float fa, float mb) {
   const int ou = own.split - c0 - B0;
   if (ou >= 0 && ou < 8) {
@@ -755,15 +771,15 @@ __device__ __forceinline__ void batch_accumulate(MergeLane<CH, D>& L, typename C
   for (int u = 0; u < 8; ++u) {
     L.l_acc += w[u];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) L.acc[c] += w[u] * chunk_value<D>(t[u], c);
+    for (int c = 0; c < CH; ++c) L.acc[c] += w[u] * chunk_value<PT::kF32>(t[u], c);
   }
   L.m_acc = mb;
 }
 
-template <int CH, int D>
-__device__ __forceinline__ void init_lane(MergeLane<CH, D>& L, int mt, int r0, int hi) {
-  const int rr = r0 + mt / MergeLane<CH, D>::kLanesPerRow;
-  L.cl = mt % MergeLane<CH, D>::kLanesPerRow;
+template <int CH, typename PT>
+__device__ __forceinline__ void init_lane(MergeLane<CH, PT>& L, int mt, int r0, int hi) {
+  const int rr = r0 + mt / MergeLane<CH, PT>::kLanesPerRow;
+  L.cl = mt % MergeLane<CH, PT>::kLanesPerRow;
   L.active = rr < hi && rr < 32;
   L.row = L.active ? rr : r0;
 #pragma unroll
@@ -773,22 +789,22 @@ __device__ __forceinline__ void init_lane(MergeLane<CH, D>& L, int mt, int r0, i
 }
 
 // The merged row goes out (CH channels per thread) with its log-sum-exp.
-template <int CH, int D>
-__device__ __forceinline__ void merged_row_address(const AttnParams& p, MergeLane<CH, D>& L, int row0, int64_t orow_pair) {
+template <int CH, typename PT>
+__device__ __forceinline__ void merged_row_address(const AttnParams& p, MergeLane<CH, PT>& L, int row0, int64_t orow_pair) {
   const int grow = row0 + L.row;
   const int oi = (int)(((uint64_t)(uint32_t)grow * p.g_magic) >> 32), oj = grow - oi * p.G;
   L.orow = (L.active && grow < p.M) ? orow_pair + (int64_t)oi * p.Hq + oj : -1;
   asm volatile("" : "+v"(L.orow));                       // worked out here, not behind the wait for the outputs
 }
-template <int CH, int D>
-__device__ __forceinline__ void store_merged(const AttnParams& p, const MergeLane<CH, D>& L) {
+template <int CH, typename PT>
+__device__ __forceinline__ void store_merged(const AttnParams& p, const MergeLane<CH, PT>& L) {
   const int64_t orow = L.orow;
   if (orow < 0) return;
   const float inv = L.l_acc > 0.f ? __builtin_amdgcn_rcpf(L.l_acc) : 0.f;   // a row that saw no key at all: zero, lse = -inf
-  typename ChunkOf<CH, 128>::type o;                     // CH bf16 values
+  typename ChunkOf<CH, false>::type o;                     // CH bf16 values
 #pragma unroll
   for (int c = 0; c < CH / 2; ++c) o[c] = pack_bf16(L.acc[2 * c] * inv, L.acc[2 * c + 1] * inv);
-  *reinterpret_cast<typename ChunkOf<CH, 128>::type*>(static_cast<__hip_bfloat16*>(p.out) + orow * D + L.cl * CH) = o;
+  *reinterpret_cast<typename ChunkOf<CH, false>::type*>(static_cast<__hip_bfloat16*>(p.out) + orow * PT::D + PT::channel(L.cl, CH)) = o;
   if (p.lse && L.cl == 0) p.lse[orow] = (L.m_acc + log2f(L.l_acc)) * 0.6931471805599453f;
 }
 
@@ -804,41 +820,41 @@ __device__ __forceinline__ void chunks_wait16(T (&a)[8], T (&b)[8]) {
 // Splits c0 .. c0 + 15 of the lane's row, once their records are in (poll_records): fetches their
 // outputs and, while those are on their way, forms the weights.  The own split's rows, if LDS holds
 // them, must be complete.
-template <int CH, int D>
-__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH, D>& L, int pair, int row0, int S,
+template <int CH, typename PT>
+__device__ __forceinline__ void merge_fetch_weigh(const AttnParams& p, MergeLane<CH, PT>& L, int pair, int row0, int S,
                                                   int c0, const OwnRows& own, int64_t orow_pair) {
-  const uint32_t voff = (uint32_t)((row0 + L.row) * kRowBytes + L.cl * (int)sizeof(typename MergeLane<CH, D>::Chunk));
+  const uint32_t voff = (uint32_t)((row0 + L.row) * PT::kBytes + L.cl * (int)sizeof(typename MergeLane<CH, PT>::Chunk));
   // (straight-line code between every hand-issued load and its wait: the compiler does not know
   // that the registers are still in flight, and a copy it places at a branch or a join in between
   // would copy what was there before)
   if (c0 + 8 < S) {
-    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, S, c0);
-    fetch_batch<CH, D, 8>(p, L.t1, pair, voff, S, c0);
-    batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
-    batch_weights<CH, D, 8>(L, c0, own, L.mb0, L.w1, L.fa1, L.mb1);
+    fetch_batch<CH, PT, 0>(p, L.t0, pair, voff, S, c0);
+    fetch_batch<CH, PT, 8>(p, L.t1, pair, voff, S, c0);
+    batch_weights<CH, PT, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
+    batch_weights<CH, PT, 8>(L, c0, own, L.mb0, L.w1, L.fa1, L.mb1);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait16(L.t0, L.t1);
   } else {
-    fetch_batch<CH, D, 0>(p, L.t0, pair, voff, S, c0);
-    batch_weights<CH, D, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
+    fetch_batch<CH, PT, 0>(p, L.t0, pair, voff, S, c0);
+    batch_weights<CH, PT, 0>(L, c0, own, L.m_acc, L.w0, L.fa0, L.mb0);
     merged_row_address(p, L, row0, orow_pair);
     chunks_wait(L.t0);
   }
 }
-template <int CH, int D>
-__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH, D>& L, int S, int c0, const OwnRows& own) {
-  batch_accumulate<CH, D, 0>(L, L.t0, c0, own, L.w0, L.fa0, L.mb0);
-  if (c0 + 8 < S) batch_accumulate<CH, D, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
+template <int CH, typename PT>
+__device__ __forceinline__ void merge_finish(const AttnParams& p, MergeLane<CH, PT>& L, int S, int c0, const OwnRows& own) {
+  batch_accumulate<CH, PT, 0>(L, L.t0, c0, own, L.w0, L.fa0, L.mb0);
+  if (c0 + 8 < S) batch_accumulate<CH, PT, 8>(L, L.t1, c0, own, L.w1, L.fa1, L.mb1);
 }
 
 // Merges rows lo <= r < hi of the row group (all passes, all splits) and writes them out.  Returns
 // false for the whole wavefront, with nothing of the current pass written, when a record was still
-// missing after `budget` polls.  Called by the two merging wavefronts, each for itself.
-template <int CH, int D>
+// missing after `budget` polls.  Called by the merging wavefronts, each for itself.
+template <int CH, typename PT>
 __device__ __forceinline__ bool merge_rows(const AttnParams& p, int S, int lo, int hi, int budget, uint32_t tag, int pair,
                                            int row0, int64_t orow_pair, int mt, const OwnRows& own) {
-  for (int r0 = lo; r0 < hi; r0 += MergeLane<CH, D>::kRowsPerPass) {
-    MergeLane<CH, D> L;
+  for (int r0 = lo; r0 < hi; r0 += MergeLane<CH, PT>::kRowsPerPass) {
+    MergeLane<CH, PT> L;
     init_lane(L, mt, r0, hi);
     if (!__any(L.active)) continue;
     for (int c0 = 0; c0 < S; c0 += 16) {
@@ -1265,13 +1281,14 @@ __device__ __forceinline__ bool share_out_splits(const AttnParams& p, int pairs,
 // cost is its instruction count: 0.5 instead of 1.0 us), four wavefronts instead of eight load
 // query fragments, and the tiles that arrive last are computed by wavefronts that have the SIMD
 // to themselves.  Also (MODE kGather): which of the up-front loads go out first, see below.
-// kThinTiles: the same where there are more splits than wavefronts need: tiles go to the splits in turn, instead of eight at a
-// time (which is 0.03 us per launch faster where all have eight).
+// kThinTiles (thin_plan): the same where there are more splits than wavefronts need: tiles go to the splits in turn, instead of
+// eight at a time (which is 0.03 us per launch faster where all have eight), and the partials are fp32.
 // SHARE: see share_out_splits.
 constexpr int kManyTiles = 0, kOneTilePerWave = 1, kThinTiles = 2;
 template <int D, int MODE, int TILES, int SHARE = kAsPlanned>
 __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p, int pairs) {
   constexpr bool kOneTile = TILES != kManyTiles;
+  typedef Partials<D, D == 64 || TILES == kThinTiles> PT;
   // one stage per wavefront, plus one for draft tile 0 (its owner then streams its cache tile
   // at the same time); after the main loop stage w becomes wavefront w's fp32 output buffer
   __shared__ __attribute__((aligned(1024))) unsigned char smem[(kWaves + 1) * kStageBytes<D>];
@@ -1762,13 +1779,13 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // ---- what happens to the workgroup's result --------------------------------------------------------
   // One split: wavefronts 0 .. 3 write out / lse.  Otherwise the splits of a group are merged by
   // all its workgroups, each a slice of p.slice_rows rows:
-  //  - wavefronts 0 .. 3 write the workgroup's partial (normalised output in bf16) through to
+  //  - wavefronts 0 .. 3 write the workgroup's partial (normalised output) through to
   //    device-coherent memory, leave the rows of the workgroup's own slice in LDS as well, and,
   //    once the stores have been acknowledged, write a record per row (maximum, tag, denominator,
   //    tag; tag = this call's);
-  //  - meanwhile wavefronts 4 and 5 wait (bounded) until the other splits' records of the slice's
-  //    rows carry the tag and fetch those partials; behind one barrier they add the own rows from
-  //    LDS, in split order (bit-stable: the same sums whoever computes them), and write out / lse.
+  //  - meanwhile wavefronts 4 and 5 (and 6 and 7 where a partial row is 512 bytes) wait (bounded) until the other splits'
+  //    records of the slice's rows carry the tag and fetch those partials; once a counter in LDS says that the own rows are
+  //    there they add those, in split order (bit-stable: the same sums whoever computes them), and write out / lse.
   //    In the workgroup that is last of its group everything but that final sum has happened by
   //    the time its own partial exists; in the others the merge is one poll and one round of loads
   //    behind the last record.  No return trip through an atomic lies on that path.
@@ -1779,14 +1796,15 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
   // before it and merges them too.  So every row is merged whatever is resident when, and every
   // wait ends.  The words of calls with an even / odd tag alternate; the last arriver clears the
   // other one and moves the call counter on (which also works under graph replay).
-  const bool single = S == 1;
+  const bool single = TILES != kThinTiles && S == 1;       // (thin plans have several)
   const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)epoch_word) + 1u;
   const int wait_polls = wait_polls_of(__builtin_amdgcn_readfirstlane((int)(uint32_t)(epoch_word >> 32)));
   uint64_t* const arrivals = p.tickets + (int64_t)group * kTicketWords + (tag & 1u);
   const int R = S == p.n_splits ? p.slice_rows : (32 + min(S, 16) - 1) / min(S, 16);
   const int lo = split * R, hi = min(lo + R, 32);            // the workgroup's own slice (empty if lo >= 32)
-  unsigned char* const own_o = x_stage;                     // [R][256 bytes], R <= 16
-  float* const own_ml = reinterpret_cast<float*>(x_stage + 16 * kRowBytes);
+  unsigned char* const own_o = x_stage;                     // [R][PT::kBytes], R <= 16
+  float* const own_ml = reinterpret_cast<float*>(x_stage + 16 * PT::kBytes);
+  static_assert(16 * PT::kBytes + 16 * 8 <= kStageBytes<D>, "the own rows fit the stage");
   int64_t pr_rec = 0;
   float mw = -INFINITY, lw = 0.f;
   const int r = tid >> 3, c16 = tid & 7;                     // (wavefronts 0 .. 3) row, block of D / 8 channels
@@ -1816,16 +1834,21 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         racc[4 * nt + 3] = __builtin_fmaf(t.w, fw[w], racc[4 * nt + 3]);
       }
     const float inv = lw > 0.f ? __builtin_amdgcn_rcpf(lw) : 0.f;
-    // 32 bytes of the partial row: sixteen channels in bf16, or eight in fp32
-    u32x4 o0, o1;
+    // this thread's part of the partial row: sixteen channels in bf16, eight in fp32, or (o2, o3 as well) sixteen in fp32
+    constexpr bool kLongRow = PT::kBytes == 512;
+    u32x4 o0, o1, o2, o3;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      if constexpr (D == 128) {
+      if constexpr (!PT::kF32) {
         o0[c] = pack_bf16(racc[2 * c] * inv, racc[2 * c + 1] * inv);
         o1[c] = pack_bf16(racc[8 + 2 * c] * inv, racc[8 + 2 * c + 1] * inv);
       } else {
         o0[c] = __float_as_uint(racc[c] * inv);
         o1[c] = __float_as_uint(racc[4 + c] * inv);
+        if constexpr (kLongRow) {
+          o2[c] = __float_as_uint(racc[8 + c] * inv);
+          o3[c] = __float_as_uint(racc[12 + c] * inv);
+        }
       }
     }
     const int orow_row = row0 + r;
@@ -1834,7 +1857,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         const int oi = (int)(((uint64_t)(uint32_t)orow_row * p.g_magic) >> 32), oj = orow_row - oi * p.G;
         const int64_t orow = orow_pair + (int64_t)oi * p.Hq + oj;
         __hip_bfloat16* dst = static_cast<__hip_bfloat16*>(p.out) + orow * D + c16 * (D / 8);
-        if constexpr (D == 128) {
+        if constexpr (!PT::kF32) {
           *reinterpret_cast<u32x4*>(dst) = o0;
           *reinterpret_cast<u32x4*>(dst + 8) = o1;
         } else {
@@ -1847,28 +1870,47 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       }
     } else {
       pr_rec = ((int64_t)pair * p.split_stride + split) * p.Mpad + orow_row;
-      // Each of the two store instructions covers whole 128-byte lines (the eight threads of a row
-      // write eight consecutive 16-byte chunks; threads c and c ^ 4 trade their second chunk): the
+      // Each store instruction covers whole 128-byte lines (the eight threads of a row write eight
+      // consecutive 16-byte chunks; in a row of 256 bytes threads c and c ^ 4 trade their second chunk): the
       // L2 then passes complete lines on instead of twice as many half-written ones.
       const bool low = c16 < 4;
-      u32x4 got;
+      u32x4 got, first, second;
+      if constexpr (!kLongRow) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) got[c] = swap_lanes_xor4(o1[c]);
-      const u32x4 first = low ? o0 : got, second = low ? got : o0;
-      char* dst = reinterpret_cast<char*>(p.part_o) + pr_rec * kRowBytes;
-      char* dst0 = dst + (low ? 2 * c16 : 2 * c16 - 7) * 16;
+        for (int c = 0; c < 4; ++c) got[c] = swap_lanes_xor4(o1[c]);
+        first = low ? o0 : got, second = low ? got : o0;
+      }
+      char* dst = reinterpret_cast<char*>(p.part_o) + pr_rec * PT::kBytes;
+      char* dst0 = dst + (kLongRow ? c16 : low ? 2 * c16 : 2 * c16 - 7) * 16;
       char* dst1 = dst + (low ? 2 * c16 + 9 : 2 * c16) * 16;
       const bool one_xcd = sm_one_xcd != 0;               // (the same for the whole workgroup)
       if (one_xcd) {
-        store_l2_16(dst0, first);
-        store_l2_16(dst1, second);
+        if constexpr (kLongRow) {
+          store_l2_16(dst0, o0);
+          store_l2_16(dst0 + 128, o1);
+          store_l2_16(dst0 + 256, o2);
+          store_l2_16(dst0 + 384, o3);
+        } else {
+          store_l2_16(dst0, first);
+          store_l2_16(dst1, second);
+        }
+      } else if constexpr (kLongRow) {
+        store_coherent16(dst0, o0);
+        store_coherent16(dst0 + 128, o1);
+        store_coherent16(dst0 + 256, o2);
+        store_coherent16(dst0 + 384, o3);
       } else {
         store_coherent16(dst0, first);
         store_coherent16(dst1, second);
       }
       if (r >= lo && r < hi) {
-        *reinterpret_cast<u32x4*>(own_o + (r - lo) * kRowBytes + c16 * 32) = o0;
-        *reinterpret_cast<u32x4*>(own_o + (r - lo) * kRowBytes + c16 * 32 + 16) = o1;
+        unsigned char* const own = own_o + (r - lo) * PT::kBytes + c16 * (kLongRow ? 16 : 32);
+        *reinterpret_cast<u32x4*>(own) = o0;
+        *reinterpret_cast<u32x4*>(own + (kLongRow ? 128 : 16)) = o1;
+        if constexpr (kLongRow) {
+          *reinterpret_cast<u32x4*>(own + 256) = o2;
+          *reinterpret_cast<u32x4*>(own + 384) = o3;
+        }
         if (c16 == 0) {
           own_ml[2 * (r - lo)] = mw;
           own_ml[2 * (r - lo) + 1] = lw;
@@ -1901,15 +1943,15 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       }
     }
   }
-  if (single || (wave != kMergeWave0 && wave != kMergeWave0 + 1)) return;      // (no barrier from here on)
+  if (single || (PT::kMergeWaves == 2 ? wave != kMergeWave0 && wave != kMergeWave0 + 1 : wave < kMergeWave0)) return;      // (no barrier from here on)
 
   const int mt = tid - kMergeWave0 * 64;
-  constexpr int WM = kWideMerge<D>;
-  const bool ch4 = D == 64 || R <= 4;                        // 4 channels per merging thread, else 8
+  constexpr int WM = PT::kWide;
+  const bool ch4 = WM == 4 || R <= 4;                        // 4 channels per merging thread, else 8
   // one pass over the rows and one batch of records: the other splits' records are waited for now
   const bool prefetch = S <= 16 && R <= 8 && lo < 32;
-  MergeLane<4, D> L4;
-  MergeLane<WM, D> L8;
+  MergeLane<4, PT> L4;
+  MergeLane<WM, PT> L8;
   bool records_in = false;
   // the own rows are in LDS once wavefronts 0 .. 3 have all said so (they wait for nobody); the
   // polls for the records look at that counter as well
@@ -1967,8 +2009,8 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
         todo &= todo - 1u;
         const bool from_lds = x == split;                  // the own slice's own rows are in LDS
         const OwnRows own = {own_o, own_ml, lo, from_lds ? split : -1};
-        const bool ok = ch4 ? merge_rows<4, D>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
-                            : merge_rows<WM, D>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
+        const bool ok = ch4 ? merge_rows<4, PT>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own)
+                            : merge_rows<WM, PT>(p, S, x * R, min(x * R + R, 32), budget, tag, pair, row0, orow_pair, mt, own);
         gave_up = !ok;                                     // (only with a bounded budget: the own slice in round 0)
       }
       if (gave_up) {
@@ -2458,7 +2500,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_rows_kernel(AttnPar
         todo &= todo - 1u;
         bool ok = true;
         for (int mrg = x; ok && mrg < nrg; mrg += S)
-          ok = merge_rows<kWideMerge<D>, D>(p, S, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
+          ok = merge_rows<UsualPartials<D>::kWide, UsualPartials<D>>(p, S, r_lo, r_lo + 8, budget, tag, pair, (zs * kWaves + mrg) * 32, orow_pair, mt, nothing_in_lds);
         gave_up = !ok;
       }
       if (gave_up) {
@@ -2555,20 +2597,22 @@ static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64
 // computes them four at a time, so a pair's tiles are spread thinly where there are units to spare: two to a
 // workgroup, up to sixteen splits (a merging thread's records are one poll, its chunks two batches of
 // eight; seventeen splits are a second pass over both), and one to a workgroup up to eight (one batch).  us per reuse / anchor launch,
-// D = 128, splits of a tile per wavefront -> these:
-//   8 pairs: 17 tiles 10.8 / 14.8 (2 splits) -> 7.3 / 10.6 (8); 33 tiles 8.8 / 12.2 (4) -> 7.5 / 10.9 (16); 65 tiles 9.4 / 13.0 (8)
-//   -> 8.8 / 12.2 (16)
-//   16 pairs of 33 tiles 9.6 / 13.3 (4) -> 8.0 / 11.8 (16); 32 pairs: 17 tiles 11.0 / 15.6 (2) -> 7.8 / 11.7 (8), 33 tiles 10.6 / 14.6 (4) -> 9.5 / 13.3
-//   (8); 64 pairs of 17 tiles 12.0 / 17.0 (2) -> 9.7 / 14.7 (4)
+// D = 128, five drafts, splits of a tile per wavefront (bf16 partials, blocks selected by the workgroup) -> these (fp32 partials, which
+// cost 24 to 64 pairs 0.1 - 0.25 of it and 8 pairs nothing):
+//   8 pairs: 17 tiles 10.0 / 13.7 (2 splits) -> 7.0 / 9.6 (8); 33 tiles 9.0 / 12.5 (4) -> 7.4 / 10.0 (16); 65 tiles 9.0 / 12.5 (8)
+//   -> 8.1 / 10.8 (16)
+//   16 pairs of 33 tiles 9.2 / 12.6 (4) -> 8.0 / 10.6 (16); 32 pairs: 17 tiles 10.7 / 14.5 (2) -> 7.8 / 10.6 (8), 33 tiles 10.0 / 13.6 (4) -> 9.3 / 12.1
+//   (8); 64 pairs of 17 tiles 11.6 / 15.6 (2) -> 9.4 / 12.5 (4); 80 pairs of 15 tiles 11.2 / 15.3 (2) -> 10.9 / 14.4 (3)
 // Nine to eleven splits cost the second batch and gain less than a tile per workgroup: 24 pairs of 33 tiles 8.9 / 12.5 with eight, 9.0 / 13.1
 // with ten, of 49 tiles 9.6 / 13.9 and 10.2 / 14.2.
-// What one workgroup can take (up to nine tiles) stays with one at D = 128: a split's partial row is bf16 there, a single workgroup
-// rounds nothing but its result.  Nine tiles of 8 pairs are 7.7 / 11.9 in one split and 7.1 / 10.3 in eight, but the error against 64 bits
-// rises from 2.2e-4 to 2.6e-4 (rms); from two splits on, more of them make it smaller (1.42e-4 in four, 1.34e-4 in sixteen).  At
-// D = 64 the partials are fp32, and the line does not hold.
+// A plan that one workgroup can take (up to nine tiles) stays with one at D = 128.  That line was drawn while the partials were
+// bf16 (nine tiles of 8 pairs 7.7 / 11.9 in one split, 7.1 / 10.3 in eight, but 2.6e-4 instead of 2.2e-4 of error, rms against 64 bits) and
+// has not been measured with fp32 partials.
 static int64_t tiles_of(const svf_shape_t& s) {
   return ((int64_t)s.k_blocks * s.block_size + kTile - 1) / kTile + (s.gamma + kTile - 1) / kTile;
 }
+// A plan that spreads its tiles: with a split less there would still be a wavefront for every tile.
+static bool thin_plan(int64_t tiles, int n_splits) { return tiles - 1 <= (int64_t)kWaves * (n_splits - 1); }
 // full: a tile for every wavefront (the retrieval alone, whose workgroups share the scoring only, and plans that
 // have to be small)
 int mfma_splits(const svf_shape_t& s, bool full) {
@@ -2616,6 +2660,11 @@ constexpr int kRowsModeFrom = 3;
 bool mfma_rows_mode(const svf_shape_t& s) {
   const int M = s.gamma * (s.Hq / s.Hkv);
   return (M + 31) / 32 >= kRowsModeFrom;
+}
+
+// The split partials of the shape's plan are fp32 rows (Partials).
+bool mfma_partials_f32(const svf_shape_t& s, int n_splits) {
+  return s.d == 64 || (!mfma_rows_mode(s) && thin_plan(tiles_of(s), n_splits));
 }
 
 // Splits per (sequence, KV head, set of eight row groups) of the rows kernel: cover the compute
@@ -2713,7 +2762,7 @@ static hipError_t launch_attn(const AttnParams& p, hipStream_t st) {
   // one tile per wavefront (the owner of draft tile 0 streams a second one beside it)?  The same
   // answer for the three modes: they have to add up in the same order (same bits).
   const int64_t tiles = ((int64_t)p.k_blocks * p.block_size + kTile - 1) / kTile + (p.gamma + kTile - 1) / kTile;
-  const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits, thin = tiles - 1 <= (int64_t)kWaves * (p.n_splits - 1);
+  const bool one_tile = tiles - 1 <= (int64_t)kWaves * p.n_splits, thin = thin_plan(tiles, p.n_splits);
   const int cover = (255 + pairs * row_groups) / (pairs * row_groups);       // splits that cover the compute units
 #define SVF_LAUNCH_ATTN(DIM, MODE)                                                                                                       \
   do {                                                                                                                                   \

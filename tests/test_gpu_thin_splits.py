@@ -56,3 +56,49 @@ def test_short_lists_are_rounded_once(d, k_blocks):
         bound = half + len(keys) * 2.0 ** -23 * keys.abs().mean(0)
         got = run.out[0, i].double().cpu().view(cfg.Hkv, cfg.Hq // cfg.Hkv, d)
         assert ((got - mean[:, None]).abs() <= bound[:, None]).all(), (i, d, k_blocks)
+
+
+THIN = {                                                 # splits of the plan; lists of one to all of its tiles
+    "sixteen_splits": small(B=2, Hq=32, Hkv=8, gamma=4, T=1100, k_blocks=17, page_size=0),
+    "sixteen_splits_two_row_groups": small(B=2, Hq=16, Hkv=2, gamma=7, T=1100, block_size=32, k_blocks=33),
+    "eight_splits": small(B=4, Hq=32, Hkv=8, gamma=5, T=2100, k_blocks=16),
+    "four_splits": small(B=8, Hq=16, Hkv=8, gamma=3, T=600, k_blocks=8),
+    "three_splits": small(B=10, Hq=8, Hkv=8, gamma=2, T=500, k_blocks=7),
+    "d64_sixteen_splits": small(B=2, Hq=32, Hkv=8, d=64, gamma=4, T=1100, k_blocks=17),
+}
+
+
+@pytest.mark.parametrize("by", ["length", "count"])
+@pytest.mark.parametrize("name", sorted(THIN))
+def test_lists_shorter_than_the_plan_are_rounded_once(name, by):
+    """The same for lists of one tile to all of the plan's, because a sequence is short or because few blocks are handed
+    over: spread over the plan's splits, whose partials hold fp32."""
+    cfg = THIN[name]
+    x = W.make_layer(cfg)
+    x["q"] = torch.zeros_like(x["q"])
+    most = cfg.k_blocks * cfg.block_size
+    pairs = cfg.B * cfg.Hkv
+    tokens = [[1 + (most - 1) * ((b * cfg.Hkv + h) ** 2) // (pairs - 1) ** 2 for h in range(cfg.Hkv)] for b in range(cfg.B)]
+    if by == "length":
+        tokens = [[t[0]] * cfg.Hkv for t in tokens]
+        x["seq_lens"] = torch.tensor([t[0] for t in tokens], dtype=torch.int32).minimum(x["seq_lens"])
+    count = torch.tensor([[-(-n // cfg.block_size) for n in t] for t in tokens], dtype=torch.int32)
+    idx = torch.arange(cfg.k_blocks, dtype=torch.int32).expand(cfg.B, cfg.Hkv, -1).contiguous()
+    idx[idx >= count[..., None]] = -1
+    run = DeviceRun(cfg, to_gpu(x)).verify_attn(mask=None, sel_idx=idx.cuda(), sel_cnt=count.cuda()).sync()
+    got = run.out.double().cpu().view(cfg.B, cfg.gamma, cfg.Hkv, cfg.Hq // cfg.Hkv, cfg.d)
+    for b in range(cfg.B):
+        for h in range(cfg.Hkv):
+            n = min(int(count[b, h]) * cfg.block_size, int(x["seq_lens"][b]))
+            if x["block_table"] is None:
+                v = x["v_pool"][b, :n, h]
+            else:
+                t = torch.arange(n)
+                v = x["v_pool"][x["block_table"][b, t // cfg.page_size].long(), t % cfg.page_size, h]
+            for i in range(cfg.gamma):
+                keys = torch.cat([v, x["v_draft"][b, :i + 1, h]]).double()
+                mean = keys.mean(0)
+                half = 2.0 ** (torch.frexp(mean.float())[1].double() - 9)
+                # (an addition for each key and split, products with a weight and a reciprocal in each of the two steps)
+                bound = half + (len(keys) + 24) * 2.0 ** -23 * keys.abs().mean(0)
+                assert ((got[b, i, h] - mean).abs() <= bound).all(), (b, h, i, n)
