@@ -1968,7 +1968,7 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
     }
   }
   if (!own_rows_in) {
-    for (int it = 0; it < kLastResortPolls; ++it) {
+    for (;;) {                                           // (no limit, as below)
       uint32_t n;
       asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(n) : "v"(ready) : "memory");
       if (__builtin_amdgcn_readfirstlane((int)n) == 4) break;
@@ -2029,9 +2029,9 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       }
     }
     if (round == 0) {
-      // (wavefront 0 waits for nobody)
+      // (no limit: wavefront 0 waits for nobody, and what it says must not be missed: it may be slices that are left to this workgroup)
       uint32_t word = 0u;
-      for (int it = 0; it < kLastResortPolls && !(word >> 31); ++it) {
+      for (int it = 0; !(word >> 31); ++it) {
         if (it) __builtin_amdgcn_s_sleep(1);
         uint32_t w;
         asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(w) : "v"((uint32_t)(uintptr_t)SVF_LDS_PTR(&sm_ticket)) : "memory");
