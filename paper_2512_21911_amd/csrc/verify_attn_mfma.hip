@@ -2688,7 +2688,8 @@ int mfma_select_splits(const svf_shape_t& s) { return mfma_rows_mode(s) ? row_sp
 // The retrieval of kSelect without the attention behind it (the stand-alone block selection of a
 // shape the retrieving attention kernel handles): the workgroups of a (sequence, KV head) share
 // the scoring through the key exchange, the last split publishes the kept blocks, and the
-// workgroup that finishes last moves the group's tag on.  No page table is touched (p.kv.page_size
+// workgroup that finishes last moves the group's tag on.  FEW: one workgroup per (sequence, KV head)
+// (n_splits = 1), which scores all blocks itself; no exchange, no tag.  No page table is touched (p.kv.page_size
 // must be 0 here) and no gather list is written.
 // grid: x = kXcds * n_splits, y = ceil(pairs / kXcds)
 template <int D, bool FEW>
@@ -2727,10 +2728,13 @@ __global__ __launch_bounds__(kThreads) void retrieve_only_kernel(AttnParams p, i
   }
 }
 
-hipError_t launch_retrieve_only(const AttnParams& p, hipStream_t st) {
+hipError_t launch_retrieve_only(const AttnParams& params, hipStream_t st) {
+  AttnParams p = params;
   const int pairs = p.B * p.Hkv;
+  const bool few = p.nb_max <= kWaveSelectBlocks;
+  if (few) p.n_splits = 1;
   const dim3 grid((unsigned)(kXcds * p.n_splits), (unsigned)((pairs + kXcds - 1) / kXcds));
-  if (p.nb_max <= kWaveSelectBlocks) {
+  if (few) {
     if (p.d == 64) hipLaunchKernelGGL((retrieve_only_kernel<64, true>), grid, dim3(kThreads), 0, st, p, pairs);
     else hipLaunchKernelGGL((retrieve_only_kernel<128, true>), grid, dim3(kThreads), 0, st, p, pairs);
   } else {
