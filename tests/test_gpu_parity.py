@@ -395,7 +395,8 @@ def test_repeated_calls_are_bit_stable():
         assert torch.equal(run.out.view(torch.int16), out0.view(torch.int16))
 
 
-def same_bits_whatever_the_wait(cfg):
+def same_bits_whatever_the_wait(cfg, exchanges=None):
+    """exchanges: whether the anchor calls exchange block keys (None: either)."""
     x = W.make_layer(cfg)
     run = DeviceRun(cfg, to_gpu(x))
     run.block_reps().score_select().verify_attn().sync()
@@ -419,6 +420,7 @@ def same_bits_whatever_the_wait(cfg):
         assert after[0] >= before[0] and after[1] >= before[1]
         if polls == 0:                             # (every shape tested this way has several splits)
             assert after[1] > before[1], "no merge fallback counted although nobody waits"
+            assert exchanges is None or (after[0] > before[0]) == exchanges
             print(f"\n[{cfg.name}] polls=0: exchange fallbacks +{after[0] - before[0]}, merge fallbacks +{after[1] - before[1]}")
         if polls in (64, -1):
             print(f"\n[{cfg.name}] polls={polls}: exchange fallbacks +{after[0] - before[0]}, merge fallbacks +{after[1] - before[1]}")
@@ -443,11 +445,28 @@ def same_bits_whatever_the_wait(cfg):
 @pytest.mark.parametrize("cfg_id,T", [(3, 8192), (5, 65536), (4, 131072), (3, 32768), (2, 8192)])
 def test_same_bits_whatever_the_workgroups_wait_for_each_other(cfg_id, T):
     """The workgroups of a group wait for each other twice, with a bounded number of polls: for the
-    block keys of the shared scoring (anchor layers), and for the split partials before each merges
-    its slice of the rows.  A budget of zero or one poll sends some or all of them down the other
+    block keys of the shared scoring (anchor layers of more than 128 blocks: not (3, 8192) and (2, 8192)), and for the
+    split partials before each merges its slice of the rows.  A budget of zero or one poll sends some or all of them down the other
     paths (score everything oneself; leave the slice to the workgroup that arrives last): the same
     bits in every step mode, call after call (the tags move on)."""
     same_bits_whatever_the_wait(W.shrink(W.CONFIGS[cfg_id], T) if T < W.CONFIGS[cfg_id].T else W.CONFIGS[cfg_id])
+
+
+# Thin plans, whose partials are fp32: (shape, whether keys are exchanged)
+THIN_WAIT = {
+    "sixteen_splits_exchange": (small(B=1, Hq=32, Hkv=8, gamma=5, T=8300, k_blocks=16), True),
+    "eight_splits_exchange_two_row_groups": (small(B=2, Hq=32, Hkv=8, gamma=12, tree_depth=4, T=9000, k_blocks=9), True),
+    "four_splits": (small(B=8, Hq=16, Hkv=8, gamma=3, T=600, k_blocks=8), False),
+    "three_splits_two_passes": (small(B=10, Hq=8, Hkv=8, gamma=2, T=500, k_blocks=7), False),
+    "short_lists": (small(B=4, Hq=32, Hkv=8, gamma=5, T=2100, k_blocks=16, min_len=10), False),
+    "d64_sixteen_splits_exchange": (small(B=2, Hq=32, Hkv=8, d=64, gamma=4, T=9000, k_blocks=17), True),
+}
+
+
+@pytest.mark.parametrize("name", sorted(THIN_WAIT))
+def test_thin_plans_same_bits_whatever_the_workgroups_wait_for_each_other(name):
+    cfg, exchanges = THIN_WAIT[name]
+    same_bits_whatever_the_wait(cfg, exchanges)
 
 
 # The kernel for many query rows merges up to 16 splits itself, by the same protocol: nine splits of

@@ -5,8 +5,10 @@ can take is rounded once."""
 import pytest
 import torch
 
+import paper_2512_21911_amd as S
 import workloads as W
-from svf_harness import DeviceRun, full_parity, to_gpu
+from oracle import svf_oracle as O
+from svf_harness import LSE_TOL, OUT_TOL, DeviceRun, full_parity, to_gpu
 from test_gpu_parity import small
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +18,8 @@ CASES = {
     "draft_only_splits_empty": small(B=2, Hq=8, Hkv=2, gamma=3, T=300, k_blocks=4, min_len=1),
     "nine_tiles_one_split": small(B=1, Hq=8, Hkv=8, gamma=4, T=900, k_blocks=4),
     "seventeen_tiles_eight_splits": small(B=4, Hq=32, Hkv=8, gamma=8, T=1100, k_blocks=8),
-    "eighteen_tiles_nine_to_eight": small(B=3, Hq=8, Hkv=8, gamma=3, T=1100, block_size=32, k_blocks=17),
+    "eighteen_tiles_eight_splits": small(B=3, Hq=8, Hkv=8, gamma=3, T=1100, block_size=32, k_blocks=17),
+    "33_tiles_ten_splits_cut_to_eight": small(B=3, Hq=32, Hkv=8, gamma=6, T=1500, k_blocks=16),
     "33_tiles_sixteen_splits": small(B=1, Hq=32, Hkv=8, gamma=5, T=1500, k_blocks=16, page_size=0),
     "34_tiles_seventeenth_split_not_taken": small(B=1, Hq=32, Hkv=8, gamma=5, T=1500, block_size=32, k_blocks=33),
     "129_tiles_full_wavefronts": small(B=1, Hq=8, Hkv=2, gamma=3, T=4500, k_blocks=64),
@@ -56,6 +59,16 @@ def test_short_lists_are_rounded_once(d, k_blocks):
         bound = half + len(keys) * 2.0 ** -23 * keys.abs().mean(0)
         got = run.out[0, i].double().cpu().view(cfg.Hkv, cfg.Hq // cfg.Hkv, d)
         assert ((got - mean[:, None]).abs() <= bound[:, None]).all(), (i, d, k_blocks)
+
+
+def limit_shape(d, nb):
+    """Eight pairs with lists of 33 tiles and so many blocks that their scores fill most of the static array."""
+    return S.make_shape(B=1, gamma=4, Hq=32, Hkv=8, d=d, dtype="bf16", block_size=64, max_seq_len=64 * nb, k_blocks=16, page_size=64,
+                        max_pages_per_seq=nb, kv_strides=(64 * 8 * d, 8 * d, d))
+
+
+# the last numbers of blocks (in steps of eight: 256 bytes of scores) whose sixteen splits, and whose four, fit the array
+AT_THE_LIMIT = {128: (456168, 515048), 64: (489448, 515560)}
 
 
 THIN = {                                                 # splits of the plan; lists of one to all of its tiles
@@ -102,3 +115,34 @@ def test_lists_shorter_than_the_plan_are_rounded_once(name, by):
                 # (an addition for each key and split, products with a weight and a reciprocal in each of the two steps)
                 bound = half + (len(keys) + 24) * 2.0 ** -23 * keys.abs().mean(0)
                 assert ((got[b, i, h] - mean).abs() <= bound).all(), (b, h, i, n)
+
+
+@pytest.mark.parametrize("by", [0, 1])
+@pytest.mark.parametrize("d", [64, 128])
+def test_plans_at_the_size_of_the_static_array(d, by):
+    """On either side of the limit (test_split_plans.py): the entry point with the static array gives the bits of the one with a
+    workspace, and what the oracle gives."""
+    for nb in (AT_THE_LIMIT[d][by], AT_THE_LIMIT[d][by] + 8):
+        shape = limit_shape(d, nb)
+        g = torch.Generator().manual_seed(d + by)
+        r = lambda *dims: torch.randn(*dims, generator=g).to(torch.bfloat16)
+        x = dict(q=r(1, 4, 32, d), k=r(16, 64, 8, d), v=r(16, 64, 8, d), kd=r(1, 4, 8, d), vd=r(1, 4, 8, d),
+                 lens=torch.tensor([1000], dtype=torch.int32), table=torch.zeros(1, nb, dtype=torch.int32),
+                 idx=torch.arange(16, dtype=torch.int32).expand(1, 8, 16).contiguous(),
+                 cnt=torch.tensor([[16, 15, 12, 8, 4, 2, 1, 0]], dtype=torch.int32))
+        x["table"][0, :16] = torch.randperm(16, generator=g).to(torch.int32)
+        c = {k: t.cuda() for k, t in x.items()}
+        out = torch.full_like(c["q"], float("nan"))
+        lse = torch.full((1, 4, 32), float("nan"), device="cuda")
+        args = (shape, c["q"], c["k"], c["v"], c["table"], c["lens"], c["kd"], c["vd"], None, c["idx"], c["cnt"])
+        S.svf_verify_attn(*args, out, S.new_workspace(shape), lse)
+        ref, lref = O.verify_attn(x["q"], x["k"], x["v"], x["table"], x["lens"], x["kd"], x["vd"], None, x["idx"], x["cnt"], 64, None)
+        assert abs(out.double().cpu().numpy() - ref).max() <= OUT_TOL["bf16"]
+        assert abs(lse.double().cpu().numpy() - lref).max() <= LSE_TOL["bf16"]
+        again, lagain = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+        if S.svf_workspace_bytes(shape) <= S.svf_static_workspace_bytes():
+            S.svf_verify_attn_static_ws(*args, again, lagain)
+            assert torch.equal(out.view(torch.int16), again.view(torch.int16)) and torch.equal(lse, lagain)
+        elif d == 128:
+            with pytest.raises(S.SvfError):
+                S.svf_verify_attn_static_ws(*args, again, lagain)
