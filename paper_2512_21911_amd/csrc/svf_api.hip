@@ -379,7 +379,7 @@ static int score_select_impl(const svf_shape_t* shape, const void* q, const floa
   {
     // Shapes the retrieving attention kernel handles, when neither the scores nor a gather list
     // are asked for: its retrieval alone, one launch (the workgroups of a (sequence, KV head)
-    // share the scoring), the same blocks bit for bit.
+    // share the scoring; up to 128 blocks one does it), the same blocks bit for bit.
     if (pl.fused_select && !scores_or_null && !with_gather) {
       char* w = static_cast<char*>(ws);
       AttnParams a{};

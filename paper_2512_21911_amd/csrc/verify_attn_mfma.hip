@@ -19,13 +19,14 @@
 // workgroup, so that every selected key/value is read from HBM once and used by all of them
 // (with more than 32 rows the row groups of a pair run on one XCD and share its L2).  The
 // selected tokens plus the draft tokens are cut into 32-token tiles; tile t belongs to
-// wavefront t mod NW, NW = 8 * n_splits wavefronts per (pair, row group).
+// wavefront t mod NW, NW = 8 * n_splits wavefronts per (pair, row group), counted split by split, or
+// where there are more wavefronts than tiles (thin_plan) through all splits in turn.
 //
 // Data path.  K and V rows go straight into LDS with 16-byte direct-to-LDS loads (no registers
 // in between), one 16 KB stage per wavefront, private to it: no workgroup barrier in the main
 // loop.  The wavefront that owns draft tile 0 keeps it in a ninth stage, so that its prefix
-// tile streams at the same time.  In launches where no wavefront has a second cache tile every
-// wavefront still fetches a tile, but wavefronts 4 .. 7 leave theirs to wavefronts 0 .. 3 (one
+// tile streams at the same time.  In launches where no wavefront has a second cache tile
+// wavefronts 4 .. 7 fetch theirs, if there is one for them, and leave it to wavefronts 0 .. 3 (one
 // barrier), which halves what has to be combined afterwards.  The 16-byte chunks of a row sit at an XOR-swizzled position
 // (chosen on the global-address side; the LDS side of such a load is fixed by the lane id),
 // which keeps the fragment reads off each other's banks.  The LDS reads of the main loop are
@@ -1498,7 +1499,10 @@ __global__ __launch_bounds__(kThreads) void verify_attn_mfma_kernel(AttnParams p
       table_row = p.table + (int64_t)b * p.kv.max_pages;
       NW = kWaves * S;
       // D = 64: tiles to the splits in turn; eight at a time, the last split of a pair would have as little as one tile and the
-      // others a second one for each wavefront.  D = 128, whose partial rows are bf16: eight at a time all the same, because a split
+      // others a second one for each wavefront.  us per call, eight at a time -> in turn, ten shapes at D = 64: four sequences of 32k, 256 blocks of 64
+      // over eight heads 11.5 - 12.5 -> 10.9 - 11.6, three of 20k, 160 blocks of 128 over heads of eight 18.3 -> 16.9, eight of 8k, 128 blocks 13.3
+      // -> 12.1; seven others within 1 % either way, the error against 64 bits the same to six digits.
+      // D = 128, whose partial rows are bf16 here: eight at a time all the same, because a split
       // that outweighs the others is rounded like the result and adds little to its error; dealt in turn, 120 blocks of 128 over
       // eight heads had 1.010e-4 (rms, against 64 bits) instead of 1.002e-4, and eight of ten such shapes a little more than before
       // (four sequences, 256 blocks of 64 over eight heads: 18.0 us in turn, 18.9 so).
@@ -2570,7 +2574,7 @@ bool mfma_supported(const svf_shape_t& s) {
 }
 
 // Splits of a group such that all workgroups of the launch are resident at once, if the least number of
-// splits `lo` allows that, else `want`.  A compute unit holds one workgroup: at D = 128 its LDS, at D = 64 its registers (144 - 150
+// splits `lo` allows that, else `want`.  A compute unit holds one workgroup: at D = 128 its LDS, at D = 64 its registers (147 - 154
 // vector registers make three wavefronts per SIMD, two workgroups would be four).  All splits and groups of a pair
 // go to one XCD of 32 compute units: with 48 pairs in six splits an XCD gets 36 workgroups, and the four that wait for a free place cost a
 // whole second round.  Fewer splits with another tile for some wavefronts cost far less.  us per reuse / anchor
@@ -2598,7 +2602,7 @@ static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64
 // workgroup, up to sixteen splits (a merging thread's records are one poll, its chunks two batches of
 // eight; seventeen splits are a second pass over both), and one to a workgroup up to eight (one batch).  us per reuse / anchor launch,
 // D = 128, five drafts, splits of a tile per wavefront (bf16 partials, blocks selected by the workgroup) -> these (fp32 partials, which
-// cost 24 to 64 pairs 0.1 - 0.25 of it and 8 pairs nothing):
+// cost 24 to 64 pairs 0.1 - 0.25 us of it and 8 pairs nothing):
 //   8 pairs: 17 tiles 10.0 / 13.7 (2 splits) -> 7.0 / 9.6 (8); 33 tiles 9.0 / 12.5 (4) -> 7.4 / 10.0 (16); 65 tiles 9.0 / 12.5 (8)
 //   -> 8.1 / 10.8 (16)
 //   16 pairs of 33 tiles 9.2 / 12.6 (4) -> 8.0 / 10.6 (16); 32 pairs: 17 tiles 10.7 / 14.5 (2) -> 7.8 / 10.6 (8), 33 tiles 10.0 / 13.6 (4) -> 9.3 / 12.1
