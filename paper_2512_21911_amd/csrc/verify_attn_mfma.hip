@@ -2609,7 +2609,11 @@ static int64_t one_round_splits(const svf_shape_t& s, int groups_per_pair, int64
 //   (8); 64 pairs of 17 tiles 11.6 / 15.6 (2) -> 9.4 / 12.5 (4); 80 pairs of 15 tiles 11.2 / 15.3 (2) -> 10.9 / 14.4 (3)
 // Nine to eleven splits cost the second batch and gain less than a tile per workgroup: 24 pairs of 33 tiles 8.9 / 12.5 with eight, 9.0 / 13.1
 // with ten, of 49 tiles 9.6 / 13.9 and 10.2 / 14.2.
-// A plan that one workgroup can take (up to nine tiles) stays with one at D = 128.  That line was drawn while the partials were
+// A plan that one workgroup can take has eight tiles and the drafts' at most.  At D = 64 it is spread if it has all nine and four or more
+// workgroups share them: 8 - 64 pairs 7.3 - 7.8 / 9.9 - 10.1 in one split, 6.9 - 7.4 / 8.9 - 9.5 in eight to four, but 80 pairs 7.8 / 10.0 and in three
+// 8.5 / 10.6, 112 pairs 7.8 / 10.2 and in two 9.3 / 11.2.  Fewer tiles are slower in several splits whatever the number of either: 32 pairs of three
+// 5.3 / 8.1 and 8.2 / 10.2, of eight 6.4 / 9.2 and 7.2 / 9.3.
+// At D = 128 it stays with one.  That line was drawn while the partials were
 // bf16 (nine tiles of 8 pairs 7.7 / 11.9 in one split, 7.1 / 10.3 in eight, but 2.6e-4 instead of 2.2e-4 of error, rms against 64 bits) and
 // has not been measured with fp32 partials.
 static int64_t tiles_of(const svf_shape_t& s) {
@@ -2626,7 +2630,7 @@ int mfma_splits(const svf_shape_t& s, bool full) {
   const int64_t lo = (tiles + kWaves * kMaxTiles - 1) / (kWaves * kMaxTiles);
   const int64_t filled = (tiles - 1 + kWaves - 1) / kWaves > 0 ? (tiles - 1 + kWaves - 1) / kWaves : 1;
   int64_t most = filled;
-  if (!full && (filled > 1 || s.d == 64)) {
+  if (!full && (filled > 1 || (s.d == 64 && tiles > kWaves))) {
     int64_t thin = tiles - 1 < 8 ? tiles - 1 : (tiles - 1) / 2;
     if (thin < 8 && tiles > 8) thin = 8;
     if (thin > 16) thin = 16;
@@ -2638,6 +2642,7 @@ int mfma_splits(const svf_shape_t& s, bool full) {
   if (!full) {
     want = one_round_splits(s, row_groups, want, lo);
     if (want > 8 && want < 12 && filled <= 8) want = 8;
+    if (filled == 1 && want < 4) want = 1;
   }
   return (int)want;
 }

@@ -75,6 +75,18 @@ def test_plan_of(name):
     assert planned(shape_of({**CASES, **THIN}[name])) == PLANS[name]
 
 
+@pytest.mark.parametrize("d,pairs,tokens,plan", [
+    (64, 2, 64, (1, False)), (64, 16, 96, (1, False)), (64, 112, 192, (1, False)), (64, 32, 224, (1, False)), (64, 8, 256, (8, True)),
+    (64, 48, 256, (5, True)), (64, 64, 256, (4, True)), (64, 80, 256, (1, False)), (64, 112, 256, (1, False)), (64, 80, 288, (3, True)),
+    (128, 8, 256, (1, False)), (128, 112, 256, (1, False)), (128, 80, 288, (3, True)),
+])
+def test_lists_that_one_workgroup_can_take(d, pairs, tokens, plan):
+    """Up to eight tiles and the drafts': one split, but for nine tiles at d = 64 that four or more workgroups share."""
+    shape = S.make_shape(B=pairs // 2, gamma=4, Hq=8, Hkv=2, d=d, dtype="bf16", block_size=32, max_seq_len=4096, k_blocks=tokens // 32,
+                         kv_strides=(4096 * 2 * d, 2 * d, d))
+    assert planned(shape) == plan
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_plans_at_the_size_of_the_static_array(d):
     """33 tiles of eight pairs: sixteen splits where they fit the array, the four of a tile per wavefront where only
