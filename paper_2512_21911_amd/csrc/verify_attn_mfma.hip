@@ -134,14 +134,17 @@ __device__ __forceinline__ u32x2 lds_read8_tr(uint32_t addr) {
   return v;
 }
 // The eight transposing reads of one k-step of the second product: piece 2 nt + h is chunk 4 nt + vc of the token rows
-// vtok + 8 h (+ 16 KS2).  Where a V row's chunks sit: the four tokens that 16 lanes address, and the
-// eight of the wavefront's, would hit the same sixteen of 64 banks if a row's place were shifted by its
-// token within one group of four chunks; so the token's low two bits select the group.
-//   D = 128: chunk c of token t at c ^ 4 (t & 3): group nt ^ (t & 3), one address per nt (of), h and KS2 immediate.
-//   D = 64 (K and V share a row, and sixteen K rows must differ as well): at c ^ (4 (t & 3) + ((t >> 2) & 3)); h is bit 1 of
-//   t >> 2, which flips bit 1 of the place within the group: an address per (nt, h).
-// (With chunk c at c ^ (t & 15): 6.5 conflict cycles per transposing read, 57 % of the LDS cycles of a 60-node tree's launch.)
-struct VAddress { uint32_t at[4]; };                     // D = 128: of nt; D = 64: of 2 (nt - 2) + h
+// vtok + 8 h (+ 16 KS2).  Where a V row's chunks sit:
+//   D = 128: chunk c of token t at c ^ 4 (t & 3).  The four tokens that 16 lanes address, and the eight of the wavefront's, would hit
+//   the same sixteen of 64 banks if a row's place were shifted by its token within one group of four chunks; so the token's low two
+//   bits select the group: group nt ^ (t & 3), one address per nt, h and KS2 immediate.
+//   (With chunk c at c ^ (t & 15): 6.5 conflict cycles per transposing read, 57 % of the LDS cycles of a 60-node tree's launch.)
+//   D = 64 (K and V share a row): at c ^ (t & 15), as the K chunks.  With L = vc ^ (vtok & 3) (bits 0, 1), g = bit 2 of vtok and h =
+//   bit 3 of the token that is 16 L + 64 ((nt & 1) ^ g) + 128 ((nt >> 1) ^ h), and 64 ((nt & 1) ^ g) = 64 (nt & 1) + 64 g for even nt,
+//   64 (nt & 1) - 64 g for odd: an address for even and one for odd nt, the rest immediate.  The tile is bound by its vector instructions
+//   (weights in three terms), not by its reads: at c ^ (4 (t & 3) + ((t >> 2) & 3)), without conflicts but with an address per (nt, h),
+//   112 pairs of 160 rows over 46 tiles took 37.5 us per reuse launch instead of 36.7, 64 over 118 43.7 instead of 42.9.
+struct VAddress { uint32_t at[4]; };                     // D = 128: of nt; D = 64: [0] of even, [1] of odd nt
 template <int D>
 __device__ __forceinline__ VAddress v_address(uint32_t stage, int l32, int g) {
   // This lane addresses, for piece h of a k-step, token 8*h + 4*g + q and the four channels
@@ -149,17 +152,22 @@ __device__ __forceinline__ VAddress v_address(uint32_t stage, int l32, int g) {
   const uint32_t q = (uint32_t)((l32 & 15) >> 2), vc = (uint32_t)(2 * ((l32 >> 4) & 1) + ((l32 & 3) >> 1));
   const uint32_t base = (4u * (uint32_t)g + q) * kRowBytes + ((uint32_t)(l32 & 1) << 3);
   VAddress a;
+  if constexpr (D == 128) {
 #pragma unroll
-  for (uint32_t i = 0; i < 4; ++i) {
-    if constexpr (D == 128) a.at[i] = stage + kTileBytes + (base + (vc << 4) + ((i ^ q) << 6));
-    else a.at[i] = stage + (base + ((vc ^ (uint32_t)g ^ (2u * (i & 1u))) << 4) + (((2u + (i >> 1)) ^ q) << 6));
+    for (uint32_t i = 0; i < 4; ++i) a.at[i] = stage + kTileBytes + (base + (vc << 4) + ((i ^ q) << 6));
+  } else {
+    const uint32_t at = stage + base + ((vc ^ q) << 4);
+    a.at[0] = at + ((uint32_t)g << 6);
+    a.at[1] = at - ((uint32_t)g << 6);
   }
   return a;
 }
 template <int D, int E, int KS2>
 __device__ __forceinline__ u32x2 lds_read_vt_piece(const VAddress& a) {
   constexpr int nt = E >> 1, h = E & 1;
-  return lds_read8_tr<h * 8 * kRowBytes + KS2 * 16 * kRowBytes>(a.at[D == 128 ? nt : 2 * (nt - 2) + h]);
+  constexpr int off = h * 8 * kRowBytes + KS2 * 16 * kRowBytes;
+  if constexpr (D == 128) return lds_read8_tr<off>(a.at[nt]);
+  else return lds_read8_tr<off + 64 * (nt & 1) + 128 * ((nt >> 1) ^ h)>(a.at[nt & 1]);
 }
 // Both k-steps at D = 64: the V row is chunks 8 .. 15, i.e. products nt = 2, 3; x[4 * KS2 + 2 * (nt - 2) + h].
 __device__ __forceinline__ void lds_read_vt64(u32x2 (&x)[8], const VAddress& a) {
@@ -182,11 +190,6 @@ __device__ __forceinline__ void lds_read_vt(u32x2 (&x)[8], const VAddress& a) {
   x[5] = lds_read_vt_piece<128, 5, KS2>(a);
   x[6] = lds_read_vt_piece<128, 6, KS2>(a);
   x[7] = lds_read_vt_piece<128, 7, KS2>(a);
-}
-// Place of chunk 0 of token t's K row (D = 64: and V row), in chunks; chunk c is at c ^ this.
-template <int D>
-__device__ __forceinline__ uint32_t k_swizzle(uint32_t t) {
-  return D == 128 ? t & 15u : ((t & 3u) << 2) | ((t >> 2) & 3u);
 }
 // Waits for all LDS reads; the registers pass through the statement so that no use of them can
 // be scheduled above the wait.
@@ -322,7 +325,8 @@ __device__ __forceinline__ void row_lanes_from(uint32_t x, uint32_t (&out)[8]) {
 // Requests the K and V rows of tokens 4n .. 4n + 3 (sixteen lanes per token) into kilobyte n of a stage
 // (D = 128: of its K part and of its V part).  kb: K row of the group's first token (scalar), dv: from there to the V row
 // (scalar), off: this lane's token within the group in bytes, dst: the kilobyte.  Which of the row's sixteen 16-byte
-// chunks this lane fetches follows from where they sit (k_swizzle, VAddress): place lane % 16 of row 4n + lane / 16.
+// chunks this lane fetches follows from where they sit: place lane % 16 of row 4n + lane / 16, K chunk c of token t at c ^ (t & 15), V chunks
+// see VAddress.
 struct LaneChunks {
   uint32_t k, v;
   __device__ __forceinline__ explicit LaneChunks(int lane) : k((uint32_t)((lane & 15) ^ (lane >> 4))), v((uint32_t)((lane & 15) ^ ((lane >> 4) << 2))) {}
@@ -334,7 +338,7 @@ __device__ __forceinline__ void request_rows(const char* kb, int64_t dv, uint32_
     __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(kb + dv + (off + (c.v << 4))), SVF_LDS_PTR(dst + kTileBytes), 16, 0, 2);
   } else {
     // (chunks 8 .. 15 are the V row's)
-    const uint32_t chunk = c.v ^ (uint32_t)(n & 3);
+    const uint32_t chunk = c.k ^ (uint32_t)((4 * n) & 15);
     const char* src = (chunk & 8u) ? kb + dv : kb;
     __builtin_amdgcn_global_load_lds(SVF_GLOBAL_PTR(src + (off + ((chunk & 7u) << 4))), SVF_LDS_PTR(dst), 16, 0, 2);
   }
@@ -380,7 +384,7 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
                                              float& l_run, floatx16 (&oacc)[D / 32]) {
   // K fragment of k-step ks: row l32, 16-byte chunk 2*ks + g at swizzled position
   const uint32_t kbase = stage + l32 * kRowBytes;
-  const uint32_t kx = ((uint32_t)g ^ k_swizzle<D>((uint32_t)l32)) << 4;
+  const uint32_t kx = (uint32_t)((g ^ (l32 & 15)) << 4);
   // V^T fragments by transposing reads: A row m (= lane mod 32) of the nt-th product is channel
   // 32 * nt + m; k-slot e of lane group g is token 8*(e/4) + 4*g + e%4 (+16 for the second k-step).
   const VAddress va = v_address<D>(stage, l32, g);
@@ -389,8 +393,8 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
   floatx16 sacc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
-  // Every read is issued well ahead of what waits for it: the K fragments all at once, the V^T fragments
-  // (x0, x1: of the two k-steps, [2 * nt + h]; D = 64: both in x0) behind the products that free the K fragments' registers.
+  // The K fragments are requested all at once, the V^T fragments (x0, x1: of the two k-steps, [2 * nt + h]; D = 64: both in x0)
+  // behind the products that free the K fragments' registers.
   u32x4 kf[D / 64][4];
   u32x2 x0[8], x1[8];
 #pragma unroll
@@ -408,9 +412,9 @@ __device__ __forceinline__ void process_tile(uint32_t stage, const bf16x8 (&qf)[
     scores(D / 64 - 1);
     lds_read_vt<1>(x1, va);
   } else {
-    lds_read_vt64(x0, va);
-    lds_wait4<8>(kf[0]);
+    lds_wait4<0>(kf[0]);
     scores(0);
+    lds_read_vt64(x0, va);
   }
 
   // online softmax; value v of a lane is token 8*(v/4) + 4*g + v%4 of the tile.
@@ -2574,7 +2578,7 @@ bool mfma_supported(const svf_shape_t& s) {
 }
 
 // Splits of a group such that all workgroups of the launch are resident at once, if the least number of
-// splits `lo` allows that, else `want`.  A compute unit holds one workgroup: at D = 128 its LDS, at D = 64 its registers (147 - 154
+// splits `lo` allows that, else `want`.  A compute unit holds one workgroup: at D = 128 its LDS, at D = 64 its registers (144 - 150
 // vector registers make three wavefronts per SIMD, two workgroups would be four).  All splits and groups of a pair
 // go to one XCD of 32 compute units: with 48 pairs in six splits an XCD gets 36 workgroups, and the four that wait for a free place cost a
 // whole second round.  Fewer splits with another tile for some wavefronts cost far less.  us per reuse / anchor
